@@ -149,6 +149,8 @@ int check_model(const tsd_model_cfg& m, const char* name, std::string& why) {
   return TSD_OK;
 }
 
+constexpr size_t kMaxSortSlots = 144 * 1024;  // (token, choice) pairs one expert sort takes: a byte each in LDS
+
 int check_config(const tsd_config* c, std::string& why) {
   if (!c) {
     why = "cfg is NULL";
@@ -179,7 +181,7 @@ int check_config(const tsd_config* c, std::string& why) {
   if ((c->max_tokens + c->page_tokens - 1) / c->page_tokens > 64)
     return bad("max_tokens / page_tokens must not exceed 64 pages per series");
   for (const tsd_model_cfg* m : {&c->target, &c->draft})
-    if (m->n_experts > 0 && (size_t)std::max((long)c->max_batch * (c->K + 1), (long)c->max_tokens) * m->top_k > 144 * 1024)
+    if (m->n_experts > 0 && (size_t)std::max((long)c->max_batch * (c->K + 1), (long)c->max_tokens) * m->top_k > kMaxSortSlots)
       return bad("max_batch * (K + 1) * top_k too large for the expert sort (one byte per assignment in 144 KB of LDS)");
   for (const tsd_model_cfg* m : {&c->target, &c->draft})
     if (attention_lds_bytes(c->dtype, m->d_model / m->n_heads, c->max_tokens, c->page_tokens) > 160 * 1024)
@@ -188,6 +190,25 @@ int check_config(const tsd_config* c, std::string& why) {
 }
 
 constexpr int kTraceMax = 512;  // stage stamps tsd_trace_draft can return
+
+// Rows the activation workspace holds at most beyond what a decode pass needs: the context pass of a batch runs in as few
+// passes as fit.  A pass is a chain of launches that each cost 4-5 us however few rows they cover, and each reads its weights
+// once, so the workspace is sized for whole batches instead of one round's tokens (context passes, ms, before / with 16384
+// rows: 8 fp32 series of 31 patches 1.79 / 0.25; 256 series of 29 patches, 8 layers of 512, 2.5 / 1.1; 93 of 76, 12 layers
+// of 768, 10.6 / 2.7; 1024 of 59, 24 layers of 1024, 59.4 / 54.9; 512 of 127, 16 routed layers of 768, 58.1 / 43.3).
+// Against 16384: 8192 rows 57.1 and 48.0 on the last two, 32768 rows 56.2 and 42.0, 65536 rows 56.8 and 43.1 (the residual
+// stream then no longer fits the 256 MB last-level cache).
+constexpr long kContextRows = 16384;
+
+// Rows of the activation workspace: a round's tokens of the whole batch, the longest context of one series, and the
+// contexts of the batch as far as kContextRows (and the expert sort of a routed model) allow.
+size_t workspace_rows(const tsd_config& c) {
+  const long must = std::max((long)c.max_batch * (c.K + 1), (long)c.max_tokens);
+  long want = std::min((long)c.max_batch * c.max_tokens, kContextRows);
+  for (const tsd_model_cfg* m : {&c.target, &c.draft})
+    if (m->n_experts > 0) want = std::min(want, (long)kMaxSortSlots / m->top_k);
+  return (size_t)std::max(must, want);
+}
 
 struct Carver {
   size_t off = 0;
@@ -287,7 +308,7 @@ size_t carve(const tsd_config& c, tsd_ctx* ctx) {
   size_t o_ell = cv.take((size_t)B * K * 4), o_logu = cv.take((size_t)B * K * 4);
   size_t o_diag = cv.take((size_t)(3 * P + 1) * 4);
   const size_t Dm = std::max(c.target.d_model, c.draft.d_model), Fm = std::max(c.target.d_ff, c.draft.d_ff);
-  const size_t rows = std::max((size_t)B * (K + 1), (size_t)c.max_tokens);
+  const size_t rows = workspace_rows(c);
   size_t o_xb = cv.take(rows * Dm * es);
   size_t o_x = cv.take(rows * Dm * 4), o_q = cv.take(rows * Dm * es), o_a = cv.take(rows * Dm * es), o_h = cv.take(rows * Fm * es);
   size_t o_trace = cv.take(kTraceMax * 8);
@@ -369,6 +390,10 @@ Shape shape_of(const tsd_ctx* ctx, int which, int amode, int epi, const GemmP& g
   return Shape{which, gemm_variant(ctx->cfg.dtype, amode, epi, g), g.M, g.N, g.K};
 }
 
+// Context passes take the skinny products only where the whole batch's context would (so that a series' bits do not
+// depend on how many series share the pass).
+int context_skinny(const tsd_ctx* ctx, int nq) { return ctx->skinny && (long)ctx->cfg.max_batch * nq <= 32 ? 1 : 0; }
+
 // Launches `fn` on `st`; if kernel family `cls` is being profiled (or all are), brackets it with two events.
 template <typename F>
 hipError_t timed_launch(tsd_ctx* ctx, int cls, double work, hipStream_t st, F fn, Shape sh = Shape()) {
@@ -404,6 +429,7 @@ struct Pass {
   float* out;  // NULL = skip the head
   long out_stride_b;
   int t_skip;
+  int skinny;  // the pass's products may take the skinny kernel (fixed per handle and kind of pass)
 };
 
 // One causal pass of `nq` new tokens per series through a model, against its paged KV cache.
@@ -414,7 +440,7 @@ int run_pass(tsd_ctx* ctx, const Pass& ps, hipStream_t st) {
   if (M > ctx->rows_max) return fail(ctx, TSD_E_OUT_OF_RANGE, "pass exceeds the activation workspace");
   GemmP g;
   std::memset(&g, 0, sizeof(g));
-  g.allow_skinny = ctx->skinny;
+  g.allow_skinny = ps.skinny;
   g.no_wide = (c.flags & TSD_FLAG_NO_WIDE_GEMM) ? 1 : 0;
   g.M = M;
   g.nq = ps.nq;
@@ -437,7 +463,7 @@ int run_pass(tsd_ctx* ctx, const Pass& ps, hipStream_t st) {
     char* pool = md.kv_pool + (size_t)l * md.layer_pool_bytes;
     GemmP q;
     std::memset(&q, 0, sizeof(q));
-    q.allow_skinny = ctx->skinny;
+    q.allow_skinny = ps.skinny;
     q.no_wide = (c.flags & TSD_FLAG_NO_WIDE_GEMM) ? 1 : 0;
     q.M = M;
     q.nq = ps.nq;
@@ -489,7 +515,7 @@ int run_pass(tsd_ctx* ctx, const Pass& ps, hipStream_t st) {
     HIP_TRY(ctx, timed_launch(ctx, TSD_K_ATTN, attn_bytes, st, [&] { return launch_attention(c.dtype, a, c.max_tokens, st); }, Shape{ps.which, 0, M, D, 0}));
     GemmP o;
     std::memset(&o, 0, sizeof(o));
-    o.allow_skinny = ctx->skinny;
+    o.allow_skinny = ps.skinny;
     o.no_wide = (c.flags & TSD_FLAG_NO_WIDE_GEMM) ? 1 : 0;
     o.M = M;
     o.nq = ps.nq;
@@ -568,7 +594,7 @@ int run_pass(tsd_ctx* ctx, const Pass& ps, hipStream_t st) {
     }
     GemmP f1;
     std::memset(&f1, 0, sizeof(f1));
-    f1.allow_skinny = ctx->skinny;
+    f1.allow_skinny = ps.skinny;
     f1.no_wide = (c.flags & TSD_FLAG_NO_WIDE_GEMM) ? 1 : 0;
     f1.M = M;
     f1.nq = ps.nq;
@@ -582,7 +608,7 @@ int run_pass(tsd_ctx* ctx, const Pass& ps, hipStream_t st) {
                               shape_of(ctx, ps.which, A_NORM, EP_GELU, f1)));
     GemmP f2;
     std::memset(&f2, 0, sizeof(f2));
-    f2.allow_skinny = ctx->skinny;
+    f2.allow_skinny = ps.skinny;
     f2.no_wide = (c.flags & TSD_FLAG_NO_WIDE_GEMM) ? 1 : 0;
     f2.M = M;
     f2.nq = ps.nq;
@@ -599,7 +625,7 @@ int run_pass(tsd_ctx* ctx, const Pass& ps, hipStream_t st) {
   if (ps.out) {
     GemmP h;
     std::memset(&h, 0, sizeof(h));
-    h.allow_skinny = ctx->skinny;
+    h.allow_skinny = ps.skinny;
     h.no_wide = (c.flags & TSD_FLAG_NO_WIDE_GEMM) ? 1 : 0;
     h.M = M;
     h.nq = ps.nq;
@@ -1050,6 +1076,7 @@ int tsd_prefill(tsd_ctx* ctx, const float* series_dev, int32_t B, int32_t n_ctx_
       ps.B = std::min(chunk, B - s0);
       ps.s0 = s0;
       ps.nq = nq;
+      ps.skinny = context_skinny(ctx, nq);
       ps.base_pos = nullptr;
       ps.pos_off = 0;
       ps.src0 = ctx->znorm + (size_t)s0 * N * P;
@@ -1096,6 +1123,7 @@ int tsd_refill(tsd_ctx* ctx, const int32_t* slots_host, int32_t n, const float* 
       ps.B = std::min(chunk, n - s0);
       ps.act = ctx->refill_list + s0;
       ps.nq = nq;
+      ps.skinny = context_skinny(ctx, nq);
       ps.base_pos = nullptr;
       ps.pos_off = 0;
       ps.src0 = ctx->znorm;  // rows are gathered by slot
@@ -1199,6 +1227,7 @@ int tsd_draft_propose(tsd_ctx* ctx, void* stream) {
   Pass ps;
   std::memset(&ps, 0, sizeof(ps));
   ps.which = TSD_DRAFT;
+  ps.skinny = ctx->skinny;
   ps.B = cv.n;
   ps.act = cv.act;
   ps.n_dev = cv.n_dev;
@@ -1242,6 +1271,7 @@ int tsd_draft_propose(tsd_ctx* ctx, void* stream) {
   for (int i = 2; i <= Kr; ++i) {  // step i consumes x_{i-1} at position len + i - 1, emits x_i
     std::memset(&ps, 0, sizeof(ps));
     ps.which = TSD_DRAFT;
+    ps.skinny = ctx->skinny;
     ps.B = cv.n;
     ps.act = cv.act;
     ps.n_dev = cv.n_dev;
@@ -1271,6 +1301,7 @@ int tsd_target_verify(tsd_ctx* ctx, void* stream) {
   Pass ps;
   std::memset(&ps, 0, sizeof(ps));
   ps.which = TSD_TARGET;
+  ps.skinny = ctx->skinny;
   ps.B = cv.n;
   ps.act = cv.act;
   ps.n_dev = cv.n_dev;
@@ -1347,6 +1378,7 @@ int tsd_target_step(tsd_ctx* ctx, void* stream) {
     const Cover cv = cover(ctx);
     if (cv.n == 0) return TSD_OK;
     ps.which = TSD_TARGET;
+    ps.skinny = ctx->skinny;
     ps.B = cv.n;
     ps.act = cv.act;
     ps.n_dev = cv.n_dev;
