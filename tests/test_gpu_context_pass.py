@@ -1,0 +1,30 @@
+"""The context pass on a kept handle: batches of one shape after another replay captured launches, a change of shape
+rebuilds them.  Every forecast must equal, to the bit, the one a fresh handle makes of the same series."""
+import numpy as np
+import pytest
+
+from harness import Case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("name", ["cfg1", "mini2", "mini5"])
+def test_forecasts_of_a_kept_handle_equal_a_fresh_handles(name):
+    case = Case(name, B=6)
+    c = case.cfg
+    P, N, H = c.patch, c.n_ctx, c.horizon
+    sess = case.session()
+    rng = np.random.default_rng(5)
+    # (series, context patches, horizon): the same shape three times (launch by launch, captured, replayed), then other
+    # batch sizes, contexts and horizons, and the first shape again
+    for B, n, h in [(6, N, H)] * 3 + [(4, N, H)] * 2 + [(4, N - 1, H), (4, N - 1, H - P)] + [(6, N, H)] * 2:
+        ctx = np.roll(case.context[:B, :n * P], int(rng.integers(1, n * P)), axis=1)   # other inputs every time
+        sess.prefill(ctx, n, h)
+        sess.run_rounds()
+        got = sess.get_forecast().cpu().numpy()
+        fresh = case.session()
+        fresh.prefill(ctx, n, h)
+        fresh.run_rounds()
+        np.testing.assert_array_equal(got, fresh.get_forecast().cpu().numpy(), err_msg=f"{B} series of {n} patches, {h} steps")
+        fresh.close()
+    sess.close()
