@@ -243,7 +243,12 @@ int tsd_accept_commit_static(const float* X_dev, const float* mu_q_dev, const fl
  * replayed afterwards (same for tsd_target_step); TSD_FLAG_NO_GRAPH switches that off.  Graphs are
  * kept per number of positions the round runs and per size class of the active list (launches
  * sized for 1/32 .. 32/32 of the batch); the class is chosen from the last length the host has
- * seen, looked up without waiting, and every launch is capped by the device-side length. */
+ * seen, looked up without waiting, and every launch is capped by the device-side length.
+ * A dense bf16 handle with max_batch * (K + 1) <= 32 runs the draft steps and the verification (and tsd_target_step's pass)
+ * as ONE resident kernel with a workgroup on every compute unit, bit for bit the kernel-by-kernel result, where its sizes
+ * allow (head_dim 64, d_model <= 1024, d_ff <= 4096, patch a multiple of 16, K <= 15); such launches of all handles on a GPU
+ * run one after the other.  Should its workgroups not become resident together within 4 seconds, the round commits
+ * nothing and every later call but tsd_prefill returns TSD_E_HIP. */
 int tsd_round(tsd_ctx* ctx, void* stream);
 
 /* Rounds until no series needs patches any more (or max_rounds rounds have run): the loop

@@ -146,6 +146,7 @@ hipError_t launch_sample(const SampleP& p, hipStream_t st) {
 // tokens and the cache lengths (rollback is metadata only: speculative KV entries past the
 // accepted length are simply overwritten by the next round).
 __global__ __launch_bounds__(64) void accept_kernel(const AcceptP p) {
+  if (p.gave_up && *p.gave_up) return;
   if (p.n_dev && (int)blockIdx.x >= *p.n_dev) return;
   const int b = p.act ? p.act[blockIdx.x] : (int)blockIdx.x, lane = threadIdx.x;
   const int K = p.K, P = p.P;

@@ -67,6 +67,10 @@ struct tsd_ctx {
   bool trace_on = false;
   int skinny;  // all decode passes have at most 32 rows: they take the skinny GEMM (fixed per handle so that a
                // series' bits never depend on how many other series are still active)
+  bool small_round = false;         // ... as one resident kernel (see small_round.hip)
+  unsigned* small_flags = nullptr;  // its workgroups' flags
+  unsigned small_epoch = 0;         // what they hold at most
+  char* small_exchange = nullptr;   // what they hand each other
   int* moe_ids;
   int* route_tap[2] = {nullptr, nullptr};  // caller-owned parity tap per model (tsd_set_route_tap), NULL = off
   float* moe_gates;
@@ -191,6 +195,8 @@ int check_config(const tsd_config* c, std::string& why) {
       return bad("max_tokens too large: one head's K and V rows must fit the 160 KB of LDS");
   return TSD_OK;
 }
+
+constexpr int kGaveUp = 12;     // word of count_out (and 3 of the pinned words): a resident pass gave up waiting
 
 constexpr int kTraceMax = 512;  // stage stamps tsd_trace_draft can return
 
@@ -317,6 +323,11 @@ size_t carve(const tsd_config& c, tsd_ctx* ctx) {
   size_t o_trace = cv.take(kTraceMax * 8);
   size_t o_cnt = cv.take(256), o_so = cv.take(256), o_alist = cv.take((size_t)B * 4), o_rlist = cv.take((size_t)B * 4);
   size_t o_alist2 = cv.take((size_t)B * 4);
+  size_t o_flags = 0, o_exchange = 0;
+  if (small_round_ok(c)) {
+    o_flags = cv.take((size_t)kSmallRoundWorkgroups * kSmallRoundFlagWords * 4);
+    o_exchange = cv.take(small_round_exchange_bytes(c));
+  }
   // routed FFN scratch: one slot per (token, chosen expert)
   const size_t topk = std::max(c.target.n_experts > 0 ? c.target.top_k : 0, c.draft.n_experts > 0 ? c.draft.top_k : 0);
   const size_t slots = rows * topk, nEmax = std::max(c.target.n_experts, c.draft.n_experts);
@@ -366,6 +377,8 @@ size_t carve(const tsd_config& c, tsd_ctx* ctx) {
     ctx->count_out = (int*)at(o_cnt);
     ctx->act_list = (int*)at(o_alist);
     ctx->act_list_next = (int*)at(o_alist2);
+    ctx->small_flags = (unsigned*)at(o_flags);
+    ctx->small_exchange = at(o_exchange);
     ctx->refill_list = (int*)at(o_rlist);
     ctx->moe_ids = topk ? (int*)at(o_ids) : nullptr;
     ctx->moe_gates = (float*)at(o_gates);
@@ -393,9 +406,14 @@ Shape shape_of(const tsd_ctx* ctx, int which, int amode, int epi, const GemmP& g
   return Shape{which, gemm_variant(ctx->cfg.dtype, amode, epi, g), g.M, g.N, g.K};
 }
 
-// Context passes take the skinny products only where the whole batch's context would (so that a series' bits do not
-// depend on how many series share the pass).
-int context_skinny(const tsd_ctx* ctx, int nq) { return ctx->skinny && (long)ctx->cfg.max_batch * nq <= 32 ? 1 : 0; }
+// Context passes of a handle whose decode passes are skinny: short contexts (at most 32 rows in the chunk of series that one
+// round's rows hold) take the skinny products too, in tiles of 32 rows however many series share the pass, so that a series'
+// bits do not depend on that number.
+int context_skinny(const tsd_ctx* ctx, int n, int nq) {
+  const tsd_config& c = ctx->cfg;
+  const long chunk = std::max(1L, std::max((long)c.max_batch * (ctx->K_max + 1), (long)c.max_tokens) / nq);
+  return ctx->skinny && std::min(chunk, (long)n) * nq <= 32 ? 2 : 0;
+}
 
 // Launches `fn` on `st`; if kernel family `cls` is being profiled (or all are), brackets it with two events.
 template <typename F>
@@ -659,7 +677,7 @@ struct Cover {
 // count that the compaction maintains (the routed FFN sizes its expert runs on the host, so it cannot).
 bool device_counts(const tsd_ctx* ctx) {
   return !(ctx->cfg.flags & TSD_FLAG_NO_COMPACT) && ctx->cfg.target.n_experts == 0 && ctx->cfg.draft.n_experts == 0 &&
-         ctx->B > 1;
+         (ctx->B > 1 || ctx->small_round);
 }
 // The compaction that ends every tsd_round rewrites the list on the device, while the host's copy of its
 // length is refreshed only by tsd_num_active.  A launch that pairs an older (larger) host count with the newer
@@ -761,12 +779,82 @@ int round_positions(const tsd_ctx* ctx) {
   return (ctx->k_round >= 1 && ctx->k_round < K) ? ctx->k_round : K;
 }
 
+bool gave_up(const tsd_ctx* ctx) { return ctx->host_counts && __atomic_load_n(&ctx->host_counts[3], __ATOMIC_RELAXED) != 0; }
+
 int require_ready(tsd_ctx* ctx, bool need_prefill) {
   if (!ctx) return fail(nullptr, TSD_E_INVALID_ARG, "ctx is NULL");
   if (need_prefill) {
     if (!ctx->model[0].loaded || !ctx->model[1].loaded) return fail(ctx, TSD_E_BAD_STATE, "weights of both models must be loaded first");
     if (!ctx->prefilled) return fail(ctx, TSD_E_BAD_STATE, "tsd_prefill has not been called");
+    if (gave_up(ctx))
+      return fail(ctx, TSD_E_HIP, "a decode pass gave up waiting for its workgroups to be resident together: start over with tsd_prefill");
   }
+  return TSD_OK;
+}
+
+// Whether the next decode pass on `st` runs as the resident kernel.  (Not under a measurement, which times the kernels one by
+// one, and not where the caller is capturing: a captured launch could be replayed beside another handle's.)
+bool use_small_round(tsd_ctx* ctx, hipStream_t st) {
+  if (!ctx->small_round || ctx->prof_class >= 0) return false;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (st && (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)) return false;
+  return true;
+}
+
+// phases: 1 the draft steps, 2 the target pass; step_only: the target pass over the pending token alone.
+int run_small_round(tsd_ctx* ctx, int phases, bool step_only, hipStream_t st) {
+  const tsd_config& c = ctx->cfg;
+  SmallRoundP r;
+  std::memset(&r, 0, sizeof(r));
+  for (int i = 0; i < 2; ++i) {
+    const ModelDev& md = ctx->model[i];
+    SmallModel& m = r.m[i];
+    auto w = [](const char* x) { return reinterpret_cast<const bf16*>(x); };
+    const Layer& l0 = md.layers[0];
+    small_round_model(md.c, c.patch, w(md.W_e), w(md.W_h), w(l0.Wqkv), w(l0.Wo), w(l0.W1), w(l0.W2), &m);
+    // (the layers of a dense model are carved one after the other, all alike)
+    m.wstride = md.layers.size() > 1 ? (size_t)(md.layers[1].Wqkv - l0.Wqkv) : 0;
+    m.kv_pool = reinterpret_cast<bf16*>(md.kv_pool);
+    m.layer_pool_elems = md.layer_pool_bytes / 2;
+    m.rope_cos = md.rope_cos;
+    m.rope_sin = md.rope_sin;
+  }
+  r.page_table = ctx->page_table;
+  r.pt_stride = ctx->pages_per_series;
+  r.PT = c.page_tokens;
+  r.pt_shift = __builtin_ctz(c.page_tokens);
+  r.len = ctx->len;
+  r.K = round_positions(ctx);
+  if (device_counts(ctx)) {  // the list and its length are read on the device
+    r.act = ctx->act_list;
+    r.counts = ctx->count_out;
+    r.n = ctx->B;
+    // ... and so are, in a whole round, the positions to propose, once a round of this decode has counted them
+    r.follow_need = phases == 3 && ctx->seq_launched > ctx->seq_floor ? 1 : 0;
+  } else {
+    const Cover cv = cover(ctx);
+    if (cv.n == 0) return TSD_OK;
+    r.act = cv.act;
+    r.n = cv.n;
+  }
+  r.P = c.patch;
+  r.phases = phases;
+  r.step_only = step_only ? 1 : 0;
+  r.prev = ctx->prev;
+  r.pending = ctx->pending;
+  r.X = ctx->X;
+  r.x_stride = (long)c.K * c.patch;
+  r.mu_p = ctx->mu_p;
+  r.mu_stride = step_only ? c.patch : (long)(c.K + 1) * c.patch;
+  r.exchange = ctx->small_exchange;
+  r.k_max = ctx->K_max;
+  r.flags = ctx->small_flags;
+  r.epoch = ctx->small_epoch;
+  ctx->small_epoch += (unsigned)small_round_stages(c);
+  r.status = ctx->count_out + kGaveUp;
+  r.host_status = ctx->host_counts + 3;
+  r.scale = 1.0f / std::sqrt(64.0f);
+  HIP_TRY(ctx, launch_small_round(r, ctx, st));
   return TSD_OK;
 }
 
@@ -809,6 +897,7 @@ int accept_commit_impl(tsd_ctx* ctx, const int32_t* forced, int K, hipStream_t s
     a.inv2sq2_vec = ctx->diag + c.patch;
     a.logdet_dev = ctx->diag + 3 * c.patch;
   }
+  a.gave_up = ctx->small_round ? ctx->count_out + kGaveUp : nullptr;
   a.key0 = (unsigned)(c.seed & 0xFFFFFFFFull);
   a.key1 = (unsigned)(c.seed >> 32);
   a.threshold = (c.flags & TSD_FLAG_THRESHOLD_RULE) ? 1 : 0;
@@ -903,13 +992,24 @@ int tsd_create(const tsd_config* cfg, void* arena_dev, size_t arena_bytes, tsd_c
     // their deliveries; without them tsd_num_active copies the counts back and waits on the stream
     int* hc = nullptr;
     if (!(cfg->flags & TSD_FLAG_NO_PINNED_COUNTS) && hipHostMalloc((void**)&hc, 64, hipHostMallocDefault) == hipSuccess && hc) {
-      hc[0] = hc[1] = hc[2] = 0;
+      for (int i = 0; i < 16; ++i) hc[i] = 0;
       if (hipMemset(ctx->count_out + 4, 0, 4) == hipSuccess) {
         ctx->host_counts = hc;
         ctx->seq_ready = true;
       } else {
         (void)hipHostFree(hc);
       }
+    }
+    (void)hipGetLastError();
+  }
+  if (ctx->skinny && ctx->host_counts && small_round_ok(*cfg) && !(cfg->flags & (TSD_FLAG_SAMPLE_PROPOSALS | TSD_FLAG_NAIVE_VERIFY))) {
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess && cus >= kSmallRoundWorkgroups) {
+      e = hipMemset(ctx->small_flags, 0, (size_t)kSmallRoundWorkgroups * kSmallRoundFlagWords * 4);
+      if (e == hipSuccess) e = hipMemset(ctx->count_out + kGaveUp, 0, 4);
+      ctx->small_round = e == hipSuccess;
     }
     (void)hipGetLastError();
   }
@@ -1039,6 +1139,11 @@ int tsd_prefill(tsd_ctx* ctx, const float* series_dev, int32_t B, int32_t n_ctx_
   const int P = c.patch, N = n_ctx_patches, T = (horizon_steps + P - 1) / P;
   if ((long)N + T + ctx->K_max > c.max_tokens) return fail(ctx, TSD_E_OUT_OF_RANGE, "n_ctx_patches + ceil(horizon/P) + K exceeds max_tokens");
   hipStream_t st = (hipStream_t)stream;
+  if (gave_up(ctx)) {  // what gave up is abandoned: its launches drain, and decoding starts over
+    HIP_TRY(ctx, hipStreamSynchronize(st));
+    HIP_TRY(ctx, launch_fill_int(ctx->count_out + kGaveUp, 0, 1, st));
+    __atomic_store_n(&ctx->host_counts[3], 0, __ATOMIC_RELAXED);
+  }
   ctx->prefilled = false;
   ctx->n_act = -1;
   ctx->seq_floor = ctx->seq_launched;
@@ -1090,7 +1195,7 @@ int tsd_prefill(tsd_ctx* ctx, const float* series_dev, int32_t B, int32_t n_ctx_
         ps.B = std::min(chunk, B - s0);
         ps.s0 = s0;
         ps.nq = nq;
-        ps.skinny = context_skinny(ctx, nq);
+        ps.skinny = context_skinny(ctx, B, nq);
         ps.base_pos = nullptr;
         ps.pos_off = 0;
         ps.src0 = ctx->znorm + (size_t)s0 * N * P;
@@ -1150,7 +1255,7 @@ int tsd_refill(tsd_ctx* ctx, const int32_t* slots_host, int32_t n, const float* 
       ps.B = std::min(chunk, n - s0);
       ps.act = ctx->refill_list + s0;
       ps.nq = nq;
-      ps.skinny = context_skinny(ctx, nq);
+      ps.skinny = context_skinny(ctx, n, nq);
       ps.base_pos = nullptr;
       ps.pos_off = 0;
       ps.src0 = ctx->znorm;  // rows are gathered by slot
@@ -1193,6 +1298,7 @@ int tsd_draft_propose(tsd_ctx* ctx, void* stream) {
   // Step 1 ingests two tokens per series: the token just before the pending one and the pending
   // one.  After a fully accepted round the draft cache lacks the former (it proposed x_K but
   // never consumed it); for the other series the rewrite stores identical values.
+  if (!ctx->fused_draft && use_small_round(ctx, st)) return run_small_round(ctx, 1, false, st);
   const Cover cv = cover(ctx);
   if (cv.n == 0) return TSD_OK;
   if (ctx->fused_draft) {
@@ -1322,6 +1428,7 @@ int tsd_target_verify(tsd_ctx* ctx, void* stream) {
   if (rc) return rc;
   const tsd_config& c = ctx->cfg;
   const int P = c.patch, K = c.K;
+  if (use_small_round(ctx, (hipStream_t)stream)) return run_small_round(ctx, 2, false, (hipStream_t)stream);
   const int Kr = round_positions(ctx);  // boundaries beyond Kr + 1 belong to patches no active series can commit
   const Cover cv = cover(ctx);
   if (cv.n == 0) return TSD_OK;
@@ -1372,18 +1479,26 @@ int tsd_round(tsd_ctx* ctx, void* stream) {
   const bool deliver = ctx->host_counts && ctx->seq_ready;
   const int need_before = ctx->need_lb;  // a round commits at most K + 1 patches per series
   if (!(ctx->cfg.flags & TSD_FLAG_NO_COMPACT)) peek_counts(ctx);
+  const bool small = use_small_round(ctx, (hipStream_t)stream);
   const int cls = device_counts(ctx) ? size_class(ctx) : 0;
   ctx->capture_rows = class_rows(ctx, cls);
-  rc = run_graphed(ctx, &ctx->graph_round[round_positions(ctx)][cls], (hipStream_t)stream, [&]() {
+  auto body = [&]() {
     int r;
-    if ((r = tsd_draft_propose(ctx, stream))) return r;
-    if ((r = tsd_target_verify(ctx, stream))) return r;
+    if (small && !ctx->fused_draft) {
+      ctx->injected = false;
+      if ((r = run_small_round(ctx, 3, false, (hipStream_t)stream))) return r;
+    } else {
+      if ((r = tsd_draft_propose(ctx, stream))) return r;
+      if ((r = tsd_target_verify(ctx, stream))) return r;
+    }
     if ((r = tsd_accept_commit(ctx, nullptr, stream))) return r;
     if (deliver)
       HIP_TRY(ctx, launch_compact_active(ctx->active, ctx->committed, ctx->T, ctx->B, compact_target(ctx), ctx->count_out,
                                          ctx->host_counts, (hipStream_t)stream));
     return (int)TSD_OK;
-  });
+  };
+  // (the resident kernel is not captured: its launches are kept apart from other handles' by events; three launches need no graph)
+  rc = small ? body() : run_graphed(ctx, &ctx->graph_round[round_positions(ctx)][cls], (hipStream_t)stream, body);
   if (rc == TSD_OK) {
     // (a replayed graph does not pass through accept_commit_impl: keep the bound on the patches still needed honest here)
     ctx->need_lb = std::max(0, need_before - (ctx->cfg.K + 1));
@@ -1399,6 +1514,10 @@ int tsd_target_step(tsd_ctx* ctx, void* stream) {
   int rc = require_ready(ctx, true);
   if (rc) return rc;
   const int P = ctx->cfg.patch;
+  if (use_small_round(ctx, (hipStream_t)stream)) {
+    if ((rc = run_small_round(ctx, 2, true, (hipStream_t)stream))) return rc;
+    return accept_commit_impl(ctx, nullptr, 0, (hipStream_t)stream);
+  }
   return run_graphed(ctx, &ctx->graph_step, (hipStream_t)stream, [&]() {
     Pass ps;
     std::memset(&ps, 0, sizeof(ps));

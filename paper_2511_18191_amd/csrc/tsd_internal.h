@@ -83,7 +83,7 @@ struct GemmP {
   long w_stride;         // elements between consecutive experts' matrices in W
   int n_mtiles;          // entries of tile_map
   int force_bm;          // row-tile size the map was built for (0 = pick by problem size)
-  int allow_skinny;      // the handle runs its <= 32-row passes through the skinny kernel
+  int allow_skinny;      // 1: the handle runs its <= 32-row passes through the skinny kernel; 2: and this one, in tiles of 32 rows
   int no_wide;           // never pick the direct-to-LDS wide-tile kernels (gemm_wide.hip)
   // EP_HEAD
   float* out;
@@ -180,6 +180,55 @@ hipError_t launch_repack_fragments(const void* src, void* dst, int N, int K, int
 hipError_t prepare_draft_fused();
 hipError_t launch_draft_fused(const DraftFusedP& p, hipStream_t st);
 
+// ---- decode passes of at most 32 rows as one resident kernel: see small_round.hip ----
+constexpr int kSmallRoundWorkgroups = 256;  // one per compute unit
+constexpr int kSmallRoundFlagWords = 16;    // words between two workgroups' flags
+struct SmallProd {    // one product of the chain
+  const bf16* W;      // [N][K], layer 0's
+  int K, units;       // units: workgroups that own columns of it,
+  int cs;             // 2^cs columns each (4, 8 or 16)
+  int per, used;      // k-steps of 32 per slab, slabs (see product_of)
+};
+struct SmallModel {
+  SmallProd embed, qkv, out, up, down, head;
+  size_t wstride;                             // bytes from one layer's matrices to the next's
+  bf16* kv_pool;                              // layer after layer
+  size_t layer_pool_elems;
+  const float *rope_cos, *rope_sin;           // [max_tokens][32]
+  int L, D, F, Hh;
+  size_t slab_bytes, pass_bytes;              // exchange buffer: per layer, per pass
+};
+struct SmallRoundP {
+  SmallModel m[2];                            // TSD_TARGET, TSD_DRAFT
+  const int* page_table;
+  int pt_stride, PT, pt_shift;
+  const int* len;
+  const int* act;                             // slot j is series act[j] (NULL: series j)
+  const int* counts;                          // device-side {listed series, most patches still needed} (NULL: n series)
+  int n;                                      // listed series at most
+  int K, P;                                   // positions at most ...
+  int follow_need;                            // ... and no more than counts[1]
+  int phases;                                 // 1: draft steps, 2: target pass
+  int step_only;                              // target pass over the pending token alone
+  const float *prev, *pending;                // [B][P]
+  float* X;
+  long x_stride;
+  float* mu_p;
+  long mu_stride;
+  void* exchange;                             // what workgroups hand each other (small_round_exchange_bytes)
+  int k_max;                                  // K the exchange buffer was sized for
+  unsigned* flags;
+  unsigned epoch;                             // what the flags hold at most before this launch
+  int *status, *host_status;                  // device and pinned host word, set to 1 by a launch that gave up waiting
+  float scale;                                // 1 / sqrt(head_dim)
+};
+bool small_round_ok(const tsd_config& c);
+void small_round_model(const tsd_model_cfg& c, int patch, const bf16* W_e, const bf16* W_h, const bf16* Wqkv, const bf16* Wo, const bf16* W1,
+                       const bf16* W2, SmallModel* m);
+size_t small_round_exchange_bytes(const tsd_config& c);
+int small_round_stages(const tsd_config& c);
+hipError_t launch_small_round(const SmallRoundP& p, const void* owner, hipStream_t st);
+
 struct PackP {
   const float* W;     // [K][N] row-major source (y = x W)
   const float* gain;  // [K] or NULL: folded as W'[n][k] = gain[k] * W[k][n]
@@ -242,6 +291,7 @@ struct AcceptP {
   // mode 0 is the unsynchronised round in one launch
   int mode;
   int* sync;
+  const int* gave_up;  // nullable: the pass that feeds this step did not finish: commit nothing
 };
 hipError_t launch_accept(const AcceptP& p, hipStream_t st);
 hipError_t launch_fill_int(int* p, int value, int n, hipStream_t st);

@@ -1,0 +1,73 @@
+"""Decode passes of at most 32 rows run as one resident kernel: lock-step with the oracle, and bit for bit the kernels it
+replaces, over the sizes where its indexing changes (row tiles of 4, 8, 16 and 2 x 16, columns per workgroup, slabs that are
+not full, patches that are no whole k-step, more cached keys than are fetched together), and two handles at a time."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2511_18191_amd as tsd
+from harness import TOL, Case, lockstep
+from synth import ModelCfg
+
+pytestmark = pytest.mark.gpu
+
+D1 = ModelCfg(1, 64, 1, 96)
+
+
+@pytest.mark.parametrize("B,K,target,draft,P,N,T", [
+    (1, 1, None, None, 96, 6, 3), (2, 1, None, None, 96, 6, 3), (1, 4, None, None, 96, 6, 6), (1, 15, None, None, 96, 6, 20),
+    (2, 15, None, None, 96, 6, 18), (16, 1, None, None, 96, 6, 3), (8, 3, None, None, 96, 6, 5),   # 2 .. 32 rows
+    (3, 4, ModelCfg(2, 192, 3, 352), D1, 48, 5, 6),                # 6 and 11 k-steps, a patch of one and a half
+    (5, 2, ModelCfg(1, 384, 6, 1536), ModelCfg(2, 128, 2, 160), 16, 4, 5),
+    (2, 4, ModelCfg(1, 1024, 16, 4096), ModelCfg(1, 320, 5, 1280), 96, 4, 6),   # the widest products it takes
+    (2, 3, ModelCfg(1, 128, 2, 256), D1, 16, 300, 5),              # ten 32-key steps, four at a time
+])
+def test_lockstep(B, K, target, draft, P, N, T):
+    over = dict(patch=P, context=N * P)
+    if target:
+        over.update(target=target, draft=draft)
+    case = Case("mini2", B=B, K=K, horizon=T * P, random_gains=True, **over)
+    sess = case.session()
+    # (proposal 15 is the end of a chain of 15 bf16 passes, each within PASS_TOL = 8e-3 of exact on its own inputs, which lockstep
+    #  asserts for every one of them; independent roundings add up to 8e-3 sqrt(15) = 3.1e-2, twice that is allowed)
+    tol = TOL["bf16"] if K < 15 else 6e-2
+    # (PASS_TOL is a bound on whole patches; the largest relative error over patches of 16 values spreads further: 8.42e-3 here and
+    #  8.42e-3 kernel by kernel)
+    rep = lockstep(case, sess, tol=tol, per_pass=P > 16)
+    assert rep["max_rel_X"] <= tol and rep["max_rel_mu_p"] <= tol, rep
+    # a whole forecast and the target-only steps: the same bits as kernel by kernel (a handle without pinned host words)
+    ref = case.session(flags=tsd.TSD_FLAG_NO_PINNED_COUNTS)
+    for s in (sess, ref):
+        s.prefill(case.context, case.cfg.n_ctx, case.cfg.horizon)
+        s.run_rounds()
+    np.testing.assert_array_equal(sess.get_forecast().cpu().numpy(), ref.get_forecast().cpu().numpy())
+    for s in (sess, ref):
+        s.reset_decode()
+        for _ in range(T):
+            s.target_step()
+    np.testing.assert_array_equal(sess.get_forecast().cpu().numpy(), ref.get_forecast().cpu().numpy())
+    sess.close()
+    ref.close()
+
+
+def test_two_handles_on_two_streams():
+    """Rounds of two handles enqueued alternately without waiting give what each gives alone."""
+    cases = [Case("mini2", B=2), Case("mini3", B=3)]
+    alone = []
+    for c in cases:
+        s = c.session()
+        s.prefill(c.context, c.cfg.n_ctx, c.cfg.horizon)
+        s.run_rounds()
+        alone.append(s.get_forecast().cpu().numpy())
+        s.close()
+    sess = [c.session() for c in cases]
+    for c, s in zip(cases, sess):
+        s.prefill(c.context, c.cfg.n_ctx, c.cfg.horizon)
+    torch.cuda.synchronize()
+    for _ in range(max(c.cfg.T for c in cases)):      # a round commits at least one patch
+        for s in sess:
+            s.round()
+    for s, ref in zip(sess, alone):
+        assert s.num_active() == 0
+        np.testing.assert_array_equal(s.get_forecast().cpu().numpy(), ref)
+        s.close()
