@@ -74,6 +74,7 @@ extern "C" {
 #define TSD_FLAG_NO_FUSED_DRAFT 1024u /* always run the draft phase kernel by kernel                       */
 #define TSD_FLAG_FUSED_DRAFT 2048u /* run the draft phase as one launch wherever that kernel is supported */
 #define TSD_FLAG_NO_WIDE_GEMM 4096u /* never use the wide-tile direct-to-LDS GEMM kernels (same bits, for A/B timing) */
+#define TSD_FLAG_CLEAR_REST 8192u  /* tsd_accept_commit_static: zero the committed rows' buffer behind the round's last patch */
 
 typedef struct tsd_ctx tsd_ctx; /* opaque */
 
@@ -218,21 +219,18 @@ int tsd_accept_commit(tsd_ctx* ctx, const int32_t* forced_len_dev, void* stream)
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid it) and that run their own models: the acceptance / correction / commit step of ONE
  * round (the rule of tsd_accept_commit, same kernel) on caller tensors, without a handle or an arena.  The
- * state the kernel keeps (per-series round counter, committed count, active flag, pending / previous token,
- * counters, the synchronised round's minimum) lives in a fixed device array inside the library, about 2.8 MB,
- * held on every GPU the library has run this call on until the process ends; the call allocates nothing and
- * frees nothing.  Limits: B <= 4096, K <= 16, B * P <= 262144; larger sizes return TSD_E_OUT_OF_RANGE.
+ * call allocates nothing, frees nothing and keeps nothing but the synchronised round's minimum, one device word
+ * per GPU inside the library.  Limits: B <= 4096, K <= 16, B * P <= 262144; larger sizes return TSD_E_OUT_OF_RANGE.
  *   inputs (device): X, mu_q [B,K,P]; mu_p [B,K+1,P]; round_dev int32 [B] (nullable = all 0): the second word
  *     of each series' Philox counter, as the handle keeps it per series.
- *   sigma_p, sigma_q, fallback_r, seed: as in tsd_config.  flags: TSD_FLAG_NO_TEMPERING, TSD_FLAG_THRESHOLD_RULE
- *     and TSD_FLAG_BATCH_SYNC apply; any other bit is an error.
+ *   sigma_p, sigma_q, fallback_r, seed: as in tsd_config.  flags: TSD_FLAG_NO_TEMPERING, TSD_FLAG_THRESHOLD_RULE,
+ *     TSD_FLAG_BATCH_SYNC and TSD_FLAG_CLEAR_REST apply; any other bit is an error.
  *   outputs (device): n_acc int32 [B]: leading accepts found by each series' own test; commit [B,K+1,P]: rows
  *     0..n-1 = x_1..x_n and row n = the corrected (n < K) or bonus (n = K) patch, n = n_acc or, synchronised, the
- *     batch's smallest; later rows are left untouched; ell, logu [B,K] (nullable): the statistics and log draws,
+ *     batch's smallest; later rows are left untouched (zeroed with TSD_FLAG_CLEAR_REST); ell, logu [B,K] (nullable): the statistics and log draws,
  *     NaN where a position was not tested.
- * Every call on a GPU shares that GPU's array and overwrites the previous call's state (nothing carries over:
- * the state is set up afresh by a small kernel at the start of every call); calls that overlap on one GPU,
- * on different streams or from different threads, race.  Asynchronous on `stream`. */
+ * Nothing carries over from one call to the next.  Synchronised calls on a GPU share that GPU's word: those that
+ * overlap, on different streams or from different threads, race.  Asynchronous on `stream`. */
 int tsd_accept_commit_static(const float* X_dev, const float* mu_q_dev, const float* mu_p_dev, const int32_t* round_dev,
                              int32_t B, int32_t K, int32_t P, float sigma_p, float sigma_q, float fallback_r,
                              uint64_t seed, uint32_t flags, int32_t* n_acc_dev, float* commit_dev, float* ell_dev,

@@ -10,7 +10,7 @@ TSD_F32, TSD_BF16 = 0, 1
 TSD_TARGET, TSD_DRAFT = 0, 1
 TSD_FLAG_SCRAMBLE_PAGES, TSD_FLAG_NO_TEMPERING, TSD_FLAG_NO_GRAPH, TSD_FLAG_NO_COMPACT, TSD_FLAG_NO_SKINNY, TSD_FLAG_SAMPLE_PROPOSALS, TSD_FLAG_NAIVE_VERIFY = 1, 2, 4, 8, 16, 32, 64
 TSD_FLAG_THRESHOLD_RULE, TSD_FLAG_BATCH_SYNC, TSD_FLAG_NO_PINNED_COUNTS, TSD_FLAG_NO_FUSED_DRAFT, TSD_FLAG_FUSED_DRAFT = 128, 256, 512, 1024, 2048
-TSD_FLAG_NO_WIDE_GEMM = 4096
+TSD_FLAG_NO_WIDE_GEMM, TSD_FLAG_CLEAR_REST = 4096, 8192
 KERNEL_CLASSES = ["embed", "qkv", "attn", "resid", "gelu", "head", "accept", "route", "draft"]   # TSD_K_* order
 
 
@@ -125,6 +125,12 @@ def _check(rc, ctx=None):
         raise TsdError(rc, msg.decode() if msg else "")
 
 
+def _raw_stream(device):
+    """torch's current stream on `device` as a pointer (without building a Stream object, which takes longer than a launch)."""
+    import torch
+    return torch._C._cuda_getCurrentRawStream(device.index if device.index is not None else torch.cuda.current_device())
+
+
 def bench_gemm(A, Wt, out=None, variant=0):
     """C = A @ Wt.T through libtsd's tiled GEMM on torch's current stream.  A: [M,K], Wt: [N,K]
     (both bf16 or both fp32, on the GPU); returns fp32 [M,N].  variant 1 fuses the RMSNorm row
@@ -147,14 +153,18 @@ def accept_commit_static(X, mu_q, mu_p, sigma_p, sigma_q=None, rounds=None, fall
     import torch
     B, K, P = X.shape
     dev = X.device
-    n_acc = torch.full((B,), -7, dtype=torch.int32, device=dev)
-    commit = torch.zeros(B, K + 1, P, dtype=torch.float32, device=dev)
-    ell = torch.zeros(B, K, dtype=torch.float32, device=dev) if want_taps else None
-    logu = torch.zeros(B, K, dtype=torch.float32, device=dev) if want_taps else None
-    ptr = lambda t: None if t is None else t.data_ptr()
-    _check(lib().tsd_accept_commit_static(X.data_ptr(), mu_q.data_ptr(), mu_p.data_ptr(), ptr(rounds), B, K, P, sigma_p,
-                                          sigma_p if sigma_q is None else sigma_q, fallback_r, seed, flags, n_acc.data_ptr(),
-                                          commit.data_ptr(), ptr(ell), ptr(logu), torch.cuda.current_stream(dev).cuda_stream))
+    # (the kernel writes every entry: nothing to fill beforehand)
+    n_acc = torch.empty(B, dtype=torch.int32, device=dev)
+    commit = torch.empty(B, K + 1, P, dtype=torch.float32, device=dev)
+    ell = logu = e_ptr = l_ptr = None
+    if want_taps:
+        ell, logu = torch.empty(2, B, K, dtype=torch.float32, device=dev).unbind(0)
+        e_ptr, l_ptr = ell.data_ptr(), logu.data_ptr()
+    rc = lib().tsd_accept_commit_static(X.data_ptr(), mu_q.data_ptr(), mu_p.data_ptr(), None if rounds is None else rounds.data_ptr(),
+                                        B, K, P, sigma_p, sigma_p if sigma_q is None else sigma_q, fallback_r, seed, flags | TSD_FLAG_CLEAR_REST,
+                                        n_acc.data_ptr(), commit.data_ptr(), e_ptr, l_ptr, _raw_stream(dev))
+    if rc:
+        _check(rc)
     return dict(n_acc=n_acc, commit=commit, ell=ell, logu=logu)
 
 

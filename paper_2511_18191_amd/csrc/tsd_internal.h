@@ -269,13 +269,13 @@ struct AcceptP {
   float* pending;
   float* prev;
   float* forecast;    // [B][T*P] normalised
-  int* len;
+  int* len;           // NULL: a call without a handle (nothing committed before, no state but n_acc and the taps is kept)
   int* committed;
-  int* round;
+  int* round;         // (without a handle: read only, NULL = 0)
   int* active;
   int* n_acc;         // [B]
   float* ell;
-  float* logu;        // [B][max(K,1)]
+  float* logu;        // [B][max(K,1)] (without a handle: nullable)
   long long* stat;    // [B][5]: rounds, tested, accepted, committed, near_ties
   int B, K, P, T;
   float inv2sp2, inv2sq2, logdet, temper;  // temper = 1 (Eq. 5) or P (ablation without 1/d)
@@ -291,6 +291,7 @@ struct AcceptP {
   // mode 0 is the unsynchronised round in one launch
   int mode;
   int* sync;
+  int clear_rest;  // zero the forecast's rows behind the round's last patch, up to T
   const int* gave_up;  // nullable: the pass that feeds this step did not finish: commit nothing
 };
 hipError_t launch_accept(const AcceptP& p, hipStream_t st);
