@@ -287,14 +287,12 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
   load_global(kt0 + 1, ra1, rb1);
   // Epilogue inputs that do not depend on the product are requested now, so their latency hides
   // behind the main loop: the KV position/page of each row (QKV), the old residual values (RESID).
-  int my_pos = 0, my_page = 0;
+  int2 my_meta = make_int2(0, 0);
   if constexpr (EP == EP_QKV) {
-    if (tid < BM) {
-      const int gm = min(m0 + tid, m_lim - 1);
-      const int bl = gm / p.nq, t = gm - bl * p.nq, b = p.act ? p.act[bl] : p.s0 + bl;
-      my_pos = (p.base_pos ? p.base_pos[b] : 0) + p.pos_off + t;
-      my_page = p.page_table[(long)b * p.pt_stride + (my_pos >> p.pt_shift)];
-    }
+    if (tid < BM) my_meta = p.row_meta[min(m0 + tid, m_lim - 1)];
+  }
+  if constexpr (AM == A_TOK) {
+    if (p.row_meta && tn == 0 && tid < BM) my_meta = row_meta_of(p, min(m0 + tid, m_lim - 1));
   }
   constexpr bool kPrefetchC = (EP == EP_RESID) && BM == 64;
   constexpr int NPRE = kPrefetchC ? 64 * (BN / 4) / NT : 1;
@@ -347,9 +345,12 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
 
   if constexpr (EP == EP_QKV) {
     if (tid < BM) {
-      row_pos[tid] = my_pos;
-      row_page[tid] = my_page;
+      row_pos[tid] = my_meta.x;
+      row_page[tid] = my_meta.y;
     }
+  }
+  if constexpr (AM == A_TOK) {
+    if (p.row_meta && tn == 0 && tid < BM && m0 + tid < m_lim) p.row_meta[m0 + tid] = my_meta;
   }
   // ---- RMSNorm row scale --------------------------------------------------------------------
   if constexpr (kNorm) {

@@ -88,12 +88,13 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const GemmP p) {
   // epilogue inputs that do not depend on the product
   if constexpr (EP == EP_QKV) {
     if (tid < kRowsMax) {
-      const int gm = m0 + min(tid, M - 1);
-      const int bl = gm / p.nq, t = gm - bl * p.nq, b = p.act ? p.act[bl] : p.s0 + bl;
-      const int pos = (p.base_pos ? p.base_pos[b] : 0) + p.pos_off + t;
-      row_pos[tid] = pos;
-      row_page[tid] = p.page_table[(long)b * p.pt_stride + (pos >> p.pt_shift)];
+      const int2 meta = p.row_meta[m0 + min(tid, M - 1)];
+      row_pos[tid] = meta.x;
+      row_page[tid] = meta.y;
     }
+  }
+  if constexpr (AM == A_TOK) {
+    if (p.row_meta && blockIdx.x == 0 && tid < M) p.row_meta[m0 + tid] = row_meta_of(p, m0 + tid);
   }
 
   // ---- this wavefront's share of K, in steps of 32 ----

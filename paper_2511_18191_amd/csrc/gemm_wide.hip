@@ -5,7 +5,8 @@
 // What bounds a GEMM on this chip is the number of requests its compute units send to L2 (counters: at 64 bytes per
 // request the 128 L2 channels saturate near one request per clock each, ~12 TB/s, long before the matrix cores do).
 // So a k-tile is 64 wide (a row of it is one whole 128-byte cache line: one request instead of two) and the tile is
-// as large as the product's tile count allows (256 x 128 where that still fills the chip, else 128 x 128).
+// as large as the product's tile count allows (256 x 128 where that still fills the chip, else 128 x 128, and 64 x 64 with
+// a deeper ring for products of less than one such tile per compute unit).
 //
 //   * A stage is its rows back to back (A rows, then B rows), 128 bytes per row; the eight 16-byte chunks of a row
 //     sit at chunk ^ ((row >> 1) & 7), which makes the fragment reads (32 consecutive rows, one chunk) conflict-free
@@ -21,17 +22,8 @@
 //     16-byte chunk position of a 64-wide k-run, each a chain of packed bf16 dot products, combined as
 //     ((P0 + P4) + (P2 + P6)) + ((P1 + P5) + (P3 + P7)).  The products accumulate k in the same order with the
 //     same instruction, so both kernels give the same bits and the launcher may pick either by the product's shape.
-#include <cstdlib>
-
 #include "gemm_epilogue.h"
 #include "tsd_internal.h"
-
-// Timing experiments (never defined in the library build): bits of TSD_WIDE_PROBE switch pieces of the k loop off
-// to price them (1 loads, 2 fragment reads, 4 MFMAs, 8 barrier, 16 epilogue arithmetic and stores, 32 the whole epilogue);
-// the results are then garbage, every access stays in bounds and every wavefront meets the same barriers.
-#ifndef TSD_WIDE_PROBE
-#define TSD_WIDE_PROBE 0
-#endif
 
 namespace tsd {
 
@@ -117,15 +109,31 @@ __global__ __launch_bounds__(S::NT, 2) void gemm_wide_kernel(const GemmP p) {
     Wp += (long)tmap.x * p.w_stride;
   }
 
+  // Epilogue inputs that do not depend on the product are requested before the operands (loads return in order, so nothing
+  // older than the stages' loads disturbs their counted waits) and land behind the main loop.
+  int2 my_meta = make_int2(0, 0);
   if constexpr (EP == EP_QKV) {
-    for (int r = tid; r < BM; r += S::NT) {
-      const int gm = min(m0 + r, m_lim - 1);
-      const int bl = gm / p.nq, t = gm - bl * p.nq, b = p.act ? p.act[bl] : p.s0 + bl;
-      const int pos = (p.base_pos ? p.base_pos[b] : 0) + p.pos_off + t;
-      row_pos[r] = pos;
-      row_page[r] = p.page_table[(long)b * p.pt_stride + (pos >> p.pt_shift)];
-    }
+    static_assert(BM <= S::NT, "one row per lane");
+    my_meta = p.row_meta[min(m0 + min(tid, BM - 1), m_lim - 1)];
   }
+
+  // EP_RESID: the old residual values of a pass are requested one pass ahead (those of pass 0 before the accumulators'
+  // trip through LDS; of 64-row tiles, which have one pass only, before the operands), so that their latency hides
+  // behind LDS traffic and the previous pass's stores instead of being paid once per item (a read that follows a store
+  // to the same array cannot be moved up by the compiler).
+  constexpr int NPRE = (EP == EP_RESID) ? 64 * (BN / 4) / S::NT : 1;
+  float4 oldc[2][NPRE];
+  auto fetch_old = [&](int pass, float4* dst) {
+    if constexpr (EP == EP_RESID) {
+#pragma unroll
+      for (int it = 0; it < NPRE; ++it) {
+        const int g = tid + it * S::NT;
+        const int gm = min(m0 + pass * 64 + g / (BN / 4), m_lim - 1), gn = n0 + (g % (BN / 4)) * 4;  // (N is a multiple of BN)
+        dst[it] = *reinterpret_cast<const float4*>(p.Cf + (long)gm * N + gn);
+      }
+    }
+  };
+  if constexpr (BM == 64) fetch_old(0, oldc[0]);
 
   // ---- loads: wavefront w fills the stage rows [NL * RPL * w, NL * RPL * (w + 1)); stage row R is A row R (R < BM) or B
   // row R - BM.  Lane l of load j covers row (w NL + j) RPL + l / CPR and the physical chunk l % CPR of it, i.e. the
@@ -149,7 +157,6 @@ __global__ __launch_bounds__(S::NT, 2) void gemm_wide_kernel(const GemmP p) {
     gp[j] = row + chunk * 8 - (j * 1024 - BIAS) / 2;
   }
   auto issue_loads = [&](int slot, int kt) {
-    if constexpr (TSD_WIDE_PROBE & 1) return;  // probe: no operand loads
     void __attribute__((address_space(3)))* base = TSD_LDS_PTR(smem + slot * STAGE + wid * REGION + BIAS);
     issue_stage_loads<0, NL, BIAS>(gp, (long)kt * BK, base);
   };
@@ -196,7 +203,6 @@ __global__ __launch_bounds__(S::NT, 2) void gemm_wide_kernel(const GemmP p) {
   // (a bare s_barrier: __syncthreads() would also wait for every load in flight)
   bf16x8 fa[2][TM], fb[2][TN];
   auto read_frags = [&](int kt, int s, bf16x8* af, bf16x8* bfr) {
-    if constexpr (TSD_WIDE_PROBE & 2) return;  // probe: no fragment reads (the MFMAs run on whatever the registers hold)
     const unsigned char* st = smem + (kt % NS) * STAGE;
 #pragma unroll
     for (int i = 0; i < TM; ++i) af[i] = *reinterpret_cast<const bf16x8*>(st + offA[i] + (((2 * s + hi) ^ swA[i]) << 4));
@@ -217,13 +223,7 @@ __global__ __launch_bounds__(S::NT, 2) void gemm_wide_kernel(const GemmP p) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        if constexpr (TSD_WIDE_PROBE & 4) {  // probe: no MFMAs (the fragments are still consumed)
-          asm volatile("" ::"v"(af[i]), "v"(bfr[j]));
-        } else {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-        }
-      }
+      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
   };
   // `arrived`: an empty statement that uses a fragment set, placed BEFORE the next set's reads are issued.  The compiler
   // waits for LDS data right before its first use and cannot tell the two sets' reads apart by count here, so without it
@@ -247,10 +247,7 @@ __global__ __launch_bounds__(S::NT, 2) void gemm_wide_kernel(const GemmP p) {
       if constexpr (s + 1 < NSUB) {
         read_frags(kt, s + 1, fa[(s + 1) & 1], fb[(s + 1) & 1]);
       } else if constexpr (PEND >= 0) {
-        if constexpr (TSD_WIDE_PROBE & 8)  // probe: no barrier
-          asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        else
-          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(PEND) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(PEND) : "memory");
         if constexpr (REFILL) issue_loads(kt % NS, kt + NS);
         read_frags(kt + 1, 0, fa[(s + 1) & 1], fb[(s + 1) & 1]);
       }
@@ -268,8 +265,6 @@ __global__ __launch_bounds__(S::NT, 2) void gemm_wide_kernel(const GemmP p) {
 
   // ---- main loop (K is a multiple of 64, at least NS 64-wide runs) ------------------------------------------------------
   const int nk = K / BK;
-  // (nothing older may be in flight when the counted waits begin: the counts assume only the stages' loads)
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
   for (int s = 0; s < NS; ++s) issue_loads(s, s);
   asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 1) * NL) : "memory");  // k-tile 0 has landed for everybody
@@ -300,17 +295,17 @@ __global__ __launch_bounds__(S::NT, 2) void gemm_wide_kernel(const GemmP p) {
       fold(kt + 1);
     }
     // tail: k-tile nk - NS + t leaves NS - 2 - t stages in flight at its barrier; the last one has no barrier
-    if constexpr (NS == 2) {
-      tile(IC<0>{}, kt, IC<0>{}, IC<0>{});
-      fold(kt + 1);
-      tile(IC<0>{}, kt + 1, IC<-1>{}, IC<0>{});
-    } else {
-      tile(IC<0>{}, kt, IC<NL>{}, IC<0>{});
-      fold(kt + 1);
-      tile(IC<0>{}, kt + 1, IC<0>{}, IC<0>{});
-      fold(kt + 2);
-      tile(IC<0>{}, kt + 2, IC<-1>{}, IC<0>{});
-    }
+    auto tail = [&](auto self, auto tc) {
+      constexpr int t = decltype(tc)::value;
+      if constexpr (t + 1 < NS) {
+        tile(IC<0>{}, kt + t, IC<(NS - 2 - t) * NL>{}, IC<0>{});
+        fold(kt + t + 1);
+        self(self, IC<t + 1>{});
+      } else {
+        tile(IC<0>{}, kt + t, IC<-1>{}, IC<0>{});
+      }
+    };
+    tail(tail, IC<0>{});
     if constexpr (kQuarters) {
       if (quarters) {  // the last run joins the sum of the first three
 #pragma unroll
@@ -334,6 +329,12 @@ __global__ __launch_bounds__(S::NT, 2) void gemm_wide_kernel(const GemmP p) {
     tile(IC<1>{}, kt + 3, IC<-1>{}, IC<0>{});
   }
 
+  if constexpr (EP == EP_QKV) {
+    if (tid < BM) {
+      row_pos[tid] = my_meta.x;
+      row_page[tid] = my_meta.y;
+    }
+  }
   // ---- RMSNorm row scale: this lane's chains are the chunk positions hi, 2 + hi, 4 + hi, 6 + hi ---------------------------
   if constexpr (kNorm) {
 #pragma unroll
@@ -345,32 +346,8 @@ __global__ __launch_bounds__(S::NT, 2) void gemm_wide_kernel(const GemmP p) {
   }
 
   // ---- epilogue, 64 rows at a time through LDS ------------------------------------------------------------------
-  // EP_RESID: the old residual values of a pass are requested one pass ahead (those of pass 0 before the accumulators'
-  // trip through LDS), so that their latency hides behind LDS traffic and the previous pass's stores instead of being
-  // paid once per item (a read that follows a store to the same array cannot be moved up by the compiler).
   auto read_c4 = [&](int row, int col) { return *reinterpret_cast<const float4*>(Cs + row * LDC + col); };
-  constexpr int NPRE = (EP == EP_RESID) ? 64 * (BN / 4) / S::NT : 1;
-  float4 oldc[2][NPRE];
-  auto fetch_old = [&](int pass, float4* dst) {
-    if constexpr (EP == EP_RESID) {
-#pragma unroll
-      for (int it = 0; it < NPRE; ++it) {
-        const int g = tid + it * S::NT;
-        const int gm = min(m0 + pass * 64 + g / (BN / 4), m_lim - 1), gn = n0 + (g % (BN / 4)) * 4;  // (N is a multiple of BN)
-        dst[it] = *reinterpret_cast<const float4*>(p.Cf + (long)gm * N + gn);
-      }
-    }
-  };
-  if constexpr (TSD_WIDE_PROBE & 32) {  // probe: no epilogue at all (the accumulators are still produced)
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) asm volatile("" ::"v"(acc[i][j][r]));
-    return;
-  }
-  fetch_old(0, oldc[0]);
+  if constexpr (BM != 64) fetch_old(0, oldc[0]);
 #pragma unroll
   for (int pass = 0; pass < BM / 64; ++pass) {
     __syncthreads();  // the stages (or the previous pass's rows) are no longer read
@@ -390,45 +367,51 @@ __global__ __launch_bounds__(S::NT, 2) void gemm_wide_kernel(const GemmP p) {
     }
     if (pass + 1 < BM / 64) fetch_old(pass + 1, oldc[(pass + 1) & 1]);
     __syncthreads();
-    if constexpr (TSD_WIDE_PROBE & 16) continue;  // probe: the accumulators' trip through LDS, but no epilogue arithmetic or stores
     epilogue_pass<bf16, EP, kNorm, BN, S::NT, EP == EP_RESID, true>(p, read_c4, row_scale, row_pos, row_page, m0, n0, pass, m_lim, N,
                                                                     tid, oldc[pass & 1]);
   }
 }
 
 // ---- host side -------------------------------------------------------------------------------------------------
-#ifndef TSD_WIDE_SHAPE_256
-#define TSD_WIDE_SHAPE_256 WideShape<256, 128, 64, 4, 2, 2>  // eight wavefronts of 64 x 64, one workgroup per compute unit
-#endif
-#ifndef TSD_WIDE_SHAPE_128
-#define TSD_WIDE_SHAPE_128 WideShape<128, 128, 64, 2, 2, 2>  // four wavefronts of 64 x 64, two workgroups per compute unit
-#endif
-using Wide256 = TSD_WIDE_SHAPE_256;
-using Wide128 = TSD_WIDE_SHAPE_128;
+using Wide256 = WideShape<256, 128, 64, 4, 2, 2>;  // eight wavefronts of 64 x 64, one workgroup per compute unit
+using Wide128 = WideShape<128, 128, 64, 2, 2, 2>;  // four wavefronts of 64 x 64, two workgroups per compute unit
+// Small products, mostly a decode pass's.  Four wavefronts of 32 x 32 leave a k-tile only 4 MFMAs per wavefront, so what
+// bounds such a tile is the way of its operands from L2 or HBM; four k-tiles in flight (64 KB, two workgroups per
+// compute unit) are the best ring: 1280x1536x512 8.1 -> 7.0 us, 512x3072x1024 11.9 -> 9.6, 558x2304x768 8.8 -> 8.0 against the
+// register-staged tiles (two k-tiles in flight).  Of the other depths three (48 KB, three workgroups) is as fast alone
+// and 2 % slower in a whole pass of 93 series, where the weights come from HBM; six (one workgroup) is 10 % slower.
+using Wide64 = WideShape<64, 64, 64, 2, 2, 4>;
 
 // Which row-tile size, if any, this product should take (0: the register-staged kernels of gemm.hip).
 int gemm_wide_bm(int dtype, int amode, int epi, const GemmP& p) {
   if (dtype != TSD_BF16 || p.no_wide) return 0;
   const bool combo = (amode == A_ACT && (epi == EP_STORE || epi == EP_RESID)) ||
                      (amode == A_NORM && (epi == EP_STORE || epi == EP_GELU || epi == EP_QKV));
-  if (!combo || (p.K % 64) || p.K < 192 || (p.N % 128)) return 0;
+  if (!combo || (p.K % 64) || p.K < 192) return 0;
+  // 64 x 64 tiles: every dense product that leaves less than a 128-row tile per compute unit, except the long
+  // contractions with at most one tile per unit.  Those are latency-bound chains of k-steps, where four groups of wavefronts
+  // that stream a quarter of K each (gemm.hip) are faster: 1280x512x2048 10.2 us split, 11.5 here; 512x1024x4096 17.2 / 18.9.
+  const bool split = amode == A_ACT && p.K >= kQuarterK && (long)((p.M + 63) / 64) * ((p.N + 63) / 64) <= 256;
+  const int narrow = !split && !p.tile_map && !p.src_row && !p.force_bm && p.K >= 64 * Wide64::NS && p.N % 64 == 0 ? 64 : 0;
+  if (p.N % 128) return narrow;
   // grouped products of the routed FFN: their tile map was built for force_bm-row tiles, and the 128-row map exists
   // only where the product already has 1.5 tiles per compute unit
   if (p.tile_map) return p.force_bm == 128 ? 128 : 0;
   if (p.src_row || p.force_bm) return 0;
-  static const int forced = [] { const char* e = getenv("TSD_WIDE_FORCE"); return e ? atoi(e) : 0; }();  // A/B timing aid
-  if (forced == 256 || forced == 128) return forced;
   const long cols = p.N / 128;
   const long t256 = (long)((p.M + 255) / 256) * cols, t128 = (long)((p.M + 127) / 128) * cols;
-  // Measured over the products of the configurations (narrow / 128 / 256 timed side by side, same bits): two
-  // workgroups of 128 x 128 per compute unit hide one's epilogue behind the other's k loop and win wherever there are
-  // plenty of tiles; the 256-row tiles (one workgroup per unit, fewest operand requests) win the long-K products
-  // with few tile columns; below about one tile per unit the 64 x 64 register-staged tiles keep more units busy.
+  // Measured over the products of the configurations (64 / 128 / 256 timed side by side, same bits): two workgroups of
+  // 128 x 128 per compute unit hide one's epilogue behind the other's k loop and win wherever there are plenty of tiles;
+  // the 256-row tiles (one workgroup per unit, fewest operand requests) win the long-K products with few tile columns.
+  // Below about one 128-row tile per unit 64 x 64 tiles keep more units busy (us, 64 / 128: 2048x1024x1024, 128 tiles
+  // of 128 rows, 9.9 / 14.0; 4096x768x768, 192, 11.5 / 11.6), from one tile on the larger tile wins (4096x1024x1024, 256,
+  // 17.9 / 16.1; 7424x768x768, 348, 21.2 / 18.4; 16343x384x384, 384, 16.5 / 14.6), short contractions need some more of
+  // them (7424x512x512, 232, 11.0 / 10.5; 12000x384x384, 282, 11.6 / 12.0).
   if (t128 >= 512) return 128;
   if (t128 >= 400 && t256 >= 200) return 256;
-  if (p.K >= 2048) return t256 >= 140 ? 256 : t128 >= 200 ? 128 : 0;
-  if (cols >= 12 && t128 >= 240) return 128;
-  return 0;
+  if (p.K >= 2048) return t256 >= 140 ? 256 : t128 >= 200 ? 128 : narrow;
+  if (t128 >= 384 || (t128 >= 240 && p.K >= 512)) return 128;
+  return narrow;
 }
 
 template <int AM, int EP, typename S>
@@ -442,7 +425,7 @@ static hipError_t launch_wide_t(const GemmP& p, hipStream_t st) {
 
 template <int AM, int EP>
 static hipError_t launch_wide_bm(int bm, const GemmP& p, hipStream_t st) {
-  return bm == 256 ? launch_wide_t<AM, EP, Wide256>(p, st) : launch_wide_t<AM, EP, Wide128>(p, st);
+  return bm == 256 ? launch_wide_t<AM, EP, Wide256>(p, st) : bm == 128 ? launch_wide_t<AM, EP, Wide128>(p, st) : launch_wide_t<AM, EP, Wide64>(p, st);
 }
 
 hipError_t launch_gemm_wide(int amode, int epi, int bm, const GemmP& p, hipStream_t st) {
@@ -458,6 +441,9 @@ template <int AM, int EP>
 static hipError_t raise_wide() {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_wide_kernel<AM, EP, Wide256>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)Wide256::SMEM);
+  if (e != hipSuccess) return e;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_wide_kernel<AM, EP, Wide64>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (int)Wide64::SMEM);
   if (e != hipSuccess) return e;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_wide_kernel<AM, EP, Wide128>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)Wide128::SMEM);

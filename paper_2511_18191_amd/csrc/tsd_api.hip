@@ -58,6 +58,7 @@ struct tsd_ctx {
   float* diag;  // [3P + 1]: 1/(2 s_p^2), 1/(2 s_q^2), s_q, then the log-det scalar (diagonal surrogate)
   bool diag_on = false;
   float diag_min_sp = 0.f;
+  int2* row_meta;  // position and cache page of every row of the pass in flight
   float* x;   // residual stream, fp32
   char* xb;   // its bf16 shadow (GEMM A operand in bf16 mode)
   char *qbuf, *abuf, *hbuf;
@@ -318,6 +319,7 @@ size_t carve(const tsd_config& c, tsd_ctx* ctx) {
   size_t o_diag = cv.take((size_t)(3 * P + 1) * 4);
   const size_t Dm = std::max(c.target.d_model, c.draft.d_model), Fm = std::max(c.target.d_ff, c.draft.d_ff);
   const size_t rows = workspace_rows(c);
+  size_t o_meta = cv.take(rows * 8);
   size_t o_xb = cv.take(rows * Dm * es);
   size_t o_x = cv.take(rows * Dm * 4), o_q = cv.take(rows * Dm * es), o_a = cv.take(rows * Dm * es), o_h = cv.take(rows * Fm * es);
   size_t o_trace = cv.take(kTraceMax * 8);
@@ -365,6 +367,7 @@ size_t carve(const tsd_config& c, tsd_ctx* ctx) {
     ctx->logu = (float*)at(o_logu);
     ctx->diag = (float*)at(o_diag);
     ctx->x = (float*)at(o_x);
+    ctx->row_meta = (int2*)at(o_meta);
     ctx->xb = at(o_xb);
     ctx->qbuf = at(o_q);
     ctx->abuf = at(o_a);
@@ -475,6 +478,13 @@ int run_pass(tsd_ctx* ctx, const Pass& ps, hipStream_t st) {
   g.n0 = ps.n0;
   g.act = ps.act;
   g.n_dev = ps.n_dev;
+  g.page_table = ctx->page_table;
+  g.pt_stride = ctx->pages_per_series;
+  g.pt_shift = __builtin_ctz(c.page_tokens);
+  g.base_pos = ps.base_pos;
+  g.pos_off = ps.pos_off;
+  g.s0 = ps.s0;
+  g.row_meta = ctx->row_meta;
   g.W = md.W_e;
   g.Cf = ctx->x;
   g.Cb = ctx->xb;
@@ -494,12 +504,7 @@ int run_pass(tsd_ctx* ctx, const Pass& ps, hipStream_t st) {
     q.W = md.layers[l].Wqkv;
     q.q_out = ctx->qbuf;
     q.kv_pool = pool;
-    q.page_table = ctx->page_table;
-    q.pt_stride = ctx->pages_per_series;
-    q.base_pos = ps.base_pos;
-    q.pos_off = ps.pos_off;
-    q.s0 = ps.s0;
-    q.act = ps.act;
+    q.row_meta = ctx->row_meta;
     q.n_dev = ps.n_dev;
     q.rope_cos = md.rope_cos;
     q.rope_sin = md.rope_sin;

@@ -75,6 +75,9 @@ struct GemmP {
   const int* n_dev;  // device-side series count for launches replayed from a graph: rows = min(M, *n_dev * nq) (NULL: M)
   const float* rope_cos;
   const float* rope_sin;  // [max_tokens][hd/2]
+  // [M] position and cache page of every row: written by the pass's patch embedding, read by its QKV products (looked up
+  // there, series list -> length -> page table, they were three dependent memory round trips in front of every layer's product)
+  int2* row_meta;
   int D, Hh, hd, PT;
   int pt_shift;  // log2(PT)
   // grouped (routed-FFN) mode: the row tiles come from a device-side map, one expert per tile
@@ -90,6 +93,15 @@ struct GemmP {
   long out_stride_b;
   int t_skip;
 };
+
+#if defined(__HIPCC__)
+// position and cache page of row gm of a pass
+__device__ __forceinline__ int2 row_meta_of(const GemmP& p, int gm) {
+  const int bl = gm / p.nq, t = gm - bl * p.nq, b = p.act ? p.act[bl] : p.s0 + bl;
+  const int pos = (p.base_pos ? p.base_pos[b] : 0) + p.pos_off + t;
+  return make_int2(pos, p.page_table[(long)b * p.pt_stride + (pos >> p.pt_shift)]);
+}
+#endif
 
 struct AttnP {
   const void* q;       // T [rows][D]

@@ -1,0 +1,36 @@
+"""The 64 x 64 direct-to-LDS tiles (products that leave less than a 128-row tile per compute unit) against the
+register-staged tiles, bit for bit, and against float64."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,N,K,variant", [
+    (1, 64, 256, 1), (63, 192, 256, 3), (64, 128, 320, 2), (65, 64, 512, 0),     # shortest contraction (no steady k-tile), ragged rows
+    (558, 2304, 768, 1), (1281, 2048, 512, 3), (4097, 320, 384, 2),              # a last tile of one row, columns of no 128-multiple
+    (1025, 1024, 1024, 2), (1030, 1024, 4096, 0), (4160, 448, 1088, 2),          # four runs of k-tiles (one tile more than the split takes)
+])
+def test_small_direct_tiles_same_bits_as_register_staged_and_fp64(M, N, K, variant):
+    import paper_2511_18191_amd as tsd
+    g = torch.Generator().manual_seed(M + N + K + variant)
+    A = torch.randn(M, K, generator=g).to(torch.bfloat16).cuda()
+    W = (torch.randn(N, K, generator=g) * 0.05).to(torch.bfloat16).cuda()
+    outs = []
+    for no_wide in (0, 8):
+        out = torch.full((M, N), 0.5, dtype=torch.bfloat16 if variant == 3 else torch.float32, device="cuda")
+        tsd.bench_gemm(A, W, out=out, variant=variant + no_wide)
+        torch.cuda.synchronize()
+        outs.append(out.cpu())
+    assert torch.equal(outs[0], outs[1]), f"{(outs[0].float() - outs[1].float()).abs().max():.3e}"
+    a, w = A.cpu().double(), W.cpu().double()
+    ref = a @ w.T
+    if variant in (1, 3):
+        ref = ref * torch.rsqrt((a * a).mean(-1, keepdim=True) + 1e-6)
+    if variant == 3:
+        ref = torch.nn.functional.gelu(ref, approximate="tanh")
+    if variant == 2:
+        ref = ref + 0.5
+    err = (outs[0].double() - ref).abs().max() / ref.abs().max()
+    # fp32 accumulation: sqrt(K) roundings of 2^-24 with a factor for the growing partial sums; a bf16 result adds 2^-9
+    assert err < (6e-3 if variant == 3 else 2e-6 * K ** 0.5), f"{err:.3e}"
