@@ -103,6 +103,7 @@ struct tsd_ctx {
   hipGraphExec_t graph_context = nullptr;  // the context pass of a whole batch (see tsd_prefill)
   int context_B = 0, context_N = 0;        // batch and context length of the last context pass
   int pt_B = 0, pt_need = 0;               // batch and pages per series the device's page table was filled for
+  bool pt_captured = false;                // a caller captured an upload, which a replay may repeat at any time
   bool capturing = false;  // a graph capture of this handle's launches is in progress
   int capture_rows = 0;    // series the launches being captured are sized for
   int seq_floor = 0;       // deliveries of the counts up to this launch number describe an earlier decode
@@ -1161,9 +1162,13 @@ int tsd_prefill(tsd_ctx* ctx, const float* series_dev, int32_t B, int32_t n_ctx_
   if (B != ctx->B || T != ctx->T) drop_graphs(ctx);
   // page table: every series reserves the pages its whole forecast can touch
   const int need = (N + T + ctx->K_max + c.page_tokens - 1) / c.page_tokens;
-  if (B != ctx->pt_B || need != ctx->pt_need) {  // (its contents follow from these two)
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (st) HIP_TRY(ctx, hipStreamIsCapturing(st, &cs));
+  if (cs != hipStreamCaptureStatusNone) ctx->pt_captured = true;
+  if (ctx->pt_captured || B != ctx->pt_B || need != ctx->pt_need) {  // (its contents follow from the two sizes)
     ctx->pt_B = ctx->pt_need = 0;
-    HIP_TRY(ctx, hipStreamSynchronize(st));  // an earlier upload may still read the host copy
+    // an earlier upload may still read the host copy (a caller that is capturing cannot be waited for, nor its replays be seen)
+    if (cs == hipStreamCaptureStatusNone) HIP_TRY(ctx, hipStreamSynchronize(st));
     std::vector<int> perm;
     if (c.flags & TSD_FLAG_SCRAMBLE_PAGES) {
       perm.resize(ctx->n_pages);

@@ -2,7 +2,9 @@
 rebuilds them.  Every forecast must equal, to the bit, the one a fresh handle makes of the same series."""
 import numpy as np
 import pytest
+import torch
 
+import paper_2511_18191_amd as tsd
 from harness import Case
 
 pytestmark = pytest.mark.gpu
@@ -28,3 +30,24 @@ def test_forecasts_of_a_kept_handle_equal_a_fresh_handles(name):
         np.testing.assert_array_equal(got, fresh.get_forecast().cpu().numpy(), err_msg=f"{B} series of {n} patches, {h} steps")
         fresh.close()
     sess.close()
+
+
+def test_eager_prefill_after_a_captured_one_uploads_the_page_table():
+    """A prefill the caller captures runs at its replays only: the next eager one must not take its page table for uploaded."""
+    case = Case("mini2", B=4)
+    c = case.cfg
+    sess = case.session()
+    sess.prefill(case.context[:2], c.n_ctx, c.horizon)
+    series = sess._to_dev(case.context, torch.float32)
+    sess.sync()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=sess.stream, capture_error_mode="thread_local"):
+        rc = tsd.lib().tsd_prefill(sess.h, series.data_ptr(), 4, c.n_ctx, c.horizon, sess.stream.cuda_stream)
+    assert rc == 0
+    fresh = case.session()
+    for s in (sess, fresh):
+        s.prefill(case.context, c.n_ctx, c.horizon)
+        s.run_rounds()
+    np.testing.assert_array_equal(sess.get_forecast().cpu().numpy(), fresh.get_forecast().cpu().numpy())
+    sess.close()
+    fresh.close()
