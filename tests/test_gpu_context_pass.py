@@ -5,7 +5,8 @@ import pytest
 import torch
 
 import paper_2511_18191_amd as tsd
-from harness import Case
+import synth
+from harness import TOL, Case, lockstep
 
 pytestmark = pytest.mark.gpu
 
@@ -51,3 +52,14 @@ def test_eager_prefill_after_a_captured_one_uploads_the_page_table():
     np.testing.assert_array_equal(sess.get_forecast().cpu().numpy(), fresh.get_forecast().cpu().numpy())
     sess.close()
     fresh.close()
+
+
+@pytest.mark.parametrize("B,N", [(1, 17), (3, 18), (3, 34), (5, 50), (9, 82)])
+def test_context_of_several_query_tiles(B, N):
+    """Contexts of 16, 17, 33, 49 and 81 rows: one to six 16-query tiles per (series, head), whole and ragged last ones,
+    numbers of (series, head) that are and are not multiples of eight, against the oracle."""
+    case = Case("mini2", B=B, context=N * synth.CONFIGS["mini2"].patch)
+    sess = case.session()
+    rep = lockstep(case, sess, max_rounds=1)
+    assert rep["max_rel_X"] <= TOL["bf16"] and rep["max_rel_mu_p"] <= TOL["bf16"], rep
+    sess.close()
