@@ -128,6 +128,8 @@ def _check(rc, ctx=None):
 def _raw_stream(device):
     """torch's current stream on `device` as a pointer (without building a Stream object, which takes longer than a launch)."""
     import torch
+    if device.type != "cuda":  # (what torch.cuda.current_stream says; a host pointer must not reach a kernel)
+        raise ValueError(f"Expected a cuda device, but got: {device}")
     return torch._C._cuda_getCurrentRawStream(device.index if device.index is not None else torch.cuda.current_device())
 
 
@@ -153,6 +155,7 @@ def accept_commit_static(X, mu_q, mu_p, sigma_p, sigma_q=None, rounds=None, fall
     import torch
     B, K, P = X.shape
     dev = X.device
+    stream = _raw_stream(dev)
     # (the kernel writes every entry: nothing to fill beforehand)
     n_acc = torch.empty(B, dtype=torch.int32, device=dev)
     commit = torch.empty(B, K + 1, P, dtype=torch.float32, device=dev)
@@ -162,7 +165,7 @@ def accept_commit_static(X, mu_q, mu_p, sigma_p, sigma_q=None, rounds=None, fall
         e_ptr, l_ptr = ell.data_ptr(), logu.data_ptr()
     rc = lib().tsd_accept_commit_static(X.data_ptr(), mu_q.data_ptr(), mu_p.data_ptr(), None if rounds is None else rounds.data_ptr(),
                                         B, K, P, sigma_p, sigma_p if sigma_q is None else sigma_q, fallback_r, seed, flags | TSD_FLAG_CLEAR_REST,
-                                        n_acc.data_ptr(), commit.data_ptr(), e_ptr, l_ptr, _raw_stream(dev))
+                                        n_acc.data_ptr(), commit.data_ptr(), e_ptr, l_ptr, stream)
     if rc:
         _check(rc)
     return dict(n_acc=n_acc, commit=commit, ell=ell, logu=logu)

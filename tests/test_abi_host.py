@@ -126,3 +126,16 @@ def test_static_accept_validates_before_touching_the_gpu():
     assert call(8, 4, 16, X=None) == -1
     assert L.tsd_accept_commit_static(dummy, dummy, dummy, None, 8, 4, 16, 0.0, 1.0, 0.0, 0, 0, dummy, dummy, None, None, None) == -1
     assert L.tsd_accept_commit_static(dummy, dummy, dummy, None, 8, 4, 16, 1.0, 1.0, 2.0, 0, 0, dummy, dummy, None, None, None) == -1
+
+
+def test_static_accept_refuses_tensors_of_the_host(monkeypatch):
+    # their pointers would reach a kernel; as on a machine with a GPU, where the current device and its stream can be asked for
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda index: 0, raising=False)
+    called = []
+    monkeypatch.setattr(tsd.binding, "lib", lambda: type("L", (), {"tsd_accept_commit_static": lambda self, *a: called.append(a) or 0})())
+    X, p = torch.zeros(2, 3, 8), torch.zeros(2, 4, 8)
+    with pytest.raises(ValueError, match="cuda"):
+        tsd.accept_commit_static(X, X, p, 1.0)
+    assert not called
