@@ -20,7 +20,7 @@
 //     down product: its fp32 residual never leaves LDS, only the bf16 shadow the next products read does.
 //   * Attention: one (series, head) per workgroup; the keys of earlier passes are fetched before the hop.
 //   * What workgroups hand each other is written through to memory (agent scope, "sc1") at an address nobody has read in
-//     this launch, so no cache is written back or invalidated at a hop (see Part).
+//     this launch, so no cache is written back or invalidated at a hop (see the exchange buffer below).
 //   * Every sum is formed in the order of the kernels this replaces (gemm_skinny.hip, attn_mfma.h): same bits.
 //
 // All workgroups of a launch have to be resident together: one per compute unit, and launches of this kernel are kept one
@@ -37,9 +37,9 @@ namespace tsd {
 namespace {
 
 constexpr int kWg = kSmallRoundWorkgroups;
-constexpr int kWorkers = 4;
+constexpr int kWorkers = kSmallRoundWorkers;
 constexpr int kThreads = (kWorkers + 1) * 64;
-constexpr int kRowsMax = 32;
+constexpr int kRowsMax = kSmallRoundRows;
 constexpr int kFlagWords = kSmallRoundFlagWords;  // one flag per 64-byte line
 constexpr int kLdp = 18;                          // columns of a partial-sum row in LDS (padded)
 constexpr long long kWaitTicks = 400000000;       // 4 s of the 100 MHz wall clock
@@ -82,13 +82,25 @@ struct Weights {
   bf16x8 f[8];
 };
 
+// (off: the lane's column and place inside a k-step)
 template <int CW>
-__device__ __forceinline__ void load_weights(const bf16* W, unsigned off, int per, Weights& w) {
+__device__ __forceinline__ void load_weights(const bf16* W, unsigned off, int per, int used, int wave, int li, Weights& w) {
   constexpr int PB = CW / 4, SB = 16 / CW;
+  if constexpr (SB == 1) {  // (a slab is the whole wavefront's)
 #pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    const int j = t / PB, i = t % PB;
-    if (j < per) w.f[t] = *reinterpret_cast<const bf16x8*>(W + (SB * i * per + j) * 32 + off);
+    for (int t = 0; t < 8; ++t) {
+      const int j = t / PB, i = t % PB;
+      if (j < per) w.f[t] = *reinterpret_cast<const bf16x8*>(W + (slab_read(wave, i, used) * per + j) * 32 + off);
+    }
+  } else {
+    unsigned at[PB];
+#pragma unroll
+    for (int i = 0; i < PB; ++i) at[i] = off + (unsigned)(slab_read(wave, SB * i + li / CW, used) * per * 32);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int j = t / PB, i = t % PB;
+      if (j < per) w.f[t] = *reinterpret_cast<const bf16x8*>(W + j * 32 + at[i]);
+    }
   }
 }
 
@@ -98,10 +110,10 @@ __device__ __forceinline__ void prefetch(const SmallProd& d, const bf16* W, int 
   if ((int)blockIdx.x >= d.units || 4 * wave >= d.used) return;
   asm volatile("" : "+v"(lane));  // (an opaque copy: keeps the address arithmetic below from being hoisted to the kernel's top)
   const int li = lane & 15, col = column_of<QKV>(d, blockIdx.x, li & ((1 << d.cs) - 1));
-  const unsigned off = (unsigned)(col * d.K + (4 * wave + (li >> d.cs)) * d.per * 32 + (lane >> 4) * 8);
-  if (d.cs == 2) load_weights<4>(W, off, d.per, w);
-  else if (d.cs == 3) load_weights<8>(W, off, d.per, w);
-  else load_weights<16>(W, off, d.per, w);
+  const unsigned off = (unsigned)(col * d.K + (lane >> 4) * 8);
+  if (d.cs == 2) load_weights<4>(W, off, d.per, d.used, wave, li, w);
+  else if (d.cs == 3) load_weights<8>(W, off, d.per, d.used, wave, li, w);
+  else load_weights<16>(W, off, d.per, d.used, wave, li, w);
 }
 
 // The embedding's k range may end inside a k-step or a slab: clamped reads, against zero activations.
@@ -146,13 +158,19 @@ struct Shared {
 // slab agree, which is all that is kept.  No lane then fetches what another one has fetched already: 5 rows cost half the
 // loads of 16, 4 columns a quarter.
 template <int R, int NT, int CW>
-__device__ __forceinline__ void product_t(const bf16* A, int K, int per, int M, bool norm, int wave, int lane, const Weights& w, Shared& sh) {
+__device__ __forceinline__ void product_t(const bf16* A, int K, int per, int used, int M, bool norm, int wave, int lane, const Weights& w, Shared& sh) {
   asm volatile("" : "+v"(lane));
   constexpr int SA = 16 / R, SB = 16 / CW, G = SA < SB ? SA : SB, NACC = 4 / G, PA = R / 4, PB = CW / 4;
   const int li = lane & 15, lg = lane >> 4;
-  unsigned row[NT];  // element offsets from A (uniform base, 32-bit offset: one address register per load)
+  // element offsets from A (uniform base, 32-bit offset: one address register per load), of the lane's slabs where these differ
+  // between lanes
+  constexpr int NS = SA == 1 ? 1 : PA;
+  unsigned row[NT][NS];
 #pragma unroll
-  for (int r = 0; r < NT; ++r) row[r] = (unsigned)(min(r * 16 + li % R, M - 1) * K + (4 * wave + li / R) * per * 32 + lg * 8);
+  for (int r = 0; r < NT; ++r)
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+      row[r][i] = (unsigned)(min(r * 16 + li % R, M - 1) * K + lg * 8 + (SA == 1 ? 0 : slab_read(wave, SA * i + li / R, used) * per * 32));
   f32x4 acc[NT][NACC];  // g: slabs 4 wave + g G .. + G - 1
   float ss[NT][PA];
 #pragma unroll
@@ -175,7 +193,8 @@ __device__ __forceinline__ void product_t(const bf16* A, int K, int per, int M, 
 #pragma unroll
       for (int r = 0; r < NT; ++r)
 #pragma unroll
-        for (int i = 0; i < PA; ++i) a[j][r][i] = *reinterpret_cast<const bf16x8*>(A + (SA * i * per + j0 + j) * 32 + row[r]);
+        for (int i = 0; i < PA; ++i)
+          a[j][r][i] = *reinterpret_cast<const bf16x8*>(A + ((SA == 1 ? slab_read(wave, i, used) * per : 0) + j0 + j) * 32 + row[r][SA == 1 ? 0 : i]);
     }
 #pragma unroll
     for (int j = 0; j < JC; ++j) {
@@ -226,9 +245,9 @@ __device__ __forceinline__ void product_t(const bf16* A, int K, int per, int M, 
 
 template <int R, int NT>
 __device__ __forceinline__ void product_cw(const SmallProd& d, const bf16* A, int M, bool norm, int wave, int lane, const Weights& w, Shared& sh) {
-  if (d.cs == 2) product_t<R, NT, 4>(A, d.K, d.per, M, norm, wave, lane, w, sh);
-  else if (d.cs == 3) product_t<R, NT, 8>(A, d.K, d.per, M, norm, wave, lane, w, sh);
-  else product_t<R, NT, 16>(A, d.K, d.per, M, norm, wave, lane, w, sh);
+  if (d.cs == 2) product_t<R, NT, 4>(A, d.K, d.per, d.used, M, norm, wave, lane, w, sh);
+  else if (d.cs == 3) product_t<R, NT, 8>(A, d.K, d.per, d.used, M, norm, wave, lane, w, sh);
+  else product_t<R, NT, 16>(A, d.K, d.per, d.used, M, norm, wave, lane, w, sh);
 }
 
 __device__ __forceinline__ void product(const SmallProd& d, const bf16* A, int M, bool norm, int wave, int lane, const Weights& w, Shared& sh) {
@@ -506,9 +525,7 @@ struct Walk {
 // of an XCD share one fetch through their L2; only the stores have to go through to memory.  (Reading reused buffers past
 // the caches: 6.7 us per FFN down stage for one series through 4096 x 1024, most of it 256 workgroups fetching 40 KB each
 // from the last-level cache.)
-enum Part { kIn, kQuery, kMixed, kMid, kHidden };  // of a layer
-inline size_t slab_bytes(int D, int F) { return (size_t)kRowsMax * (4 * D + F) * 2; }
-inline size_t pass_bytes(int L, int D, int F) { return L * slab_bytes(D, F) + (size_t)kRowsMax * D * 4; }
+// (Its layout: small_round_plan.h.)
 
 enum Kind { kQkv, kAttend, kOut, kUp, kDown };
 
@@ -526,7 +543,7 @@ struct PassView {
   }
   // rows entering layer l, its queries, attention output, rows between the two halves, hidden rows; residual for the head
   __device__ __forceinline__ bf16* rows(int l, int which) const {
-    return reinterpret_cast<bf16*>(x + (size_t)l * m->slab_bytes + (size_t)which * (kRowsMax * 2) * D);
+    return reinterpret_cast<bf16*>(x + (size_t)l * m->slab_bytes + small_part_offset(D, which));
   }
   __device__ __forceinline__ float* residual() const { return reinterpret_cast<float*>(x + (size_t)m->L * m->slab_bytes); }
   __device__ __forceinline__ const bf16* weights(const SmallProd& d, int l) const {
@@ -871,40 +888,20 @@ __global__ __launch_bounds__(kThreads) void small_round_kernel(const SmallRoundP
     worker_loop(p, n, Kr, Kd, n_pass, wave, lane, sh);
 }
 
-// Fewest columns per workgroup with which N columns fit the grid (0: they do not).
-int columns_per_wg(int N) {
-  for (int cw : {4, 8, 16})
-    if (N % cw == 0 && N / cw <= kWg) return cw;
-  return 0;
-}
-
-// The k range of a product is summed in slabs of consecutive k-steps of 32, each from zero, the slabs added in order: the
-// order of the skinny kernel (gemm_skinny.hip: 16 wavefronts from K = 512 on, else 4), so that either gives the same bits.
 SmallProd product_of(const bf16* W, int K, int N) {
-  const int nks = (K + 31) / 32, n = K >= 512 ? 16 : 4, cw = columns_per_wg(N);
   SmallProd d;
+  static_cast<SmallPlan&>(d) = small_plan(K, N);
   d.W = W;
-  d.K = K;
-  d.cs = cw ? __builtin_ctz(cw) : 0;
-  d.units = cw ? N / cw : 0;
-  d.per = (nks + n - 1) / n;
-  d.used = (nks + d.per - 1) / d.per;
   return d;
-}
-
-// A product of bf16 activations fits: its columns the grid, a worker's share of its weights eight pieces, its k range whole slabs.
-bool product_ok(int K, int N) {
-  const SmallProd d = product_of(nullptr, K, N);
-  return d.units && K % 32 == 0 && d.per * ((1 << d.cs) / 4) <= 8 && d.per * d.used * 32 == K;
 }
 
 bool model_ok(const tsd_model_cfg& c, int patch) {
   const int D = c.d_model, F = c.d_ff;
   if (c.n_experts || D != 64 * c.n_heads || D > 1024 || patch > 1024) return false;
-  const SmallProd e = product_of(nullptr, patch, D);
+  const SmallPlan e = small_plan(patch, D);
   // (the embedding and the head, widths up to 1024, are four columns per workgroup: see product_f32)
-  return product_ok(D, 3 * D) && product_ok(D, D) && product_ok(D, F) && product_ok(F, D) && product_ok(D, patch) && e.units &&
-         e.cs == 2 && e.per <= 4 && columns_per_wg(patch) == 4;
+  return small_product_ok(D, 3 * D) && small_product_ok(D, D) && small_product_ok(D, F) && small_product_ok(F, D) &&
+         small_product_ok(D, patch) && e.units && e.cs == 2 && e.per <= 4 && columns_per_wg(patch) == 4;
 }
 
 }  // namespace
@@ -928,12 +925,12 @@ void small_round_model(const tsd_model_cfg& c, int patch, const bf16* W_e, const
   m->D = c.d_model;
   m->F = c.d_ff;
   m->Hh = c.n_heads;
-  m->slab_bytes = slab_bytes(c.d_model, c.d_ff);
-  m->pass_bytes = pass_bytes(c.n_layers, c.d_model, c.d_ff);
+  m->slab_bytes = small_slab_bytes(c.d_model, c.d_ff);
+  m->pass_bytes = small_pass_bytes(c.n_layers, c.d_model, c.d_ff);
 }
 
 size_t small_round_exchange_bytes(const tsd_config& c) {
-  return c.K * pass_bytes(c.draft.n_layers, c.draft.d_model, c.draft.d_ff) + pass_bytes(c.target.n_layers, c.target.d_model, c.target.d_ff);
+  return c.K * small_pass_bytes(c.draft.n_layers, c.draft.d_model, c.draft.d_ff) + small_pass_bytes(c.target.n_layers, c.target.d_model, c.target.d_ff);
 }
 
 // Most stages a launch can have (the flags' epoch advances by this much per launch).

@@ -1,0 +1,54 @@
+// How the resident decode kernel (small_round.hip) deals its products out: sizes and index rules, in plain C++ so that they can be
+// checked without a GPU (tests/test_small_round_plan.py).
+#pragma once
+#include <cstddef>
+
+namespace tsd {
+
+constexpr int kSmallRoundWorkgroups = 256;  // one per compute unit
+constexpr int kSmallRoundRows = 32;         // rows of a pass at most
+constexpr int kSmallRoundWorkers = 4;       // wavefronts that split a product's k range, four slabs each
+
+struct SmallPlan {
+  int K, units;   // units: workgroups that own columns of the product,
+  int cs;         // 2^cs columns each (4, 8 or 16)
+  int per, used;  // k-steps of 32 per slab, slabs
+};
+
+// Fewest columns per workgroup with which N columns fit the grid (0: they do not).
+constexpr int columns_per_wg(int N) {
+  for (int cw = 4; cw <= 16; cw *= 2)
+    if (N % cw == 0 && N / cw <= kSmallRoundWorkgroups) return cw;
+  return 0;
+}
+
+// The k range of a product is summed in slabs of consecutive k-steps of 32, each from zero, the slabs added in order: the
+// order of the skinny kernel (gemm_skinny.hip: 16 wavefronts from K = 512 on, else 4), so that either gives the same bits.
+constexpr SmallPlan small_plan(int K, int N) {
+  const int nks = (K + 31) / 32, n = K >= 512 ? 16 : 4, cw = columns_per_wg(N);
+  const int per = (nks + n - 1) / n;
+  return SmallPlan{K, cw ? N / cw : 0, cw == 16 ? 4 : cw == 8 ? 3 : cw == 4 ? 2 : 0, per, (nks + per - 1) / per};
+}
+
+// A product of bf16 activations fits: its columns the grid, a worker's share of its weights eight pieces, its k range whole slabs.
+constexpr bool small_product_ok(int K, int N) {
+  const SmallPlan d = small_plan(K, N);
+  return d.units && K % 32 == 0 && d.per * ((1 << d.cs) / 4) <= 8 && d.per * d.used * 32 == K;
+}
+
+// Which slab worker `wave` reads as the `part`-th (0 .. 3) of its four.  The last worker may have fewer: it then reads the last
+// one again, and the sums of it are dropped.  (Read past the end of row 31, the lines behind it are the next part of
+// the exchange buffer, which nobody may have read before it is written: see small_round.hip.)
+constexpr int slab_read(int wave, int part, int used) {
+  const int s = kSmallRoundWorkers * wave + part;
+  return s < used ? s : used - 1;
+}
+
+// The exchange buffer: of a layer, the rows entering it, its queries, attention output, the rows between its two halves, hidden
+// rows; of a pass, its layers and the fp32 residual.
+enum SmallPart { kIn, kQuery, kMixed, kMid, kHidden };
+constexpr size_t small_part_offset(int D, int part) { return (size_t)part * (kSmallRoundRows * 2) * D; }
+constexpr size_t small_slab_bytes(int D, int F) { return (size_t)kSmallRoundRows * (4 * D + F) * 2; }
+constexpr size_t small_pass_bytes(int L, int D, int F) { return L * small_slab_bytes(D, F) + (size_t)kSmallRoundRows * D * 4; }
+
+}  // namespace tsd

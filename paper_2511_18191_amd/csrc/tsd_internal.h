@@ -6,6 +6,7 @@
 #include <string>
 #include <vector>
 
+#include "small_round_plan.h"
 #include "tsd.h"
 
 namespace tsd {
@@ -193,13 +194,9 @@ hipError_t prepare_draft_fused();
 hipError_t launch_draft_fused(const DraftFusedP& p, hipStream_t st);
 
 // ---- decode passes of at most 32 rows as one resident kernel: see small_round.hip ----
-constexpr int kSmallRoundWorkgroups = 256;  // one per compute unit
 constexpr int kSmallRoundFlagWords = 16;    // words between two workgroups' flags
-struct SmallProd {    // one product of the chain
-  const bf16* W;      // [N][K], layer 0's
-  int K, units;       // units: workgroups that own columns of it,
-  int cs;             // 2^cs columns each (4, 8 or 16)
-  int per, used;      // k-steps of 32 per slab, slabs (see product_of)
+struct SmallProd : SmallPlan {  // one product of the chain
+  const bf16* W;                // [N][K], layer 0's
 };
 struct SmallModel {
   SmallProd embed, qkv, out, up, down, head;

@@ -50,6 +50,26 @@ def test_lockstep(B, K, target, draft, P, N, T):
     ref.close()
 
 
+W192, W640, W960 = ModelCfg(2, 192, 3, 384), ModelCfg(2, 640, 10, 2560), ModelCfg(2, 960, 15, 3840)
+
+
+@pytest.mark.parametrize("B,K,target,draft", [
+    (8, 3, W192, W192), (8, 3, W640, W192), (4, 7, W960, W640), (2, 15, W640, W192), (16, 1, W192, W640), (2, 15, W960, W960)])
+def test_32_rows_with_partly_used_workers(B, K, target, draft):
+    """Passes of exactly 32 rows through products whose last worker has fewer than four slabs (6, 20 and 30 k-steps; 4, 8 and 16
+    columns per workgroup): a read past the end of row 31 would fetch lines that the same stage publishes."""
+    P, N, T = 96, 5, 2 * K + 3
+    case = Case("mini2", B=B, K=K, patch=P, context=N * P, horizon=T * P, random_gains=True, target=target, draft=draft)
+    out = []
+    for s in (case.session(), case.session(flags=tsd.TSD_FLAG_NO_PINNED_COUNTS)):
+        for _ in range(2):      # the second forecast finds the first one's exchange buffer
+            s.prefill(case.context, case.cfg.n_ctx, case.cfg.horizon)
+            s.run_rounds()
+        out.append(s.get_forecast().cpu().numpy())
+        s.close()
+    np.testing.assert_array_equal(*out)
+
+
 def test_two_handles_on_two_streams():
     """Rounds of two handles enqueued alternately without waiting give what each gives alone."""
     cases = [Case("mini2", B=2), Case("mini3", B=3)]
