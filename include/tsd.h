@@ -243,8 +243,11 @@ int tsd_accept_commit_static(const float* X_dev, const float* mu_q_dev, const fl
  * sized for 1/32 .. 32/32 of the batch); the class is chosen from the last length the host has
  * seen, looked up without waiting, and every launch is capped by the device-side length.
  * A dense bf16 handle with max_batch * (K + 1) <= 32 runs the draft steps and the verification (and tsd_target_step's pass)
- * as ONE resident kernel with a workgroup on every compute unit, bit for bit the kernel-by-kernel result, where its sizes
- * allow (head_dim 64, d_model <= 1024, d_ff <= 4096, patch a multiple of 16, K <= 15); such launches of all handles on a GPU
+ * as ONE resident kernel with a workgroup on every compute unit, bit for bit the kernel-by-kernel result, where the sizes of
+ * both models allow: head_dim 64, d_model <= 1024, d_ff <= 4096, patch a multiple of 16, K <= 15, and d_model and d_ff
+ * whole slabs, i.e. multiples of 32 s with s = ceil(width / (32 n)) and n = 16 from width 512 on, else 4 (every d_model but 320
+ * and 448).  Not on a stream the caller is capturing, nor between tsd_profile_begin
+ * and tsd_profile_end, which time the kernels one by one; tsd_resident_passes tells how often it ran.  Such launches of all handles on a GPU
  * run one after the other.  Should its workgroups not become resident together within 4 seconds, the round commits
  * nothing and every later call but tsd_prefill returns TSD_E_HIP. */
 int tsd_round(tsd_ctx* ctx, void* stream);
@@ -376,6 +379,10 @@ typedef struct {
   double work;
 } tsd_launch_rec;
 int tsd_profile_launches(tsd_ctx* ctx, tsd_launch_rec* out_host, int32_t max_records, int32_t* n_host);
+
+/* Launches of the resident decode kernel (see tsd_round) this handle has made since tsd_create: one per tsd_round,
+ * tsd_target_step, tsd_draft_propose or tsd_target_verify that took it.  Host-only. */
+int tsd_resident_passes(tsd_ctx* ctx, int64_t* n_host);
 
 /* Measurement tap: one product through the same tiled kernel, tile selection and tile order the
  * transformer passes use.  dtype TSD_BF16: A and Wt are bf16; TSD_F32: fp32.  variant 0:

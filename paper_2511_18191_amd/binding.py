@@ -72,6 +72,7 @@ SYMBOLS = {
     "tsd_profile_end": ([C.c_void_p, C.POINTER(C.c_int64), C.POINTER(C.c_double), C.POINTER(C.c_double), C.c_void_p], C.c_int),
     "tsd_set_route_tap": ([C.c_void_p, C.c_int, C.c_void_p, C.c_size_t], C.c_int),
     "tsd_profile_launches": ([C.c_void_p, C.c_void_p, C.c_int32, C.POINTER(C.c_int32)], C.c_int),
+    "tsd_resident_passes": ([C.c_void_p, C.POINTER(C.c_int64)], C.c_int),
     "tsd_bench_gemm": ([C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p], C.c_int),
     "tsd_bench_copy": ([C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p], C.c_int),
     "tsd_bench_mfma": ([C.c_int32, C.c_int32, C.c_void_p, C.c_void_p], C.c_int),
@@ -355,6 +356,12 @@ class Session:
         n, ms, work = C.c_int64(), C.c_double(), C.c_double()
         _check(lib().tsd_profile_end(self.h, C.byref(n), C.byref(ms), C.byref(work), self._stream()), self.h)
         return n.value, ms.value, work.value
+
+    def resident_passes(self):
+        """Decode passes (or whole rounds) this handle has launched on the resident kernel so far."""
+        n = C.c_int64()
+        _check(lib().tsd_resident_passes(self.h, C.byref(n)), self.h)
+        return n.value
 
     def route_tap(self, which=TSD_TARGET):
         """Install (and return) an int32 tensor [layers, max_batch, max_tokens, top_k], filled with -1, in which

@@ -72,6 +72,7 @@ struct tsd_ctx {
   unsigned* small_flags = nullptr;  // its workgroups' flags
   unsigned small_epoch = 0;         // what they hold at most
   char* small_exchange = nullptr;   // what they hand each other
+  int64_t small_passes = 0;         // passes launched on it
   int* moe_ids;
   int* route_tap[2] = {nullptr, nullptr};  // caller-owned parity tap per model (tsd_set_route_tap), NULL = off
   float* moe_gates;
@@ -861,6 +862,7 @@ int run_small_round(tsd_ctx* ctx, int phases, bool step_only, hipStream_t st) {
   r.host_status = ctx->host_counts + 3;
   r.scale = 1.0f / std::sqrt(64.0f);
   HIP_TRY(ctx, launch_small_round(r, ctx, st));
+  ctx->small_passes++;
   return TSD_OK;
 }
 
@@ -1750,6 +1752,13 @@ int tsd_profile_launches(tsd_ctx* ctx, tsd_launch_rec* out_host, int32_t max_rec
   if (ctx->prof_class >= 0) return fail(ctx, TSD_E_BAD_STATE, "a measurement is still running: call tsd_profile_end first");
   *n_host = (int32_t)ctx->prof_recs.size();
   for (size_t i = 0; i < ctx->prof_recs.size() && i < (size_t)max_records; ++i) out_host[i] = ctx->prof_recs[i];
+  return TSD_OK;
+}
+
+int tsd_resident_passes(tsd_ctx* ctx, int64_t* n_host) {
+  if (!ctx) return fail(nullptr, TSD_E_INVALID_ARG, "ctx is NULL");
+  if (!n_host) return fail(ctx, TSD_E_INVALID_ARG, "n_host is NULL");
+  *n_host = ctx->small_passes;
   return TSD_OK;
 }
 

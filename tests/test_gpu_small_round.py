@@ -1,6 +1,7 @@
 """Decode passes of at most 32 rows run as one resident kernel: lock-step with the oracle, and bit for bit the kernels it
-replaces, over the sizes where its indexing changes (row tiles of 4, 8, 16 and 2 x 16, columns per workgroup, slabs that are
-not full, patches that are no whole k-step, more cached keys than are fetched together), and two handles at a time."""
+replaces, over the sizes where its indexing changes (row tiles of 4, 8, 16 and 2 x 16, 4, 8 and 16 columns per workgroup, workers
+with fewer than four slabs, patches that are no whole k-step, more cached keys than are fetched together), and two handles at a
+time.  Every case asserts that the one side ran on that kernel and the other did not."""
 import numpy as np
 import pytest
 import torch
@@ -17,9 +18,15 @@ D1 = ModelCfg(1, 64, 1, 96)
 @pytest.mark.parametrize("B,K,target,draft,P,N,T", [
     (1, 1, None, None, 96, 6, 3), (2, 1, None, None, 96, 6, 3), (1, 4, None, None, 96, 6, 6), (1, 15, None, None, 96, 6, 20),
     (2, 15, None, None, 96, 6, 18), (16, 1, None, None, 96, 6, 3), (8, 3, None, None, 96, 6, 5),   # 2 .. 32 rows
-    (3, 4, ModelCfg(2, 192, 3, 352), D1, 48, 5, 6),                # 6 and 11 k-steps, a patch of one and a half
-    (5, 2, ModelCfg(1, 384, 6, 1536), ModelCfg(2, 128, 2, 160), 16, 4, 5),
-    (2, 4, ModelCfg(1, 1024, 16, 4096), ModelCfg(1, 320, 5, 1280), 96, 4, 6),   # the widest products it takes
+    (3, 4, ModelCfg(2, 192, 3, 288), D1, 48, 5, 6),                # 6 and 9 k-steps (three slabs), a patch of one and a half
+    (5, 2, ModelCfg(1, 384, 6, 1536), ModelCfg(2, 128, 2, 192), 16, 4, 5),      # 8 columns, 15 rows
+    (2, 4, ModelCfg(1, 1024, 16, 4096), ModelCfg(1, 384, 6, 1536), 96, 4, 6),   # the widest products it takes, 10 rows
+    # 8 and 16 columns at 2, 6, 15 and 30 rows, two layers of both models
+    (1, 1, ModelCfg(2, 384, 6, 1536), ModelCfg(2, 384, 6, 768), 32, 4, 4), (1, 1, ModelCfg(2, 768, 12, 3072), D1, 96, 4, 3),
+    (2, 2, ModelCfg(2, 384, 6, 1536), ModelCfg(2, 512, 8, 1024), 96, 4, 5), (2, 2, ModelCfg(2, 768, 12, 3072), D1, 112, 4, 5),
+    (3, 4, ModelCfg(2, 512, 8, 2048), ModelCfg(2, 384, 6, 1536), 96, 4, 6), (3, 4, ModelCfg(2, 896, 14, 3584), D1, 96, 4, 6),
+    (5, 5, ModelCfg(2, 512, 8, 2048), ModelCfg(2, 256, 4, 1024), 96, 4, 7), (5, 5, ModelCfg(2, 1024, 16, 4096), ModelCfg(2, 384, 6, 1536), 96, 4, 7),
+    (2, 3, ModelCfg(2, 256, 4, 512), D1, 560, 4, 5),               # an embedding of 17 and a half k-steps, two per slab
     (2, 3, ModelCfg(1, 128, 2, 256), D1, 16, 300, 5),              # ten 32-key steps, four at a time
 ])
 def test_lockstep(B, K, target, draft, P, N, T):
@@ -46,6 +53,8 @@ def test_lockstep(B, K, target, draft, P, N, T):
         for _ in range(T):
             s.target_step()
     np.testing.assert_array_equal(sess.get_forecast().cpu().numpy(), ref.get_forecast().cpu().numpy())
+    # two launches per lock-step round, one per round, one per target step
+    assert sess.resident_passes() >= 2 * rep["rounds"] + (T + K) // (K + 1) + T and ref.resident_passes() == 0
     sess.close()
     ref.close()
 
@@ -66,6 +75,7 @@ def test_32_rows_with_partly_used_workers(B, K, target, draft):
             s.prefill(case.context, case.cfg.n_ctx, case.cfg.horizon)
             s.run_rounds()
         out.append(s.get_forecast().cpu().numpy())
+        assert (s.resident_passes() > 0) == (len(out) == 1)
         s.close()
     np.testing.assert_array_equal(*out)
 

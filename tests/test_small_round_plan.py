@@ -69,3 +69,16 @@ def test_reads_of_a_full_four_slabs_would_leave_their_part(tmp_path):
     """What the rule is for: with the slab taken as it comes, the walk above finds reads outside."""
     source = READS.replace("slab_read(wave, part, d.used) * d.per", "(kSmallRoundWorkers * wave + part) * d.per")
     assert source != READS and _run(tmp_path, source)[2] > 0
+
+
+def test_widths_the_kernel_takes(tmp_path):
+    """As include/tsd.h states them: of the widths up to 1024 in whole heads all but 320 and 448."""
+    out = _run(tmp_path, '''
+#include <cstdio>
+#include "small_round_plan.h"
+int main() {
+  for (int D = 64; D <= 1024; D += 64)
+    if (!tsd::small_product_ok(D, 3 * D) || !tsd::small_product_ok(D, D)) printf("%d ", D);
+}
+''')
+    assert out == [320, 448]
