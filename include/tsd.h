@@ -247,8 +247,8 @@ int tsd_accept_commit_static(const float* X_dev, const float* mu_q_dev, const fl
  * both models allow: head_dim 64, d_model <= 1024, d_ff <= 4096, patch a multiple of 16, K <= 15, and d_model and d_ff
  * whole slabs, i.e. multiples of 32 s with s = ceil(width / (32 n)) and n = 16 from width 512 on, else 4 (every d_model but 320
  * and 448).  Not on a stream the caller is capturing, nor between tsd_profile_begin
- * and tsd_profile_end, which time the kernels one by one; tsd_resident_passes tells how often it ran.  Such launches of all handles on a GPU
- * run one after the other.  Should its workgroups not become resident together within 4 seconds, the round commits
+ * and tsd_profile_end, which time the kernels one by one, nor while another handle's passes are in flight on another stream
+ * (launch by launch the two overlap); tsd_resident_passes tells how often it ran.  Should its workgroups not become resident together within 4 seconds, the round commits
  * nothing and every later call but tsd_prefill returns TSD_E_HIP. */
 int tsd_round(tsd_ctx* ctx, void* stream);
 

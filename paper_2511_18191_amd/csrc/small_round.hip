@@ -23,11 +23,14 @@
 //     this launch, so no cache is written back or invalidated at a hop (see the exchange buffer below).
 //   * Every sum is formed in the order of the kernels this replaces (gemm_skinny.hip, attn_mfma.h): same bits.
 //
-// All workgroups of a launch have to be resident together: one per compute unit, and launches of this kernel are kept one
-// after the other per device (launch_small_round).  Every wait is bounded: a workgroup that has watched for kWaitTicks
+// All workgroups of a launch have to be resident together: one per compute unit, and a process has one launch of this kernel
+// on a device at a time (launch_small_round).  Every wait is bounded: a workgroup that has watched for kWaitTicks
 // or sees another's give-up sets the status word and leaves, the acceptance kernel then commits nothing and the host
 // reports the failure.
+#include <algorithm>
+#include <atomic>
 #include <mutex>
+#include <vector>
 
 #include "gemm_epilogue.h"
 #include "tsd_internal.h"
@@ -936,33 +939,76 @@ size_t small_round_exchange_bytes(const tsd_config& c) {
 // Most stages a launch can have (the flags' epoch advances by this much per launch).
 int small_round_stages(const tsd_config& c) { return c.K * (2 + 5 * c.draft.n_layers) + 2 + 5 * c.target.n_layers; }
 
-// Launches of different handles must not be resident together (each needs every compute unit): a launch waits for the
-// previous one on its device unless that was the same handle's on the same stream, which is ordered before it anyway.
-hipError_t launch_small_round(const SmallRoundP& p, const void* owner, hipStream_t st) {
-  constexpr int kMaxDevices = 64;
-  struct Last {
-    hipEvent_t done = nullptr;
-    const void* owner = nullptr;
-    hipStream_t stream = nullptr;
-  };
-  static std::mutex mu;
-  static Last last[kMaxDevices];
-  int dev = -1;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-  std::lock_guard<std::mutex> lock(mu);
-  Last& la = last[dev];
-  if (!la.done) {
-    if ((e = hipEventCreateWithFlags(&la.done, hipEventDisableTiming)) != hipSuccess) return e;
-  } else if (la.owner != owner || la.stream != st) {
-    if ((e = hipStreamWaitEvent(st, la.done, 0)) != hipSuccess) return e;
+// ---- who else is using the device ----
+// Two resident launches that no stream orders must not run together: each needs every compute unit.  And beside anything else a
+// resident launch is a bad neighbour: its workgroups leave too few registers for most kernels, whose streams then take turns with it
+// where launch by launch they overlap.  So a pass runs as the resident kernel only while no other handle's passes are in flight on
+// another stream; with the same bits either way, nothing else depends on it.  (Two handles
+// on two streams, ms for a decode of each, taking turns through an event / now: one series through 24 layers of 1024 16.8 / 14.5
+// (alone 8.4), five through 8 layers of 512 5.3 / 4.4; 30 decodes of the former beside 51 of 256 series 487 / 384.)
+namespace {
+std::mutex uses_mutex;
+std::vector<PassUse*> uses;         // of all handles
+std::atomic<int> resident_handles;  // those among them that may run the resident kernel
+
+std::thread::id thread_of(hipStream_t st) {  // (hipStreamPerThread names another stream in every thread)
+  return st == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id();
+}
+
+hipError_t record_use(PassUse* use, hipStream_t st) {
+  hipError_t e = hipSuccess;
+  if (!use->done && (e = hipEventCreateWithFlags(&use->done, hipEventDisableTiming)) != hipSuccess) return e;
+  if ((e = hipEventRecord(use->done, st)) != hipSuccess) return e;
+  use->stream = st;
+  use->thread = thread_of(st);
+  use->in_flight = true;
+  return e;
+}
+}  // namespace
+
+void add_use(PassUse* use, int device, bool resident) {
+  std::lock_guard<std::mutex> lock(uses_mutex);
+  use->device = device;
+  use->resident = resident;
+  uses.push_back(use);
+  if (resident) ++resident_handles;
+}
+
+void remove_use(PassUse* use) {
+  std::lock_guard<std::mutex> lock(uses_mutex);
+  uses.erase(std::remove(uses.begin(), uses.end(), use), uses.end());
+  if (use->resident) --resident_handles;
+  if (use->done) (void)hipEventDestroy(use->done);
+}
+
+hipError_t note_pass(PassUse* use, hipStream_t st) {
+  if (resident_handles.load(std::memory_order_relaxed) <= (use->resident ? 1 : 0)) return hipSuccess;  // nobody else asks
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (st) {
+    hipError_t e = hipStreamIsCapturing(st, &cs);
+    if (e != hipSuccess || cs != hipStreamCaptureStatusNone) return e;
+  }
+  std::lock_guard<std::mutex> lock(uses_mutex);
+  return record_use(use, st);
+}
+
+hipError_t launch_small_round(const SmallRoundP& p, PassUse* use, hipStream_t st, bool* busy) {
+  *busy = false;
+  std::lock_guard<std::mutex> lock(uses_mutex);
+  for (PassUse* u : uses) {
+    if (u == use || u->device != use->device || !u->in_flight || (u->stream == st && u->thread == thread_of(st))) continue;
+    const hipError_t e = hipEventQuery(u->done);
+    if (e == hipErrorNotReady) {
+      (void)hipGetLastError();
+      *busy = true;
+      return hipSuccess;
+    }
+    if (e != hipSuccess) return e;
+    u->in_flight = false;
   }
   hipLaunchKernelGGL(small_round_kernel, dim3(kWg), dim3(kThreads), 0, st, p);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  la.owner = owner;
-  la.stream = st;
-  return hipEventRecord(la.done, st);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : record_use(use, st);
 }
 
 }  // namespace tsd

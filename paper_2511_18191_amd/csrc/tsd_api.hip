@@ -73,6 +73,7 @@ struct tsd_ctx {
   unsigned small_epoch = 0;         // what they hold at most
   char* small_exchange = nullptr;   // what they hand each other
   int64_t small_passes = 0;         // passes launched on it
+  PassUse use;                      // what other handles see of this one's passes
   int* moe_ids;
   int* route_tap[2] = {nullptr, nullptr};  // caller-owned parity tap per model (tsd_set_route_tap), NULL = off
   float* moe_gates;
@@ -808,7 +809,10 @@ bool use_small_round(tsd_ctx* ctx, hipStream_t st) {
   return true;
 }
 
-// phases: 1 the draft steps, 2 the target pass; step_only: the target pass over the pending token alone.
+constexpr int kResidentBusy = 1;  // (error codes are negative)
+
+// phases: 1 the draft steps, 2 the target pass; step_only: the target pass over the pending token alone.  kResidentBusy:
+// nothing was launched, the pass has to run kernel by kernel.
 int run_small_round(tsd_ctx* ctx, int phases, bool step_only, hipStream_t st) {
   const tsd_config& c = ctx->cfg;
   SmallRoundP r;
@@ -857,11 +861,13 @@ int run_small_round(tsd_ctx* ctx, int phases, bool step_only, hipStream_t st) {
   r.k_max = ctx->K_max;
   r.flags = ctx->small_flags;
   r.epoch = ctx->small_epoch;
-  ctx->small_epoch += (unsigned)small_round_stages(c);
   r.status = ctx->count_out + kGaveUp;
   r.host_status = ctx->host_counts + 3;
   r.scale = 1.0f / std::sqrt(64.0f);
-  HIP_TRY(ctx, launch_small_round(r, ctx, st));
+  bool busy = false;
+  HIP_TRY(ctx, launch_small_round(r, &ctx->use, st, &busy));
+  if (busy) return kResidentBusy;
+  ctx->small_epoch += (unsigned)small_round_stages(c);
   ctx->small_passes++;
   return TSD_OK;
 }
@@ -1053,6 +1059,9 @@ int tsd_create(const tsd_config* cfg, void* arena_dev, size_t arena_bytes, tsd_c
       return fail(nullptr, TSD_E_HIP, msg);
     }
   }
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  add_use(&ctx->use, dev, ctx->small_round);
   *out = ctx;
   return TSD_OK;
 }
@@ -1060,6 +1069,7 @@ int tsd_create(const tsd_config* cfg, void* arena_dev, size_t arena_bytes, tsd_c
 int tsd_destroy(tsd_ctx* ctx) {
   if (!ctx) return fail(nullptr, TSD_E_INVALID_ARG, "ctx is NULL");
   hipError_t e = hipDeviceSynchronize();
+  remove_use(&ctx->use);
   drop_graphs(ctx);
   if (ctx->host_counts) (void)hipHostFree(ctx->host_counts);
   for (auto& ev : ctx->prof_events) {
@@ -1231,6 +1241,7 @@ int tsd_prefill(tsd_ctx* ctx, const float* series_dev, int32_t B, int32_t n_ctx_
   const int rc = (again && B <= chunk) ? run_graphed(ctx, &ctx->graph_context, st, context, /*counts=*/false) : context();
   if (rc) return rc;
   ctx->prefilled = true;
+  if (!ctx->small_round) HIP_TRY(ctx, note_pass(&ctx->use, st));  // (a small handle's context is short, its first round tells)
   return TSD_OK;
 }
 
@@ -1281,6 +1292,7 @@ int tsd_refill(tsd_ctx* ctx, const int32_t* slots_host, int32_t n, const float* 
   ctx->compact_pending = false;
   ctx->k_round = 0;
   ctx->need_lb = 0;
+  if (!ctx->small_round) HIP_TRY(ctx, note_pass(&ctx->use, st));
   return TSD_OK;
 }
 
@@ -1310,7 +1322,7 @@ int tsd_draft_propose(tsd_ctx* ctx, void* stream) {
   // Step 1 ingests two tokens per series: the token just before the pending one and the pending
   // one.  After a fully accepted round the draft cache lacks the former (it proposed x_K but
   // never consumed it); for the other series the rewrite stores identical values.
-  if (!ctx->fused_draft && use_small_round(ctx, st)) return run_small_round(ctx, 1, false, st);
+  if (!ctx->fused_draft && use_small_round(ctx, st) && (rc = run_small_round(ctx, 1, false, st)) != kResidentBusy) return rc;
   const Cover cv = cover(ctx);
   if (cv.n == 0) return TSD_OK;
   if (ctx->fused_draft) {
@@ -1367,6 +1379,7 @@ int tsd_draft_propose(tsd_ctx* ctx, void* stream) {
     const double D = f.D, tok = (double)cv.n * (Kr + 1);
     const double flops = 2.0 * tok * (2.0 * P * D + f.L * (4.0 * D * D + 2.0 * D * f.F));
     HIP_TRY(ctx, timed_launch(ctx, TSD_K_DRAFT, flops, st, [&] { return launch_draft_fused(f, st); }, Shape{TSD_DRAFT, 0, cv.n, Kr, 0}));
+    HIP_TRY(ctx, note_pass(&ctx->use, st));
     return TSD_OK;
   }
   Pass ps;
@@ -1432,6 +1445,7 @@ int tsd_draft_propose(tsd_ctx* ctx, void* stream) {
     if ((rc = run_pass(ctx, ps, st))) return rc;
     if ((rc = draw(i))) return rc;
   }
+  HIP_TRY(ctx, note_pass(&ctx->use, st));
   return TSD_OK;
 }
 
@@ -1440,7 +1454,7 @@ int tsd_target_verify(tsd_ctx* ctx, void* stream) {
   if (rc) return rc;
   const tsd_config& c = ctx->cfg;
   const int P = c.patch, K = c.K;
-  if (use_small_round(ctx, (hipStream_t)stream)) return run_small_round(ctx, 2, false, (hipStream_t)stream);
+  if (use_small_round(ctx, (hipStream_t)stream) && (rc = run_small_round(ctx, 2, false, (hipStream_t)stream)) != kResidentBusy) return rc;
   const int Kr = round_positions(ctx);  // boundaries beyond Kr + 1 belong to patches no active series can commit
   const Cover cv = cover(ctx);
   if (cv.n == 0) return TSD_OK;
@@ -1472,9 +1486,11 @@ int tsd_target_verify(tsd_ctx* ctx, void* stream) {
       ps.out = ctx->mu_p + (size_t)(i - 1) * P;
       if ((rc = run_pass(ctx, ps, (hipStream_t)stream))) return rc;
     }
-    return TSD_OK;
+  } else if ((rc = run_pass(ctx, ps, (hipStream_t)stream))) {
+    return rc;
   }
-  return run_pass(ctx, ps, (hipStream_t)stream);
+  HIP_TRY(ctx, note_pass(&ctx->use, (hipStream_t)stream));
+  return TSD_OK;
 }
 
 int tsd_accept_commit(tsd_ctx* ctx, const int32_t* forced_len_dev, void* stream) {
@@ -1491,15 +1507,18 @@ int tsd_round(tsd_ctx* ctx, void* stream) {
   const bool deliver = ctx->host_counts && ctx->seq_ready;
   const int need_before = ctx->need_lb;  // a round commits at most K + 1 patches per series
   if (!(ctx->cfg.flags & TSD_FLAG_NO_COMPACT)) peek_counts(ctx);
-  const bool small = use_small_round(ctx, (hipStream_t)stream);
+  bool small = use_small_round(ctx, (hipStream_t)stream);
+  const bool whole = small && !ctx->fused_draft;  // draft steps and verification in one launch
+  if (whole) {
+    ctx->injected = false;
+    if ((rc = run_small_round(ctx, 3, false, (hipStream_t)stream)) == kResidentBusy) small = false;
+    else if (rc) return rc;
+  }
   const int cls = device_counts(ctx) ? size_class(ctx) : 0;
   ctx->capture_rows = class_rows(ctx, cls);
   auto body = [&]() {
     int r;
-    if (small && !ctx->fused_draft) {
-      ctx->injected = false;
-      if ((r = run_small_round(ctx, 3, false, (hipStream_t)stream))) return r;
-    } else {
+    if (!(whole && small)) {
       if ((r = tsd_draft_propose(ctx, stream))) return r;
       if ((r = tsd_target_verify(ctx, stream))) return r;
     }
@@ -1509,9 +1528,10 @@ int tsd_round(tsd_ctx* ctx, void* stream) {
                                          ctx->host_counts, (hipStream_t)stream));
     return (int)TSD_OK;
   };
-  // (the resident kernel is not captured: its launches are kept apart from other handles' by events; three launches need no graph)
+  // (the resident kernel is not captured: whether it may run is known at its launch; three launches need no graph)
   rc = small ? body() : run_graphed(ctx, &ctx->graph_round[round_positions(ctx)][cls], (hipStream_t)stream, body);
   if (rc == TSD_OK) {
+    if (!small) HIP_TRY(ctx, note_pass(&ctx->use, (hipStream_t)stream));
     // (a replayed graph does not pass through accept_commit_impl: keep the bound on the patches still needed honest here)
     ctx->need_lb = std::max(0, need_before - (ctx->cfg.K + 1));
     if (deliver) {
@@ -1526,11 +1546,11 @@ int tsd_target_step(tsd_ctx* ctx, void* stream) {
   int rc = require_ready(ctx, true);
   if (rc) return rc;
   const int P = ctx->cfg.patch;
-  if (use_small_round(ctx, (hipStream_t)stream)) {
-    if ((rc = run_small_round(ctx, 2, true, (hipStream_t)stream))) return rc;
+  if (use_small_round(ctx, (hipStream_t)stream) && (rc = run_small_round(ctx, 2, true, (hipStream_t)stream)) != kResidentBusy) {
+    if (rc) return rc;
     return accept_commit_impl(ctx, nullptr, 0, (hipStream_t)stream);
   }
-  return run_graphed(ctx, &ctx->graph_step, (hipStream_t)stream, [&]() {
+  rc = run_graphed(ctx, &ctx->graph_step, (hipStream_t)stream, [&]() {
     Pass ps;
     std::memset(&ps, 0, sizeof(ps));
     const Cover cv = cover(ctx);
@@ -1553,6 +1573,9 @@ int tsd_target_step(tsd_ctx* ctx, void* stream) {
     if (r) return r;
     return accept_commit_impl(ctx, nullptr, 0, (hipStream_t)stream);  // K = 0: commit the target's mean
   }, /*counts=*/false);  // target-only decoding finishes every series in the same step: nothing to compact
+  if (rc) return rc;
+  HIP_TRY(ctx, note_pass(&ctx->use, (hipStream_t)stream));
+  return TSD_OK;
 }
 
 int tsd_num_active(tsd_ctx* ctx, int32_t* out_host, void* stream) {

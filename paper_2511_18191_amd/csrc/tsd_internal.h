@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "small_round_plan.h"
@@ -236,7 +237,20 @@ void small_round_model(const tsd_model_cfg& c, int patch, const bf16* W_e, const
                        const bf16* W2, SmallModel* m);
 size_t small_round_exchange_bytes(const tsd_config& c);
 int small_round_stages(const tsd_config& c);
-hipError_t launch_small_round(const SmallRoundP& p, const void* owner, hipStream_t st);
+// A handle's latest pass, as the other handles on its device see it (see small_round.hip).
+struct PassUse {
+  int device = -1;
+  bool resident = false;          // the handle may run the resident kernel
+  hipEvent_t done = nullptr;
+  hipStream_t stream = nullptr;
+  std::thread::id thread;         // with hipStreamPerThread
+  bool in_flight = false;         // recorded and not yet seen finished
+};
+void add_use(PassUse* use, int device, bool resident);
+void remove_use(PassUse* use);
+hipError_t note_pass(PassUse* use, hipStream_t st);
+// *busy: another handle's pass is in flight on another stream, and nothing was launched
+hipError_t launch_small_round(const SmallRoundP& p, PassUse* use, hipStream_t st, bool* busy);
 
 struct PackP {
   const float* W;     // [K][N] row-major source (y = x W)

@@ -81,7 +81,8 @@ def test_32_rows_with_partly_used_workers(B, K, target, draft):
 
 
 def test_two_handles_on_two_streams():
-    """Rounds of two handles enqueued alternately without waiting give what each gives alone."""
+    """Rounds of two handles enqueued alternately without waiting give what each gives alone, and only the one that is alone
+    on the GPU takes the resident kernel."""
     cases = [Case("mini2", B=2), Case("mini3", B=3)]
     alone = []
     for c in cases:
@@ -94,10 +95,53 @@ def test_two_handles_on_two_streams():
     for c, s in zip(cases, sess):
         s.prefill(c.context, c.cfg.n_ctx, c.cfg.horizon)
     torch.cuda.synchronize()
+    for _ in range(20):            # (a few milliseconds of work; the next call comes a fraction of one later)
+        sess[0].reset_decode()
+        sess[0].round()
+    assert sess[0].resident_passes() == 20
+    sess[1].round()
+    assert sess[1].resident_passes() == 0      # the other stream's passes are in flight: kernel by kernel, the GPU shared
+    torch.cuda.synchronize()
+    sess[1].round()
+    assert sess[1].resident_passes() == 1
+    for s in sess:
+        s.reset_decode()
     for _ in range(max(c.cfg.T for c in cases)):      # a round commits at least one patch
         for s in sess:
             s.round()
     for s, ref in zip(sess, alone):
         assert s.num_active() == 0
         np.testing.assert_array_equal(s.get_forecast().cpu().numpy(), ref)
+        s.close()
+
+
+def test_beside_a_large_batch():
+    """A handle of any kind that is busy on another stream keeps a small one off the resident kernel; on the same stream, which
+    orders the two, it does not."""
+    big, small = Case("mini2", B=64), Case("mini2", B=2)
+    sb, ss = big.session(), small.session()
+    for c, s in ((big, sb), (small, ss)):
+        s.prefill(c.context, c.cfg.n_ctx, c.cfg.horizon)
+    torch.cuda.synchronize()
+    for _ in range(20):
+        sb.reset_decode()
+        sb.round()
+    assert sb.resident_passes() == 0
+    ss.round()
+    assert ss.resident_passes() == 0
+    torch.cuda.synchronize()
+    ss.reset_decode()
+    ss.stream = sb.stream
+    torch.cuda.synchronize()
+    for _ in range(20):
+        sb.reset_decode()
+        sb.round()
+    ss.run_rounds()
+    assert ss.resident_passes() > 0
+    got = ss.get_forecast().cpu().numpy()
+    ref = small.session(flags=tsd.TSD_FLAG_NO_PINNED_COUNTS)
+    ref.prefill(small.context, small.cfg.n_ctx, small.cfg.horizon)
+    ref.run_rounds()
+    np.testing.assert_array_equal(got, ref.get_forecast().cpu().numpy())
+    for s in (sb, ss, ref):
         s.close()
