@@ -248,8 +248,10 @@ int tsd_accept_commit_static(const float* X_dev, const float* mu_q_dev, const fl
  * whole slabs, i.e. multiples of 32 s with s = ceil(width / (32 n)) and n = 16 from width 512 on, else 4 (every d_model but 320
  * and 448).  Not on a stream the caller is capturing, nor between tsd_profile_begin
  * and tsd_profile_end, which time the kernels one by one, nor while another handle's passes are in flight on another stream
- * (launch by launch the two overlap); tsd_resident_passes tells how often it ran.  Should its workgroups not become resident together within 4 seconds, the round commits
- * nothing and every later call but tsd_prefill returns TSD_E_HIP. */
+ * (launch by launch the two overlap); tsd_resident_passes tells how often it ran.  Should its
+ * workgroups not become resident together (another process's launch may hold compute units) within the time of
+ * tsd_set_resident_wait, one workgroup finishes the pass alone: the results are the same, the pass takes some 3 us per workgroup and
+ * stage, and the handle runs kernel by kernel from then on. */
 int tsd_round(tsd_ctx* ctx, void* stream);
 
 /* Rounds until no series needs patches any more (or max_rounds rounds have run): the loop
@@ -264,7 +266,8 @@ int tsd_round(tsd_ctx* ctx, void* stream);
 int tsd_run_rounds(tsd_ctx* ctx, int32_t max_rounds, int32_t* rounds_host, int32_t* active_host, void* stream);
 
 /* Target-only autoregressive baseline (Eq. 1) from the same kernels: one target pass over the
- * pending token, whose output is committed for every active series. */
+ * pending token, whose output is committed for every active series.  The draft does not see the step: a forecast that
+ * goes on with rounds may propose from a draft cache that misses a position (prefill or reset first to compare proposals). */
 int tsd_target_step(tsd_ctx* ctx, void* stream);
 
 /* Number of series that still need patches.  Synchronises `stream`.  Passes cover only the series
@@ -383,6 +386,10 @@ int tsd_profile_launches(tsd_ctx* ctx, tsd_launch_rec* out_host, int32_t max_rec
 /* Launches of the resident decode kernel (see tsd_round) this handle has made since tsd_create: one per tsd_round,
  * tsd_target_step, tsd_draft_propose or tsd_target_verify that took it.  Host-only. */
 int tsd_resident_passes(tsd_ctx* ctx, int64_t* n_host);
+
+/* How long the workgroups of later launches of the resident kernel wait for one another, 1000 ms unless set; 0: not at
+ * all, i.e. the next pass is finished by one workgroup and the handle runs kernel by kernel afterwards.  Host-only. */
+int tsd_set_resident_wait(tsd_ctx* ctx, int32_t milliseconds);
 
 /* Measurement tap: one product through the same tiled kernel, tile selection and tile order the
  * transformer passes use.  dtype TSD_BF16: A and Wt are bf16; TSD_F32: fp32.  variant 0:

@@ -73,6 +73,7 @@ SYMBOLS = {
     "tsd_set_route_tap": ([C.c_void_p, C.c_int, C.c_void_p, C.c_size_t], C.c_int),
     "tsd_profile_launches": ([C.c_void_p, C.c_void_p, C.c_int32, C.POINTER(C.c_int32)], C.c_int),
     "tsd_resident_passes": ([C.c_void_p, C.POINTER(C.c_int64)], C.c_int),
+    "tsd_set_resident_wait": ([C.c_void_p, C.c_int32], C.c_int),
     "tsd_bench_gemm": ([C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p], C.c_int),
     "tsd_bench_copy": ([C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p], C.c_int),
     "tsd_bench_mfma": ([C.c_int32, C.c_int32, C.c_void_p, C.c_void_p], C.c_int),
@@ -362,6 +363,10 @@ class Session:
         n = C.c_int64()
         _check(lib().tsd_resident_passes(self.h, C.byref(n)), self.h)
         return n.value
+
+    def set_resident_wait(self, milliseconds):
+        """How long the resident kernel's workgroups wait for one another before one of them does the work alone."""
+        _check(lib().tsd_set_resident_wait(self.h, milliseconds), self.h)
 
     def route_tap(self, which=TSD_TARGET):
         """Install (and return) an int32 tensor [layers, max_batch, max_tokens, top_k], filled with -1, in which

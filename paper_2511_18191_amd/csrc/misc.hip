@@ -150,7 +150,6 @@ hipError_t launch_sample(const SampleP& p, hipStream_t st) {
 // positions in fours and the state words one after the other, took 10.6 us at 1024 series of 6 x 96, 7.9 at one of 4 x 96.
 __global__ __launch_bounds__(256) void accept_kernel(const AcceptP p) {
   __shared__ float energy[2][16];
-  if (p.gave_up && *p.gave_up) return;
   if (p.n_dev && (int)blockIdx.x >= *p.n_dev) return;
   const int b = p.act ? p.act[blockIdx.x] : (int)blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int K = p.K, P = p.P;

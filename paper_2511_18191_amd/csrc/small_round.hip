@@ -24,9 +24,9 @@
 //   * Every sum is formed in the order of the kernels this replaces (gemm_skinny.hip, attn_mfma.h): same bits.
 //
 // All workgroups of a launch have to be resident together: one per compute unit, and a process has one launch of this kernel
-// on a device at a time (launch_small_round).  Every wait is bounded: a workgroup that has watched for kWaitTicks
-// or sees another's give-up sets the status word and leaves, the acceptance kernel then commits nothing and the host
-// reports the failure.
+// on a device at a time (launch_small_round).  Other processes are not seen: where two launches have taken each other's compute units,
+// neither can go on.  So every wait is bounded: a workgroup that has waited since its start for p.wait_ticks, or sees that another
+// gave up, leaves, and small_round_alone_kernel behind the launch does the launch's work.
 #include <algorithm>
 #include <atomic>
 #include <mutex>
@@ -45,7 +45,6 @@ constexpr int kThreads = (kWorkers + 1) * 64;
 constexpr int kRowsMax = kSmallRoundRows;
 constexpr int kFlagWords = kSmallRoundFlagWords;  // one flag per 64-byte line
 constexpr int kLdp = 18;                          // columns of a partial-sum row in LDS (padded)
-constexpr long long kWaitTicks = 400000000;       // 4 s of the 100 MHz wall clock
 constexpr int kSc1 = 16;                          // cache policy of the exchange: agent scope
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -109,10 +108,10 @@ __device__ __forceinline__ void load_weights(const bf16* W, unsigned off, int pe
 
 // Starts the loads of this worker's share of the workgroup's weights of a product, W its matrix.
 template <bool QKV>
-__device__ __forceinline__ void prefetch(const SmallProd& d, const bf16* W, int wave, int lane, Weights& w) {
-  if ((int)blockIdx.x >= d.units || 4 * wave >= d.used) return;
+__device__ __forceinline__ void prefetch(const SmallProd& d, const bf16* W, int wg, int wave, int lane, Weights& w) {
+  if (wg >= d.units || 4 * wave >= d.used) return;
   asm volatile("" : "+v"(lane));  // (an opaque copy: keeps the address arithmetic below from being hoisted to the kernel's top)
-  const int li = lane & 15, col = column_of<QKV>(d, blockIdx.x, li & ((1 << d.cs) - 1));
+  const int li = lane & 15, col = column_of<QKV>(d, wg, li & ((1 << d.cs) - 1));
   const unsigned off = (unsigned)(col * d.K + (lane >> 4) * 8);
   if (d.cs == 2) load_weights<4>(W, off, d.per, d.used, wave, li, w);
   else if (d.cs == 3) load_weights<8>(W, off, d.per, d.used, wave, li, w);
@@ -120,11 +119,11 @@ __device__ __forceinline__ void prefetch(const SmallProd& d, const bf16* W, int 
 }
 
 // The embedding's k range may end inside a k-step or a slab: clamped reads, against zero activations.
-__device__ __forceinline__ void prefetch_embed(const SmallProd& d, const bf16* W, int wave, int lane, Weights& w) {
-  if ((int)blockIdx.x >= d.units || 4 * wave >= d.used) return;
+__device__ __forceinline__ void prefetch_embed(const SmallProd& d, const bf16* W, int wg, int wave, int lane, Weights& w) {
+  if (wg >= d.units || 4 * wave >= d.used) return;
   asm volatile("" : "+v"(lane));
   const int li = lane & 15, k0 = (4 * wave + (li >> 2)) * d.per * 32 + (lane >> 4) * 8;
-  const bf16* row = W + (blockIdx.x * 4 + (li & 3)) * d.K;
+  const bf16* row = W + (wg * 4 + (li & 3)) * d.K;
 #pragma unroll
   for (int j = 0; j < 4; ++j)
     if (j < d.per) w.f[j] = *reinterpret_cast<const bf16x8*>(row + min(k0 + j * 32, d.K - 8));
@@ -567,10 +566,73 @@ __device__ __forceinline__ void set_rows(const SmallRoundP& p, const PassView& v
   }
 }
 
+// Eight values of a row's patch, from value k on.  (Patches are exchanged through reused lines: read past the caches; all three
+// arrays lie behind `pending`.)
+__device__ __forceinline__ Rsrc patches_of(const SmallRoundP& p) { return rsrc_of(p.pending, 0x7fffffff); }
+__device__ __forceinline__ void load_patch(const SmallRoundP& p, const PassView& v, const Shared& sh, Rsrc patches, int r, int k, float* f) {
+  const int P = p.P, sl = r / v.nq, t = r - sl * v.nq;
+  const long b = sh.ser[r];
+  const float* src;
+  if (v.draft)
+    src = v.step == 1 ? (t == 0 ? p.prev : p.pending) + b * P : p.X + b * p.x_stride + (long)(v.step - 2) * P;
+  else
+    src = t == 0 ? p.pending + b * P : p.X + b * p.x_stride + (long)(t - 1) * P;
+  const int off = (int)(reinterpret_cast<const char*>(src + k) - reinterpret_cast<const char*>(p.pending));
+  *reinterpret_cast<u32x4*>(f) = load16(patches, off);
+  *reinterpret_cast<u32x4*>(f + 4) = load16(patches, off + 16);
+}
+
+// Column pairs of a product's columns, one after the other along the rows, over the lanes of a wavefront.
+template <typename Fn>
+__device__ __forceinline__ void each_pair(const SmallProd& d, int M, int lane, Fn fn) {
+  const int sft = d.cs - 1;
+  for (int i = lane; i < M << sft; i += 64) {
+    const int row = i >> sft;
+    fn(row, (i & ((1 << sft) - 1)) * 2);
+  }
+}
+
+// Epilogues that need nothing but the partial sums: FFN up with GELU, and the head.
+__device__ __forceinline__ void finish_up(const SmallModel& m, const PassView& v, int l, int wg, int lane, const Shared& sh) {
+  const SmallProd& d = m.up;
+  bf16* hid = v.rows(l, kHidden) + (wg << d.cs);
+  each_pair(d, v.M, lane, [&](int row, int c) {
+    const Sums z = sums_of<false, true>(sh, row, c, 0, d.used);
+    const float2 s = z.a;
+    const float rs = norm_scale(z.ss, v.D);
+    publish_bf16x2(hid + row * m.F + c, gelu_tanh(s.x * rs), gelu_tanh(s.y * rs));
+  });
+}
+__device__ __forceinline__ void finish_head(const SmallRoundP& p, const SmallModel& m, const PassView& v, int wg, int lane, const Shared& sh) {
+  const SmallProd& d = m.head;
+  const int P = p.P;
+  each_pair(d, v.M, lane, [&](int row, int c) {
+    const int sl = row / v.nq, t = row - sl * v.nq, col = (wg << d.cs) + c;
+    const Sums z = sums_of<false, true>(sh, row, c, 0, d.used);
+    const float rs = norm_scale(z.ss, v.D);
+    float2 s = z.a;
+    s.x *= rs;
+    s.y *= rs;
+    const long b = sh.ser[row];
+    if (!v.draft) {
+      *reinterpret_cast<float2*>(p.mu_p + b * p.mu_stride + (long)t * P + col) = s;
+    } else if (t == v.nq - 1) {  // (step 1 emits from the pending token only)
+      float* x = p.X + b * p.x_stride + (long)(v.step - 1) * P + col;
+      publish4(x, __builtin_bit_cast(unsigned, s.x));
+      publish4(x + 1, __builtin_bit_cast(unsigned, s.y));
+    }
+  });
+}
+
 // The stage's results are published.
 __device__ __forceinline__ void raise_flag(const SmallRoundP& p, int wg, int lane, unsigned value) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   if (lane == 0) __hip_atomic_store(p.flags + wg * kFlagWords, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void give_up(const SmallRoundP& p) {
+  __hip_atomic_store(p.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(p.host_status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 __device__ __forceinline__ bool hop_worker(Shared& sh) {
@@ -579,18 +641,17 @@ __device__ __forceinline__ bool hop_worker(Shared& sh) {
 }
 
 __device__ __forceinline__ void worker_loop(const SmallRoundP& p, int n, int Kr, int Kd, int n_pass, int wave, int lane, Shared& sh) {
-  const int wg = blockIdx.x, P = p.P;
+  const int wg = blockIdx.x;
   Weights w;
   {
     const PassView v(p, 0, Kd, Kr, n);
-    prefetch_embed(v.m->embed, v.m->embed.W, wave, lane, w);
+    prefetch_embed(v.m->embed, v.m->embed.W, wg, wave, lane, w);
   }
   for (int ps = 0; ps < n_pass; ++ps) {
     const PassView v(p, ps, Kd, Kr, n);
     const SmallModel& m = *v.m;
     const int D = v.D, M = v.M, nq = v.nq, tasks = n * m.Hh;
-    // (patches are exchanged through reused lines: read past the caches; all three arrays lie behind `pending`)
-    const Rsrc patches = rsrc_of(p.pending, 0x7fffffff);
+    const Rsrc patches = patches_of(p);
     wg_barrier();  // (the previous pass's rows are no longer read)
     set_rows(p, v, sh);
     wg_barrier();
@@ -606,22 +667,11 @@ __device__ __forceinline__ void worker_loop(const SmallRoundP& p, int n, int Kr,
 
     if (wg < m.embed.units) {
       if (!hop_worker(sh)) return;
-      product_f32<false>(m.embed, M, wave, lane, w, sh, [&](int r, int k, float* f) {
-        const int sl = r / nq, t = r - sl * nq;
-        const long b = sh.ser[r];
-        const float* src;
-        if (v.draft)
-          src = v.step == 1 ? (t == 0 ? p.prev : p.pending) + b * P : p.X + b * p.x_stride + (long)(v.step - 2) * P;
-        else
-          src = t == 0 ? p.pending + b * P : p.X + b * p.x_stride + (long)(t - 1) * P;
-        const int off = (int)(reinterpret_cast<const char*>(src + k) - reinterpret_cast<const char*>(p.pending));
-        *reinterpret_cast<u32x4*>(f) = load16(patches, off);
-        *reinterpret_cast<u32x4*>(f + 4) = load16(patches, off + 16);
-      });
+      product_f32<false>(m.embed, M, wave, lane, w, sh, [&](int r, int k, float* f) { load_patch(p, v, sh, patches, r, k, f); });
       wg_barrier();
     }
     // (after the barrier: the control wavefront does not wait for the loads to be issued)
-    prefetch<true>(m.qkv, m.qkv.W, wave, lane, w);
+    prefetch<true>(m.qkv, m.qkv.W, wg, wave, lane, w);
 
     for (int l = 0; l < m.L; ++l) {
       // One body for the products of a layer (written out four times they crowd the instruction cache and the scalar registers),
@@ -649,10 +699,10 @@ __device__ __forceinline__ void worker_loop(const SmallRoundP& p, int n, int Kr,
         }
         // the weights of the workgroup's next product
         if (kind == kDown && l + 1 < m.L) {
-          prefetch<true>(m.qkv, v.weights(m.qkv, l + 1), wave, lane, w);
+          prefetch<true>(m.qkv, v.weights(m.qkv, l + 1), wg, wave, lane, w);
         } else {
           const SmallProd& nx = kind == kQkv ? m.out : kind == kOut ? m.up : kind == kUp ? m.down : m.head;
-          prefetch<false>(nx, kind == kDown ? nx.W : v.weights(nx, l), wave, lane, w);
+          prefetch<false>(nx, kind == kDown ? nx.W : v.weights(nx, l), wg, wave, lane, w);
         }
       }
     }
@@ -669,14 +719,14 @@ __device__ __forceinline__ void worker_loop(const SmallRoundP& p, int n, int Kr,
     }
     if (more) {
       const SmallModel& nm = p.m[ps + 1 < Kd ? 1 : 0];
-      prefetch_embed(nm.embed, nm.embed.W, wave, lane, w);
+      prefetch_embed(nm.embed, nm.embed.W, wg, wave, lane, w);
     }
   }
 }
 
 __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr, int Kd, int n_pass, int lane, Shared& sh) {
-  const int wg = blockIdx.x, P = p.P;
-  const long long deadline = wall_clock64() + kWaitTicks;
+  const int wg = blockIdx.x;
+  const long long deadline = wall_clock64() + p.wait_ticks;
   Walk walk{p.epoch, 0};
   // The previous stage's results are there (false: give up); the workers are let go.
   auto hop = [&]() -> bool {
@@ -697,8 +747,7 @@ __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr
           const int gone = __hip_atomic_load(p.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           if (gone || wall_clock64() > deadline) {
             if (lane == 0) {
-              __hip_atomic_store(p.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              __hip_atomic_store(p.host_status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+              give_up(p);
               sh.quit = 1;
             }
             go = false;
@@ -715,17 +764,9 @@ __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr
   for (int ps = 0; ps < n_pass; ++ps) {
     const PassView v(p, ps, Kd, Kr, n);
     const SmallModel& m = *v.m;
-    const int D = v.D, F = m.F, Hh = m.Hh, M = v.M, nq = v.nq;
+    const int D = v.D, Hh = m.Hh, M = v.M, nq = v.nq;
     wg_barrier();
     wg_barrier();
-    // this wavefront's elements of a product: column pairs, one after the other along the rows
-    auto each_pair = [&](const SmallProd& d, auto fn) {
-      const int sft = d.cs - 1;
-      for (int i = lane; i < M << sft; i += 64) {
-        const int row = i >> sft;
-        fn(row, (i & ((1 << sft) - 1)) * 2);
-      }
-    };
     // its elements of the QKV product (the same in every layer): row, column inside the head, rotary factors
     const SmallProd& q = m.qkv;
     const int qhalf = 1 << (q.cs - 1), qsft = q.cs - 1, qn = M << qsft;
@@ -752,7 +793,7 @@ __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr
       if (!hop()) return;
       wg_barrier();
       bf16* x0 = v.rows(0, kIn) + (wg << e.cs);
-      each_pair(e, [&](int row, int c) {
+      each_pair(e, M, lane, [&](int row, int c) {
         const float2 s = sums_of<false, false>(sh, row, c, 0, e.used).a;
         sh.xown[row][c] = s.x;
         sh.xown[row][c + 1] = s.y;
@@ -809,7 +850,7 @@ __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr
           wg_barrier();
           const int at0 = wg << d.cs;
           float* res = v.residual();
-          each_pair(d, [&](int row, int c) {
+          each_pair(d, M, lane, [&](int row, int c) {
             float2 s = sums_of<false, false>(sh, row, c, 0, d.used).a;
             s.x += sh.xown[row][c];
             s.y += sh.xown[row][c + 1];
@@ -835,13 +876,7 @@ __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr
       if (wg < f1.units) {
         if (!hop()) return;
         wg_barrier();
-        bf16* hid = v.rows(l, kHidden) + (wg << f1.cs);
-        each_pair(f1, [&](int row, int c) {
-          const Sums z = sums_of<false, true>(sh, row, c, 0, f1.used);
-          const float2 s = z.a;
-          const float rs = norm_scale(z.ss, D);
-          publish_bf16x2(hid + row * F + c, gelu_tanh(s.x * rs), gelu_tanh(s.y * rs));
-        });
+        finish_up(m, v, l, wg, lane, sh);
         raise();
       }
       walk.done(f1.units);
@@ -853,42 +888,157 @@ __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr
     if (wg < hd.units) {
       if (!hop()) return;
       wg_barrier();
-      each_pair(hd, [&](int row, int c) {
-        const int sl = row / nq, t = row - sl * nq, col = (wg << hd.cs) + c;
-        const Sums z = sums_of<false, true>(sh, row, c, 0, hd.used);
-        const float rs = norm_scale(z.ss, D);
-        float2 s = z.a;
-        s.x *= rs;
-        s.y *= rs;
-        const long b = sh.ser[row];
-        if (!v.draft) {
-          *reinterpret_cast<float2*>(p.mu_p + b * p.mu_stride + (long)t * P + col) = s;
-        } else if (t == nq - 1) {  // (step 1 emits from the pending token only)
-          float* x = p.X + b * p.x_stride + (long)(v.step - 1) * P + col;
-          publish4(x, __builtin_bit_cast(unsigned, s.x));
-          publish4(x + 1, __builtin_bit_cast(unsigned, s.y));
-        }
-      });
+      finish_head(p, m, v, wg, lane, sh);
       raise();
     }
     walk.done(hd.units);
   }
 }
 
+// The passes of a launch: series still decoding, positions proposed, draft steps, passes.
+struct Extent {
+  int n, Kr, Kd, n_pass;
+  __device__ __forceinline__ explicit Extent(const SmallRoundP& p) {
+    n = p.counts ? min(p.counts[0], p.n) : p.n;
+    Kr = p.step_only ? 0 : (p.follow_need ? max(1, min(p.K, p.counts[1])) : p.K);
+    Kd = (p.phases & 1) ? Kr : 0;
+    n_pass = Kd + ((p.phases & 2) ? 1 : 0);
+  }
+};
+
 __global__ __launch_bounds__(kThreads) void small_round_kernel(const SmallRoundP p) {
   __shared__ __attribute__((aligned(16))) Shared sh;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n = p.counts ? min(p.counts[0], p.n) : p.n;  // series still decoding
-  if (n <= 0) return;                                    // (uniform over the grid)
-  const int Kr = p.step_only ? 0 : (p.follow_need ? max(1, min(p.K, p.counts[1])) : p.K);
-  const int Kd = (p.phases & 1) ? Kr : 0;  // draft steps
-  const int n_pass = Kd + ((p.phases & 2) ? 1 : 0);
+  const int gone = *p.status;  // an earlier launch gave up: this one is left to the kernel below
+  const Extent x(p);
+  if (gone || x.n <= 0) return;
+  if (p.wait_ticks <= 0) {  // (uniform over the grid)
+    if (blockIdx.x == 0 && threadIdx.x == 0) give_up(p);
+    return;
+  }
   if (threadIdx.x == 0) sh.quit = 0;
   wg_barrier();
   if (wave == kWorkers)
-    control_loop(p, n, Kr, Kd, n_pass, lane, sh);
+    control_loop(p, x.n, x.Kr, x.Kd, x.n_pass, lane, sh);
   else
-    worker_loop(p, n, Kr, Kd, n_pass, wave, lane, sh);
+    worker_loop(p, x.n, x.Kr, x.Kd, x.n_pass, wave, lane, sh);
+}
+
+// Launched behind every launch of the kernel above, and idle (4 us of a round of 380) unless that one gave up: the same passes from their
+// beginning by ONE workgroup, which takes the units of a stage one after the other and waits for nobody.  Nothing of a pass is lost
+// by that: what it overwrites (the cache rows of its tokens, proposals, target means) follows from what was committed
+// before.  Slow (some 3 us per unit and stage) and rare: from the next call on the handle runs kernel by kernel.
+__global__ __launch_bounds__(kThreads) void small_round_alone_kernel(const SmallRoundP p) {
+  __shared__ __attribute__((aligned(16))) Shared sh;
+  if (*p.status == 0) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool worker = wave < kWorkers;
+  const Extent x(p);
+  if (x.n <= 0) return;
+  const Rsrc patches = patches_of(p);
+  Weights w;
+  for (int ps = 0; ps < x.n_pass; ++ps) {
+    const PassView v(p, ps, x.Kd, x.Kr, x.n);
+    const SmallModel& m = *v.m;
+    const int D = v.D, M = v.M, nq = v.nq, Hh = m.Hh;
+    float* res = v.residual();  // (the residual of all columns: here in memory)
+    __syncthreads();
+    set_rows(p, v, sh);
+    __syncthreads();
+    // a product: the workers' share of every unit, then its epilogue
+    auto units = [&](const SmallProd& d, auto share, auto finish) {
+      for (int u = 0; u < d.units; ++u) {
+        if (worker) share(u);
+        __syncthreads();
+        if (!worker) finish(u);
+        __syncthreads();
+      }
+    };
+    auto add_residual = [&](const SmallProd& d, bf16* out, bool first, bool last) {
+      return [&, out, first, last](int u) {
+        const int at0 = u << d.cs;
+        each_pair(d, M, lane, [&](int row, int c) {
+          float2 s = sums_of<false, false>(sh, row, c, 0, d.used).a;
+          float* r = res + row * D + at0 + c;
+          if (!first) {
+            s.x += r[0];
+            s.y += r[1];
+          }
+          r[0] = s.x;
+          r[1] = s.y;
+          if (!last) publish_bf16x2(out + row * D + at0 + c, s.x, s.y);
+        });
+      };
+    };
+    auto share_of = [&](const SmallProd& d, const bf16* W, const bf16* A, bool norm) {
+      return [&, W, A, norm](int u) {
+        prefetch<false>(d, W, u, wave, lane, w);
+        product(d, A, M, norm, wave, lane, w, sh);
+      };
+    };
+
+    units(m.embed,
+          [&](int u) {
+            prefetch_embed(m.embed, m.embed.W, u, wave, lane, w);
+            product_f32<false>(m.embed, M, wave, lane, w, sh, [&](int r, int k, float* f) { load_patch(p, v, sh, patches, r, k, f); });
+          },
+          add_residual(m.embed, v.rows(0, kIn), true, false));
+    for (int l = 0; l < m.L; ++l) {
+      bf16* pool = m.kv_pool + (size_t)l * m.layer_pool_elems;
+      units(m.qkv,
+            [&](int u) {
+              prefetch<true>(m.qkv, v.weights(m.qkv, l), u, wave, lane, w);
+              product(m.qkv, v.rows(l, kIn), M, true, wave, lane, w, sh);
+            },
+            [&](int u) {
+              const int qhalf = 1 << (m.qkv.cs - 1), c0 = column_of<true>(m.qkv, u, 0), which = c0 < D ? 0 : c0 < 2 * D ? 1 : 2;
+              const int h = (c0 - which * D) >> 6, d0 = c0 & 63;
+              each_pair(m.qkv, M, lane, [&](int row, int c) {
+                const int f = d0 + (c < qhalf ? c : c - qhalf), d = d0 + (c < qhalf ? c : 32 + c - qhalf), pos = sh.pos[row];
+                const Sums z = sums_of<true, true>(sh, row, c, c < qhalf ? c + qhalf : c - qhalf, m.qkv.used);
+                const float rs = norm_scale(z.ss, D);
+                float2 s = z.a;
+                s.x *= rs;
+                s.y *= rs;
+                if (which < 2) {
+                  const float2 cs = *reinterpret_cast<const float2*>(m.rope_cos + (long)pos * 32 + f);
+                  const float2 sn = *reinterpret_cast<const float2*>(m.rope_sin + (long)pos * 32 + f);
+                  const float sg = c < qhalf ? -rs : rs;
+                  s.x = s.x * cs.x + sg * z.b.x * sn.x;
+                  s.y = s.y * cs.y + sg * z.b.y * sn.y;
+                }
+                const unsigned to = which == 0 ? (unsigned)(row * D + h * 64 + d)
+                                               : (unsigned)((((sh.page[row] * 2 + (which - 1)) * Hh + h) * p.PT + (pos & (p.PT - 1))) * 64 + d);
+                publish_bf16x2((which == 0 ? v.rows(l, kQuery) : pool) + to, s.x, s.y);
+              });
+            });
+      for (int u = 0; u < x.n * Hh; ++u) {
+        const int sl = u / Hh, head = u - sl * Hh, r0 = sl * nq;
+        const int base = __builtin_amdgcn_readfirstlane(sh.pos[r0]);
+        if (worker) {
+          const int my_page = p.page_table[(long)sh.ser[r0] * p.pt_stride + min(lane, p.pt_stride - 1)];
+          attend(p, pool, v.rows(l, kQuery) + r0 * D + head * 64, v.rows(l, kMixed) + r0 * D + head * 64, D, head, Hh, my_page, base, nq, wave,
+                 lane, sh, [] { return true; });
+        } else {
+          attend_barriers(base + nq);
+        }
+        __syncthreads();
+      }
+      const bool last = l + 1 == m.L;
+      units(m.out, share_of(m.out, v.weights(m.out, l), v.rows(l, kMixed), false), add_residual(m.out, v.rows(l, kMid), false, false));
+      units(m.up, share_of(m.up, v.weights(m.up, l), v.rows(l, kMid), true), [&](int u) { finish_up(m, v, l, u, lane, sh); });
+      units(m.down, share_of(m.down, v.weights(m.down, l), v.rows(l, kHidden), false), add_residual(m.down, v.rows(l + 1, kIn), false, last));
+    }
+    units(m.head,
+          [&](int u) {
+            prefetch<false>(m.head, m.head.W, u, wave, lane, w);
+            product_f32<true>(m.head, M, wave, lane, w, sh, [&](int r, int k, float* f) {
+              *reinterpret_cast<float4*>(f) = *reinterpret_cast<const float4*>(res + (r * D + k));
+              *reinterpret_cast<float4*>(f + 4) = *reinterpret_cast<const float4*>(res + (r * D + k + 4));
+            });
+          },
+          [&](int u) { finish_head(p, m, v, u, lane, sh); });
+  }
 }
 
 SmallProd product_of(const bf16* W, int K, int N) {
@@ -1007,7 +1157,10 @@ hipError_t launch_small_round(const SmallRoundP& p, PassUse* use, hipStream_t st
     u->in_flight = false;
   }
   hipLaunchKernelGGL(small_round_kernel, dim3(kWg), dim3(kThreads), 0, st, p);
-  const hipError_t e = hipGetLastError();
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(small_round_alone_kernel, dim3(1), dim3(kThreads), 0, st, p);
+  e = hipGetLastError();
   return e != hipSuccess ? e : record_use(use, st);
 }
 

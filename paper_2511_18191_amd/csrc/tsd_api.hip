@@ -73,6 +73,7 @@ struct tsd_ctx {
   unsigned small_epoch = 0;         // what they hold at most
   char* small_exchange = nullptr;   // what they hand each other
   int64_t small_passes = 0;         // passes launched on it
+  long long small_wait = 100000000; // ticks of 10 ns its workgroups wait for one another
   PassUse use;                      // what other handles see of this one's passes
   int* moe_ids;
   int* route_tap[2] = {nullptr, nullptr};  // caller-owned parity tap per model (tsd_set_route_tap), NULL = off
@@ -200,7 +201,7 @@ int check_config(const tsd_config* c, std::string& why) {
   return TSD_OK;
 }
 
-constexpr int kGaveUp = 12;     // word of count_out (and 3 of the pinned words): a resident pass gave up waiting
+constexpr int kGaveUp = 12;     // word of count_out (and 3 of the pinned words): a launch of the resident kernel gave up waiting
 
 constexpr int kTraceMax = 512;  // stage stamps tsd_trace_draft can return
 
@@ -787,23 +788,20 @@ int round_positions(const tsd_ctx* ctx) {
   return (ctx->k_round >= 1 && ctx->k_round < K) ? ctx->k_round : K;
 }
 
-bool gave_up(const tsd_ctx* ctx) { return ctx->host_counts && __atomic_load_n(&ctx->host_counts[3], __ATOMIC_RELAXED) != 0; }
-
 int require_ready(tsd_ctx* ctx, bool need_prefill) {
   if (!ctx) return fail(nullptr, TSD_E_INVALID_ARG, "ctx is NULL");
   if (need_prefill) {
     if (!ctx->model[0].loaded || !ctx->model[1].loaded) return fail(ctx, TSD_E_BAD_STATE, "weights of both models must be loaded first");
     if (!ctx->prefilled) return fail(ctx, TSD_E_BAD_STATE, "tsd_prefill has not been called");
-    if (gave_up(ctx))
-      return fail(ctx, TSD_E_HIP, "a decode pass gave up waiting for its workgroups to be resident together: start over with tsd_prefill");
   }
   return TSD_OK;
 }
 
-// Whether the next decode pass on `st` runs as the resident kernel.  (Not under a measurement, which times the kernels one by
-// one, and not where the caller is capturing: a captured launch could be replayed beside another handle's.)
+// Whether the next decode pass on `st` may run as the resident kernel.  (Not under a measurement, which times the kernels one by
+// one, not where the caller is capturing: a captured launch could be replayed beside another handle's, and not once a launch
+// gave up: whatever held compute units then may do so again, and cost the wait each time.)
 bool use_small_round(tsd_ctx* ctx, hipStream_t st) {
-  if (!ctx->small_round || ctx->prof_class >= 0) return false;
+  if (!ctx->small_round || ctx->prof_class >= 0 || __atomic_load_n(&ctx->host_counts[3], __ATOMIC_RELAXED)) return false;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (st && (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)) return false;
   return true;
@@ -863,6 +861,7 @@ int run_small_round(tsd_ctx* ctx, int phases, bool step_only, hipStream_t st) {
   r.epoch = ctx->small_epoch;
   r.status = ctx->count_out + kGaveUp;
   r.host_status = ctx->host_counts + 3;
+  r.wait_ticks = ctx->small_wait;
   r.scale = 1.0f / std::sqrt(64.0f);
   bool busy = false;
   HIP_TRY(ctx, launch_small_round(r, &ctx->use, st, &busy));
@@ -911,7 +910,6 @@ int accept_commit_impl(tsd_ctx* ctx, const int32_t* forced, int K, hipStream_t s
     a.inv2sq2_vec = ctx->diag + c.patch;
     a.logdet_dev = ctx->diag + 3 * c.patch;
   }
-  a.gave_up = ctx->small_round ? ctx->count_out + kGaveUp : nullptr;
   a.key0 = (unsigned)(c.seed & 0xFFFFFFFFull);
   a.key1 = (unsigned)(c.seed >> 32);
   a.threshold = (c.flags & TSD_FLAG_THRESHOLD_RULE) ? 1 : 0;
@@ -1157,11 +1155,6 @@ int tsd_prefill(tsd_ctx* ctx, const float* series_dev, int32_t B, int32_t n_ctx_
   const int P = c.patch, N = n_ctx_patches, T = (horizon_steps + P - 1) / P;
   if ((long)N + T + ctx->K_max > c.max_tokens) return fail(ctx, TSD_E_OUT_OF_RANGE, "n_ctx_patches + ceil(horizon/P) + K exceeds max_tokens");
   hipStream_t st = (hipStream_t)stream;
-  if (gave_up(ctx)) {  // what gave up is abandoned: its launches drain, and decoding starts over
-    HIP_TRY(ctx, hipStreamSynchronize(st));
-    HIP_TRY(ctx, launch_fill_int(ctx->count_out + kGaveUp, 0, 1, st));
-    __atomic_store_n(&ctx->host_counts[3], 0, __ATOMIC_RELAXED);
-  }
   ctx->prefilled = false;
   ctx->n_act = -1;
   ctx->seq_floor = ctx->seq_launched;
@@ -1782,6 +1775,13 @@ int tsd_resident_passes(tsd_ctx* ctx, int64_t* n_host) {
   if (!ctx) return fail(nullptr, TSD_E_INVALID_ARG, "ctx is NULL");
   if (!n_host) return fail(ctx, TSD_E_INVALID_ARG, "n_host is NULL");
   *n_host = ctx->small_passes;
+  return TSD_OK;
+}
+
+int tsd_set_resident_wait(tsd_ctx* ctx, int32_t milliseconds) {
+  if (!ctx) return fail(nullptr, TSD_E_INVALID_ARG, "ctx is NULL");
+  if (milliseconds < 0) return fail(ctx, TSD_E_INVALID_ARG, "milliseconds must not be negative");
+  ctx->small_wait = (long long)milliseconds * 100000;
   return TSD_OK;
 }
 

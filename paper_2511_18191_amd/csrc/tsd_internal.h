@@ -229,7 +229,8 @@ struct SmallRoundP {
   int k_max;                                  // K the exchange buffer was sized for
   unsigned* flags;
   unsigned epoch;                             // what the flags hold at most before this launch
-  int *status, *host_status;                  // device and pinned host word, set to 1 by a launch that gave up waiting
+  int *status, *host_status;                  // device and pinned host word, set to 1 by a launch that gave up waiting, for good
+  long long wait_ticks;                       // how long a workgroup waits, in ticks of the 100 MHz wall clock (0: the launch gives up at once)
   float scale;                                // 1 / sqrt(head_dim)
 };
 bool small_round_ok(const tsd_config& c);
@@ -315,7 +316,6 @@ struct AcceptP {
   int mode;
   int* sync;
   int clear_rest;  // zero the forecast's rows behind the round's last patch, up to T
-  const int* gave_up;  // nullable: the pass that feeds this step did not finish: commit nothing
 };
 hipError_t launch_accept(const AcceptP& p, hipStream_t st);
 hipError_t launch_fill_int(int* p, int value, int n, hipStream_t st);

@@ -145,3 +145,57 @@ def test_beside_a_large_batch():
     np.testing.assert_array_equal(got, ref.get_forecast().cpu().numpy())
     for s in (sb, ss, ref):
         s.close()
+
+
+@pytest.mark.parametrize("B,K,target,draft,P,N", [
+    (1, 4, None, None, 96, 6), (16, 1, W192, W640, 96, 5), (2, 15, W640, W192, 96, 5),
+    (3, 4, ModelCfg(2, 192, 3, 288), D1, 48, 5), (2, 3, ModelCfg(2, 768, 12, 3072), ModelCfg(2, 384, 6, 1536), 560, 4),
+    (2, 3, ModelCfg(1, 128, 2, 256), D1, 16, 300)])
+def test_a_launch_that_gives_up_is_finished_alone(B, K, target, draft, P, N):
+    """A launch whose workgroups do not wait for one another is finished by one workgroup: the same bits, no error to miss, and the
+    handle runs kernel by kernel afterwards."""
+    over = dict(patch=P, context=N * P, horizon=(2 * K + 3) * P)
+    if target:
+        over.update(target=target, draft=draft)
+    case = Case("mini2", B=B, K=K, random_gains=True, **over)
+    c = case.cfg
+    T = 2 * K + 3
+
+    def decode(s, give_up_at):
+        """A forecast call by call; from call `give_up_at` on the launches do not wait."""
+        out, calls = [], [s.draft_propose, s.target_verify, s.accept_commit, s.round, s.round]
+        s.prefill(case.context, c.n_ctx, c.horizon)
+        for i, call in enumerate(calls):
+            if i == give_up_at:
+                s.set_resident_wait(0)
+            before = s.resident_passes()
+            call()
+            if i == give_up_at:
+                assert s.resident_passes() == before + 1
+            s.sync()
+            io = s.get_round_io()
+            out += [io[k].cpu().numpy() for k in (("X",), ("X", "mu_p"), io, io, ())[i]]      # (what this call is sure to have written)
+        n = s.resident_passes()
+        for _ in range(3):                   # rounds enqueued without looking, then the rest
+            s.round()
+        s.run_rounds()
+        assert give_up_at is None or s.resident_passes() == n
+        return out + [s.get_forecast().cpu().numpy()]
+
+    ref = case.session(flags=tsd.TSD_FLAG_NO_PINNED_COUNTS)
+    want = decode(ref, None)
+    ref.close()
+    for give_up_at in (0, 1, 3, 4):          # draft steps, verification, a round, a round that follows the device's counts
+        s = case.session()
+        for a, b in zip(decode(s, give_up_at), want):
+            np.testing.assert_array_equal(a, b)
+        s.close()
+    # a whole forecast enqueued before anybody looks
+    for s in (case.session(), case.session(flags=tsd.TSD_FLAG_NO_PINNED_COUNTS)):
+        s.set_resident_wait(0)
+        s.prefill(case.context, c.n_ctx, c.horizon)
+        for _ in range(T):
+            s.target_step()
+        want.append(s.get_forecast().cpu().numpy())
+        s.close()
+    np.testing.assert_array_equal(want[-2], want[-1])
