@@ -741,7 +741,7 @@ __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr
         for (int j = 0; j < 4; ++j) x[j] = __hip_atomic_load(f[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         bool ok = true;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) ok = ok && (int)(x[j] - walk.ep) >= 0;
+        for (int j = 0; j < 4; ++j) ok = ok && small_flag_reached(x[j], walk.ep);
         if (__all(ok)) break;
         if ((spin & 63) == 0) {
           const int gone = __hip_atomic_load(p.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -51,4 +51,12 @@ constexpr size_t small_part_offset(int D, int part) { return (size_t)part * (kSm
 constexpr size_t small_slab_bytes(int D, int F) { return (size_t)kSmallRoundRows * (4 * D + F) * 2; }
 constexpr size_t small_pass_bytes(int L, int D, int F) { return L * small_slab_bytes(D, F) + (size_t)kSmallRoundRows * D * 4; }
 
+// The workgroups' flags count stages on from launch to launch: those of a launch run from `epoch` + 1, and a wait for `value` is over
+// where flag - value is not negative as a signed number.  A launch that finds no series active advances the epoch and raises no
+// flag, so a flag may lag by any number of launches; at 2^31 it would count as raised.  Before an epoch passes the limit the flags
+// are cleared and it starts from 0 again.
+constexpr unsigned kSmallEpochLimit = 1u << 30;
+constexpr bool small_epoch_spent(unsigned epoch, unsigned stages) { return epoch > kSmallEpochLimit - stages; }
+constexpr bool small_flag_reached(unsigned flag, unsigned value) { return (int)(flag - value) >= 0; }
+
 }  // namespace tsd

@@ -858,6 +858,11 @@ int run_small_round(tsd_ctx* ctx, int phases, bool step_only, hipStream_t st) {
   r.exchange = ctx->small_exchange;
   r.k_max = ctx->K_max;
   r.flags = ctx->small_flags;
+  const unsigned stages = (unsigned)small_round_stages(c);
+  if (small_epoch_spent(ctx->small_epoch, stages)) {  // (earlier launches are ordered before this one)
+    HIP_TRY(ctx, launch_fill_int(reinterpret_cast<int*>(ctx->small_flags), 0, kSmallRoundWorkgroups * kSmallRoundFlagWords, st));
+    ctx->small_epoch = 0;
+  }
   r.epoch = ctx->small_epoch;
   r.status = ctx->count_out + kGaveUp;
   r.host_status = ctx->host_counts + 3;
@@ -866,7 +871,7 @@ int run_small_round(tsd_ctx* ctx, int phases, bool step_only, hipStream_t st) {
   bool busy = false;
   HIP_TRY(ctx, launch_small_round(r, &ctx->use, st, &busy));
   if (busy) return kResidentBusy;
-  ctx->small_epoch += (unsigned)small_round_stages(c);
+  ctx->small_epoch += stages;
   ctx->small_passes++;
   return TSD_OK;
 }
@@ -1021,6 +1026,7 @@ int tsd_create(const tsd_config* cfg, void* arena_dev, size_t arena_bytes, tsd_c
     if (e == hipSuccess && cus >= kSmallRoundWorkgroups) {
       e = hipMemset(ctx->small_flags, 0, (size_t)kSmallRoundWorkgroups * kSmallRoundFlagWords * 4);
       if (e == hipSuccess) e = hipMemset(ctx->count_out + kGaveUp, 0, 4);
+      ctx->small_epoch = kSmallEpochLimit - 4 * (unsigned)small_round_stages(*cfg);  // (the flags are cleared once after some launches)
       ctx->small_round = e == hipSuccess;
     }
     (void)hipGetLastError();

@@ -82,3 +82,41 @@ int main() {
 }
 ''')
     assert out == [320, 448]
+
+
+EPOCHS = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "small_round_plan.h"
+using namespace tsd;
+int main() {
+  // launches in which no series is active, one after the other, past two turns of the counter, then one that waits: no stage of it may
+  // find its flags raised.  (Flags as some earlier launch left them, 0 once cleared.)
+  long early = 0, cleared = 0, launches = 0;
+  for (unsigned stages : {7u, 162u, 1922u}) {
+    unsigned epoch = kSmallEpochLimit - 4 * stages, flag = epoch;
+    for (unsigned long long gone = 0; gone < (2ull << 32); gone += stages, ++launches) {
+      if (small_epoch_spent(epoch, stages)) {
+        epoch = 0;
+        flag = 0;
+        ++cleared;
+      }
+      early += small_flag_reached(flag, epoch + 1) + small_flag_reached(flag, epoch + stages);
+      early += !small_flag_reached(epoch + stages, epoch + stages);  // (and a raised one counts)
+      epoch += stages;
+    }
+  }
+  printf("%ld %ld %d\n", early, cleared, launches > 1000000);
+}
+"""
+
+
+def test_flags_of_idle_launches_never_count_as_raised(tmp_path):
+    early, cleared, enough = _run(tmp_path, EPOCHS)
+    assert early == 0 and cleared >= 6 and enough
+
+
+def test_flags_never_cleared_would_count_as_raised(tmp_path):
+    """What the limit is for: without it the walk above finds stages that wait for nobody."""
+    source = EPOCHS.replace("if (small_epoch_spent(epoch, stages))", "if (false)")
+    assert source != EPOCHS and _run(tmp_path, source)[0] > 0
