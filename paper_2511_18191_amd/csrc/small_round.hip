@@ -26,12 +26,13 @@
 // All workgroups of a launch have to be resident together: one per compute unit, and a process has one launch of this kernel
 // on a device at a time (launch_small_round).  Other processes are not seen: where two launches have taken each other's compute units,
 // neither can go on.  So every wait is bounded: a workgroup that has waited since its start for p.wait_ticks, or sees that another
-// gave up, leaves, and small_round_alone_kernel behind the launch does the launch's work.
+// gave up, leaves, and the kernel behind the launch does its work (series_alone).
 #include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <vector>
 
+#include "accept_step.h"
 #include "gemm_epilogue.h"
 #include "tsd_internal.h"
 
@@ -84,25 +85,13 @@ struct Weights {
   bf16x8 f[8];
 };
 
-// (off: the lane's column and place inside a k-step)
 template <int CW>
-__device__ __forceinline__ void load_weights(const bf16* W, unsigned off, int per, int used, int wave, int li, Weights& w) {
+__device__ __forceinline__ void load_weights(const bf16* W, unsigned off, int per, Weights& w) {
   constexpr int PB = CW / 4, SB = 16 / CW;
-  if constexpr (SB == 1) {  // (a slab is the whole wavefront's)
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int j = t / PB, i = t % PB;
-      if (j < per) w.f[t] = *reinterpret_cast<const bf16x8*>(W + (slab_read(wave, i, used) * per + j) * 32 + off);
-    }
-  } else {
-    unsigned at[PB];
-#pragma unroll
-    for (int i = 0; i < PB; ++i) at[i] = off + (unsigned)(slab_read(wave, SB * i + li / CW, used) * per * 32);
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int j = t / PB, i = t % PB;
-      if (j < per) w.f[t] = *reinterpret_cast<const bf16x8*>(W + j * 32 + at[i]);
-    }
+  for (int t = 0; t < 8; ++t) {
+    const int j = t / PB, i = t % PB;
+    if (j < per) w.f[t] = *reinterpret_cast<const bf16x8*>(W + (SB * i * per + j) * 32 + off);
   }
 }
 
@@ -112,10 +101,10 @@ __device__ __forceinline__ void prefetch(const SmallProd& d, const bf16* W, int 
   if (wg >= d.units || 4 * wave >= d.used) return;
   asm volatile("" : "+v"(lane));  // (an opaque copy: keeps the address arithmetic below from being hoisted to the kernel's top)
   const int li = lane & 15, col = column_of<QKV>(d, wg, li & ((1 << d.cs) - 1));
-  const unsigned off = (unsigned)(col * d.K + (lane >> 4) * 8);
-  if (d.cs == 2) load_weights<4>(W, off, d.per, d.used, wave, li, w);
-  else if (d.cs == 3) load_weights<8>(W, off, d.per, d.used, wave, li, w);
-  else load_weights<16>(W, off, d.per, d.used, wave, li, w);
+  const unsigned off = (unsigned)(col * d.K + (4 * wave + (li >> d.cs)) * d.per * 32 + (lane >> 4) * 8);
+  if (d.cs == 2) load_weights<4>(W, off, d.per, w);
+  else if (d.cs == 3) load_weights<8>(W, off, d.per, w);
+  else load_weights<16>(W, off, d.per, w);
 }
 
 // The embedding's k range may end inside a k-step or a slab: clamped reads, against zero activations.
@@ -160,19 +149,13 @@ struct Shared {
 // slab agree, which is all that is kept.  No lane then fetches what another one has fetched already: 5 rows cost half the
 // loads of 16, 4 columns a quarter.
 template <int R, int NT, int CW>
-__device__ __forceinline__ void product_t(const bf16* A, int K, int per, int used, int M, bool norm, int wave, int lane, const Weights& w, Shared& sh) {
+__device__ __forceinline__ void product_t(const bf16* A, int K, int per, int M, bool norm, int wave, int lane, const Weights& w, Shared& sh) {
   asm volatile("" : "+v"(lane));
   constexpr int SA = 16 / R, SB = 16 / CW, G = SA < SB ? SA : SB, NACC = 4 / G, PA = R / 4, PB = CW / 4;
   const int li = lane & 15, lg = lane >> 4;
-  // element offsets from A (uniform base, 32-bit offset: one address register per load), of the lane's slabs where these differ
-  // between lanes
-  constexpr int NS = SA == 1 ? 1 : PA;
-  unsigned row[NT][NS];
+  unsigned row[NT];  // element offsets from A (uniform base, 32-bit offset: one address register per load)
 #pragma unroll
-  for (int r = 0; r < NT; ++r)
-#pragma unroll
-    for (int i = 0; i < NS; ++i)
-      row[r][i] = (unsigned)(min(r * 16 + li % R, M - 1) * K + lg * 8 + (SA == 1 ? 0 : slab_read(wave, SA * i + li / R, used) * per * 32));
+  for (int r = 0; r < NT; ++r) row[r] = (unsigned)(min(r * 16 + li % R, M - 1) * K + (4 * wave + li / R) * per * 32 + lg * 8);
   f32x4 acc[NT][NACC];  // g: slabs 4 wave + g G .. + G - 1
   float ss[NT][PA];
 #pragma unroll
@@ -195,8 +178,7 @@ __device__ __forceinline__ void product_t(const bf16* A, int K, int per, int use
 #pragma unroll
       for (int r = 0; r < NT; ++r)
 #pragma unroll
-        for (int i = 0; i < PA; ++i)
-          a[j][r][i] = *reinterpret_cast<const bf16x8*>(A + ((SA == 1 ? slab_read(wave, i, used) * per : 0) + j0 + j) * 32 + row[r][SA == 1 ? 0 : i]);
+        for (int i = 0; i < PA; ++i) a[j][r][i] = *reinterpret_cast<const bf16x8*>(A + (SA * i * per + j0 + j) * 32 + row[r]);
     }
 #pragma unroll
     for (int j = 0; j < JC; ++j) {
@@ -247,9 +229,9 @@ __device__ __forceinline__ void product_t(const bf16* A, int K, int per, int use
 
 template <int R, int NT>
 __device__ __forceinline__ void product_cw(const SmallProd& d, const bf16* A, int M, bool norm, int wave, int lane, const Weights& w, Shared& sh) {
-  if (d.cs == 2) product_t<R, NT, 4>(A, d.K, d.per, d.used, M, norm, wave, lane, w, sh);
-  else if (d.cs == 3) product_t<R, NT, 8>(A, d.K, d.per, d.used, M, norm, wave, lane, w, sh);
-  else product_t<R, NT, 16>(A, d.K, d.per, d.used, M, norm, wave, lane, w, sh);
+  if (d.cs == 2) product_t<R, NT, 4>(A, d.K, d.per, M, norm, wave, lane, w, sh);
+  else if (d.cs == 3) product_t<R, NT, 8>(A, d.K, d.per, M, norm, wave, lane, w, sh);
+  else product_t<R, NT, 16>(A, d.K, d.per, M, norm, wave, lane, w, sh);
 }
 
 __device__ __forceinline__ void product(const SmallProd& d, const bf16* A, int M, bool norm, int wave, int lane, const Weights& w, Shared& sh) {
@@ -593,9 +575,9 @@ __device__ __forceinline__ void each_pair(const SmallProd& d, int M, int lane, F
 }
 
 // Epilogues that need nothing but the partial sums: FFN up with GELU, and the head.
-__device__ __forceinline__ void finish_up(const SmallModel& m, const PassView& v, int l, int wg, int lane, const Shared& sh) {
+__device__ __forceinline__ void finish_up(const SmallModel& m, const PassView& v, bf16* hidden, int wg, int lane, const Shared& sh) {
   const SmallProd& d = m.up;
-  bf16* hid = v.rows(l, kHidden) + (wg << d.cs);
+  bf16* hid = hidden + (wg << d.cs);
   each_pair(d, v.M, lane, [&](int row, int c) {
     const Sums z = sums_of<false, true>(sh, row, c, 0, d.used);
     const float2 s = z.a;
@@ -876,7 +858,7 @@ __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr
       if (wg < f1.units) {
         if (!hop()) return;
         wg_barrier();
-        finish_up(m, v, l, wg, lane, sh);
+        finish_up(m, v, v.rows(l, kHidden), wg, lane, sh);
         raise();
       }
       walk.done(f1.units);
@@ -909,7 +891,7 @@ struct Extent {
 __global__ __launch_bounds__(kThreads) void small_round_kernel(const SmallRoundP p) {
   __shared__ __attribute__((aligned(16))) Shared sh;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int gone = *p.status;  // an earlier launch gave up: this one is left to the kernel below
+  const int gone = *p.status;  // an earlier launch gave up: this one is left to the kernel behind it
   const Extent x(p);
   if (gone || x.n <= 0) return;
   if (p.wait_ticks <= 0) {  // (uniform over the grid)
@@ -924,40 +906,50 @@ __global__ __launch_bounds__(kThreads) void small_round_kernel(const SmallRoundP
     worker_loop(p, x.n, x.Kr, x.Kd, x.n_pass, wave, lane, sh);
 }
 
-// Launched behind every launch of the kernel above, and idle (4 us of a round of 380) unless that one gave up: the same passes from their
-// beginning by ONE workgroup, which takes the units of a stage one after the other and waits for nobody.  Nothing of a pass is lost
-// by that: what it overwrites (the cache rows of its tokens, proposals, target means) follows from what was committed
-// before.  Slow (some 3 us per unit and stage) and rare: from the next call on the handle runs kernel by kernel.
-__global__ __launch_bounds__(kThreads) void small_round_alone_kernel(const SmallRoundP p) {
-  __shared__ __attribute__((aligned(16))) Shared sh;
-  if (*p.status == 0) return;
+// The same passes from their beginning for ONE series, by a workgroup of the four workers that takes the units of a stage one after
+// the other and waits for nobody: for a launch that gave up.  Nothing is lost by that: what a pass overwrites (the cache rows of
+// its tokens, proposals, target means) follows from what was committed before.  Slow (some 3 us per unit and stage) and rare: from
+// the next call on the handle runs kernel by kernel.  `place`: this workgroup's rows of the exchange buffer, place * nq and on.
+__device__ __forceinline__ void series_alone(const SmallRoundP& p, int b, int place, Shared& sh) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const bool worker = wave < kWorkers;
   const Extent x(p);
-  if (x.n <= 0) return;
   const Rsrc patches = patches_of(p);
+  const int my_page = p.page_table[(long)b * p.pt_stride + min(lane, p.pt_stride - 1)];
   Weights w;
   for (int ps = 0; ps < x.n_pass; ++ps) {
-    const PassView v(p, ps, x.Kd, x.Kr, x.n);
+    const PassView v(p, ps, x.Kd, x.Kr, 1);
     const SmallModel& m = *v.m;
-    const int D = v.D, M = v.M, nq = v.nq, Hh = m.Hh;
-    float* res = v.residual();  // (the residual of all columns: here in memory)
+    const int D = v.D, nq = v.nq, Hh = m.Hh, row0 = place * nq;
+    const int base = p.len[b] + (v.draft ? (v.step == 1 ? -1 : v.step - 1) : 0);
+    float* res = v.residual() + row0 * D;  // (the residual of all columns: here in memory)
     __syncthreads();
-    set_rows(p, v, sh);
+    if (threadIdx.x < kRowsMax) {
+      const int pos = base + min((int)threadIdx.x, nq - 1);
+      sh.ser[threadIdx.x] = b;
+      sh.pos[threadIdx.x] = pos;
+      sh.page[threadIdx.x] = p.page_table[(long)b * p.pt_stride + (pos >> p.pt_shift)];
+    }
     __syncthreads();
+    auto rows = [&](int l, int part) { return v.rows(l, part) + (long)row0 * (part == kHidden ? m.F : D); };
     // a product: the workers' share of every unit, then its epilogue
     auto units = [&](const SmallProd& d, auto share, auto finish) {
       for (int u = 0; u < d.units; ++u) {
-        if (worker) share(u);
+        share(u);
         __syncthreads();
-        if (!worker) finish(u);
+        if (wave == 0) finish(u);
         __syncthreads();
       }
+    };
+    auto product_of_rows = [&](const SmallProd& d, const bf16* W, const bf16* A, bool norm) {
+      return [&, W, A, norm](int u) {
+        prefetch<false>(d, W, u, wave, lane, w);
+        product(d, A, nq, norm, wave, lane, w, sh);
+      };
     };
     auto add_residual = [&](const SmallProd& d, bf16* out, bool first, bool last) {
       return [&, out, first, last](int u) {
         const int at0 = u << d.cs;
-        each_pair(d, M, lane, [&](int row, int c) {
+        each_pair(d, nq, lane, [&](int row, int c) {
           float2 s = sums_of<false, false>(sh, row, c, 0, d.used).a;
           float* r = res + row * D + at0 + c;
           if (!first) {
@@ -970,30 +962,24 @@ __global__ __launch_bounds__(kThreads) void small_round_alone_kernel(const Small
         });
       };
     };
-    auto share_of = [&](const SmallProd& d, const bf16* W, const bf16* A, bool norm) {
-      return [&, W, A, norm](int u) {
-        prefetch<false>(d, W, u, wave, lane, w);
-        product(d, A, M, norm, wave, lane, w, sh);
-      };
-    };
 
     units(m.embed,
           [&](int u) {
             prefetch_embed(m.embed, m.embed.W, u, wave, lane, w);
-            product_f32<false>(m.embed, M, wave, lane, w, sh, [&](int r, int k, float* f) { load_patch(p, v, sh, patches, r, k, f); });
+            product_f32<false>(m.embed, nq, wave, lane, w, sh, [&](int r, int k, float* f) { load_patch(p, v, sh, patches, r, k, f); });
           },
-          add_residual(m.embed, v.rows(0, kIn), true, false));
+          add_residual(m.embed, rows(0, kIn), true, false));
     for (int l = 0; l < m.L; ++l) {
       bf16* pool = m.kv_pool + (size_t)l * m.layer_pool_elems;
       units(m.qkv,
             [&](int u) {
               prefetch<true>(m.qkv, v.weights(m.qkv, l), u, wave, lane, w);
-              product(m.qkv, v.rows(l, kIn), M, true, wave, lane, w, sh);
+              product(m.qkv, rows(l, kIn), nq, true, wave, lane, w, sh);
             },
             [&](int u) {
               const int qhalf = 1 << (m.qkv.cs - 1), c0 = column_of<true>(m.qkv, u, 0), which = c0 < D ? 0 : c0 < 2 * D ? 1 : 2;
               const int h = (c0 - which * D) >> 6, d0 = c0 & 63;
-              each_pair(m.qkv, M, lane, [&](int row, int c) {
+              each_pair(m.qkv, nq, lane, [&](int row, int c) {
                 const int f = d0 + (c < qhalf ? c : c - qhalf), d = d0 + (c < qhalf ? c : 32 + c - qhalf), pos = sh.pos[row];
                 const Sums z = sums_of<true, true>(sh, row, c, c < qhalf ? c + qhalf : c - qhalf, m.qkv.used);
                 const float rs = norm_scale(z.ss, D);
@@ -1007,32 +993,25 @@ __global__ __launch_bounds__(kThreads) void small_round_alone_kernel(const Small
                   s.x = s.x * cs.x + sg * z.b.x * sn.x;
                   s.y = s.y * cs.y + sg * z.b.y * sn.y;
                 }
-                const unsigned to = which == 0 ? (unsigned)(row * D + h * 64 + d)
-                                               : (unsigned)((((sh.page[row] * 2 + (which - 1)) * Hh + h) * p.PT + (pos & (p.PT - 1))) * 64 + d);
-                publish_bf16x2((which == 0 ? v.rows(l, kQuery) : pool) + to, s.x, s.y);
+                bf16* to = which == 0 ? rows(l, kQuery) + (row * D + h * 64 + d)
+                                      : pool + (unsigned)((((sh.page[row] * 2 + (which - 1)) * Hh + h) * p.PT + (pos & (p.PT - 1))) * 64 + d);
+                publish_bf16x2(to, s.x, s.y);
               });
             });
-      for (int u = 0; u < x.n * Hh; ++u) {
-        const int sl = u / Hh, head = u - sl * Hh, r0 = sl * nq;
-        const int base = __builtin_amdgcn_readfirstlane(sh.pos[r0]);
-        if (worker) {
-          const int my_page = p.page_table[(long)sh.ser[r0] * p.pt_stride + min(lane, p.pt_stride - 1)];
-          attend(p, pool, v.rows(l, kQuery) + r0 * D + head * 64, v.rows(l, kMixed) + r0 * D + head * 64, D, head, Hh, my_page, base, nq, wave,
-                 lane, sh, [] { return true; });
-        } else {
-          attend_barriers(base + nq);
-        }
+      for (int h = 0; h < Hh; ++h) {
+        attend(p, pool, rows(l, kQuery) + h * 64, rows(l, kMixed) + h * 64, D, h, Hh, my_page, base, nq, wave, lane, sh, [] { return true; });
         __syncthreads();
       }
       const bool last = l + 1 == m.L;
-      units(m.out, share_of(m.out, v.weights(m.out, l), v.rows(l, kMixed), false), add_residual(m.out, v.rows(l, kMid), false, false));
-      units(m.up, share_of(m.up, v.weights(m.up, l), v.rows(l, kMid), true), [&](int u) { finish_up(m, v, l, u, lane, sh); });
-      units(m.down, share_of(m.down, v.weights(m.down, l), v.rows(l, kHidden), false), add_residual(m.down, v.rows(l + 1, kIn), false, last));
+      units(m.out, product_of_rows(m.out, v.weights(m.out, l), rows(l, kMixed), false), add_residual(m.out, rows(l, kMid), false, false));
+      units(m.up, product_of_rows(m.up, v.weights(m.up, l), rows(l, kMid), true), [&](int u) { finish_up(m, v, rows(l, kHidden), u, lane, sh); });
+      units(m.down, product_of_rows(m.down, v.weights(m.down, l), rows(l, kHidden), false),
+            add_residual(m.down, last ? nullptr : rows(l + 1, kIn), false, last));
     }
     units(m.head,
           [&](int u) {
             prefetch<false>(m.head, m.head.W, u, wave, lane, w);
-            product_f32<true>(m.head, M, wave, lane, w, sh, [&](int r, int k, float* f) {
+            product_f32<true>(m.head, nq, wave, lane, w, sh, [&](int r, int k, float* f) {
               *reinterpret_cast<float4*>(f) = *reinterpret_cast<const float4*>(res + (r * D + k));
               *reinterpret_cast<float4*>(f + 4) = *reinterpret_cast<const float4*>(res + (r * D + k + 4));
             });
@@ -1041,11 +1020,27 @@ __global__ __launch_bounds__(kThreads) void small_round_alone_kernel(const Small
   }
 }
 
+// Behind a launch of the resident kernel: a series per workgroup, and nothing to do (4 us) unless that launch gave up.
+__global__ __launch_bounds__(kWorkers * 64) void small_round_alone_kernel(const SmallRoundP p) {
+  __shared__ __attribute__((aligned(16))) Shared sh;
+  if (*p.status == 0 || (p.counts && (int)blockIdx.x >= p.counts[0])) return;
+  series_alone(p, p.act ? p.act[blockIdx.x] : (int)blockIdx.x, blockIdx.x, sh);
+}
+
+// The same at the head of the acceptance step where that follows at once: no launch of its own.
+__global__ __launch_bounds__(kWorkers * 64) void small_round_accept_kernel(const SmallRoundP r, const AcceptP p) {
+  __shared__ __attribute__((aligned(16))) Shared sh;
+  if (*r.status && p.mode != 2) {  // (mode 2: mode 1 went before)
+    const int b = p.act ? p.act[blockIdx.x] : (int)blockIdx.x;
+    if (!(p.n_dev && (int)blockIdx.x >= *p.n_dev) && p.active[b]) series_alone(r, b, blockIdx.x, sh);
+    __syncthreads();
+  }
+  accept_step(p);
+}
+
 SmallProd product_of(const bf16* W, int K, int N) {
-  SmallProd d;
-  static_cast<SmallPlan&>(d) = small_plan(K, N);
-  d.W = W;
-  return d;
+  const SmallPlan d = small_plan(K, N);
+  return SmallProd{W, d.K, d.units, d.cs, d.per, d.used};
 }
 
 bool model_ok(const tsd_model_cfg& c, int patch) {
@@ -1157,11 +1152,18 @@ hipError_t launch_small_round(const SmallRoundP& p, PassUse* use, hipStream_t st
     u->in_flight = false;
   }
   hipLaunchKernelGGL(small_round_kernel, dim3(kWg), dim3(kThreads), 0, st, p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(small_round_alone_kernel, dim3(1), dim3(kThreads), 0, st, p);
-  e = hipGetLastError();
+  const hipError_t e = hipGetLastError();
   return e != hipSuccess ? e : record_use(use, st);
+}
+
+hipError_t launch_small_round_alone(const SmallRoundP& p, hipStream_t st) {
+  hipLaunchKernelGGL(small_round_alone_kernel, dim3(p.n), dim3(kWorkers * 64), 0, st, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_small_round_accept(const SmallRoundP& r, const AcceptP& p, hipStream_t st) {
+  hipLaunchKernelGGL(small_round_accept_kernel, dim3(p.B), dim3(kWorkers * 64), 0, st, r, p);
+  return hipGetLastError();
 }
 
 }  // namespace tsd

@@ -36,19 +36,21 @@ constexpr bool small_product_ok(int K, int N) {
   return d.units && K % 32 == 0 && d.per * ((1 << d.cs) / 4) <= 8 && d.per * d.used * 32 == K;
 }
 
-// Which slab worker `wave` reads as the `part`-th (0 .. 3) of its four.  The last worker may have fewer: it then reads the last
-// one again, and the sums of it are dropped.  (Read past the end of row 31, the lines behind it are the next part of
-// the exchange buffer, which nobody may have read before it is written: see small_round.hip.)
-constexpr int slab_read(int wave, int part, int used) {
-  const int s = kSmallRoundWorkers * wave + part;
-  return s < used ? s : used - 1;
-}
+// Worker `wave` reads slabs kSmallRoundWorkers * wave and the three behind it, four k ranges whose sums it keeps side by side.  A last
+// worker with fewer than four reads past the end of its rows all the same (choosing the address takes 0.75 % of the kernel) and drops
+// the sums.  That far behind row 31, and behind the last row of weights, nothing may lie that is written during the launch: a line
+// that is read before it is published would be seen stale by the stage that needs it (see small_round.hip).
+constexpr long slab_offset(int wave, int part, int per) { return (long)(kSmallRoundWorkers * wave + part) * per * 64; }  // bytes into a row
+// At most three slabs of eight k-steps, in whole 4 KB: shorter tails move the parts to other memory channels (a round of five series
+// through 8 layers of 512: 314.4 us, back to back 315.0, with tails of 1536 bytes 318.7).
+constexpr int kSmallTail = 4096;
+static_assert(3 * 8 * 64 <= kSmallTail, "");
 
 // The exchange buffer: of a layer, the rows entering it, its queries, attention output, the rows between its two halves, hidden
-// rows; of a pass, its layers and the fp32 residual.
+// rows, each with a tail that nobody writes; of a pass, its layers and the fp32 residual.
 enum SmallPart { kIn, kQuery, kMixed, kMid, kHidden };
-constexpr size_t small_part_offset(int D, int part) { return (size_t)part * (kSmallRoundRows * 2) * D; }
-constexpr size_t small_slab_bytes(int D, int F) { return (size_t)kSmallRoundRows * (4 * D + F) * 2; }
+constexpr size_t small_part_offset(int D, int part) { return (size_t)part * (kSmallRoundRows * 2 * D + kSmallTail); }
+constexpr size_t small_slab_bytes(int D, int F) { return (size_t)kSmallRoundRows * (4 * D + F) * 2 + 5 * kSmallTail; }
 constexpr size_t small_pass_bytes(int L, int D, int F) { return L * small_slab_bytes(D, F) + (size_t)kSmallRoundRows * D * 4; }
 
 // The workgroups' flags count stages on from launch to launch: those of a launch run from `epoch` + 1, and a wait for `value` is over

@@ -284,7 +284,7 @@ size_t carve(const tsd_config& c, tsd_ctx* ctx) {
       size_t orr = m.n_experts > 0 ? cv.take(nE * D * 4) : 0;
       if (md) md->layers[l] = Layer{at(oq), at(oo), at(o1), at(o2), m.n_experts > 0 ? (float*)at(orr) : nullptr};
     }
-    o = cv.take(D * P * es);
+    o = cv.take(D * P * es + (small_round_ok(c) ? kSmallTail : 0));
     if (md) md->W_h = at(o);
     if (w == 1 && fused_draft_ok(c)) {
       const int ch = draft_fused_chunk((int)D, (int)F);
@@ -810,10 +810,10 @@ bool use_small_round(tsd_ctx* ctx, hipStream_t st) {
 constexpr int kResidentBusy = 1;  // (error codes are negative)
 
 // phases: 1 the draft steps, 2 the target pass; step_only: the target pass over the pending token alone.  kResidentBusy:
-// nothing was launched, the pass has to run kernel by kernel.
-int run_small_round(tsd_ctx* ctx, int phases, bool step_only, hipStream_t st) {
+// nothing was launched, the pass has to run kernel by kernel.  TSD_OK with r.n > 0: the caller goes on with
+// launch_small_round_alone, or with accept_commit_impl for the same `r`.
+int run_small_round(tsd_ctx* ctx, int phases, bool step_only, hipStream_t st, SmallRoundP& r) {
   const tsd_config& c = ctx->cfg;
-  SmallRoundP r;
   std::memset(&r, 0, sizeof(r));
   for (int i = 0; i < 2; ++i) {
     const ModelDev& md = ctx->model[i];
@@ -876,7 +876,16 @@ int run_small_round(tsd_ctx* ctx, int phases, bool step_only, hipStream_t st) {
   return TSD_OK;
 }
 
-int accept_commit_impl(tsd_ctx* ctx, const int32_t* forced, int K, hipStream_t st) {
+// ... and nothing behind it.
+int run_small_phase(tsd_ctx* ctx, int phase, hipStream_t st) {
+  SmallRoundP r;
+  const int rc = run_small_round(ctx, phase, false, st, r);
+  if (rc == TSD_OK && r.n > 0) HIP_TRY(ctx, launch_small_round_alone(r, st));
+  return rc;
+}
+
+// `after`: the resident launch whose results it takes (NULL or n == 0: none).
+int accept_commit_impl(tsd_ctx* ctx, const int32_t* forced, int K, hipStream_t st, const SmallRoundP* after = nullptr) {
   const tsd_config& c = ctx->cfg;
   AcceptP a;
   std::memset(&a, 0, sizeof(a));
@@ -918,15 +927,16 @@ int accept_commit_impl(tsd_ctx* ctx, const int32_t* forced, int K, hipStream_t s
   a.key0 = (unsigned)(c.seed & 0xFFFFFFFFull);
   a.key1 = (unsigned)(c.seed >> 32);
   a.threshold = (c.flags & TSD_FLAG_THRESHOLD_RULE) ? 1 : 0;
+  auto launch = [&] { return after && after->n > 0 ? launch_small_round_accept(*after, a, st) : launch_accept(a, st); };
   if ((c.flags & TSD_FLAG_BATCH_SYNC) && K > 0) {
     // the series' own counts first (their minimum lands in the sync word), then the commit
     a.sync = ctx->count_out + 8;
     HIP_TRY(ctx, launch_fill_int(a.sync, INT_MAX, 1, st));
     a.mode = 1;
-    HIP_TRY(ctx, timed_launch(ctx, TSD_K_ACCEPT, 4.0 * ctx->B * c.patch * (2.0 * K + 2), st, [&] { return launch_accept(a, st); }, Shape{-1, 0, cv.n, K, c.patch}));
+    HIP_TRY(ctx, timed_launch(ctx, TSD_K_ACCEPT, 4.0 * ctx->B * c.patch * (2.0 * K + 2), st, launch, Shape{-1, 0, cv.n, K, c.patch}));
     a.mode = 2;
   }
-  HIP_TRY(ctx, timed_launch(ctx, TSD_K_ACCEPT, 4.0 * ctx->B * c.patch * (2.0 * K + 2), st, [&] { return launch_accept(a, st); }, Shape{-1, 0, cv.n, K, c.patch}));
+  HIP_TRY(ctx, timed_launch(ctx, TSD_K_ACCEPT, 4.0 * ctx->B * c.patch * (2.0 * K + 2), st, launch, Shape{-1, 0, cv.n, K, c.patch}));
   ctx->injected = false;
   ctx->compact_pending = false;  // whatever compaction was enqueued before describes an older state
   ctx->need_lb = 0;              // ... and so does the last count of patches still needed
@@ -1321,7 +1331,7 @@ int tsd_draft_propose(tsd_ctx* ctx, void* stream) {
   // Step 1 ingests two tokens per series: the token just before the pending one and the pending
   // one.  After a fully accepted round the draft cache lacks the former (it proposed x_K but
   // never consumed it); for the other series the rewrite stores identical values.
-  if (!ctx->fused_draft && use_small_round(ctx, st) && (rc = run_small_round(ctx, 1, false, st)) != kResidentBusy) return rc;
+  if (!ctx->fused_draft && use_small_round(ctx, st) && (rc = run_small_phase(ctx, 1, st)) != kResidentBusy) return rc;
   const Cover cv = cover(ctx);
   if (cv.n == 0) return TSD_OK;
   if (ctx->fused_draft) {
@@ -1453,7 +1463,7 @@ int tsd_target_verify(tsd_ctx* ctx, void* stream) {
   if (rc) return rc;
   const tsd_config& c = ctx->cfg;
   const int P = c.patch, K = c.K;
-  if (use_small_round(ctx, (hipStream_t)stream) && (rc = run_small_round(ctx, 2, false, (hipStream_t)stream)) != kResidentBusy) return rc;
+  if (use_small_round(ctx, (hipStream_t)stream) && (rc = run_small_phase(ctx, 2, (hipStream_t)stream)) != kResidentBusy) return rc;
   const int Kr = round_positions(ctx);  // boundaries beyond Kr + 1 belong to patches no active series can commit
   const Cover cv = cover(ctx);
   if (cv.n == 0) return TSD_OK;
@@ -1508,9 +1518,10 @@ int tsd_round(tsd_ctx* ctx, void* stream) {
   if (!(ctx->cfg.flags & TSD_FLAG_NO_COMPACT)) peek_counts(ctx);
   bool small = use_small_round(ctx, (hipStream_t)stream);
   const bool whole = small && !ctx->fused_draft;  // draft steps and verification in one launch
+  SmallRoundP resident;
   if (whole) {
     ctx->injected = false;
-    if ((rc = run_small_round(ctx, 3, false, (hipStream_t)stream)) == kResidentBusy) small = false;
+    if ((rc = run_small_round(ctx, 3, false, (hipStream_t)stream, resident)) == kResidentBusy) small = false;
     else if (rc) return rc;
   }
   const int cls = device_counts(ctx) ? size_class(ctx) : 0;
@@ -1521,7 +1532,7 @@ int tsd_round(tsd_ctx* ctx, void* stream) {
       if ((r = tsd_draft_propose(ctx, stream))) return r;
       if ((r = tsd_target_verify(ctx, stream))) return r;
     }
-    if ((r = tsd_accept_commit(ctx, nullptr, stream))) return r;
+    if ((r = accept_commit_impl(ctx, nullptr, ctx->cfg.K, (hipStream_t)stream, whole && small ? &resident : nullptr))) return r;
     if (deliver)
       HIP_TRY(ctx, launch_compact_active(ctx->active, ctx->committed, ctx->T, ctx->B, compact_target(ctx), ctx->count_out,
                                          ctx->host_counts, (hipStream_t)stream));
@@ -1545,9 +1556,10 @@ int tsd_target_step(tsd_ctx* ctx, void* stream) {
   int rc = require_ready(ctx, true);
   if (rc) return rc;
   const int P = ctx->cfg.patch;
-  if (use_small_round(ctx, (hipStream_t)stream) && (rc = run_small_round(ctx, 2, true, (hipStream_t)stream)) != kResidentBusy) {
+  SmallRoundP resident;
+  if (use_small_round(ctx, (hipStream_t)stream) && (rc = run_small_round(ctx, 2, true, (hipStream_t)stream, resident)) != kResidentBusy) {
     if (rc) return rc;
-    return accept_commit_impl(ctx, nullptr, 0, (hipStream_t)stream);
+    return accept_commit_impl(ctx, nullptr, 0, (hipStream_t)stream, &resident);
   }
   rc = run_graphed(ctx, &ctx->graph_step, (hipStream_t)stream, [&]() {
     Pass ps;

@@ -196,8 +196,9 @@ hipError_t launch_draft_fused(const DraftFusedP& p, hipStream_t st);
 
 // ---- decode passes of at most 32 rows as one resident kernel: see small_round.hip ----
 constexpr int kSmallRoundFlagWords = 16;    // words between two workgroups' flags
-struct SmallProd : SmallPlan {  // one product of the chain
-  const bf16* W;                // [N][K], layer 0's
+struct SmallProd {                          // one product of the chain
+  const bf16* W;                            // [N][K], layer 0's
+  int K, units, cs, per, used;              // its SmallPlan
 };
 struct SmallModel {
   SmallProd embed, qkv, out, up, down, head;
@@ -252,6 +253,10 @@ void remove_use(PassUse* use);
 hipError_t note_pass(PassUse* use, hipStream_t st);
 // *busy: another handle's pass is in flight on another stream, and nothing was launched
 hipError_t launch_small_round(const SmallRoundP& p, PassUse* use, hipStream_t st, bool* busy);
+// One of these two has to follow it: they finish a launch that gave up, the second before it goes on with the acceptance step.
+struct AcceptP;
+hipError_t launch_small_round_alone(const SmallRoundP& p, hipStream_t st);
+hipError_t launch_small_round_accept(const SmallRoundP& r, const AcceptP& p, hipStream_t st);
 
 struct PackP {
   const float* W;     // [K][N] row-major source (y = x W)
