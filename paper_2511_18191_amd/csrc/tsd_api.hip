@@ -214,14 +214,22 @@ constexpr int kTraceMax = 512;  // stage stamps tsd_trace_draft can return
 // stream then no longer fits the 256 MB last-level cache).
 constexpr long kContextRows = 16384;
 
-// Rows of the activation workspace: a round's tokens of the whole batch, the longest context of one series, and the
-// contexts of the batch as far as kContextRows (and the expert sort of a routed model) allow.
-size_t workspace_rows(const tsd_config& c) {
-  const long must = std::max((long)c.max_batch * (c.K + 1), (long)c.max_tokens);
+// What an arena holds besides weights, caches and per-series state.  Everything runs in the least of it, in more passes and launches.
+struct Layout {
+  size_t rows;    // of the activation workspace
+  bool meta;      // the rows' positions and cache pages, looked up once per pass
+  bool resident;  // flags and exchange buffer of the resident decode kernel
+};
+
+// A round's tokens of the whole batch, or the longest context of one series.
+size_t least_rows(const tsd_config& c) { return (size_t)std::max((long)c.max_batch * (c.K + 1), (long)c.max_tokens); }
+
+// ... and the contexts of the batch as far as kContextRows (and the expert sort of a routed model) allow.
+Layout full_layout(const tsd_config& c) {
   long want = std::min((long)c.max_batch * c.max_tokens, kContextRows);
   for (const tsd_model_cfg* m : {&c.target, &c.draft})
     if (m->n_experts > 0) want = std::min(want, (long)kMaxSortSlots / m->top_k);
-  return (size_t)std::max(must, want);
+  return Layout{std::max(least_rows(c), (size_t)std::max(want, 0L)), true, small_round_ok(c)};
 }
 
 struct Carver {
@@ -256,7 +264,7 @@ bool fused_draft_ok(const tsd_config& c) {
 }
 
 // Lays out everything the handle needs inside the arena.  With ctx == nullptr only sizes it.
-size_t carve(const tsd_config& c, tsd_ctx* ctx) {
+size_t carve(const tsd_config& c, const Layout& lay, tsd_ctx* ctx) {
   Carver cv;
   char* base = ctx ? ctx->arena : nullptr;
   const size_t es = c.dtype == TSD_BF16 ? 2 : 4;
@@ -284,7 +292,7 @@ size_t carve(const tsd_config& c, tsd_ctx* ctx) {
       size_t orr = m.n_experts > 0 ? cv.take(nE * D * 4) : 0;
       if (md) md->layers[l] = Layer{at(oq), at(oo), at(o1), at(o2), m.n_experts > 0 ? (float*)at(orr) : nullptr};
     }
-    o = cv.take(D * P * es + (small_round_ok(c) ? kSmallTail : 0));
+    o = cv.take(D * P * es + (lay.resident ? kSmallTail : 0));
     if (md) md->W_h = at(o);
     if (w == 1 && fused_draft_ok(c)) {
       const int ch = draft_fused_chunk((int)D, (int)F);
@@ -322,15 +330,15 @@ size_t carve(const tsd_config& c, tsd_ctx* ctx) {
   size_t o_ell = cv.take((size_t)B * K * 4), o_logu = cv.take((size_t)B * K * 4);
   size_t o_diag = cv.take((size_t)(3 * P + 1) * 4);
   const size_t Dm = std::max(c.target.d_model, c.draft.d_model), Fm = std::max(c.target.d_ff, c.draft.d_ff);
-  const size_t rows = workspace_rows(c);
-  size_t o_meta = cv.take(rows * 8);
+  const size_t rows = lay.rows;
+  size_t o_meta = lay.meta ? cv.take(rows * 8) : 0;
   size_t o_xb = cv.take(rows * Dm * es);
   size_t o_x = cv.take(rows * Dm * 4), o_q = cv.take(rows * Dm * es), o_a = cv.take(rows * Dm * es), o_h = cv.take(rows * Fm * es);
   size_t o_trace = cv.take(kTraceMax * 8);
   size_t o_cnt = cv.take(256), o_so = cv.take(256), o_alist = cv.take((size_t)B * 4), o_rlist = cv.take((size_t)B * 4);
   size_t o_alist2 = cv.take((size_t)B * 4);
   size_t o_flags = 0, o_exchange = 0;
-  if (small_round_ok(c)) {
+  if (lay.resident) {
     o_flags = cv.take((size_t)kSmallRoundWorkgroups * kSmallRoundFlagWords * 4);
     o_exchange = cv.take(small_round_exchange_bytes(c));
   }
@@ -371,7 +379,7 @@ size_t carve(const tsd_config& c, tsd_ctx* ctx) {
     ctx->logu = (float*)at(o_logu);
     ctx->diag = (float*)at(o_diag);
     ctx->x = (float*)at(o_x);
-    ctx->row_meta = (int2*)at(o_meta);
+    ctx->row_meta = lay.meta ? (int2*)at(o_meta) : nullptr;
     ctx->xb = at(o_xb);
     ctx->qbuf = at(o_q);
     ctx->abuf = at(o_a);
@@ -397,6 +405,28 @@ size_t carve(const tsd_config& c, tsd_ctx* ctx) {
     ctx->stats_out = (long long*)at(o_so);
   }
   return (cv.off + 255) & ~(size_t)255;
+}
+
+// The layout for an arena of `bytes`: the full one where it fits (tsd_workspace_bytes asks for it), else without what costs speed
+// only, as many rows as fit.  False: not even the least does.
+bool layout_for(const tsd_config& c, size_t bytes, Layout* lay) {
+  *lay = full_layout(c);
+  if (carve(c, *lay, nullptr) <= bytes) return true;
+  const size_t most = lay->rows, least = least_rows(c);
+  const bool resident = lay->resident;
+  for (const Layout& l : {Layout{least, true, resident}, Layout{least, true, false}, Layout{least, false, false}}) {
+    *lay = l;
+    if (carve(c, *lay, nullptr) > bytes) continue;
+    for (size_t step = most - least; lay->rows < most && step > 0; step /= 2)  // (more rows never take less)
+      while (lay->rows + step <= most) {
+        Layout more = *lay;
+        more.rows += step;
+        if (carve(c, more, nullptr) > bytes) break;
+        *lay = more;
+      }
+    return true;
+  }
+  return false;
 }
 
 size_t weights_count(const tsd_model_cfg& m, int P) {
@@ -509,6 +539,14 @@ int run_pass(tsd_ctx* ctx, const Pass& ps, hipStream_t st) {
     q.q_out = ctx->qbuf;
     q.kv_pool = pool;
     q.row_meta = ctx->row_meta;
+    if (!q.row_meta) {  // (looked up by every layer instead)
+      q.page_table = ctx->page_table;
+      q.pt_stride = ctx->pages_per_series;
+      q.base_pos = ps.base_pos;
+      q.pos_off = ps.pos_off;
+      q.s0 = ps.s0;
+      q.act = ps.act;
+    }
     q.n_dev = ps.n_dev;
     q.rope_cos = md.rope_cos;
     q.rope_sin = md.rope_sin;
@@ -960,7 +998,7 @@ int tsd_workspace_bytes(const tsd_config* cfg, size_t* bytes_host) {
   int rc = check_config(cfg, why);
   if (rc) return fail(nullptr, rc, why);
   if (!bytes_host) return fail(nullptr, TSD_E_INVALID_ARG, "bytes_host is NULL");
-  *bytes_host = carve(*cfg, nullptr);
+  *bytes_host = carve(*cfg, full_layout(*cfg), nullptr);
   return TSD_OK;
 }
 
@@ -982,8 +1020,8 @@ int tsd_create(const tsd_config* cfg, void* arena_dev, size_t arena_bytes, tsd_c
   *out = nullptr;
   if (!arena_dev) return fail(nullptr, TSD_E_INVALID_ARG, "arena_dev is NULL");
   if ((uintptr_t)arena_dev & 255) return fail(nullptr, TSD_E_INVALID_ARG, "arena_dev must be 256-byte aligned");
-  size_t need = carve(*cfg, nullptr);
-  if (arena_bytes < need) return fail(nullptr, TSD_E_INVALID_ARG, "arena smaller than tsd_workspace_bytes");
+  Layout lay;
+  if (!layout_for(*cfg, arena_bytes, &lay)) return fail(nullptr, TSD_E_INVALID_ARG, "arena smaller than the least tsd_create can work in (see tsd_workspace_bytes)");
   tsd_ctx* ctx = new (std::nothrow) tsd_ctx();
   if (!ctx) return fail(nullptr, TSD_E_INVALID_ARG, "out of host memory");
   ctx->cfg = *cfg;
@@ -994,7 +1032,7 @@ int tsd_create(const tsd_config* cfg, void* arena_dev, size_t arena_bytes, tsd_c
   ctx->alpha_override = -1.f;
   ctx->n_act = -1;
   ctx->B = ctx->N = ctx->T = ctx->H = 0;
-  carve(*cfg, ctx);
+  carve(*cfg, lay, ctx);
   // rotary tables: angle(pos, i) = pos * base^(-2 i / hd), computed in double
   for (int w = 0; w < 2; ++w) {
     ModelDev& md = ctx->model[w];
@@ -1029,7 +1067,7 @@ int tsd_create(const tsd_config* cfg, void* arena_dev, size_t arena_bytes, tsd_c
     }
     (void)hipGetLastError();
   }
-  if (ctx->skinny && ctx->host_counts && small_round_ok(*cfg) && !(cfg->flags & (TSD_FLAG_SAMPLE_PROPOSALS | TSD_FLAG_NAIVE_VERIFY))) {
+  if (ctx->skinny && ctx->host_counts && lay.resident && !(cfg->flags & (TSD_FLAG_SAMPLE_PROPOSALS | TSD_FLAG_NAIVE_VERIFY))) {
     int dev = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);

@@ -103,6 +103,8 @@ __device__ __forceinline__ int2 row_meta_of(const GemmP& p, int gm) {
   const int pos = (p.base_pos ? p.base_pos[b] : 0) + p.pos_off + t;
   return make_int2(pos, p.page_table[(long)b * p.pt_stride + (pos >> p.pt_shift)]);
 }
+// ... as the patch embedding left it for the layers (NULL: an arena too small for that)
+__device__ __forceinline__ int2 row_meta_at(const GemmP& p, int gm) { return p.row_meta ? p.row_meta[gm] : row_meta_of(p, gm); }
 #endif
 
 struct AttnP {

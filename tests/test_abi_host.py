@@ -139,3 +139,19 @@ def test_static_accept_refuses_tensors_of_the_host(monkeypatch):
     with pytest.raises(ValueError, match="cuda"):
         tsd.accept_commit_static(X, X, p, 1.0)
     assert not called
+
+
+# What tsd_workspace_bytes gave while the workspace held one round's rows or one context, not the contexts of a whole batch.
+@pytest.mark.parametrize("name,before", [("cfg1", 1097728), ("cfg2", 305178368), ("cfg3", 11090615040), ("cfg4", 619119360),
+                                         ("cfg5", 6919992832), ("mini2", 1218048), ("mini3", 6980096), ("mini5", 3035136)])
+def test_arenas_of_the_former_size_are_accepted(name, before):
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("the arena below is not memory: without a GPU tsd_create stops behind the size check, at its first copy")
+    L, c, n, h = tsd.lib(), synth.get_config(name), C.c_size_t(), C.c_void_p()
+    cfg = tsd.make_config(c.target, c.draft, c.patch, c.K, c.batch, c.max_tokens, c.dtype, 1.0)
+    assert L.tsd_workspace_bytes(C.byref(cfg), C.byref(n)) == 0 and n.value > before
+    refused = -1
+    assert L.tsd_create(C.byref(cfg), 0x1000, n.value, C.byref(h)) not in (0, refused)
+    assert L.tsd_create(C.byref(cfg), 0x1000, before, C.byref(h)) not in (0, refused)
+    assert L.tsd_create(C.byref(cfg), 0x1000, before - 256, C.byref(h)) == refused and b"arena" in L.tsd_last_error(None)

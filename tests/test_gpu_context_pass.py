@@ -1,5 +1,7 @@
 """The context pass on a kept handle: batches of one shape after another replay captured launches, a change of shape
 rebuilds them.  Every forecast must equal, to the bit, the one a fresh handle makes of the same series."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -62,4 +64,55 @@ def test_context_of_several_query_tiles(B, N):
     sess = case.session()
     rep = lockstep(case, sess, max_rounds=1)
     assert rep["max_rel_X"] <= TOL["bf16"] and rep["max_rel_mu_p"] <= TOL["bf16"], rep
+    sess.close()
+
+
+@pytest.mark.parametrize("name,B", [("cfg1", 6), ("mini2", 2), ("mini2", 6), ("mini2", 40), ("mini5", 6)])
+def test_smaller_arenas(name, B):
+    """Every arena between the least and the full size decodes, to the bit as the full one does: the context in more passes, without the
+    resident kernel, without the table of row positions."""
+    case = Case(name, B=B)
+    c = case.cfg
+    L, n = tsd.lib(), C.c_size_t()
+    sess = case.session()
+    full = sess.arena_bytes
+    base = (sess.arena.data_ptr() + 255) & ~255
+
+    def arena(size):
+        sess.close()
+        h = C.c_void_p()
+        rc = L.tsd_create(C.byref(sess.cfg), base, size, C.byref(h))
+        if rc:
+            return False
+        sess.h = h
+        for which, m, w in ((tsd.TSD_TARGET, c.target, case.wt), (tsd.TSD_DRAFT, c.draft, case.wd)):
+            sess.load_weights(which, synth.flatten_weights(m, c.patch, w))
+        return True
+
+    def decode():
+        sess.prefill(case.context, c.n_ctx, c.horizon)
+        sess.run_rounds()
+        out = [sess.get_forecast().cpu().numpy()]
+        sess.reset_decode()
+        for _ in range(c.T):
+            sess.target_step()
+        return out + [sess.get_forecast().cpu().numpy()]
+
+    want = decode()
+    resident = sess.resident_passes()
+    lo, hi = 0, full                      # refused, accepted
+    while hi - lo > 256:
+        mid = (lo + hi) // 512 * 256
+        if arena(mid):
+            hi = mid
+        else:
+            lo = mid
+    least, seen = hi, set()
+    # the least; with row positions; with the resident kernel too; a few rows more; half way; all but the last rows
+    for size in (least, least + 16384, least + 65536, (least + full) // 2, full - 256, full):
+        assert arena(min(size, full))
+        for a, b in zip(decode(), want):
+            np.testing.assert_array_equal(a, b, err_msg=f"{size} of {least} .. {full} bytes")
+        seen.add(sess.resident_passes() > 0)
+    assert seen == ({False, True} if resident else {False})
     sess.close()
