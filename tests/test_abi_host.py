@@ -112,7 +112,7 @@ def test_measurement_taps_validate_before_any_launch():
 
 
 def test_static_accept_validates_before_touching_the_gpu():
-    # tsd_accept_commit_static checks sizes against its fixed device array and its flags on the host first;
+    # tsd_accept_commit_static checks sizes against its limits and its flags on the host first;
     # the pointers below are never dereferenced
     L = tsd.lib()
     dummy = C.c_void_p(4096)

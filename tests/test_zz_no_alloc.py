@@ -1,7 +1,7 @@
-"""tsd_accept_commit_static (the entry point for callers that cannot allocate: its kernel state lives in a
-fixed device array inside the library) against tsd_accept_commit on a handle, through the C ABI: same kernel,
-so every output must agree to the bit.  Two calls in a row, the second with a smaller input, so that state the
-first call left in the shared array would show."""
+"""tsd_accept_commit_static (the entry point for callers that cannot allocate: it keeps nothing but the synchronised
+round's minimum, one word per GPU inside the library) against tsd_accept_commit on a handle, through the C ABI: same
+kernel, so every output must agree to the bit.  Two calls in a row, the second with a smaller input and at a later round: a
+word that the first synchronised call left behind, or anything else carried over, would show."""
 import ctypes as C
 
 import numpy as np
