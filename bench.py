@@ -353,6 +353,9 @@ def run_config(torch, tsd, synth, a, name, steps, warmup, fam_steps, flags, case
     rounds = decode_spec(sess)
     st = sess.get_stats()
     t_spec = timed(torch, lambda: decode_spec(sess), steps)
+    n_res = sess.resident_passes()
+    decode_spec(sess)
+    n_res = sess.resident_passes() - n_res      # launches of the resident decode kernel per decode (small batches)
     log(f"{c.name}: {t_spec * 1e3:.2f} ms per speculative decode; target-only decodes")
     for _ in range(max(1, warmup // 2)):
         decode_target_only(sess, c.T)
@@ -421,7 +424,10 @@ def run_config(torch, tsd, synth, a, name, steps, warmup, fam_steps, flags, case
                          kernel=dominant, avg_us=fam[dominant]["avg_us"], launches=fam[dominant]["launches"],
                          traffic_source=traffic_src),
         "kernel_families": fam,
+        "resident_launches_per_decode": n_res,
     }
+    if n_res:
+        rec["roofline"]["path"] = f"kernel by kernel, as under the timing pass; the timed decode runs {n_res} launches of the resident kernel instead"
     return rec
 
 
@@ -492,7 +498,7 @@ def main():
     out.update({k: head[k] for k in ("speedup_vs_target_only", "target_only_steps_per_s", "target_only_ms", "prefill_ms",
                                      "rounds_per_decode", "acceptance", "mean_committed_per_round", "phase_ms", "c", "v",
                                      "predicted_speedup_eq8", "near_ties", "patch_rate_speedup", "planned_block_size",
-                                     "batch_level_prediction", "roofline", "kernel_families")})
+                                     "batch_level_prediction", "roofline", "kernel_families", "resident_launches_per_decode")})
     out["measured_peaks"] = peaks
     if cpu is not None:
         out["cpu_baseline"] = cpu
@@ -500,7 +506,7 @@ def main():
         # the five configurations, each in the deployed scheme (no ablation flags), fewer repetitions
         short = ("workload", "dtype", "value", "ms_per_step", "steps", "speedup_vs_target_only", "target_only_ms", "rounds_per_decode",
                  "acceptance", "mean_committed_per_round", "phase_ms", "c", "v", "predicted_speedup_eq8", "patch_rate_speedup",
-                 "planned_block_size", "batch_level_prediction", "roofline")
+                 "planned_block_size", "batch_level_prediction", "roofline", "resident_launches_per_decode")
         block = {}
         for name in ALL_CONFIGS:
             if name == a.config and flags == 0 and a.sigma is None and a.batch is None and a.fallback_r == 0.0:

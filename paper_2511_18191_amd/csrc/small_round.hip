@@ -1142,13 +1142,16 @@ hipError_t launch_small_round(const SmallRoundP& p, PassUse* use, hipStream_t st
   std::lock_guard<std::mutex> lock(uses_mutex);
   for (PassUse* u : uses) {
     if (u == use || u->device != use->device || !u->in_flight || (u->stream == st && u->thread == thread_of(st))) continue;
+    // (relaxed: a caller that is capturing some other stream, here or in another thread, would see the query end its capture)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
     const hipError_t e = hipEventQuery(u->done);
-    if (e == hipErrorNotReady) {
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) {  // in flight (an error of the device's shows at the launches that follow)
       (void)hipGetLastError();
       *busy = true;
       return hipSuccess;
     }
-    if (e != hipSuccess) return e;
     u->in_flight = false;
   }
   hipLaunchKernelGGL(small_round_kernel, dim3(kWg), dim3(kThreads), 0, st, p);

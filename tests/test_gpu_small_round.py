@@ -147,6 +147,37 @@ def test_beside_a_large_batch():
         s.close()
 
 
+def test_a_capture_of_the_callers_goes_on():
+    """Rounds of two handles while the caller captures a stream of its own, in the mode that refuses most: the look at the other
+    handle's passes must not end the capture."""
+    case = Case("mini2", B=2)
+    c = case.cfg
+    sess = [case.session() for _ in range(2)]
+    want = []
+    for s in sess:
+        s.prefill(case.context, c.n_ctx, c.horizon)
+        s.run_rounds()
+        want.append(s.get_forecast().cpu().numpy())
+        s.reset_decode()
+    torch.cuda.synchronize()
+    x = torch.zeros(8, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, capture_error_mode="global"):
+        x += 1
+        for _ in range(c.T):
+            for s in sess:
+                assert tsd.lib().tsd_round(s.h, s.stream.cuda_stream) == 0
+        x += 1
+    torch.cuda.synchronize()
+    for s, w in zip(sess, want):
+        assert s.num_active() == 0
+        np.testing.assert_array_equal(s.get_forecast().cpu().numpy(), w)
+        s.close()
+    for n in (1, 2, 3):
+        graph.replay()
+        assert x.cpu().tolist() == [2.0 * n] * 8
+
+
 @pytest.mark.parametrize("B,K,target,draft,P,N", [
     (1, 4, None, None, 96, 6), (16, 1, W192, W640, 96, 5), (2, 15, W640, W192, 96, 5),
     (3, 4, ModelCfg(2, 192, 3, 288), D1, 48, 5), (2, 3, ModelCfg(2, 768, 12, 3072), ModelCfg(2, 384, 6, 1536), 560, 4),
