@@ -67,7 +67,8 @@ def test_context_of_several_query_tiles(B, N):
     sess.close()
 
 
-@pytest.mark.parametrize("name,B", [("cfg1", 6), ("mini2", 2), ("mini2", 6), ("mini2", 40), ("mini5", 6)])
+@pytest.mark.parametrize("name,B", [("cfg1", 6), ("mini2", 2), ("mini2", 6), ("mini2", 40), ("mini5", 6),
+                                    ("mini3", 20), ("mini3", 1200), ("mini3", 1240)])   # (rounds on 64-, 128- and 256-row tiles)
 def test_smaller_arenas(name, B):
     """Every arena between the least and the full size decodes, to the bit as the full one does: the context in more passes, without the
     resident kernel, without the table of row positions."""
