@@ -4,14 +4,15 @@
 A step is one whole speculative decode of the batch: reset to the post-prefill state, then
 rounds (draft proposal, single-pass verification, acceptance/commit/rollback) until every series
 has its horizon.  Inputs (weights, KV cache of the context) are resident in HBM before the
-timed region.  Prints ONE JSON line: the headline workload (default cfg3, the largest configuration
+timed region.  Prints ONE JSON line, a few KB long (a log's tail holds it): the headline workload (default cfg3, the largest configuration
 that one GPU holds and the one whose GEMMs and attention the MFMA / HBM rooflines bound), its dominant
 kernel family's roofline, the CPU oracle on a bounded sample of the same workload, and a `configs`
-block with the same figures for every one of the five configurations.
+block with the main figures of every one of the five configurations.  --details FILE writes everything measured.
 
-    python bench.py [--gpus 1] [--steps K] [--warmup W] [--config cfg3] [--sigma 1.0] [--only]
+    python bench.py [--gpus 1] [--steps K] [--warmup W] [--config cfg3] [--sigma 1.0] [--only] [--details FILE]
 """
 import argparse
+import copy
 import hashlib
 import json
 import os
@@ -46,6 +47,7 @@ def parse():
                     help="wait for the stream after this many target-only steps (for runs under a counter-collecting profiler, "
                          "which stalls when thousands of launches are queued without a host wait)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
+    ap.add_argument("--details", default=None, help="write the whole record (every kernel family of every configuration, cost tables, predictions) to this file")
     ap.add_argument("--cpu-workers", type=int, default=0, help="oracle worker processes (default: the CPUs this process may use, at most 16)")
     ap.add_argument("--cpu-seconds", type=float, default=12.0, help="the oracle keeps taking series until about this much wall time has passed")
     ap.add_argument("--copy-calibration", action="store_true",
@@ -244,6 +246,41 @@ def kernel_rooflines(sess, dtype, steps, traffic, cfg=None):
         if out[key]["traffic"]:
             out[key]["hbm_frac_of_traffic"] = out[key]["traffic"] / (ms * 1e-3 / n) / 1e9 / HBM_PEAK
     return out
+
+
+def significant(x, digits=6):
+    """`x` with its floats, however deep, rounded to so many significant digits."""
+    if isinstance(x, float):
+        return float(f"{x:.{digits}g}")
+    if isinstance(x, dict):
+        return {k: significant(v, digits) for k, v in x.items()}
+    return [significant(v, digits) for v in x] if isinstance(x, (list, tuple)) else x
+
+
+def compact(out):
+    """The record as the printed line carries it: the headline's figures, its largest kernel families, and of the other
+    configurations what a table of them needs.  (The whole record is 33 KB, which cuts a log's tail off at its start.)"""
+    def plan(p):
+        return p and {rule: {k: p[rule][k] for k in ("K", "ms_per_step", "speedup_vs_target_only")} for rule in p if isinstance(p[rule], dict) and "K" in p[rule]}
+
+    def prediction(b):
+        return b and {k: {kk: b[k][kk] for kk in ("predicted_rounds", "predicted_ms", "predicted_speedup_vs_target_only")}
+                      for k in ("pooled_acceptance", "per_series_acceptance")}
+
+    def families(fam, n):
+        largest = sorted(fam, key=lambda k: -fam[k].get("total_ms", fam[k]["avg_us"] * fam[k]["launches"]))[:n]
+        return {k: {kk: fam[k][kk] for kk in ("bound", "achieved", "unit", "frac", "avg_us", "launches") if kk in fam[k]} for k in largest}
+
+    line = dict(out)
+    for rec in [line] + list(line.get("configs", {}).values()):
+        rec.update(planned_block_size=plan(rec["planned_block_size"]), batch_level_prediction=prediction(rec["batch_level_prediction"]))
+    line["kernel_families"] = families(out["kernel_families"], 8)
+    if "configs" in line:
+        own = ("value", "ms_per_step", "steps", "target_only_ms", "speedup_vs_target_only", "patch_rate_speedup", "predicted_speedup_eq8",
+               "acceptance", "mean_committed_per_round", "rounds_per_decode", "c", "v", "planned_block_size", "resident_launches_per_decode")
+        line["configs"] = {name: dict({k: rec[k] for k in own}, roofline={k: rec["roofline"][k] for k in ("kernel", "bound", "frac", "path") if k in rec["roofline"]})
+                           for name, rec in line["configs"].items()}
+    return significant(line)
 
 
 def measured_peaks(torch, tsd):
@@ -518,7 +555,10 @@ def main():
             block[name]["families"] = {k: {kk: f[kk] for kk in ("bound", "achieved", "frac", "avg_us", "launches", "unit") if kk in f}
                                        for k, f in rec["kernel_families"].items()}
         out["configs"] = block
-    print(json.dumps(out))
+    if a.details:
+        with open(a.details, "w") as f:
+            json.dump(out, f)
+    print(json.dumps(compact(copy.deepcopy(out))))
 
 
 if __name__ == "__main__":
