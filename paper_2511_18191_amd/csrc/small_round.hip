@@ -91,7 +91,7 @@ __device__ __forceinline__ void load_weights(const bf16* W, unsigned off, int pe
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
     const int j = t / PB, i = t % PB;
-    if (j < per) w.f[t] = *reinterpret_cast<const bf16x8*>(W + (SB * i * per + j) * 32 + off);
+    if (j < per) w.f[t] = *reinterpret_cast<const bf16x8*>(W + (slab_start(SB * i, per) + j * 32) + off);
   }
 }
 
@@ -101,7 +101,7 @@ __device__ __forceinline__ void prefetch(const SmallProd& d, const bf16* W, int 
   if (wg >= d.units || 4 * wave >= d.used) return;
   asm volatile("" : "+v"(lane));  // (an opaque copy: keeps the address arithmetic below from being hoisted to the kernel's top)
   const int li = lane & 15, col = column_of<QKV>(d, wg, li & ((1 << d.cs) - 1));
-  const unsigned off = (unsigned)(col * d.K + (4 * wave + (li >> d.cs)) * d.per * 32 + (lane >> 4) * 8);
+  const unsigned off = (unsigned)(col * d.K + slab_start(4 * wave + (li >> d.cs), d.per) + (lane >> 4) * 8);
   if (d.cs == 2) load_weights<4>(W, off, d.per, w);
   else if (d.cs == 3) load_weights<8>(W, off, d.per, w);
   else load_weights<16>(W, off, d.per, w);
@@ -155,7 +155,7 @@ __device__ __forceinline__ void product_t(const bf16* A, int K, int per, int M, 
   const int li = lane & 15, lg = lane >> 4;
   unsigned row[NT];  // element offsets from A (uniform base, 32-bit offset: one address register per load)
 #pragma unroll
-  for (int r = 0; r < NT; ++r) row[r] = (unsigned)(min(r * 16 + li % R, M - 1) * K + (4 * wave + li / R) * per * 32 + lg * 8);
+  for (int r = 0; r < NT; ++r) row[r] = (unsigned)(min(r * 16 + li % R, M - 1) * K + slab_start(4 * wave + li / R, per) + lg * 8);
   f32x4 acc[NT][NACC];  // g: slabs 4 wave + g G .. + G - 1
   float ss[NT][PA];
 #pragma unroll
@@ -178,7 +178,7 @@ __device__ __forceinline__ void product_t(const bf16* A, int K, int per, int M, 
 #pragma unroll
       for (int r = 0; r < NT; ++r)
 #pragma unroll
-        for (int i = 0; i < PA; ++i) a[j][r][i] = *reinterpret_cast<const bf16x8*>(A + (SA * i * per + j0 + j) * 32 + row[r]);
+        for (int i = 0; i < PA; ++i) a[j][r][i] = *reinterpret_cast<const bf16x8*>(A + (slab_start(SA * i, per) + (j0 + j) * 32) + row[r]);
     }
 #pragma unroll
     for (int j = 0; j < JC; ++j) {
@@ -891,10 +891,12 @@ struct Extent {
 __global__ __launch_bounds__(kThreads) void small_round_kernel(const SmallRoundP p) {
   __shared__ __attribute__((aligned(16))) Shared sh;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int gone = *p.status;  // an earlier launch gave up: this one is left to the kernel behind it
   const Extent x(p);
-  if (gone || x.n <= 0) return;
-  if (p.wait_ticks <= 0) {  // (uniform over the grid)
+  if (x.n <= 0) return;
+  // (What decides here is the same for every wavefront.  The status word is not: another workgroup may set it between two looks, and
+  //  wavefronts of one workgroup must not part.  Behind a launch that gave up this one may run for nothing, or leave at its first
+  //  long wait; the kernel behind it goes by the word either way.)
+  if (p.wait_ticks <= 0) {
     if (blockIdx.x == 0 && threadIdx.x == 0) give_up(p);
     return;
   }

@@ -40,7 +40,7 @@ constexpr bool small_product_ok(int K, int N) {
 // worker with fewer than four reads past the end of its rows all the same (choosing the address takes 0.75 % of the kernel) and drops
 // the sums.  That far behind row 31, and behind the last row of weights, nothing may lie that is written during the launch: a line
 // that is read before it is published would be seen stale by the stage that needs it (see small_round.hip).
-constexpr long slab_offset(int wave, int part, int per) { return (long)(kSmallRoundWorkers * wave + part) * per * 64; }  // bytes into a row
+constexpr int slab_start(int slab, int per) { return slab * per * 32; }  // its first element in a row (and, of a count of slabs, their length)
 // At most three slabs of eight k-steps, in whole 4 KB: shorter tails move the parts to other memory channels (a round of five series
 // through 8 layers of 512: 314.4 us, back to back 315.0, with tails of 1536 bytes 318.7).
 constexpr int kSmallTail = 4096;

@@ -17,7 +17,7 @@ long behind(const SmallPlan& d) {
     for (int part = 0; part < 4; ++part)
       for (int j = 0; j < d.per; ++j)
         for (int piece = 0; piece < 4; ++piece) {
-          const long end = slab_offset(wave, part, d.per) + j * 64 + piece * 16 + 16 - 2L * d.K;
+          const long end = 2L * (slab_start(kSmallRoundWorkers * wave + part, d.per) + j * 32 + piece * 8 + 8 - d.K);
           if (end > most) most = end;
         }
   return most;
