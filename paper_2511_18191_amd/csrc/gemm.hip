@@ -289,7 +289,7 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
   // behind the main loop: the KV position/page of each row (QKV), the old residual values (RESID).
   int2 my_meta = make_int2(0, 0);
   if constexpr (EP == EP_QKV) {
-    if (tid < BM) my_meta = row_meta_at(p, min(m0 + tid, m_lim - 1));
+    if (tid < BM) my_meta = p.row_meta[min(m0 + tid, m_lim - 1)];
   }
   if constexpr (AM == A_TOK) {
     if (p.row_meta && tn == 0 && tid < BM) my_meta = row_meta_of(p, min(m0 + tid, m_lim - 1));

@@ -88,7 +88,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const GemmP p) {
   // epilogue inputs that do not depend on the product
   if constexpr (EP == EP_QKV) {
     if (tid < kRowsMax) {
-      const int2 meta = row_meta_at(p, m0 + min(tid, M - 1));
+      const int2 meta = p.row_meta[m0 + min(tid, M - 1)];
       row_pos[tid] = meta.x;
       row_page[tid] = meta.y;
     }

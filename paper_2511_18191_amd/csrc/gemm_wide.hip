@@ -114,7 +114,7 @@ __global__ __launch_bounds__(S::NT, 2) void gemm_wide_kernel(const GemmP p) {
   int2 my_meta = make_int2(0, 0);
   if constexpr (EP == EP_QKV) {
     static_assert(BM <= S::NT, "one row per lane");
-    my_meta = row_meta_at(p, min(m0 + min(tid, BM - 1), m_lim - 1));
+    my_meta = p.row_meta[min(m0 + min(tid, BM - 1), m_lim - 1)];
   }
 
   // EP_RESID: the old residual values of a pass are requested one pass ahead (those of pass 0 before the accumulators'

@@ -148,6 +148,15 @@ hipError_t launch_accept(const AcceptP& p, hipStream_t st) {
   return hipGetLastError();
 }
 
+__global__ __launch_bounds__(256) void row_meta_kernel(const GemmP p) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < p.M) p.row_meta[i] = row_meta_of(p, i);
+}
+hipError_t launch_row_meta(const GemmP& p, hipStream_t st) {
+  hipLaunchKernelGGL(row_meta_kernel, dim3((unsigned)((p.M + 255) / 256)), dim3(256), 0, st, p);
+  return hipGetLastError();
+}
+
 __global__ void fill_int_kernel(int* p, int value, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = value;

@@ -29,6 +29,7 @@
 // gave up, leaves, and the kernel behind the launch does its work (series_alone).
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <mutex>
 #include <vector>
 
@@ -1022,11 +1023,16 @@ __device__ __forceinline__ void series_alone(const SmallRoundP& p, int b, int pl
   }
 }
 
+// The resident launch before this kernel has finished.
+__device__ __forceinline__ void mark_done(const SmallRoundP& p) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(p.done, p.done_value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Behind a launch of the resident kernel: a series per workgroup, and nothing to do (4 us) unless that launch gave up.
 __global__ __launch_bounds__(kWorkers * 64) void small_round_alone_kernel(const SmallRoundP p) {
   __shared__ __attribute__((aligned(16))) Shared sh;
-  if (*p.status == 0 || (p.counts && (int)blockIdx.x >= p.counts[0])) return;
-  series_alone(p, p.act ? p.act[blockIdx.x] : (int)blockIdx.x, blockIdx.x, sh);
+  if (*p.status && !(p.counts && (int)blockIdx.x >= p.counts[0])) series_alone(p, p.act ? p.act[blockIdx.x] : (int)blockIdx.x, blockIdx.x, sh);
+  mark_done(p);
 }
 
 // The same at the head of the acceptance step where that follows at once: no launch of its own.
@@ -1037,6 +1043,7 @@ __global__ __launch_bounds__(kWorkers * 64) void small_round_accept_kernel(const
     if (!(p.n_dev && (int)blockIdx.x >= *p.n_dev) && p.active[b]) series_alone(r, b, blockIdx.x, sh);
     __syncthreads();
   }
+  mark_done(r);
   accept_step(p);
 }
 
@@ -1097,26 +1104,35 @@ namespace {
 std::mutex uses_mutex;
 std::vector<PassUse*> uses;         // of all handles
 std::atomic<int> resident_handles;  // those among them that may run the resident kernel
+std::atomic<long long> last_asked;  // when one of those last wanted to, in ns
+
+// A handle's passes are numbered where others look, and its stream writes the number of the last finished one to a pinned host word: the
+// kernel behind a resident launch does, behind other passes a fill kernel.  (Not events: looking at one whose stream is being
+// captured by now ends that capture.)  Such a kernel per pass costs some us (an event 0.5 % of the target-only steps of 256 series), so
+// other passes are marked only while somebody is asking: a small handle that starts beside busy ones takes the resident kernel until
+// their next passes.
+constexpr long long kAskedRecently = 100000000;
+long long now_ns() { return std::chrono::duration_cast<std::chrono::nanoseconds>(std::chrono::steady_clock::now().time_since_epoch()).count(); }
 
 std::thread::id thread_of(hipStream_t st) {  // (hipStreamPerThread names another stream in every thread)
   return st == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id();
 }
 
-hipError_t record_use(PassUse* use, hipStream_t st) {
-  hipError_t e = hipSuccess;
-  if (!use->done && (e = hipEventCreateWithFlags(&use->done, hipEventDisableTiming)) != hipSuccess) return e;
-  if ((e = hipEventRecord(use->done, st)) != hipSuccess) return e;
+bool in_flight(const PassUse& u) { return u.done && __atomic_load_n(u.done, __ATOMIC_RELAXED) != u.launched; }
+
+// The number of the pass now launched on `st`.
+int number_pass(PassUse* use, hipStream_t st) {
   use->stream = st;
   use->thread = thread_of(st);
-  use->in_flight = true;
-  return e;
+  return ++use->launched;
 }
 }  // namespace
 
-void add_use(PassUse* use, int device, bool resident) {
+void add_use(PassUse* use, int device, bool resident, int* done) {
   std::lock_guard<std::mutex> lock(uses_mutex);
   use->device = device;
   use->resident = resident;
+  use->done = done;
   uses.push_back(use);
   if (resident) ++resident_handles;
 }
@@ -1125,40 +1141,33 @@ void remove_use(PassUse* use) {
   std::lock_guard<std::mutex> lock(uses_mutex);
   uses.erase(std::remove(uses.begin(), uses.end(), use), uses.end());
   if (use->resident) --resident_handles;
-  if (use->done) (void)hipEventDestroy(use->done);
 }
 
 hipError_t note_pass(PassUse* use, hipStream_t st) {
-  if (resident_handles.load(std::memory_order_relaxed) <= (use->resident ? 1 : 0)) return hipSuccess;  // nobody else asks
+  if (resident_handles.load(std::memory_order_relaxed) <= (use->resident ? 1 : 0) || !use->done) return hipSuccess;  // nobody else could ask,
+  if (now_ns() - last_asked.load(std::memory_order_relaxed) > kAskedRecently) return hipSuccess;                    // or does
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (st) {
     hipError_t e = hipStreamIsCapturing(st, &cs);
     if (e != hipSuccess || cs != hipStreamCaptureStatusNone) return e;
   }
   std::lock_guard<std::mutex> lock(uses_mutex);
-  return record_use(use, st);
+  return launch_fill_int(use->done, number_pass(use, st), 1, st);
 }
 
-hipError_t launch_small_round(const SmallRoundP& p, PassUse* use, hipStream_t st, bool* busy) {
+hipError_t launch_small_round(SmallRoundP& p, PassUse* use, hipStream_t st, bool* busy) {
   *busy = false;
+  last_asked.store(now_ns(), std::memory_order_relaxed);
   std::lock_guard<std::mutex> lock(uses_mutex);
-  for (PassUse* u : uses) {
-    if (u == use || u->device != use->device || !u->in_flight || (u->stream == st && u->thread == thread_of(st))) continue;
-    // (relaxed: a caller that is capturing some other stream, here or in another thread, would see the query end its capture)
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    const hipError_t e = hipEventQuery(u->done);
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (e != hipSuccess) {  // in flight (an error of the device's shows at the launches that follow)
-      (void)hipGetLastError();
+  for (const PassUse* u : uses)
+    if (u != use && u->device == use->device && in_flight(*u) && (u->stream != st || u->thread != thread_of(st))) {
       *busy = true;
       return hipSuccess;
     }
-    u->in_flight = false;
-  }
+  p.done = use->done;
+  p.done_value = number_pass(use, st);
   hipLaunchKernelGGL(small_round_kernel, dim3(kWg), dim3(kThreads), 0, st, p);
-  const hipError_t e = hipGetLastError();
-  return e != hipSuccess ? e : record_use(use, st);
+  return hipGetLastError();
 }
 
 hipError_t launch_small_round_alone(const SmallRoundP& p, hipStream_t st) {

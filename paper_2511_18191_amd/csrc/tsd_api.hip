@@ -217,7 +217,7 @@ constexpr long kContextRows = 16384;
 // What an arena holds besides weights, caches and per-series state.  Everything runs in the least of it, in more passes and launches.
 struct Layout {
   size_t rows;    // of the activation workspace
-  bool meta;      // the rows' positions and cache pages, looked up once per pass
+  bool meta;      // the rows' positions and cache pages, looked up once per pass instead of before every layer
   bool resident;  // flags and exchange buffer of the resident decode kernel
 };
 
@@ -542,13 +542,10 @@ int run_pass(tsd_ctx* ctx, const Pass& ps, hipStream_t st) {
     q.q_out = ctx->qbuf;
     q.kv_pool = pool;
     q.row_meta = ctx->row_meta;
-    if (!q.row_meta) {  // (looked up by every layer instead)
-      q.page_table = ctx->page_table;
-      q.pt_stride = ctx->pages_per_series;
-      q.base_pos = ps.base_pos;
-      q.pos_off = ps.pos_off;
-      q.s0 = ps.s0;
-      q.act = ps.act;
+    if (!q.row_meta) {  // (a small arena: looked up before every layer, into the attention output, which is dead until then)
+      GemmP t = g;
+      t.row_meta = q.row_meta = reinterpret_cast<int2*>(ctx->abuf);
+      HIP_TRY(ctx, launch_row_meta(t, st));
     }
     q.n_dev = ps.n_dev;
     q.rope_cos = md.rope_cos;
@@ -947,7 +944,10 @@ int accept_commit_impl(tsd_ctx* ctx, const int32_t* forced, int K, hipStream_t s
   a.logu = ctx->logu;
   a.stat = ctx->stat;
   const Cover cv = cover(ctx);
-  if (cv.n == 0) return TSD_OK;
+  if (cv.n == 0) {
+    if (after && after->n > 0) HIP_TRY(ctx, launch_small_round_alone(*after, st));
+    return TSD_OK;
+  }
   a.B = cv.n;
   a.act = cv.act;
   a.n_dev = cv.n_dev;
@@ -1116,7 +1116,7 @@ int tsd_create(const tsd_config* cfg, void* arena_dev, size_t arena_bytes, tsd_c
   }
   int dev = 0;
   (void)hipGetDevice(&dev);
-  add_use(&ctx->use, dev, ctx->small_round);
+  add_use(&ctx->use, dev, ctx->small_round, ctx->host_counts ? ctx->host_counts + 4 : nullptr);
   *out = ctx;
   return TSD_OK;
 }

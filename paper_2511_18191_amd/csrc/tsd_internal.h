@@ -103,8 +103,6 @@ __device__ __forceinline__ int2 row_meta_of(const GemmP& p, int gm) {
   const int pos = (p.base_pos ? p.base_pos[b] : 0) + p.pos_off + t;
   return make_int2(pos, p.page_table[(long)b * p.pt_stride + (pos >> p.pt_shift)]);
 }
-// ... as the patch embedding left it for the layers (NULL: an arena too small for that)
-__device__ __forceinline__ int2 row_meta_at(const GemmP& p, int gm) { return p.row_meta ? p.row_meta[gm] : row_meta_of(p, gm); }
 #endif
 
 struct AttnP {
@@ -235,6 +233,8 @@ struct SmallRoundP {
   int *status, *host_status;                  // device and pinned host word, set to 1 by a launch that gave up waiting, for good
   long long wait_ticks;                       // how long a workgroup waits, in ticks of the 100 MHz wall clock (0: the launch gives up at once)
   float scale;                                // 1 / sqrt(head_dim)
+  int* done;                                  // pinned host word that gets done_value once the launch has finished
+  int done_value;
 };
 bool small_round_ok(const tsd_config& c);
 void small_round_model(const tsd_model_cfg& c, int patch, const bf16* W_e, const bf16* W_h, const bf16* Wqkv, const bf16* Wo, const bf16* W1,
@@ -245,17 +245,18 @@ int small_round_stages(const tsd_config& c);
 struct PassUse {
   int device = -1;
   bool resident = false;          // the handle may run the resident kernel
-  hipEvent_t done = nullptr;
+  int* done = nullptr;            // pinned word: number of the last finished pass (NULL: the handle has none, and is not watched)
+  int launched = 0;               // ... of the last launched one
   hipStream_t stream = nullptr;
   std::thread::id thread;         // with hipStreamPerThread
-  bool in_flight = false;         // recorded and not yet seen finished
 };
-void add_use(PassUse* use, int device, bool resident);
+void add_use(PassUse* use, int device, bool resident, int* done);
 void remove_use(PassUse* use);
 hipError_t note_pass(PassUse* use, hipStream_t st);
 // *busy: another handle's pass is in flight on another stream, and nothing was launched
-hipError_t launch_small_round(const SmallRoundP& p, PassUse* use, hipStream_t st, bool* busy);
-// One of these two has to follow it: they finish a launch that gave up, the second before it goes on with the acceptance step.
+hipError_t launch_small_round(SmallRoundP& p, PassUse* use, hipStream_t st, bool* busy);
+// One of these two has to follow it: they finish a launch that gave up, the second before it goes on with the acceptance step, and
+// mark the launch as done.
 struct AcceptP;
 hipError_t launch_small_round_alone(const SmallRoundP& p, hipStream_t st);
 hipError_t launch_small_round_accept(const SmallRoundP& r, const AcceptP& p, hipStream_t st);
@@ -326,6 +327,7 @@ struct AcceptP {
 };
 hipError_t launch_accept(const AcceptP& p, hipStream_t st);
 hipError_t launch_fill_int(int* p, int value, int n, hipStream_t st);
+hipError_t launch_row_meta(const GemmP& p, hipStream_t st);  // row_meta of all p.M rows
 
 struct SampleP {  // X[b, i-1] = mu_q[b, i-1] + sigma_q * eps(b, round[b], i)
   const float* mu_q;

@@ -2,6 +2,8 @@
 replaces, over the sizes where its indexing changes (row tiles of 4, 8, 16 and 2 x 16, 4, 8 and 16 columns per workgroup, workers
 with fewer than four slabs, patches that are no whole k-step, more cached keys than are fetched together), and two handles at a
 time.  Every case asserts that the one side ran on that kernel and the other did not."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -115,6 +117,43 @@ def test_two_handles_on_two_streams():
         s.close()
 
 
+def test_two_handles_in_two_threads():
+    """Two programs' worth of forecasts at once, on fresh handles each time so that either thread captures its launches while the other
+    looks whether it may take the resident kernel: no error, and the results of a handle alone."""
+    case = Case("mini2", B=2)
+    c = case.cfg
+    ref = case.session()
+    want = []
+    for target_only in (False, True):
+        ref.prefill(case.context, c.n_ctx, c.horizon)
+        for _ in range(c.T):
+            ref.target_step() if target_only else ref.round()
+        want.append(ref.get_forecast().cpu().numpy())
+    ref.close()
+    errors = []
+
+    def work(s):
+        try:
+            for i in range(6):
+                s.prefill(case.context, c.n_ctx, c.horizon)
+                for _ in range(c.T):
+                    s.target_step() if i % 2 else s.round()
+                np.testing.assert_array_equal(s.get_forecast().cpu().numpy(), want[i % 2])
+        except Exception as e:
+            errors.append(e)
+
+    for _ in range(4):
+        sess = [case.session() for _ in range(2)]
+        threads = [threading.Thread(target=work, args=(s,)) for s in sess]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        for s in sess:
+            s.close()
+    assert not errors, errors
+
+
 def test_beside_a_large_batch():
     """A handle of any kind that is busy on another stream keeps a small one off the resident kernel; on the same stream, which
     orders the two, it does not."""
@@ -123,12 +162,14 @@ def test_beside_a_large_batch():
     for c, s in ((big, sb), (small, ss)):
         s.prefill(c.context, c.cfg.n_ctx, c.cfg.horizon)
     torch.cuda.synchronize()
+    ss.round()                     # (others' passes are watched while somebody asks, i.e. has asked in the last 100 ms)
+    assert ss.resident_passes() == 1
     for _ in range(20):
         sb.reset_decode()
         sb.round()
     assert sb.resident_passes() == 0
     ss.round()
-    assert ss.resident_passes() == 0
+    assert ss.resident_passes() == 1
     torch.cuda.synchronize()
     ss.reset_decode()
     ss.stream = sb.stream
@@ -137,7 +178,7 @@ def test_beside_a_large_batch():
         sb.reset_decode()
         sb.round()
     ss.run_rounds()
-    assert ss.resident_passes() > 0
+    assert ss.resident_passes() > 1
     got = ss.get_forecast().cpu().numpy()
     ref = small.session(flags=tsd.TSD_FLAG_NO_PINNED_COUNTS)
     ref.prefill(small.context, small.cfg.n_ctx, small.cfg.horizon)
