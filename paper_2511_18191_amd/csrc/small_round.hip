@@ -1098,8 +1098,8 @@ int small_round_stages(const tsd_config& c) { return c.K * (2 + 5 * c.draft.n_la
 // resident launch is a bad neighbour: its workgroups leave too few registers for most kernels, whose streams then take turns with it
 // where launch by launch they overlap.  So a pass runs as the resident kernel only while no other handle's passes are in flight on
 // another stream; with the same bits either way, nothing else depends on it.  (Two handles
-// on two streams, ms for a decode of each, taking turns through an event / now: one series through 24 layers of 1024 16.8 / 14.5
-// (alone 8.4), five through 8 layers of 512 5.3 / 4.4; 30 decodes of the former beside 51 of 256 series 487 / 384.)
+// on two streams, ms for a decode of each, taking turns through an event / now: one series through 24 layers of 1024 16.8 / 14.3
+// (alone 8.5), five through 8 layers of 512 5.3 / 4.4; 29 decodes of the former beside 50 of 256 series 480 / 375.)
 namespace {
 std::mutex uses_mutex;
 std::vector<PassUse*> uses;         // of all handles

@@ -41,9 +41,10 @@ constexpr bool small_product_ok(int K, int N) {
 // the sums.  That far behind row 31, and behind the last row of weights, nothing may lie that is written during the launch: a line
 // that is read before it is published would be seen stale by the stage that needs it (see small_round.hip).
 constexpr int slab_start(int slab, int per) { return slab * per * 32; }  // its first element in a row (and, of a count of slabs, their length)
-// At most three slabs of eight k-steps, in whole 4 KB: shorter tails move the parts to other memory channels (a round of five series
-// through 8 layers of 512: 314.4 us, back to back 315.0, with tails of 1536 bytes 318.7).
-constexpr int kSmallTail = 4096;
+// At most three slabs of eight k-steps, in whole 8 KB: the length decides on which memory channels the parts of a layer start (a round of
+// one series through 24 layers of 1024 / of five through 8 of 512, us: back to back 687 / 315.0, tails of 2 KB 689 / 315.5, 4 KB
+// 681 / 314.0, 8 KB 674 / 314.0, 16 KB 683 / 314.2).
+constexpr int kSmallTail = 8192;
 static_assert(3 * 8 * 64 <= kSmallTail, "");
 
 // The exchange buffer: of a layer, the rows entering it, its queries, attention output, the rows between its two halves, hidden
