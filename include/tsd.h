@@ -73,7 +73,7 @@ extern "C" {
 #define TSD_FLAG_NO_PINNED_COUNTS 512u /* tsd_num_active copies the counts back and waits on the stream */
 #define TSD_FLAG_NO_FUSED_DRAFT 1024u /* always run the draft phase kernel by kernel                       */
 #define TSD_FLAG_FUSED_DRAFT 2048u /* run the draft phase as one launch wherever that kernel is supported */
-#define TSD_FLAG_NO_WIDE_GEMM 4096u /* never use the wide-tile direct-to-LDS GEMM kernels (same bits, for A/B timing) */
+#define TSD_FLAG_NO_WIDE_GEMM 4096u /* never use the direct-to-LDS GEMM kernels (same bits, for A/B timing) */
 #define TSD_FLAG_CLEAR_REST 8192u  /* tsd_accept_commit_static: zero the committed rows' buffer behind the round's last patch */
 
 typedef struct tsd_ctx tsd_ctx; /* opaque */
@@ -376,8 +376,8 @@ int tsd_profile_end(tsd_ctx* ctx, int64_t* launches_host, double* ms_host, doubl
 /* The launches of the measurement that the last tsd_profile_end closed, one record each, in launch order:
  * family, model (TSD_TARGET / TSD_DRAFT, -1 for the acceptance kernel), and for the GEMM families the kernel the
  * launcher picked (`tile`: 128 or 64 = tile size of the tiled kernel, 464 = 64 x 64 tiles with K split over four
- * wavefront groups, 16 = the skinny weight-streaming kernel, 2064 / 2128 / 2256 = the direct-to-LDS kernels with 64 x 64,
- * 128 x 128 and 256 x 128 tiles) and the product's shape as launched (rows M as
+ * wavefront groups, 16 = the skinny weight-streaming kernel, 2064 / 2127 / 2128 / 2129 / 2256 / 2257 = the direct-to-LDS
+ * kernels with 64 x 64, 128 x 64, 128 x 128, 128 x 256, 256 x 128 and 256 x 256 tiles) and the product's shape as launched (rows M as
  * sized on the host: a replayed or device-capped launch may run fewer); attention: M = query rows, N = model
  * width; duration between the two events in milliseconds; algorithmic work as summed by tsd_profile_end.
  * out_host: max_records entries; *n_host receives the number of launches recorded (which may exceed
@@ -402,7 +402,7 @@ int tsd_set_resident_wait(tsd_ctx* ctx, int32_t milliseconds);
  * C[M,N] = A[M,K] * Wt[N,K]^T (fp32 result); variant 1: the same with each row of the product
  * scaled by rsqrt(mean(A_row^2) + 1e-6) (the fused RMSNorm); variant 2: C += A * Wt^T (the
  * residual epilogue); variant 3 (bf16 only): C = GELU_tanh(RMSNorm-scaled product), stored as bf16 [M,N]: the
- * FFN-up product exactly as the passes run it; variant + 8: the same without the wide-tile kernels.  K must be a
+ * FFN-up product exactly as the passes run it; variant + 8: the same without the direct-to-LDS kernels.  K must be a
  * multiple of 8, N of 4.  No handle needed. */
 int tsd_bench_gemm(int dtype, int variant, int M, int N, int K, const void* A_dev, const void* Wt_dev, void* C_dev,
                    void* stream);

@@ -163,8 +163,8 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
         }
       } else {
         if constexpr (kNorm) {
-          // a chain of packed bf16 dot products per 16-byte chunk position: the wide-tile kernel (gemm_wide.hip)
-          // forms the same chains from its MFMA fragments, so either kernel gives a row the same scale
+          // a chain of packed bf16 dot products per 16-byte chunk position: the direct-to-LDS kernels (gemm_direct64.hip)
+          // form the same chains from their MFMA fragments, so any kernel gives a row the same scale
           typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
           const bf16x8 v = *reinterpret_cast<const bf16x8*>(&ra[i]);
 #pragma unroll
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
   const int ty = gt >> 4, tx = gt & 15;  // fp32 path: 4x4 micro-tile at (ty*4, tx*4)
   // Long contractions of activations (K >= kQuarterK) are summed in four runs of ceil(nk / 4) k-steps, each from
   // zero, the runs added in order: the order the split workgroups (G = 4) produce by construction.  Every bf16
-  // kernel that can take such a product (this one, the split one, the wide-tile ones) keeps to it, so which of them
+  // kernel that can take such a product (this one, the split one, the direct-to-LDS ones) keeps to it, so which of them
   // the launcher picks, which follows the rows still active, changes no bit.
   constexpr bool kQuarters = kBf && AM == A_ACT && G == 1 && BM == 64;
   f32x16 tot[kQuarters ? TM : 1][kQuarters ? TN : 1];
@@ -454,7 +454,7 @@ static hipError_t launch_cfg(const GemmP& p, hipStream_t st) {
   constexpr bool kBf = !std::is_same<T, float>::value;
   if constexpr (kBf) {
     // (the 128-row register-staged tiles have no room for the running sum of a long contraction's four runs: such
-    //  products of activations go to the wide-tile kernels or stay on 64-row tiles)
+    //  products of activations go to the direct-to-LDS kernels or stay on 64-row tiles)
     const bool long_act = AM == A_ACT && p.K >= kQuarterK;
     if (long_act && p.tile_map && p.force_bm == 128) return hipErrorInvalidValue;  // (the caller builds 64-row maps for these)
     if (!long_act && gemm_row_tile(TSD_BF16, p.M, p.N, p.force_bm) == 128) return launch_tile<T, AM, EP, 128, 128, 64>(p, st);
@@ -486,6 +486,7 @@ hipError_t prepare_gemm(int dtype) {
   if (dtype != TSD_BF16) return hipSuccess;
   hipError_t e;
   if ((e = prepare_gemm_wide()) != hipSuccess) return e;
+  if ((e = prepare_gemm_direct64()) != hipSuccess) return e;
   if ((e = raise_cfg<bf16, A_TOK, EP_STORE>()) != hipSuccess) return e;
   if ((e = raise_cfg<bf16, A_NORM, EP_QKV>()) != hipSuccess) return e;
   if ((e = raise_cfg<bf16, A_ACT, EP_RESID>()) != hipSuccess) return e;
@@ -510,7 +511,7 @@ static hipError_t launch_t(int amode, int epi, const GemmP& p, hipStream_t st) {
 int gemm_variant(int dtype, int amode, int epi, const GemmP& p) {
   if (p.allow_skinny && skinny_applicable(dtype, amode, epi, p)) return 16;
   if (dtype != TSD_BF16) return 64;
-  if (const int bm = gemm_wide_bm(dtype, amode, epi, p)) return 2000 + bm;
+  if (const int tile = gemm_direct_tile(dtype, amode, epi, p)) return 2000 + tile;
   if (!(amode == A_ACT && p.K >= kQuarterK) && gemm_row_tile(TSD_BF16, p.M, p.N, p.force_bm) == 128) return 128;
   return (amode == A_ACT && gemm_split(p)) ? 464 : 64;
 }
@@ -518,7 +519,8 @@ int gemm_variant(int dtype, int amode, int epi, const GemmP& p) {
 hipError_t launch_gemm(int dtype, int amode, int epi, const GemmP& p, hipStream_t st) {
   if (p.M <= 0 || p.N <= 0 || p.K <= 0) return hipErrorInvalidValue;
   if (p.allow_skinny && skinny_applicable(dtype, amode, epi, p)) return launch_gemm_skinny(amode, epi, p, st);
-  if (const int bm = gemm_wide_bm(dtype, amode, epi, p)) return launch_gemm_wide(amode, epi, bm, p, st);
+  if (const DirectTile tile = gemm_direct_tile(dtype, amode, epi, p))
+    return tile == kTile64 ? launch_gemm_direct64(amode, epi, p, st) : launch_gemm_wide(amode, epi, tile, p, st);
   return dtype == TSD_BF16 ? launch_t<bf16>(amode, epi, p, st) : launch_t<float>(amode, epi, p, st);
 }
 

@@ -600,7 +600,7 @@ int run_pass(tsd_ctx* ctx, const Pass& ps, hipStream_t st) {
       const int E = md.c.n_experts, topk = md.c.top_k, slots = M * topk;
       int bm = gemm_row_tile(c.dtype, slots, F, 0);
       if (bm == 128 && F >= kQuarterK) {
-        // the experts' second product is a long contraction of activations: at 128-row tiles only the wide-tile
+        // the experts' second product is a long contraction of activations: at 128-row tiles only the direct-to-LDS
         // kernels take it (they keep the running sum of its four runs); where they do not apply, 64-row tiles
         GemmP probe;
         std::memset(&probe, 0, sizeof(probe));
@@ -610,7 +610,7 @@ int run_pass(tsd_ctx* ctx, const Pass& ps, hipStream_t st) {
         probe.tile_map = ctx->moe_tmap;
         probe.force_bm = 128;
         probe.no_wide = (c.flags & TSD_FLAG_NO_WIDE_GEMM) ? 1 : 0;
-        if (gemm_wide_bm(c.dtype, A_ACT, EP_STORE, probe) != 128) bm = 64;
+        if (gemm_direct_tile(c.dtype, A_ACT, EP_STORE, probe) != kTile128) bm = 64;
       }
       const int n_mtiles = (slots + bm - 1) / bm + E;
       HIP_TRY(ctx, timed_launch(ctx, TSD_K_ROUTE, 4.0 * M * D, st, [&] {
@@ -1846,7 +1846,7 @@ int tsd_set_resident_wait(tsd_ctx* ctx, int32_t milliseconds) {
 
 int tsd_bench_gemm(int dtype, int variant, int M, int N, int K, const void* A_dev, const void* Wt_dev, void* C_dev,
                    void* stream) {
-  const int no_wide = (variant & 8) ? 1 : 0;  // + 8: never the wide-tile kernels
+  const int no_wide = (variant & 8) ? 1 : 0;  // + 8: never the direct-to-LDS kernels
   variant &= ~8;
   if (variant < 0 || variant > 3) return fail(nullptr, TSD_E_INVALID_ARG, "variant must be 0, 1, 2 or 3 (+ 8)");
   if (variant == 3 && dtype != TSD_BF16) return fail(nullptr, TSD_E_INVALID_ARG, "variant 3 is bf16 only");

@@ -89,7 +89,7 @@ struct GemmP {
   int n_mtiles;          // entries of tile_map
   int force_bm;          // row-tile size the map was built for (0 = pick by problem size)
   int allow_skinny;      // 1: the handle runs its <= 32-row passes through the skinny kernel; 2: and this one, in tiles of 32 rows
-  int no_wide;           // never pick the direct-to-LDS wide-tile kernels (gemm_wide.hip)
+  int no_wide;           // never pick the direct-to-LDS kernels (gemm_direct64.hip, gemm_wide.hip)
   // EP_HEAD
   float* out;
   long out_stride_b;
@@ -132,12 +132,15 @@ constexpr int kQuarterK = 1024;
 bool skinny_applicable(int dtype, int amode, int epi, const GemmP& p);
 hipError_t launch_gemm_skinny(int amode, int epi, const GemmP& p, hipStream_t st);
 int gemm_row_tile(int dtype, int M, int N, int force_bm);
-// wide-tile kernels (gemm_wide.hip): row-tile size for this product (256 or 128), or 0 for the register-staged kernels
-int gemm_wide_bm(int dtype, int amode, int epi, const GemmP& p);
-hipError_t launch_gemm_wide(int amode, int epi, int bm, const GemmP& p, hipStream_t st);
+// direct-to-LDS kernels (gemm_direct64.hip, gemm_wide.hip): the tile for this product, or kTileNone for the register-staged kernels
+enum DirectTile { kTileNone = 0, kTile64 = 64, kTile128x64 = 127, kTile128 = 128, kTile128x256 = 129, kTile256x128 = 256, kTile256 = 257 };
+DirectTile gemm_direct_tile(int dtype, int amode, int epi, const GemmP& p);
+hipError_t launch_gemm_direct64(int amode, int epi, const GemmP& p, hipStream_t st);
+hipError_t prepare_gemm_direct64();
+hipError_t launch_gemm_wide(int amode, int epi, DirectTile tile, const GemmP& p, hipStream_t st);
 hipError_t prepare_gemm_wide();
 // which kernel launch_gemm picks for this product: 16 = skinny, 64 / 128 = tile size, 464 = 64 x 64 tiles with K split over four wavefront groups,
-// 2256 / 2128 = the wide-tile kernels with 256 / 128-row tiles
+// 2000 + DirectTile = the direct-to-LDS kernels
 int gemm_variant(int dtype, int amode, int epi, const GemmP& p);
 // s_max: upper bound on (position of the pass's last token) + 1 over all series; sizes the score buffer.
 hipError_t launch_attention(int dtype, const AttnP& p, int s_max, hipStream_t st);
