@@ -47,8 +47,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const GemmP p) {
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int li = lane & 15, lg = lane >> 4;
-  const int m0 = blockIdx.y * kRowsMax, M = min(p.M - m0, kRowsMax);  // this workgroup's rows (one tile of them but for context passes)
-  const int N = p.N, K = p.K;
+  const int M = p.M, N = p.N, K = p.K;
 
   // ---- the 16 columns of this workgroup ----
   int col_of[2];  // first global column of LDS columns 0..7 and 8..15
@@ -69,7 +68,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const GemmP p) {
   const char* arow[2];
 #pragma unroll
   for (int r = 0; r < 2; ++r) {
-    const int gm = m0 + min(r * 16 + li, M - 1);
+    const int gm = min(r * 16 + li, M - 1);
     if constexpr (AM == A_TOK) {
       int b = gm / p.nq;
       const int t = gm % p.nq;
@@ -88,13 +87,13 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const GemmP p) {
   // epilogue inputs that do not depend on the product
   if constexpr (EP == EP_QKV) {
     if (tid < kRowsMax) {
-      const int2 meta = p.row_meta[m0 + min(tid, M - 1)];
+      const int2 meta = p.row_meta[min(tid, M - 1)];
       row_pos[tid] = meta.x;
       row_page[tid] = meta.y;
     }
   }
   if constexpr (AM == A_TOK) {
-    if (p.row_meta && blockIdx.x == 0 && tid < M) p.row_meta[m0 + tid] = row_meta_of(p, m0 + tid);
+    if (p.row_meta && blockIdx.x == 0 && tid < M) p.row_meta[tid] = row_meta_of(p, tid);
   }
 
   // ---- this wavefront's share of K, in steps of 32 ----
@@ -188,8 +187,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const GemmP p) {
   if (tid >= kRowsMax * 4) return;
   const int row = tid >> 2, c4 = (tid & 3) * 4;
   // a launch replayed from a graph stores only the rows of series that are still active
-  if (row >= (p.n_dev ? min(M, *p.n_dev * p.nq - m0) : M)) return;
-  const int gm = m0 + row;
+  if (row >= (p.n_dev ? min(M, *p.n_dev * p.nq) : M)) return;
+  const int gm = row;
   const int gn = col_of[c4 >> 3] + (c4 & 7);
   if (gn >= N) return;
   float4 v = make_float4(0.f, 0.f, 0.f, 0.f), pv = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -268,7 +267,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const GemmP p) {
 
 template <int AM, int EP>
 hipError_t launch_nw(const GemmP& p, hipStream_t st) {
-  const dim3 grid((unsigned)(p.N / 16), (unsigned)((p.M + kRowsMax - 1) / kRowsMax));
+  const dim3 grid((unsigned)(p.N / 16));
   if (p.K >= 512)
     hipLaunchKernelGGL((gemm_skinny_kernel<AM, EP, 16>), grid, dim3(16 * 64), 0, st, p);
   else
@@ -278,10 +277,10 @@ hipError_t launch_nw(const GemmP& p, hipStream_t st) {
 
 }  // namespace
 
-// True when the skinny kernel can take this product (bf16, at most 32 rows or, where allow_skinny is 2, any number in tiles of 32, whole 16-column groups,
-// dense, and for the QKV product head_dim 64 so that rotary partners pair up as 8 + 8 columns).
+// True when the skinny kernel can take this product (bf16, at most 32 rows, whole 16-column groups, dense, and
+// for the QKV product head_dim 64 so that rotary partners pair up as 8 + 8 columns).
 bool skinny_applicable(int dtype, int amode, int epi, const GemmP& p) {
-  if (dtype != TSD_BF16 || (p.M > kRowsMax && p.allow_skinny < 2) || p.M < 1 || (p.N % 16) || (p.K % 8) || p.K < 8 || p.tile_map) return false;
+  if (dtype != TSD_BF16 || p.M > kRowsMax || p.M < 1 || (p.N % 16) || (p.K % 8) || p.K < 8 || p.tile_map) return false;
   if (epi == EP_QKV && p.hd != 64) return false;
   return true;
 }

@@ -88,7 +88,7 @@ struct GemmP {
   long w_stride;         // elements between consecutive experts' matrices in W
   int n_mtiles;          // entries of tile_map
   int force_bm;          // row-tile size the map was built for (0 = pick by problem size)
-  int allow_skinny;      // 1: the handle runs its <= 32-row passes through the skinny kernel; 2: and this one, in tiles of 32 rows
+  int allow_skinny;      // the handle runs its <= 32-row passes through the skinny kernel
   int no_wide;           // never pick the direct-to-LDS kernels (gemm_direct64.hip, gemm_wide.hip)
   // EP_HEAD
   float* out;
