@@ -520,7 +520,9 @@ hipError_t launch_gemm(int dtype, int amode, int epi, const GemmP& p, hipStream_
   if (p.M <= 0 || p.N <= 0 || p.K <= 0) return hipErrorInvalidValue;
   if (p.allow_skinny && skinny_applicable(dtype, amode, epi, p)) return launch_gemm_skinny(amode, epi, p, st);
   if (const DirectTile tile = gemm_direct_tile(dtype, amode, epi, p))
-    return tile == kTile64 ? launch_gemm_direct64(amode, epi, p, st) : launch_gemm_wide(amode, epi, tile, p, st);
+    return tile == kTile64     ? launch_gemm_direct64(amode, epi, p, st)
+           : tile == kTileRuns ? launch_gemm_runs(p, st)
+                               : launch_gemm_wide(amode, epi, tile, p, st);
   return dtype == TSD_BF16 ? launch_t<bf16>(amode, epi, p, st) : launch_t<float>(amode, epi, p, st);
 }
 

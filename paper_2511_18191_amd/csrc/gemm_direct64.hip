@@ -13,9 +13,8 @@
 //     without padding.  A load instruction fills 1 KB = 8 rows; lane l fetches the chunk that belongs at l.
 //   * A wavefront owns one contiguous run of every stage and addresses its loads through the instruction's immediate
 //     offset around one base, so M0 (the LDS base of such a load) is written once per k-tile.
-//   * The k loop is software-pipelined by k16 sub-steps: while the MFMAs of one sub-step run, the fragments of the next
-//     are on their way from LDS, also across k-tiles.  One barrier per k-tile, before its LAST sub-step: by then every
-//     wavefront holds all of the k-tile's fragments in registers, so the k-tile's own slot is refilled at once.
+//   * The fragments of a k-tile are requested from LDS a k-tile ahead.  One barrier per k-tile: by then every wavefront holds all of the
+//     k-tile's fragments in registers, so the k-tile's own slot is refilled at once.
 //   * The RMSNorm row sums come from the A fragments on their way to the matrix cores (A never sits in registers
 //     otherwise), in the summation order of the register-staged kernel (gemm.hip): per row eight partial sums, one per
 //     16-byte chunk position of a 64-wide k-run, each a chain of packed bf16 dot products, combined as
@@ -26,7 +25,8 @@
 
 namespace tsd {
 
-namespace {
+namespace d64 {
+
 constexpr int BM = 64, BN = 64, BK = 64, NS = 4;  // tile, stages
 constexpr int NW = 4, NT = NW * 64;               // wavefronts, 2 x 2 blocks of 32 x 32
 constexpr int ROWB = BK * 2, CPR = ROWB / 16;     // bytes and 16-byte chunks of a stage row
@@ -36,36 +36,22 @@ constexpr int NL = STAGE / 1024 / NW;             // load instructions of a wave
 constexpr int REGION = NL * 1024;                 // a wavefront's bytes of a stage
 constexpr int BIAS = REGION / 2;                  // M0 points here inside the region: immediates stay small
 constexpr int LDC = BN + 4;
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+constexpr int kSc1 = 16;  // cache policy of what workgroups hand each other: agent scope
 constexpr size_t SMEM = (size_t)NS * STAGE + BM * 12;  // stages, then row_scale / row_pos / row_page
 static_assert(64 * LDC * 4 <= NS * STAGE, "the epilogue's buffer reuses the stages");
-}  // namespace
 
-template <int AM, int EP>
-__global__ __launch_bounds__(NT, 2) void gemm_direct64_kernel(const GemmP p) {
+// Rows m0 .. min(m0 + 64, M) - 1, columns n0 .. n0 + 63, by a workgroup of NT lanes.  ldk: elements between rows of A and of W.
+// kRun (EP_STORE): p.K is one run of a longer contraction, its sums are for another workgroup of the launch.
+template <int AM, int EP, bool kRun>
+__device__ __forceinline__ void tile64(const GemmP& p, int ldk, int M, int m0, int n0, unsigned char* smem) {
   constexpr bool kNorm = (AM == A_NORM);
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   float* Cs = reinterpret_cast<float*>(smem);                            // [64][LDC], after the main loop
   float* row_scale = reinterpret_cast<float*>(smem + NS * STAGE);        // [BM]
   int* row_pos = reinterpret_cast<int*>(smem + NS * STAGE + BM * 4);     // [BM] EP_QKV
   int* row_page = row_pos + BM;                                          // [BM] EP_QKV
-
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wid >> 1, wn = wid & 1;
-  // rows of the product: fixed at launch, or capped by a device-side series count (workgroups past the cap leave)
-  const int M = p.n_dev ? min(p.M, *p.n_dev * p.nq) : p.M;
   const int N = p.N, K = p.K;
-  // tile order: every XCD walks one contiguous run of the tile list, the list ordered in groups of 8 tile columns
-  // walked row by row (see gemm.hip)
-  const int tiles_m = (M + BM - 1) / BM, tiles_n = N / BN;
-  const int n_tiles = tiles_m * tiles_n;
-  const int per_xcd = (n_tiles + 7) >> 3;
-  if ((int)(blockIdx.x >> 3) >= per_xcd) return;
-  const int lin = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (lin >= n_tiles) return;
-  constexpr int GW = 8;
-  const int gc = lin / (GW * tiles_m), rem = lin - gc * (GW * tiles_m);
-  const int gw = min(GW, tiles_n - gc * GW);
-  const int tm = rem / gw, tn = gc * GW + rem - tm * gw;
-  const int m0 = tm * BM, n0 = tn * BN;
 
   // Epilogue inputs that do not depend on the product are requested before the operands (loads return in order, so nothing
   // older than the stages' loads disturbs their counted waits) and land behind the main loop.
@@ -99,9 +85,9 @@ __global__ __launch_bounds__(NT, 2) void gemm_direct64_kernel(const GemmP p) {
     const int chunk = (lane % CPR) ^ swizzle(R);
     const bf16* row;
     if ((wid * NL + j) * RPL < BM) {  // (uniform per instruction: BM is a multiple of the rows it covers)
-      row = Ap + (long)min(m0 + R, M - 1) * K;  // rows past M are clamped to the last row: their products are never stored
+      row = Ap + (long)min(m0 + R, M - 1) * ldk;  // rows past M are clamped to the last row: their products are never stored
     } else {
-      row = Wp + (long)(n0 + R - BM) * K;
+      row = Wp + (long)(n0 + R - BM) * ldk;
     }
     gp[j] = row + chunk * 8 - (j * 1024 - BIAS) / 2;
   }
@@ -115,61 +101,54 @@ __global__ __launch_bounds__(NT, 2) void gemm_direct64_kernel(const GemmP p) {
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
   // Long contractions of activations are summed in four runs of ceil(nk / 4) k-tiles, each from zero, the runs added in
   // order (the order of the split workgroups of gemm.hip, which every kernel that can take such a product keeps to)
-  constexpr bool kQuarters = AM == A_ACT;
+  constexpr bool kQuarters = AM == A_ACT && !kRun;
   f32x16 tot;
   float ss[4] = {0.f, 0.f, 0.f, 0.f};  // row-sum chains of this lane: chunk positions hi, 2 + hi, 4 + hi, 6 + hi of a 64-wide k-run
   const int r31 = lane & 31, hi = lane >> 5;
   const int RA = wm * 32 + r31, RB = BM + wn * 32 + r31;
   const int offA = RA * ROWB, offB = RB * ROWB, swA = swizzle(RA), swB = swizzle(RB);
 
-  // The k loop by k16 sub-steps (two fragment reads, one MFMA each), two fragment sets F[0], F[1] in turn:
-  //   sub-step s of k-tile kt:   read F[(s + 1) & 1] <- the next sub-step;   MFMAs on F[s & 1]
-  // and before the read of the LAST sub-step's successor (sub-step 0 of k-tile kt + 1) the barrier of k-tile kt:
+  // The k loop: a k-tile is four k16 sub-steps, one MFMA each, a chain of dependent sums that leaves LDS latency nothing to hide behind.
+  // So the fragments of a whole k-tile are requested at once, a k-tile ahead, in two sets in turn (with one sub-step of lookahead
+  // 256x1536x512 took 5.96 us instead of 5.80, 256x2304x768 7.03 / 6.80, 256x3072x1024 8.13 / 7.75).  One barrier per k-tile:
   //   this wavefront's loads of k-tile kt + 1 are done (only those of later k-tiles may still be in flight) and its
-  //   fragments of k-tile kt all sit in registers (LDS counter at zero: they were requested a sub-step's MFMAs ago);
+  //   fragments of k-tile kt all sit in registers (LDS counter at zero);
   //   after the barrier that holds for everybody, so k-tile kt + 1 can be read and the slot of k-tile kt itself refilled
   //   with k-tile kt + NS.
   // (a bare s_barrier: __syncthreads() would also wait for every load in flight)
-  bf16x8 fa[2], fb[2];
-  auto read_frags = [&](int kt, int s) {
+  bf16x8 fa[2][4], fb[2][4];
+  auto read_frags = [&](auto set, int kt) {
+    constexpr int F = decltype(set)::value;
     const unsigned char* st = smem + (kt % NS) * STAGE;
-    fa[s & 1] = *reinterpret_cast<const bf16x8*>(st + offA + (((2 * s + hi) ^ swA) << 4));
-    fb[s & 1] = *reinterpret_cast<const bf16x8*>(st + offB + (((2 * s + hi) ^ swB) << 4));
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      fa[F][s] = *reinterpret_cast<const bf16x8*>(st + offA + (((2 * s + hi) ^ swA) << 4));
+      fb[F][s] = *reinterpret_cast<const bf16x8*>(st + offB + (((2 * s + hi) ^ swB) << 4));
+    }
   };
-  // `arrived`: an empty statement that uses a fragment set, placed BEFORE the next set's reads are issued.  The compiler
-  // waits for LDS data right before its first use and cannot tell the two sets' reads apart by count here, so without it
-  // the wait would land after the next set's reads were issued and cover those too (a full LDS round trip exposed per
-  // sub-step); with it the wait covers only reads issued a sub-step ago, which have long landed.
-  // One k-tile.  PEND: the loads this wavefront may leave in flight at the barrier (those of the k-tiles after kt + 1), or
-  // -1 for the last k-tile (no barrier, nothing left to read); REFILL: k-tile kt + NS exists.
-  auto tile = [&](int kt, auto pend, auto refill) {
-    constexpr int PEND = decltype(pend)::value;
+  // One k-tile.  SET: its fragments; PEND: the loads this wavefront may leave in flight at the barrier (those of the k-tiles after
+  // kt + 1), or -1 for the last k-tile (no barrier, nothing left to read); REFILL: k-tile kt + NS exists.
+  auto tile = [&](auto set, int kt, auto pend, auto refill) {
+    constexpr int F = decltype(set)::value, PEND = decltype(pend)::value;
     constexpr bool REFILL = decltype(refill)::value != 0;
-    const auto sub = [&](auto sc) {
-      constexpr int s = decltype(sc)::value;
-      asm volatile("" : "+v"(fa[s & 1]), "+v"(fb[s & 1]));
-      if constexpr (s < 3) {
-        read_frags(kt, s + 1);
-      } else if constexpr (PEND >= 0) {
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(PEND) : "memory");
-        if constexpr (REFILL) issue_stage(kt % NS, kt + NS);
-        read_frags(kt + 1, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
+    if constexpr (PEND >= 0) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(PEND) : "memory");
+#pragma unroll
+    for (int s = 0; s < 4; ++s) asm volatile("" : "+v"(fa[F][s]), "+v"(fb[F][s]));  // (waited for here, not behind the next set's requests)
+    if constexpr (PEND >= 0) read_frags(IC<1 - F>{}, kt + 1);
+    if constexpr (REFILL) issue_stage(kt % NS, kt + NS);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
       if constexpr (kNorm) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const bf16x2 pr = {fa[s & 1][2 * e], fa[s & 1][2 * e + 1]};
+          const bf16x2 pr = {fa[F][s][2 * e], fa[F][s][2 * e + 1]};
           ss[s] = __builtin_amdgcn_fdot2_f32_bf16(pr, pr, ss[s], false);
         }
       }
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s & 1], fb[s & 1], acc, 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    sub(IC<0>{});
-    sub(IC<1>{});
-    sub(IC<2>{});
-    sub(IC<3>{});
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[F][s], fb[F][s], acc, 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
   };
 
   // ---- main loop (K is a multiple of 64, at least NS of them) ------------------------------------------------------
@@ -177,8 +156,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_direct64_kernel(const GemmP p) {
 #pragma unroll
   for (int s = 0; s < NS; ++s) issue_stage(s, s);
   asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 1) * NL) : "memory");  // k-tile 0 has landed for everybody
-  read_frags(0, 0);
-  // steady state: k-tiles 0 .. nk - NS - 1 (each refills its slot); then the last NS k-tiles
+  // steady state: k-tiles 0 .. nk - NS - 1 (each refills its slot); then the last NS k-tiles, the first of them with set 0
   const int n_steady = nk - NS;
   const bool quarters = kQuarters && K >= kQuarterK;
   const int run = (nk + 3) / 4;
@@ -193,19 +171,29 @@ __global__ __launch_bounds__(NT, 2) void gemm_direct64_kernel(const GemmP p) {
     }
   };
   int kt = 0;
-  for (; kt < n_steady; ++kt) {
-    tile(kt, IC<(NS - 2) * NL>{}, IC<1>{});
-    fold(kt + 1);
+  auto steady = [&](auto set) {
+    tile(set, kt, IC<(NS - 2) * NL>{}, IC<1>{});
+    fold(++kt);
+  };
+  if (n_steady & 1) {
+    read_frags(IC<1>{}, 0);
+    steady(IC<1>{});
+  } else {
+    read_frags(IC<0>{}, 0);
+  }
+  while (kt < n_steady) {
+    steady(IC<0>{});
+    steady(IC<1>{});
   }
   // tail: k-tile nk - NS + t leaves NS - 2 - t stages in flight at its barrier; the last one has no barrier
   auto tail = [&](auto self, auto tc) {
     constexpr int t = decltype(tc)::value;
     if constexpr (t + 1 < NS) {
-      tile(kt + t, IC<(NS - 2 - t) * NL>{}, IC<0>{});
+      tile(IC<t & 1>{}, kt + t, IC<(NS - 2 - t) * NL>{}, IC<0>{});
       fold(kt + t + 1);
       self(self, IC<t + 1>{});
     } else {
-      tile(kt + t, IC<-1>{}, IC<0>{});
+      tile(IC<t & 1>{}, kt + t, IC<-1>{}, IC<0>{});
     }
   };
   tail(tail, IC<0>{});
@@ -235,14 +223,119 @@ __global__ __launch_bounds__(NT, 2) void gemm_direct64_kernel(const GemmP p) {
 #pragma unroll
   for (int r = 0; r < 16; ++r) Cs[(wm * 32 + (r >> 2) * 8 + hi * 4 + (r & 3)) * LDC + wn * 32 + r31] = acc[r];
   __syncthreads();
-  epilogue_pass<bf16, EP, kNorm, BN, NT, EP == EP_RESID>(p, read_c4, row_scale, row_pos, row_page, m0, n0, 0, M, N, tid, oldc);
+  if constexpr (kRun) {  // written through to memory
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(p.Cf, 0, 0x7fffffff, 0x00020000);
+#pragma unroll
+    for (int it = 0; it < 64 * (BN / 4) / NT; ++it) {
+      const int g = tid + it * NT, row = g / (BN / 4), col = g % (BN / 4) * 4;
+      if (m0 + row < M)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, read_c4(row, col)), rsrc, (int)(((long)(m0 + row) * N + n0 + col) * 4), 0, kSc1);
+    }
+  } else {
+    epilogue_pass<bf16, EP, kNorm, BN, NT, EP == EP_RESID>(p, read_c4, row_scale, row_pos, row_page, m0, n0, 0, M, N, tid, oldc);
+  }
+}
+
+// x += A W^T for rows m0 .. min(m0 + 64, M) - 1, columns n0 .. n0 + 63, one of the four runs of the contraction (K >= kQuarterK: see gemm.hip) per
+// workgroup: each stores its 64 x 64 sums to `parts` (part_elems apart), the last one to finish, by the tile's counter, adds the four in
+// order and leaves the counter at zero.  Nothing waits for another workgroup.  What the other three wrote has gone through to memory
+// before they counted, and nobody has read those lines in this launch, so the loads past L1 find it.
+// word: of LDS, behind the tile's.  Cb may not be NULL.
+__device__ __forceinline__ void resid_run64(const bf16* A, const bf16* W, int K, float* x, bf16* xb, int N, float* parts, long part_elems, int run,
+                                            unsigned* count, int M, int m0, int n0, unsigned char* smem, int* word) {
+  const int tid = threadIdx.x, nk = K >> 6, r = (nk + 3) >> 2;
+  GemmP g;
+  g.N = N;
+  g.K = min(r, nk - run * r) * 64;
+  g.A = A + run * r * 64;
+  g.W = W + run * r * 64;
+  g.Cf = parts + run * part_elems;
+  g.Cb = nullptr;
+  tile64<A_ACT, EP_STORE, true>(g, K, M, m0, n0, smem);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // every wavefront's sums are there
+  __syncthreads();
+  if (tid == 0) *word = (int)__hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (*word != 3) return;
+  if (tid == 0) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  constexpr int NI = BM * (BN / 4) / NT;
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(parts, 0, 0x7fffffff, 0x00020000);
+  float4 v[NI][4], old[NI];
+  auto at = [&](int i) { return (long)min(m0 + (tid >> 4) + 16 * i, M - 1) * N + n0 + (tid & 15) * 4; };
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+#pragma unroll
+    for (int w = 0; w < 4; ++w) v[i][w] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)((w * part_elems + at(i)) * 4), 0, kSc1));
+    old[i] = *reinterpret_cast<const float4*>(x + at(i));
+  }
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    float4 s = v[i][0];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) {
+      s.x += v[i][w].x;
+      s.y += v[i][w].y;
+      s.z += v[i][w].z;
+      s.w += v[i][w].w;
+    }
+    s.x = old[i].x + s.x;
+    s.y = old[i].y + s.y;
+    s.z = old[i].z + s.z;
+    s.w = old[i].w + s.w;
+    if (m0 + (tid >> 4) + 16 * i < M) {
+      *reinterpret_cast<float4*>(x + at(i)) = s;
+      store4<bf16>(xb + at(i), s);
+    }
+  }
+}
+
+}  // namespace d64
+
+template <int AM, int EP>
+__global__ __launch_bounds__(d64::NT, 2) void gemm_direct64_kernel(const GemmP p) {
+  using namespace d64;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  // rows of the product: fixed at launch, or capped by a device-side series count (workgroups past the cap leave)
+  const int M = p.n_dev ? min(p.M, *p.n_dev * p.nq) : p.M;
+  // tile order: every XCD walks one contiguous run of the tile list, the list ordered in groups of 8 tile columns
+  // walked row by row (see gemm.hip)
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = p.N / BN;
+  const int n_tiles = tiles_m * tiles_n;
+  const int per_xcd = (n_tiles + 7) >> 3;
+  if ((int)(blockIdx.x >> 3) >= per_xcd) return;
+  const int lin = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (lin >= n_tiles) return;
+  constexpr int GW = 8;
+  const int gc = lin / (GW * tiles_m), rem = lin - gc * (GW * tiles_m);
+  const int gw = min(GW, tiles_n - gc * GW);
+  const int tm = rem / gw, tn = gc * GW + rem - tm * gw;
+  const int m0 = tm * BM, n0 = tn * BN;
+  tile64<AM, EP, false>(p, p.K, M, m0, n0, smem);
+}
+
+// The long contractions of few rows, x += A W^T, a run of the four per workgroup (resid_run64).  With one workgroup per tile, whatever its
+// wavefronts do, the few busy compute units pull 0.5 to 0.8 MB of operands each at 75 GB/s (gemm.hip's split workgroups: 256x512x2048
+// 11.1 us); here four times as many share them.
+__global__ __launch_bounds__(d64::NT, 2) void gemm_runs_kernel(const GemmP p) {
+  using namespace d64;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const int M = p.n_dev ? min(p.M, *p.n_dev * p.nq) : p.M;
+  const int tiles_m = (M + BM - 1) / BM, n_tasks = tiles_m * (p.N / BN) * 4;
+  // every XCD takes one contiguous run of the tasks, the four runs of a tile next to each other, row tiles of one column next
+  const int per_xcd = ((n_tasks >> 2) + 7) / 8 * 4;
+  if ((int)(blockIdx.x >> 3) >= per_xcd) return;
+  const int lin = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (lin >= n_tasks) return;
+  const int tile = lin >> 2, tn = tile / tiles_m, tm = tile - tn * tiles_m;
+  resid_run64(reinterpret_cast<const bf16*>(p.A), reinterpret_cast<const bf16*>(p.W), p.K, p.Cf, reinterpret_cast<bf16*>(p.Cb), p.N, p.parts,
+              (long)kRunTiles * BM * BN, lin & 3, p.counts + tile, M, tm * BM, tn * BN, smem, reinterpret_cast<int*>(smem + SMEM));
 }
 
 // ---- host side -------------------------------------------------------------------------------------------------
 template <int AM, int EP>
 static hipError_t launch_t(const GemmP& p, hipStream_t st) {
-  const long tiles = (long)((p.M + BM - 1) / BM) * (p.N / BN);
-  hipLaunchKernelGGL((gemm_direct64_kernel<AM, EP>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(NT), SMEM, st, p);
+  const long tiles = (long)((p.M + d64::BM - 1) / d64::BM) * (p.N / d64::BN);
+  hipLaunchKernelGGL((gemm_direct64_kernel<AM, EP>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(d64::NT), d64::SMEM, st, p);
   return hipGetLastError();
 }
 
@@ -255,14 +348,21 @@ hipError_t launch_gemm_direct64(int amode, int epi, const GemmP& p, hipStream_t 
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_gemm_runs(const GemmP& p, hipStream_t st) {
+  const long tiles = (long)((p.M + d64::BM - 1) / d64::BM) * (p.N / d64::BN);
+  hipLaunchKernelGGL(gemm_runs_kernel, dim3((unsigned)((tiles + 7) / 8 * 32)), dim3(d64::NT), d64::SMEM + 64, st, p);
+  return hipGetLastError();
+}
+
 template <int AM, int EP>
 static hipError_t raise() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_direct64_kernel<AM, EP>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)SMEM);
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_direct64_kernel<AM, EP>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)d64::SMEM);
 }
 
 // More than 64 KB of dynamic LDS needs a one-time opt-in per kernel, outside any stream capture.
 hipError_t prepare_gemm_direct64() {
-  hipError_t e;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_runs_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)d64::SMEM + 64);
+  if (e != hipSuccess) return e;
   if ((e = raise<A_ACT, EP_STORE>()) != hipSuccess) return e;
   if ((e = raise<A_ACT, EP_RESID>()) != hipSuccess) return e;
   if ((e = raise<A_NORM, EP_STORE>()) != hipSuccess) return e;

@@ -168,8 +168,9 @@ __global__ __launch_bounds__(S::NT, 2) void gemm_wide_kernel(const GemmP p) {
     swB[j] = swizzle(R);
   }
 
-  // The k loop by k16 sub-steps, two fragment sets in turn, one bare barrier per k-tile before its last sub-step: see
-  // gemm_direct64.hip.
+  // The k loop is software-pipelined by k16 sub-steps: while the MFMAs of one run, the fragments of the next are on their way from LDS, also
+  // across k-tiles (two sets in turn).  One bare barrier per k-tile, before its LAST sub-step: this wavefront's loads of k-tile kt + 1 are
+  // done then and its fragments of k-tile kt all sit in registers, so behind it k-tile kt + 1 can be read and the slot of k-tile kt refilled.
   bf16x8 fa[2][TM], fb[2][TN];
   auto read_frags = [&](int kt, int s, bf16x8* af, bf16x8* bfr) {
     const unsigned char* st = smem + (kt % NS) * STAGE;
@@ -483,6 +484,11 @@ DirectTile gemm_direct_tile(int dtype, int amode, int epi, const GemmP& p) {
   // Long contractions with at most one 64 x 64 tile per compute unit are latency-bound chains of k-steps, where four groups of
   // wavefronts that stream a quarter of K each (gemm.hip) are faster: 1280x512x2048 10.2 split, 11.5 here; 512x1024x4096 17.2 / 18.9.
   const bool split = amode == A_ACT && p.K >= kQuarterK && t64 <= 256;
+  // From K = 2048 on a workgroup per run (gemm_runs_kernel) is faster still while all of them are resident together, two per compute unit,
+  // with room to spare (split workgroups / a workgroup per run: 256x512x2048 9.9 / 7.0, 768x512x2048, 96 tiles, 10.2 / 10.0; 256x768x3072
+  // 13.4 / 8.8, 558x768x3072, 108, 13.7 / 12.2, 768x768x3072, 144, 13.7 / 15.6; 320x1024x4096, 80, 16.7 / 11.5, 558, 144, 17.0 / 17.1);
+  // shorter ones gain nothing (256x1024x1024 6.95 / 7.04).
+  if (split && t64 <= kRunTiles && p.parts && epi == EP_RESID && p.Cb && p.K >= 2048 && split_runs(p.K) && p.N % 64 == 0) return kTileRuns;
   const DirectTile narrow = !split && p.K >= 256 && p.N % 64 == 0 ? kTile64 : kTileNone;
   if (amode == A_NORM && epi != EP_STORE) {
     const bool heads64 = epi != EP_QKV || p.hd == 64;  // (one rotary pair of blocks per 64 columns of a wavefront)

@@ -59,6 +59,8 @@ struct tsd_ctx {
   bool diag_on = false;
   float diag_min_sp = 0.f;
   int2* row_meta;  // position and cache page of every row of the pass in flight
+  float* parts;      // sums of the runs of long contractions (NULL: not split over workgroups), with a counter per tile
+  unsigned* counts;
   float* x;   // residual stream, fp32
   char* xb;   // its bf16 shadow (GEMM A operand in bf16 mode)
   char *qbuf, *abuf, *hbuf;
@@ -219,6 +221,7 @@ struct Layout {
   size_t rows;    // of the activation workspace
   bool meta;      // the rows' positions and cache pages, looked up once per pass instead of before every layer
   bool resident;  // flags and exchange buffer of the resident decode kernel
+  bool runs;      // sums of the runs of long contractions
 };
 
 // A round's tokens of the whole batch, or the longest context of one series.
@@ -229,7 +232,7 @@ Layout full_layout(const tsd_config& c) {
   long want = std::min((long)c.max_batch * c.max_tokens, kContextRows);
   for (const tsd_model_cfg* m : {&c.target, &c.draft})
     if (m->n_experts > 0) want = std::min(want, (long)kMaxSortSlots / m->top_k);
-  return Layout{std::max(least_rows(c), (size_t)std::max(want, 0L)), true, small_round_ok(c)};
+  return Layout{std::max(least_rows(c), (size_t)std::max(want, 0L)), true, small_round_ok(c), c.dtype == TSD_BF16 && !(c.flags & TSD_FLAG_NO_WIDE_GEMM)};
 }
 
 struct Carver {
@@ -337,6 +340,7 @@ size_t carve(const tsd_config& c, const Layout& lay, tsd_ctx* ctx) {
   size_t o_trace = cv.take(kTraceMax * 8);
   size_t o_cnt = cv.take(256), o_so = cv.take(256), o_alist = cv.take((size_t)B * 4), o_rlist = cv.take((size_t)B * 4);
   size_t o_alist2 = cv.take((size_t)B * 4);
+  const size_t o_parts = lay.runs ? cv.take((size_t)4 * kRunTiles * 64 * 64 * 4) : 0, o_counts = lay.runs ? cv.take(kRunTiles * 4) : 0;
   size_t o_flags = 0, o_exchange = 0;
   if (lay.resident) {
     o_flags = cv.take((size_t)kSmallRoundWorkgroups * kSmallRoundFlagWords * 4);
@@ -380,6 +384,8 @@ size_t carve(const tsd_config& c, const Layout& lay, tsd_ctx* ctx) {
     ctx->diag = (float*)at(o_diag);
     ctx->x = (float*)at(o_x);
     ctx->row_meta = lay.meta ? (int2*)at(o_meta) : nullptr;
+    ctx->parts = lay.runs ? (float*)at(o_parts) : nullptr;
+    ctx->counts = (unsigned*)at(o_counts);
     ctx->xb = at(o_xb);
     ctx->qbuf = at(o_q);
     ctx->abuf = at(o_a);
@@ -414,7 +420,7 @@ bool layout_for(const tsd_config& c, size_t bytes, Layout* lay) {
   if (carve(c, *lay, nullptr) <= bytes) return true;
   const size_t most = lay->rows, least = least_rows(c);
   const bool resident = lay->resident;
-  for (const Layout& l : {Layout{least, true, resident}, Layout{least, true, false}, Layout{least, false, false}}) {
+  for (const Layout& l : {Layout{least, true, resident, false}, Layout{least, true, false, false}, Layout{least, false, false, false}}) {
     *lay = l;
     if (carve(c, *lay, nullptr) > bytes) continue;
     for (size_t step = most - least; lay->rows < most && step > 0; step /= 2)  // (more rows never take less)
@@ -589,6 +595,8 @@ int run_pass(tsd_ctx* ctx, const Pass& ps, hipStream_t st) {
     o.W = md.layers[l].Wo;
     o.Cf = ctx->x;
     o.Cb = ctx->xb;
+    o.parts = ctx->parts;
+    o.counts = ctx->counts;
     HIP_TRY(ctx, timed_launch(ctx, TSD_K_RESID, 2.0 * M * D * D, st, [&] { return launch_gemm(c.dtype, A_ACT, EP_RESID, o, st); }, shape_of(ctx, ps.which, A_ACT, EP_RESID, o)));
     if (md.c.n_experts > 0) {
       // routed FFN: router -> stable sort of (token, choice) by expert -> grouped up/down GEMMs -> gated combine
@@ -682,6 +690,8 @@ int run_pass(tsd_ctx* ctx, const Pass& ps, hipStream_t st) {
     f2.W = md.layers[l].W2;
     f2.Cf = ctx->x;
     f2.Cb = ctx->xb;
+    f2.parts = ctx->parts;
+    f2.counts = ctx->counts;
     HIP_TRY(ctx, timed_launch(ctx, TSD_K_RESID, 2.0 * M * D * F, st, [&] { return launch_gemm(c.dtype, A_ACT, EP_RESID, f2, st); },
                               shape_of(ctx, ps.which, A_ACT, EP_RESID, f2)));
   }
@@ -1064,6 +1074,10 @@ int tsd_create(const tsd_config* cfg, void* arena_dev, size_t arena_bytes, tsd_c
       }
     }
     (void)hipGetLastError();
+  }
+  if (ctx->parts && hipMemset(ctx->counts, 0, kRunTiles * 4) != hipSuccess) {
+    (void)hipGetLastError();
+    ctx->parts = nullptr;
   }
   if (ctx->skinny && ctx->host_counts && lay.resident && !(cfg->flags & (TSD_FLAG_SAMPLE_PROPOSALS | TSD_FLAG_NAIVE_VERIFY))) {
     int dev = 0, cus = 0;

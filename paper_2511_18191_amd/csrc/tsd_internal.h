@@ -90,6 +90,9 @@ struct GemmP {
   int force_bm;          // row-tile size the map was built for (0 = pick by problem size)
   int allow_skinny;      // the handle runs its <= 32-row passes through the skinny kernel
   int no_wide;           // never pick the direct-to-LDS kernels (gemm_direct64.hip, gemm_wide.hip)
+  // sums of the runs of a long contraction, kRunTiles tiles of 64 x 64 each, and a counter per tile, zero between launches (NULL: none)
+  float* parts;
+  unsigned* counts;
   // EP_HEAD
   float* out;
   long out_stride_b;
@@ -128,15 +131,19 @@ hipError_t launch_gemm(int dtype, int amode, int epi, const GemmP& p, hipStream_
 hipError_t prepare_gemm(int dtype);
 // bf16 products of activations with K >= kQuarterK are summed in four runs of k-steps (see gemm.hip)
 constexpr int kQuarterK = 1024;
+// ... and, where every run is at least as long as a tile's ring, the runs can be workgroups of their own (gemm_direct64.hip)
+constexpr bool split_runs(int K) { return K >= kQuarterK && K % 64 == 0 && K / 64 - 3 * ((K / 64 + 3) / 4) >= 4; }
+constexpr int kRunTiles = 112;  // 64 x 64 tiles of such a product at most
 // skinny path (at most 32 rows): see gemm_skinny.hip
 bool skinny_applicable(int dtype, int amode, int epi, const GemmP& p);
 hipError_t launch_gemm_skinny(int amode, int epi, const GemmP& p, hipStream_t st);
 int gemm_row_tile(int dtype, int M, int N, int force_bm);
 // direct-to-LDS kernels (gemm_direct64.hip, gemm_wide.hip): the tile for this product, or kTileNone for the register-staged kernels
-enum DirectTile { kTileNone = 0, kTile64 = 64, kTile128x64 = 127, kTile128 = 128, kTile128x256 = 129, kTile256x128 = 256, kTile256 = 257 };
+enum DirectTile { kTileNone = 0, kTile64 = 64, kTile128x64 = 127, kTile128 = 128, kTile128x256 = 129, kTile256x128 = 256, kTile256 = 257, kTileRuns = 464 };
 DirectTile gemm_direct_tile(int dtype, int amode, int epi, const GemmP& p);
 hipError_t launch_gemm_direct64(int amode, int epi, const GemmP& p, hipStream_t st);
 hipError_t prepare_gemm_direct64();
+hipError_t launch_gemm_runs(const GemmP& p, hipStream_t st);
 hipError_t launch_gemm_wide(int amode, int epi, DirectTile tile, const GemmP& p, hipStream_t st);
 hipError_t prepare_gemm_wide();
 // which kernel launch_gemm picks for this product: 16 = skinny, 64 / 128 = tile size, 464 = 64 x 64 tiles with K split over four wavefront groups,

@@ -3,6 +3,9 @@ register-staged tiles, bit for bit, and against float64."""
 import pytest
 import torch
 
+import paper_2511_18191_amd as tsd
+from synth import ModelCfg
+
 pytestmark = pytest.mark.gpu
 
 
@@ -12,7 +15,6 @@ pytestmark = pytest.mark.gpu
     (1025, 1024, 1024, 2), (1030, 1024, 4096, 0), (4160, 448, 1088, 2),          # four runs of k-tiles (one tile more than the split takes)
 ])
 def test_small_direct_tiles_same_bits_as_register_staged_and_fp64(M, N, K, variant):
-    import paper_2511_18191_amd as tsd
     g = torch.Generator().manual_seed(M + N + K + variant)
     A = torch.randn(M, K, generator=g).to(torch.bfloat16).cuda()
     W = (torch.randn(N, K, generator=g) * 0.05).to(torch.bfloat16).cuda()
@@ -34,3 +36,38 @@ def test_small_direct_tiles_same_bits_as_register_staged_and_fp64(M, N, K, varia
     err = (outs[0].double() - ref).abs().max() / ref.abs().max()
     # fp32 accumulation: sqrt(K) roundings of 2^-24 with a factor for the growing partial sums; a bf16 result adds 2^-9
     assert err < (6e-3 if variant == 3 else 2e-6 * K ** 0.5), f"{err:.3e}"
+
+
+@pytest.mark.parametrize("D,F,B", [
+    (512, 2048, 33), (512, 2112, 65), (256, 2560, 250), (512, 2048, 896),   # runs of unequal length, a last row tile of one row, most tiles
+    (768, 3072, 100), (512, 2048, 897), (512, 2176, 64),                    # ... one tile too many, a last run of 4 k-tiles
+])
+def test_runs_of_a_contraction_in_workgroups_of_their_own(D, F, B):
+    """FFN down of few rows: four workgroups per tile, whichever finishes last adds their sums.  Bit for bit the handle without them, over
+    steps launched one by one and replayed (the tiles' counters have to be back at zero every time)."""
+    P, N, T, K = 16, 3, 6, 2
+    m = ModelCfg(2, D, D // 64, F)
+    g = torch.Generator().manual_seed(D + F + B)
+    n = P * D + 2 * (2 * D + 4 * D * D + 2 * D * F) + D + D * P
+    w = (torch.randn(n, generator=g) * 0.05).bfloat16().float().cuda()
+    series = torch.randn(B, N * P, generator=g).cuda()
+    res = []
+    for flags in (0, tsd.TSD_FLAG_NO_WIDE_GEMM):
+        sess = tsd.Session(tsd.make_config(m, ModelCfg(1, 64, 1, 96), P, K, B, N + T + K, "bf16", 1.0, seed=3, flags=flags))
+        sess.load_weights(tsd.TSD_TARGET, w)
+        sess.load_weights(tsd.TSD_DRAFT, torch.zeros(P * 64 + 2 * 64 + 4 * 64 * 64 + 2 * 64 * 96 + 64 + 64 * P))
+        sess.prefill(series, N, T * P)
+        sess.profile_begin(3)  # TSD_K_RESID
+        sess.target_step()
+        sess.profile_end()
+        tiles = {r["tile"] for r in sess.profile_launches() if r["K"] == F}
+        assert tiles == {464 if flags or (B + 63) // 64 * (D // 64) > 112 else 2464}, tiles
+        for _ in range(3):
+            sess.prefill(series, N, T * P)
+            for _ in range(T):
+                sess.target_step()
+            res.append(sess.get_forecast().cpu())
+        sess.close()
+    assert torch.isfinite(res[0]).all()
+    for other in res[1:]:
+        assert torch.equal(res[0], other)
