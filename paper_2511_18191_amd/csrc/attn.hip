@@ -3,10 +3,10 @@
 // The keys/values of the new tokens were written into the cache by the QKV epilogue, so query t
 // (absolute position base + t) simply attends to cache positions 0 .. base + t.
 //
-// One wavefront per (series, head).  The head's K and V rows (at most a few hundred tokens) are
-// staged into LDS once with 16-byte loads that are all in flight together (the pass is bound by
-// HBM latency/bandwidth, not arithmetic); queries are then processed in chunks of QC:
-// scores with one key per lane, fp32 softmax across lanes, P.V with lanes over the head dim.
+// The head's K and V rows (at most a few hundred tokens) are staged into LDS once with 16-byte loads that are all in
+// flight together; queries are then processed in chunks of QC: scores with one key per lane, fp32 softmax across lanes,
+// P.V with lanes over the head dim.  A workgroup is one wavefront per (series, head) that walks all queries (QJ = QC), or, where
+// those leave compute units idle, one chunk of (series, head) with a wavefront per query (QJ = 1): same sums, same bits.
 #include <type_traits>
 
 #include "tsd_internal.h"
@@ -45,8 +45,8 @@ __device__ __forceinline__ void unpack16<bf16>(const uint4& r, float* o) {
 // consecutive rows start in different banks.
 __host__ __device__ constexpr int row_bytes(int hd, int es) { return hd * es + 16; }
 
-template <typename T, int HD>
-__global__ __launch_bounds__(64) void attn_kernel(const AttnP p, int s_pad) {
+template <typename T, int HD, int QJ>
+__global__ __launch_bounds__(QC / QJ * 64) void attn_kernel(const AttnP p, int s_pad) {
   constexpr int ES = (int)sizeof(T);
   constexpr int RB = row_bytes(HD, ES);
   constexpr int CPR = HD * ES / 16;   // 16-byte chunks per row
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(64) void attn_kernel(const AttnP p, int s_pad) {
   float* qs = reinterpret_cast<float*>(Vs + (size_t)s_pad * RB);  // [QC][HD]
   float* ps = qs + QC * HD;                                  // [QC][s_pad]
 
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63, j0 = (threadIdx.x >> 6) * QJ;  // (j0: the wavefront's first query of a chunk)
   const int bl = blockIdx.x / p.Hh, h = blockIdx.x % p.Hh;
   const int b = p.act ? p.act[bl] : p.s0 + bl;  // (entries past the active count are stale but valid series)
   const int PT = p.PT, Hh = p.Hh, pts = p.pt_shift;
@@ -65,21 +65,22 @@ __global__ __launch_bounds__(64) void attn_kernel(const AttnP p, int s_pad) {
   T* out = reinterpret_cast<T*>(p.out);
 
   // Independent loads first, all in flight together: this lane's page-table entry, the series'
-  // base position, and the first chunk's queries.
+  // base position, and the first chunk's queries (a wavefront keeps to its own rows of qs and ps).
   const int my_page = p.page_table[(long)b * p.pt_stride + min(lane, p.pt_stride - 1)];
   const int base = (p.base_pos ? p.base_pos[b] : 0) + p.pos_off;
   if (p.n_dev && bl >= *p.n_dev) return;  // replayed launch: this slot is past the active list
-  constexpr int QR = QC * HD / 64;
+  constexpr int QR = (QJ * HD + 63) / 64;
+  const int first = QJ < QC ? blockIdx.y * QC : 0, last = QJ < QC ? min(p.nq, first + QC) : p.nq;
   float qreg[QR];
   {
-    const int n_first = min(QC, p.nq) * HD;
+    const int n_first = min(QC, last - first) * HD;
 #pragma unroll
     for (int r = 0; r < QR; ++r) {
-      const int i = min(lane + r * 64, n_first - 1);
-      qreg[r] = (float)q[((long)bl * p.nq + i / HD) * p.D + h * HD + i % HD];
+      const int i = min(j0 * HD + lane + r * 64, n_first - 1);
+      qreg[r] = (float)q[((long)bl * p.nq + first + i / HD) * p.D + h * HD + i % HD];
     }
   }
-  const int total_keys = base + p.nq;
+  const int total_keys = base + last;
 
   // ---- stage this head's K and V rows (page ids come from other lanes' registers) ----
   {
@@ -87,12 +88,13 @@ __global__ __launch_bounds__(64) void attn_kernel(const AttnP p, int s_pad) {
     const int total = total_keys * CPR;
     constexpr int U = 4;
     // uniform trip count: every lane stays active, so the page-id shuffles see all lanes
-    for (int base_c = 0; base_c < total; base_c += 64 * U) {
-      const int c0 = base_c + lane;
+    const int nt = blockDim.x;
+    for (int base_c = 0; base_c < total; base_c += nt * U) {
+      const int c0 = base_c + threadIdx.x;
       uint4 rk[U], rv[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int c = min(c0 + u * 64, total - 1);  // clamped: always a valid row, stored only if in range
+        const int c = min(c0 + u * nt, total - 1);  // clamped: always a valid row, stored only if in range
         const int s = c / CPR, kc = c % CPR;
         const int page = __shfl(my_page, s >> pts);
         const long rowk = ((((long)page * 2 + 0) * Hh + h) * PT + (s & (PT - 1))) * HD;
@@ -102,7 +104,7 @@ __global__ __launch_bounds__(64) void attn_kernel(const AttnP p, int s_pad) {
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int c = c0 + u * 64;
+        const int c = c0 + u * nt;
         if (c < total) {
           const int s = c / CPR, kc = c % CPR;
           *reinterpret_cast<uint4*>(Ks + (size_t)s * RB + kc * 16) = rk[u];
@@ -115,14 +117,15 @@ __global__ __launch_bounds__(64) void attn_kernel(const AttnP p, int s_pad) {
   constexpr int G = 64 / HD;  // key groups in the P.V stage
   const int d = lane % HD, sg = lane / HD;
 
-  for (int q0 = 0; q0 < p.nq; q0 += QC) {
-    const int nqc = min(QC, p.nq - q0);
+  for (int q0 = first; q0 < last; q0 += QC) {
+    const int nqc = min(QC, last - q0);
     __syncthreads();  // staging done / previous chunk's ps and qs no longer read
-    if (q0 == 0) {
+    if (q0 == first) {
 #pragma unroll
-      for (int r = 0; r < QR; ++r) qs[lane + r * 64] = qreg[r] * p.scale;
+      for (int r = 0; r < QR; ++r)
+        if (lane + r * 64 < QJ * HD) qs[j0 * HD + lane + r * 64] = qreg[r] * p.scale;
     } else {
-      for (int i = lane; i < nqc * HD; i += 64) {
+      for (int i = j0 * HD + lane; i < min(nqc, j0 + QJ) * HD; i += 64) {
         const int j = i / HD, e = i % HD;
         qs[j * HD + e] = (float)q[((long)bl * p.nq + q0 + j) * p.D + h * HD + e] * p.scale;
       }
@@ -131,19 +134,19 @@ __global__ __launch_bounds__(64) void attn_kernel(const AttnP p, int s_pad) {
     const int nkeys = base + q0 + nqc;  // the chunk's last query sees keys 0 .. nkeys-1
     // ---- scores: one key per lane ----
     for (int s = lane; s < nkeys; s += 64) {
-      float sc[QC];
+      float sc[QJ];
 #pragma unroll
-      for (int j = 0; j < QC; ++j) sc[j] = 0.f;
+      for (int j = 0; j < QJ; ++j) sc[j] = 0.f;
 #pragma unroll
       for (int v = 0; v < CPR; ++v) {
         float kf[EPC];
         unpack16<T>(*reinterpret_cast<const uint4*>(Ks + (size_t)s * RB + v * 16), kf);
 #pragma unroll
-        for (int j = 0; j < QC; ++j) {
-          if (j < nqc) {
+        for (int j = 0; j < QJ; ++j) {
+          if (j0 + j < nqc) {
 #pragma unroll
             for (int e4 = 0; e4 < EPC; e4 += 4) {
-              const float4 qq = *reinterpret_cast<const float4*>(qs + j * HD + v * EPC + e4);
+              const float4 qq = *reinterpret_cast<const float4*>(qs + (j0 + j) * HD + v * EPC + e4);
               sc[j] = fmaf(kf[e4 + 0], qq.x, sc[j]);
               sc[j] = fmaf(kf[e4 + 1], qq.y, sc[j]);
               sc[j] = fmaf(kf[e4 + 2], qq.z, sc[j]);
@@ -153,29 +156,29 @@ __global__ __launch_bounds__(64) void attn_kernel(const AttnP p, int s_pad) {
         }
       }
 #pragma unroll
-      for (int j = 0; j < QC; ++j)
-        if (j < nqc) ps[j * s_pad + s] = (s <= base + q0 + j) ? sc[j] : -INFINITY;
+      for (int j = 0; j < QJ; ++j)
+        if (j0 + j < nqc) ps[(j0 + j) * s_pad + s] = (s <= base + q0 + j0 + j) ? sc[j] : -INFINITY;
     }
     // keys nkeys .. round-up-to-4 are read (as zeros) by the vectorised P.V loop
     const int nk4 = (nkeys + 3) & ~3;
-    for (int i = lane; i < nqc * (nk4 - nkeys); i += 64) {
-      const int j = i / (nk4 - nkeys), s = nkeys + i % (nk4 - nkeys);
+    for (int i = lane; i < (min(nqc, j0 + QJ) - j0) * (nk4 - nkeys); i += 64) {
+      const int j = j0 + i / (nk4 - nkeys), s = nkeys + i % (nk4 - nkeys);
       ps[j * s_pad + s] = -INFINITY;
     }
     __syncthreads();
     // ---- softmax over keys, per query ----
-    float inv_sum[QC];
+    float inv_sum[QJ];
 #pragma unroll
-    for (int j = 0; j < QC; ++j) {
+    for (int j = 0; j < QJ; ++j) {
       inv_sum[j] = 0.f;
-      if (j < nqc) {
+      if (j0 + j < nqc) {
         float m = -INFINITY;
-        for (int s = lane; s < nk4; s += 64) m = fmaxf(m, ps[j * s_pad + s]);
+        for (int s = lane; s < nk4; s += 64) m = fmaxf(m, ps[(j0 + j) * s_pad + s]);
         m = wave_max(m);
         float sum = 0.f;
         for (int s = lane; s < nk4; s += 64) {
-          const float e = __expf(ps[j * s_pad + s] - m);
-          ps[j * s_pad + s] = e;
+          const float e = __expf(ps[(j0 + j) * s_pad + s] - m);
+          ps[(j0 + j) * s_pad + s] = e;
           sum += e;
         }
         inv_sum[j] = 1.f / wave_sum(sum);
@@ -183,18 +186,18 @@ __global__ __launch_bounds__(64) void attn_kernel(const AttnP p, int s_pad) {
     }
     __syncthreads();
     // ---- P.V: lanes over the head dim (G key groups when HD < 64), four keys per step ----
-    float acc[QC];
+    float acc[QJ];
 #pragma unroll
-    for (int j = 0; j < QC; ++j) acc[j] = 0.f;
+    for (int j = 0; j < QJ; ++j) acc[j] = 0.f;
     for (int s4 = sg * 4; s4 < nk4; s4 += 4 * G) {
       float vv[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u)
         vv[u] = (s4 + u < nkeys) ? (float)*reinterpret_cast<const T*>(Vs + (size_t)(s4 + u) * RB + d * ES) : 0.f;
 #pragma unroll
-      for (int j = 0; j < QC; ++j) {
-        if (j < nqc) {
-          const float4 pp = *reinterpret_cast<const float4*>(ps + j * s_pad + s4);
+      for (int j = 0; j < QJ; ++j) {
+        if (j0 + j < nqc) {
+          const float4 pp = *reinterpret_cast<const float4*>(ps + (j0 + j) * s_pad + s4);
           acc[j] = fmaf(pp.x, vv[0], acc[j]);
           acc[j] = fmaf(pp.y, vv[1], acc[j]);
           acc[j] = fmaf(pp.z, vv[2], acc[j]);
@@ -204,14 +207,14 @@ __global__ __launch_bounds__(64) void attn_kernel(const AttnP p, int s_pad) {
     }
     if constexpr (G > 1) {
 #pragma unroll
-      for (int j = 0; j < QC; ++j)
+      for (int j = 0; j < QJ; ++j)
 #pragma unroll
         for (int o = HD; o < 64; o <<= 1) acc[j] += __shfl_xor(acc[j], o);
     }
     if (sg == 0) {
 #pragma unroll
-      for (int j = 0; j < QC; ++j)
-        if (j < nqc) out[((long)bl * p.nq + q0 + j) * p.D + h * HD + d] = (T)(acc[j] * inv_sum[j]);
+      for (int j = 0; j < QJ; ++j)
+        if (j0 + j < nqc) out[((long)bl * p.nq + q0 + j0 + j) * p.D + h * HD + d] = (T)(acc[j] * inv_sum[j]);
     }
   }
 }
@@ -263,13 +266,22 @@ size_t attention_lds_bytes(int dtype, int hd, int s_max, int page_tokens) {
 
 template <typename T, int HD>
 static hipError_t launch_hd(const AttnP& p, hipStream_t st, int s_pad, size_t smem) {
-  hipLaunchKernelGGL((attn_kernel<T, HD>), dim3((unsigned)(p.B * p.Hh)), dim3(64), smem, st, p, s_pad);
+  const unsigned units = (unsigned)(p.B * p.Hh), chunks = (unsigned)(p.nq + QC - 1) / QC;
+  // (a wavefront per (series, head) / per query, us: 32 (series, heads) of head_dim 16, 5 queries, 9.0 / 5.6, 2048 10.6 / 9.4, 4096 13.4 /
+  // 16.0; contexts of 31 queries 32.6 / 4.4 at 32, 36.8 / 33.2 at 2048; head_dim 64, 5 queries, 14.9 / 5.4 at 16, 34.6 / 15.4 at 2048)
+  if (units <= 2048)
+    hipLaunchKernelGGL((attn_kernel<T, HD, 1>), dim3(units, chunks), dim3((unsigned)min(p.nq, QC) * 64), smem, st, p, s_pad);
+  else
+    hipLaunchKernelGGL((attn_kernel<T, HD, QC>), dim3(units), dim3(64), smem, st, p, s_pad);
   return hipGetLastError();
 }
 
 template <typename T, int HD>
 static hipError_t raise_lds() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_kernel<T, HD>),
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_kernel<T, HD, 1>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_kernel<T, HD, QC>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
 }
 

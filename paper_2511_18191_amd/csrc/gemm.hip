@@ -1,33 +1,32 @@
-// Fused GEMM family: C[M,N] = A[M,K] * Wt[N,K]^T with fp32 accumulation.
+// Fused bf16 GEMM family (fp32: gemm_f32.hip): C[M,N] = A[M,K] * Wt[N,K]^T with fp32 accumulation.
 //
 // One kernel template covers every dense contraction of the transformer pass (patch embedding,
 // QKV, attention output, FFN up/down, output head).  What varies is where the A rows come from
 // (AMode) and what happens to the product (Epi); the main loop is the same:
-//   global -> registers -> LDS (double buffered) -> MFMA 32x32x16 bf16 (or fp32 FMAs) -> LDS -> epilogue.
+//   global -> registers -> LDS (double buffered) -> MFMA 32x32x16 bf16 -> LDS -> epilogue.
 // RMSNorm is never materialised: with the gain folded into the weights at load time,
 //   RMSNorm(x) W = rsqrt(mean(x^2) + eps) * (x W'),
 // so the kernel accumulates the row's sum of squares while it streams the row through and
 // scales the product's row in the epilogue.
-#include <type_traits>
 
 #include "tsd_internal.h"
 #include "gemm_epilogue.h"
 
 namespace tsd {
 
-template <typename T, int AM, int EP, int BM, int BN, int BK, int G = 1>
+template <int AM, int EP, int BM, int BN, int BK, int G = 1>
 __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
+  using T = bf16;
   constexpr int NT = 256 * G;
-  constexpr bool kBf = !std::is_same<T, float>::value;
   constexpr bool kNorm = (AM == A_NORM || AM == A_NORM32);  // RMSNorm fused as a row scale
-  // fp32 A rows in bf16 mode (patches, and the residual feeding the output head) are split into
+  // fp32 A rows (patches, and the residual feeding the output head) are split into
   // hi + lo bf16 parts, each multiplied by the same B fragment: the small GEMMs at the two ends of
   // the model then carry ~16 mantissa bits of their input instead of 8.
-  constexpr bool kSplit = kBf && (AM == A_TOK || AM == A_NORM32);
+  constexpr bool kSplit = (AM == A_TOK || AM == A_NORM32);
   constexpr int NAS = kSplit ? 2 : 1;  // A tiles kept in LDS per buffer
-  constexpr int LDT = BK + (kBf ? 8 : 1);  // padded LDS row, in elements
+  constexpr int LDT = BK + 8;  // padded LDS row, in elements
   constexpr int LDC = BN + 4;
-  static_assert(G == 1 || (kBf && BM == 64 && !kNorm), "split workgroups: bf16, 64-row tiles, no fused norm");
+  static_assert(G == 1 || (BM == 64 && !kNorm), "split workgroups: 64-row tiles, no fused norm");
   constexpr int GROUP_ELEMS = 2 * (NAS * BM + BN) * LDT;  // one group's pair of tile buffers
   constexpr int AB_BYTES = G * GROUP_ELEMS * (int)sizeof(T);
   constexpr int C_BYTES = G * 64 * LDC * 4;
@@ -74,7 +73,7 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
   }
 
   // ---- A loader set-up ----------------------------------------------------------------------
-  constexpr bool kASrcF32 = (AM == A_TOK) || (AM == A_NORM32) || !kBf;   // source rows are fp32 (bf16 mode reads the bf16 shadow of the residual)
+  constexpr bool kASrcF32 = (AM == A_TOK) || (AM == A_NORM32);  // source rows are fp32 (the others: the bf16 shadow of the residual)
   constexpr int CHA = kASrcF32 ? 4 : 8;              // elements per 16-byte chunk
   constexpr int CPRA = BK / CHA;                     // chunks per tile row
   constexpr int NA = BM * CPRA / 256;
@@ -107,7 +106,7 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
     }
   }
   // ---- B loader set-up ----------------------------------------------------------------------
-  constexpr int CHB = kBf ? 8 : 4;
+  constexpr int CHB = 8;
   constexpr int CPRB = BK / CHB;
   constexpr int NB = BN * CPRB / 256;
   static_assert(NB >= 1, "tile too small for 256 threads");
@@ -153,13 +152,8 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
           const float4 hi = make_float4((float)(bf16)f.x, (float)(bf16)f.y, (float)(bf16)f.z, (float)(bf16)f.w);
           store4<bf16>(reinterpret_cast<bf16*>(dst), hi);
           store4<bf16>(reinterpret_cast<bf16*>(dst + BM * LDT), make_float4(f.x - hi.x, f.y - hi.y, f.z - hi.z, f.w - hi.w));
-        } else if constexpr (kBf) {
-          store4<bf16>(reinterpret_cast<bf16*>(dst), f);
         } else {
-          dst[0] = f.x;
-          dst[1] = f.y;
-          dst[2] = f.z;
-          dst[3] = f.w;
+          store4<bf16>(reinterpret_cast<bf16*>(dst), f);
         }
       } else {
         if constexpr (kNorm) {
@@ -180,45 +174,27 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
     for (int i = 0; i < NB; ++i) {
       T* dst = Bs + (buf * BN + b_r[i]) * LDT + b_kc[i] * CHB;
       if (kt * BK + b_kc[i] * CHB >= K) rb[i] = make_uint4(0, 0, 0, 0);
-      if constexpr (kBf) {
-        *reinterpret_cast<uint4*>(dst) = rb[i];
-      } else {
-        float4 f = *reinterpret_cast<float4*>(&rb[i]);
-        dst[0] = f.x;
-        dst[1] = f.y;
-        dst[2] = f.z;
-        dst[3] = f.w;
-      }
+      *reinterpret_cast<uint4*>(dst) = rb[i];
     }
   };
 
   // ---- accumulators -------------------------------------------------------------------------
   const int lane = tid & 63, wid = (tid >> 6) & 3;
   const int wm = wid >> 1, wn = wid & 1;
-  constexpr int WTM = BM / 2, WTN = BN / 2;            // wave tile (bf16 path)
-  constexpr int TM = kBf ? WTM / 32 : 1, TN = kBf ? WTN / 32 : 1;
+  constexpr int WTM = BM / 2, WTN = BN / 2;            // wave tile
+  constexpr int TM = WTM / 32, TN = WTN / 32;
   f32x16 acc[TM][TN];
-  float accf[4][4];
-  if constexpr (kBf) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  } else {
-    static_assert(kBf || (BM == 64 && BN == 64), "fp32 path uses 64x64 tiles");
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) accf[i][j] = 0.f;
-  }
-  const int ty = gt >> 4, tx = gt & 15;  // fp32 path: 4x4 micro-tile at (ty*4, tx*4)
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
   // Long contractions of activations (K >= kQuarterK) are summed in four runs of ceil(nk / 4) k-steps, each from
-  // zero, the runs added in order: the order the split workgroups (G = 4) produce by construction.  Every bf16
+  // zero, the runs added in order: the order the split workgroups (G = 4) produce by construction.  Every
   // kernel that can take such a product (this one, the split one, the direct-to-LDS ones) keeps to it, so which of them
   // the launcher picks, which follows the rows still active, changes no bit.
-  constexpr bool kQuarters = kBf && AM == A_ACT && G == 1 && BM == 64;
+  constexpr bool kQuarters = AM == A_ACT && G == 1 && BM == 64;
   f32x16 tot[kQuarters ? TM : 1][kQuarters ? TN : 1];
   const bool quarters = kQuarters && p.K >= kQuarterK;
   auto fold = [&](int done) {  // `done` k-steps are in acc: at a run's end move them into the running sum
@@ -241,40 +217,25 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
   auto compute = [&](int buf) {
     const T* at = As + buf * NAS * BM * LDT;
     const T* bt = Bs + buf * BN * LDT;
-    if constexpr (kBf) {
 #pragma unroll
-      for (int k16 = 0; k16 < BK / 16; ++k16) {
-        bf16x8 af[NAS][TM], bfr[TN];
-        const int ko = k16 * 16 + (lane >> 5) * 8;
+    for (int k16 = 0; k16 < BK / 16; ++k16) {
+      bf16x8 af[NAS][TM], bfr[TN];
+      const int ko = k16 * 16 + (lane >> 5) * 8;
 #pragma unroll
-        for (int h = 0; h < NAS; ++h)
+      for (int h = 0; h < NAS; ++h)
 #pragma unroll
-          for (int i = 0; i < TM; ++i)
-            af[h][i] = *reinterpret_cast<const bf16x8*>(at + (h * BM + wm * WTM + i * 32 + (lane & 31)) * LDT + ko);
+        for (int i = 0; i < TM; ++i)
+          af[h][i] = *reinterpret_cast<const bf16x8*>(at + (h * BM + wm * WTM + i * 32 + (lane & 31)) * LDT + ko);
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-          bfr[j] = *reinterpret_cast<const bf16x8*>(bt + (wn * WTN + j * 32 + (lane & 31)) * LDT + ko);
+      for (int j = 0; j < TN; ++j)
+        bfr[j] = *reinterpret_cast<const bf16x8*>(bt + (wn * WTN + j * 32 + (lane & 31)) * LDT + ko);
 #pragma unroll
-        for (int h = NAS - 1; h >= 0; --h)  // low part first, then the high part
+      for (int h = NAS - 1; h >= 0; --h)  // low part first, then the high part
 #pragma unroll
-          for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[h][i], bfr[j], acc[i][j], 0, 0, 0);
-      }
-    } else {
-#pragma unroll
-      for (int k = 0; k < BK; ++k) {
-        float a[4], b[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = at[(ty * 4 + i) * LDT + k];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) b[j] = bt[(tx * 4 + j) * LDT + k];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) accf[i][j] = fmaf(a[i], b[j], accf[i][j]);
-      }
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[h][i], bfr[j], acc[i][j], 0, 0, 0);
     }
   };
   const int nk = (K + BK - 1) / BK;
@@ -384,47 +345,39 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
   };
   for (int pass = 0; pass < BM / 64; ++pass) {
     __syncthreads();  // tile buffers (or the previous pass's Cs) are no longer read
-    if constexpr (kBf) {
-      // accumulator element r of a 32x32 block: row (r/4)*8 + (lane/32)*4 + r%4, column lane%32
-      if (BM == 64 || wm == pass) {
-        const int rbase = (BM == 64) ? wm * WTM : 0;
+    // accumulator element r of a 32x32 block: row (r/4)*8 + (lane/32)*4 + r%4, column lane%32
+    if (BM == 64 || wm == pass) {
+      const int rbase = (BM == 64) ? wm * WTM : 0;
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < TN; ++j)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              int row = rbase + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-              int col = wn * WTN + j * 32 + (lane & 31);
-              Cs[(grp * 64 + row) * LDC + col] = acc[i][j][r];
-            }
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) Cs[(ty * 4 + i) * LDC + tx * 4 + j] = accf[i][j];
+          for (int r = 0; r < 16; ++r) {
+            int row = rbase + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+            int col = wn * WTN + j * 32 + (lane & 31);
+            Cs[(grp * 64 + row) * LDC + col] = acc[i][j][r];
+          }
     }
     __syncthreads();
     epilogue_pass<T, EP, kNorm, BN, NT, kPrefetchC>(p, read_c4, row_scale, row_pos, row_page, m0, n0, pass, m_lim, N, tid, oldc);
   }
 }
 
-template <typename T, int AM, int BM, int BN, int BK, int G = 1>
+template <int AM, int BM, int BN, int BK, int G = 1>
 constexpr size_t gemm_smem_bytes() {
-  constexpr bool kBf = !std::is_same<T, float>::value;
-  constexpr int LDT = BK + (kBf ? 8 : 1);
-  constexpr int nas = (kBf && (AM == A_TOK || AM == A_NORM32)) ? 2 : 1;
-  constexpr size_t ab = (size_t)G * 2 * (nas * BM + BN) * LDT * sizeof(T), c = (size_t)G * 64 * (BN + 4) * 4;
+  constexpr int LDT = BK + 8;
+  constexpr int nas = (AM == A_TOK || AM == A_NORM32) ? 2 : 1;
+  constexpr size_t ab = (size_t)G * 2 * (nas * BM + BN) * LDT * sizeof(bf16), c = (size_t)G * 64 * (BN + 4) * 4;
   return (ab > c ? ab : c) + BM * 12;
 }
 
-template <typename T, int AM, int EP, int BM, int BN, int BK, int G = 1>
+template <int AM, int EP, int BM, int BN, int BK, int G = 1>
 static hipError_t launch_tile(const GemmP& p, hipStream_t st) {
-  constexpr size_t smem = gemm_smem_bytes<T, AM, BM, BN, BK, G>();
+  constexpr size_t smem = gemm_smem_bytes<AM, BM, BN, BK, G>();
   const long tiles = (long)(p.tile_map ? p.n_mtiles : (p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN);
   const unsigned grid = (unsigned)(((tiles + 7) / 8) * 8);  // padded so that every XCD gets a full run
-  hipLaunchKernelGGL((gemm_kernel<T, AM, EP, BM, BN, BK, G>), dim3(grid), dim3(256 * G), smem, st, p);
+  hipLaunchKernelGGL((gemm_kernel<AM, EP, BM, BN, BK, G>), dim3(grid), dim3(256 * G), smem, st, p);
   return hipGetLastError();
 }
 
@@ -449,36 +402,28 @@ static bool gemm_split(const GemmP& p) {
   return p.K >= kQuarterK && t64 <= 256;
 }
 
-template <typename T, int AM, int EP>
+template <int AM, int EP>
 static hipError_t launch_cfg(const GemmP& p, hipStream_t st) {
-  constexpr bool kBf = !std::is_same<T, float>::value;
-  if constexpr (kBf) {
-    // (the 128-row register-staged tiles have no room for the running sum of a long contraction's four runs: such
-    //  products of activations go to the direct-to-LDS kernels or stay on 64-row tiles)
-    const bool long_act = AM == A_ACT && p.K >= kQuarterK;
-    if (long_act && p.tile_map && p.force_bm == 128) return hipErrorInvalidValue;  // (the caller builds 64-row maps for these)
-    if (!long_act && gemm_row_tile(TSD_BF16, p.M, p.N, p.force_bm) == 128) return launch_tile<T, AM, EP, 128, 128, 64>(p, st);
-    if constexpr (AM == A_ACT) {
-      if (gemm_split(p)) return launch_tile<T, AM, EP, 64, 64, 64, 4>(p, st);
-    }
-    return launch_tile<T, AM, EP, 64, 64, 64>(p, st);
-  } else {
-    return launch_tile<T, AM, EP, 64, 64, 16>(p, st);
+  // (the 128-row register-staged tiles have no room for the running sum of a long contraction's four runs: such
+  //  products of activations go to the direct-to-LDS kernels or stay on 64-row tiles)
+  const bool long_act = AM == A_ACT && p.K >= kQuarterK;
+  if (long_act && p.tile_map && p.force_bm == 128) return hipErrorInvalidValue;  // (the caller builds 64-row maps for these)
+  if (!long_act && gemm_row_tile(TSD_BF16, p.M, p.N, p.force_bm) == 128) return launch_tile<AM, EP, 128, 128, 64>(p, st);
+  if constexpr (AM == A_ACT) {
+    if (gemm_split(p)) return launch_tile<AM, EP, 64, 64, 64, 4>(p, st);
   }
+  return launch_tile<AM, EP, 64, 64, 64>(p, st);
 }
 
-template <typename T, int AM, int EP>
+template <int AM, int EP>
 static hipError_t raise_cfg() {
-  if constexpr (!std::is_same<T, float>::value) {
-    if constexpr (AM == A_ACT) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<T, AM, EP, 64, 64, 64, 4>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_smem_bytes<T, AM, 64, 64, 64, 4>());
-      if (e != hipSuccess) return e;
-    }
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<T, AM, EP, 128, 128, 64>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_smem_bytes<T, AM, 128, 128, 64>());
+  if constexpr (AM == A_ACT) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<AM, EP, 64, 64, 64, 4>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_smem_bytes<AM, 64, 64, 64, 4>());
+    if (e != hipSuccess) return e;
   }
-  return hipSuccess;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<AM, EP, 128, 128, 64>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_smem_bytes<AM, 128, 128, 64>());
 }
 
 // The 128x128x64 tiles use more than 64 KB of dynamic LDS: opt in once, outside any stream capture.
@@ -487,24 +432,23 @@ hipError_t prepare_gemm(int dtype) {
   hipError_t e;
   if ((e = prepare_gemm_wide()) != hipSuccess) return e;
   if ((e = prepare_gemm_direct64()) != hipSuccess) return e;
-  if ((e = raise_cfg<bf16, A_TOK, EP_STORE>()) != hipSuccess) return e;
-  if ((e = raise_cfg<bf16, A_NORM, EP_QKV>()) != hipSuccess) return e;
-  if ((e = raise_cfg<bf16, A_ACT, EP_RESID>()) != hipSuccess) return e;
-  if ((e = raise_cfg<bf16, A_NORM, EP_GELU>()) != hipSuccess) return e;
-  if ((e = raise_cfg<bf16, A_NORM32, EP_HEAD>()) != hipSuccess) return e;
-  if ((e = raise_cfg<bf16, A_ACT, EP_STORE>()) != hipSuccess) return e;
-  return raise_cfg<bf16, A_NORM, EP_STORE>();
+  if ((e = raise_cfg<A_TOK, EP_STORE>()) != hipSuccess) return e;
+  if ((e = raise_cfg<A_NORM, EP_QKV>()) != hipSuccess) return e;
+  if ((e = raise_cfg<A_ACT, EP_RESID>()) != hipSuccess) return e;
+  if ((e = raise_cfg<A_NORM, EP_GELU>()) != hipSuccess) return e;
+  if ((e = raise_cfg<A_NORM32, EP_HEAD>()) != hipSuccess) return e;
+  if ((e = raise_cfg<A_ACT, EP_STORE>()) != hipSuccess) return e;
+  return raise_cfg<A_NORM, EP_STORE>();
 }
 
-template <typename T>
 static hipError_t launch_t(int amode, int epi, const GemmP& p, hipStream_t st) {
-  if (amode == A_TOK && epi == EP_STORE) return launch_cfg<T, A_TOK, EP_STORE>(p, st);
-  if (amode == A_NORM && epi == EP_QKV) return launch_cfg<T, A_NORM, EP_QKV>(p, st);
-  if (amode == A_ACT && epi == EP_RESID) return launch_cfg<T, A_ACT, EP_RESID>(p, st);
-  if (amode == A_NORM && epi == EP_GELU) return launch_cfg<T, A_NORM, EP_GELU>(p, st);
-  if (amode == A_NORM32 && epi == EP_HEAD) return launch_cfg<T, A_NORM32, EP_HEAD>(p, st);
-  if (amode == A_NORM && epi == EP_STORE) return launch_cfg<T, A_NORM, EP_STORE>(p, st);
-  if (amode == A_ACT && epi == EP_STORE) return launch_cfg<T, A_ACT, EP_STORE>(p, st);
+  if (amode == A_TOK && epi == EP_STORE) return launch_cfg<A_TOK, EP_STORE>(p, st);
+  if (amode == A_NORM && epi == EP_QKV) return launch_cfg<A_NORM, EP_QKV>(p, st);
+  if (amode == A_ACT && epi == EP_RESID) return launch_cfg<A_ACT, EP_RESID>(p, st);
+  if (amode == A_NORM && epi == EP_GELU) return launch_cfg<A_NORM, EP_GELU>(p, st);
+  if (amode == A_NORM32 && epi == EP_HEAD) return launch_cfg<A_NORM32, EP_HEAD>(p, st);
+  if (amode == A_NORM && epi == EP_STORE) return launch_cfg<A_NORM, EP_STORE>(p, st);
+  if (amode == A_ACT && epi == EP_STORE) return launch_cfg<A_ACT, EP_STORE>(p, st);
   return hipErrorInvalidValue;
 }
 
@@ -523,7 +467,7 @@ hipError_t launch_gemm(int dtype, int amode, int epi, const GemmP& p, hipStream_
     return tile == kTile64     ? launch_gemm_direct64(amode, epi, p, st)
            : tile == kTileRuns ? launch_gemm_runs(p, st)
                                : launch_gemm_wide(amode, epi, tile, p, st);
-  return dtype == TSD_BF16 ? launch_t<bf16>(amode, epi, p, st) : launch_t<float>(amode, epi, p, st);
+  return dtype == TSD_BF16 ? launch_t(amode, epi, p, st) : launch_gemm_f32(amode, epi, p, st);
 }
 
 }  // namespace tsd

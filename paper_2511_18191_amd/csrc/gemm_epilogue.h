@@ -1,4 +1,4 @@
-// Epilogues of the fused GEMM family, shared by the tiled kernels: one pass over 64 rows of the product
+// Epilogues of the fused GEMM family, shared by the tiled kernels: one pass over ROWS rows of the product
 // that sit in LDS (or wherever `read_c4` finds them).
 #pragma once
 #include <type_traits>
@@ -25,9 +25,9 @@ __device__ __forceinline__ void store4<bf16>(bf16* dst, float4 v) {
 
 // T: compute dtype; kNorm: scale row r by row_scale[r] (the fused RMSNorm); BN: tile width; NT: lanes taking part;
 // kOld: the old residual values of this lane's items were fetched ahead into oldc[].
-// read_c4(row, col): four consecutive elements of row `row` (0..63 of the pass) of the product tile.
-// row_scale / row_pos / row_page are indexed by the row inside the tile (pass * 64 + row).
-template <typename T, int EP, bool kNorm, int BN, int NT, bool kOld, typename ReadC>
+// read_c4(row, col): four consecutive elements of row `row` (0..ROWS - 1 of the pass) of the product tile.
+// row_scale / row_pos / row_page are indexed by the row inside the tile (pass * ROWS + row).
+template <typename T, int EP, bool kNorm, int BN, int NT, bool kOld, int ROWS = 64, typename ReadC>
 __device__ __forceinline__ void epilogue_pass(const GemmP& p, ReadC read_c4, const float* row_scale, const int* row_pos,
                                               const int* row_page, int m0, int n0, int pass, int m_lim, int N, int tid,
                                               const float4* oldc) {
@@ -40,7 +40,7 @@ __device__ __forceinline__ void epilogue_pass(const GemmP& p, ReadC read_c4, con
     // each group's global loads wait for the previous group's stores to issue and pay a full round trip.
     // (Not in the register-staged 128 x 128 kernel: there the extra live registers cost occupancy and 9 % of a
     //  verification pass at 7168 rows.)
-    constexpr int ITS = 64 * GPR / NT, BATCH = ITS < 4 ? ITS : 4;
+    constexpr int ITS = ROWS * GPR / NT, BATCH = ITS < 4 ? ITS : 4;
     const int D = p.D, hd = p.hd, half = hd >> 1;
 #pragma unroll
     for (int it0 = 0; it0 < ITS; it0 += BATCH) {
@@ -51,20 +51,20 @@ __device__ __forceinline__ void epilogue_pass(const GemmP& p, ReadC read_c4, con
       for (int j = 0; j < BATCH; ++j) {
         const int g = tid + (it0 + j) * NT;
         const int row = g / GPR, col = (g % GPR) * 4;
-        gmv[j] = m0 + pass * 64 + row;
+        gmv[j] = m0 + pass * ROWS + row;
         gnv[j] = n0 + col;
         ok[j] = gmv[j] < m_lim && gnv[j] < N;
         const int c = gnv[j] % D, d = c % hd;
         const bool lo = d < half;
         v[j] = read_c4(row, col);
         pv[j] = read_c4(row, lo ? col + half : col - half);
-        pos[j] = ok[j] ? row_pos[pass * 64 + row] : 0;
-        page[j] = ok[j] ? row_page[pass * 64 + row] : 0;
+        pos[j] = ok[j] ? row_pos[pass * ROWS + row] : 0;
+        page[j] = ok[j] ? row_page[pass * ROWS + row] : 0;
         const int f = lo ? d : d - half;
         cs[j] = *reinterpret_cast<const float4*>(p.rope_cos + (long)pos[j] * half + f);
         sn[j] = *reinterpret_cast<const float4*>(p.rope_sin + (long)pos[j] * half + f);
         if constexpr (kNorm) {
-          const float rs = row_scale[pass * 64 + row];
+          const float rs = row_scale[pass * ROWS + row];
           v[j].x *= rs;
           v[j].y *= rs;
           v[j].z *= rs;
@@ -98,17 +98,17 @@ __device__ __forceinline__ void epilogue_pass(const GemmP& p, ReadC read_c4, con
     }
     return;
   }
-  if constexpr (EP == EP_GELU && kBf && BN % 8 == 0 && (64 * (BN / 8)) % NT == 0) {
+  if constexpr (EP == EP_GELU && kBf && BN % 8 == 0 && (ROWS * (BN / 8)) % NT == 0) {
     // eight columns per lane: one 16-byte store instead of two 8-byte ones (N is a multiple of 8 here: d_ff is)
     constexpr int G8 = BN / 8;
 #pragma unroll
-    for (int it = 0; it < 64 * G8 / NT; ++it) {
+    for (int it = 0; it < ROWS * G8 / NT; ++it) {
       const int g = tid + it * NT;
       const int row = g / G8, col = (g % G8) * 8;
-      const int gm = m0 + pass * 64 + row, gn = n0 + col;
+      const int gm = m0 + pass * ROWS + row, gn = n0 + col;
       if (gm >= m_lim || gn >= N) continue;
       const float4 v0 = read_c4(row, col), v1 = read_c4(row, col + 4);
-      const float rs = kNorm ? row_scale[pass * 64 + row] : 1.f;
+      const float rs = kNorm ? row_scale[pass * ROWS + row] : 1.f;
       bf16x8 o;
       o[0] = (bf16)gelu_tanh(v0.x * rs);
       o[1] = (bf16)gelu_tanh(v0.y * rs);
@@ -123,15 +123,15 @@ __device__ __forceinline__ void epilogue_pass(const GemmP& p, ReadC read_c4, con
     return;
   }
 #pragma unroll
-  for (int it = 0; it < 64 * GPR / NT; ++it) {
+  for (int it = 0; it < ROWS * GPR / NT; ++it) {
     const int g = tid + it * NT;
     const int row = g / GPR, col = (g % GPR) * 4;
-    const int gm = m0 + pass * 64 + row, gn = n0 + col;
+    const int gm = m0 + pass * ROWS + row, gn = n0 + col;
     if (gm >= m_lim || gn >= N) continue;
     float4 v = read_c4(row, col);
     float rs = 1.f;
     if constexpr (kNorm) {
-      rs = row_scale[pass * 64 + row];
+      rs = row_scale[pass * ROWS + row];
       v.x *= rs;
       v.y *= rs;
       v.z *= rs;
@@ -164,7 +164,7 @@ __device__ __forceinline__ void epilogue_pass(const GemmP& p, ReadC read_c4, con
       const int D = p.D, hd = p.hd, half = hd >> 1;
       const int which = gn / D, c = gn - which * D;
       const int h = c / hd, d = c - h * hd;
-      const int pos = row_pos[pass * 64 + row];
+      const int pos = row_pos[pass * ROWS + row];
       if (which < 2) {
         const bool lo = d < half;
         const int pcol = lo ? col + half : col - half;
@@ -181,7 +181,7 @@ __device__ __forceinline__ void epilogue_pass(const GemmP& p, ReadC read_c4, con
       if (which == 0) {
         store4<T>(reinterpret_cast<T*>(p.q_out) + (long)gm * D + c, v);
       } else {
-        const int page = row_page[pass * 64 + row];
+        const int page = row_page[pass * ROWS + row];
         const int tok = pos & (p.PT - 1);
         const long off = ((((long)page * 2 + (which - 1)) * p.Hh + h) * p.PT + tok) * hd + d;
         store4<T>(reinterpret_cast<T*>(p.kv_pool) + off, v);

@@ -287,7 +287,7 @@ __global__ __launch_bounds__(S::NT, 2) void gemm_wide_kernel(const GemmP p) {
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-acc[i][j] = tot[i][j] + acc[i][j];
+          acc[i][j] = tot[i][j] + acc[i][j];
     }
   }
 

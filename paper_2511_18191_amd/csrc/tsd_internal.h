@@ -141,6 +141,7 @@ int gemm_row_tile(int dtype, int M, int N, int force_bm);
 // direct-to-LDS kernels (gemm_direct64.hip, gemm_wide.hip): the tile for this product, or kTileNone for the register-staged kernels
 enum DirectTile { kTileNone = 0, kTile64 = 64, kTile128x64 = 127, kTile128 = 128, kTile128x256 = 129, kTile256x128 = 256, kTile256 = 257, kTileRuns = 464 };
 DirectTile gemm_direct_tile(int dtype, int amode, int epi, const GemmP& p);
+hipError_t launch_gemm_f32(int amode, int epi, const GemmP& p, hipStream_t st);  // (gemm_f32.hip: every fp32 product)
 hipError_t launch_gemm_direct64(int amode, int epi, const GemmP& p, hipStream_t st);
 hipError_t prepare_gemm_direct64();
 hipError_t launch_gemm_runs(const GemmP& p, hipStream_t st);
