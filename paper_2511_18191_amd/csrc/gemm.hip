@@ -49,7 +49,7 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
   // w lands on XCD w % 8.  Give every XCD one contiguous run of the tile list, and order the
   // list in groups of 8 tile columns walked row by row: the ~32 tiles an XCD runs at a time then
   // form a 4 x 8 rectangle that shares 4 row panels and 8 column panels through that L2.
-  const int tiles_m = p.tile_map ? p.n_mtiles : (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  const int tiles_m = p.tile_map ? reinterpret_cast<const int4*>(p.tile_map)[p.n_mtiles].x : (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   const int n_tiles = tiles_m * tiles_n;
   const int per_xcd = (n_tiles + 7) >> 3;
   // (a replayed launch may be larger than the tile list: workgroups past an XCD's run must not
@@ -66,7 +66,6 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
   const T* Wbase = reinterpret_cast<const T*>(p.W);
   if (p.tile_map) {  // routed FFN: this row tile belongs to one expert's run of slots
     const int4 tmap = reinterpret_cast<const int4*>(p.tile_map)[tm];
-    if (tmap.x < 0) return;
     m0 = tmap.y;
     m_lim = tmap.z;
     Wbase += (long)tmap.x * p.w_stride;

@@ -45,7 +45,7 @@ __global__ __launch_bounds__(f32::NT) void gemm_f32_kernel(const GemmP p) {
   const int N = p.N, K = p.K;
   // tile order: every XCD walks one contiguous run of the tile list, the list ordered in groups of 8 tile columns
   // walked row by row (see gemm.hip)
-  const int tiles_m = p.tile_map ? p.n_mtiles : (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  const int tiles_m = p.tile_map ? reinterpret_cast<const int4*>(p.tile_map)[p.n_mtiles].x : (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   const int n_tiles = tiles_m * tiles_n;
   const int per_xcd = (n_tiles + 7) >> 3;
   if ((int)(blockIdx.x >> 3) >= per_xcd) return;
@@ -60,7 +60,6 @@ __global__ __launch_bounds__(f32::NT) void gemm_f32_kernel(const GemmP p) {
   const float* W = reinterpret_cast<const float*>(p.W);
   if (p.tile_map) {  // routed FFN: this row tile belongs to one expert's run of slots
     const int4 tmap = reinterpret_cast<const int4*>(p.tile_map)[tm];
-    if (tmap.x < 0) return;
     m0 = tmap.y;
     m_lim = tmap.z;
     W += (long)tmap.x * p.w_stride;

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(S::NT, 2) void gemm_wide_kernel(const GemmP p) {
   const int N = p.N, K = p.K;
   // tile order: every XCD walks one contiguous run of the tile list, the list ordered in groups of 8 tile columns
   // walked row by row (see gemm.hip)
-  const int tiles_m = p.tile_map ? p.n_mtiles : (M + BM - 1) / BM, tiles_n = N / BN;
+  const int tiles_m = p.tile_map ? reinterpret_cast<const int4*>(p.tile_map)[p.n_mtiles].x : (M + BM - 1) / BM, tiles_n = N / BN;
   const int n_tiles = tiles_m * tiles_n;
   const int per_xcd = (n_tiles + 7) >> 3;
   if ((int)(blockIdx.x >> 3) >= per_xcd) return;
@@ -102,7 +102,6 @@ __global__ __launch_bounds__(S::NT, 2) void gemm_wide_kernel(const GemmP p) {
   const bf16* Wp = reinterpret_cast<const bf16*>(p.W);
   if (p.tile_map) {  // routed FFN: this row tile belongs to one expert's run of slots
     const int4 tmap = reinterpret_cast<const int4*>(p.tile_map)[tm];
-    if (tmap.x < 0) return;
     m0 = tmap.y;
     m_lim = tmap.z;
     Wp += (long)tmap.x * p.w_stride;
@@ -475,9 +474,11 @@ DirectTile gemm_direct_tile(int dtype, int amode, int epi, const GemmP& p) {
   const bool combo = (amode == A_ACT && (epi == EP_STORE || epi == EP_RESID)) ||
                      (amode == A_NORM && (epi == EP_STORE || epi == EP_GELU || epi == EP_QKV));
   if (!combo || (p.K % 64) || p.K < 192) return kTileNone;
-  // grouped products of the routed FFN: their tile map was built for force_bm-row tiles, and the 128-row map exists
-  // only where the product already has 1.5 tiles per compute unit
-  if (p.tile_map) return p.force_bm == 128 && p.N % 128 == 0 ? kTile128 : kTileNone;
+  // grouped products of the routed FFN: their tile map was built for force_bm-row tiles (routed_row_tile)
+  if (p.tile_map) {
+    if (p.force_bm == 256) return amode == A_NORM ? kTile256 : kTile256x128;
+    return p.force_bm == 128 && p.N % 128 == 0 ? kTile128 : kTileNone;
+  }
   if (p.src_row || p.force_bm) return kTileNone;
   auto tiles = [&](int bm, int bn) { return (long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
   const long t64 = tiles(64, 64), t128 = tiles(128, 128);
@@ -518,6 +519,25 @@ DirectTile gemm_direct_tile(int dtype, int amode, int epi, const GemmP& p) {
   // (12000x384x384, 282, 12.0 at 128 x 128 and 11.6 at 64 x 64)
   if (!split && (t128 >= 384 || p.K >= 512)) return kTile128;
   return narrow;
+}
+
+// Rows of a tile of the grouped products of a routed FFN (`slots` assignments, FFN D x F, E experts): both walk one tile map.
+// 256 (256 x 256 up, 256 x 128 down, one workgroup per compute unit) where the rounds of both are four fifths full, as long as the
+// experts' last tiles do not spill into another one: half a tile each on average, three quarters allowed for.  Up + down, us, 128 rows /
+// 256 rows: 768 x 3072, 8 experts, 9200 slots (2 rounds, 1) 72 + 58 / 64 + 53, 25600 167 + 165 / 152 + 159; 1024 x 4096, 4 experts,
+// 15360 168 + 159 / 151 + 138; but 768 x 3072, 10240 slots (3, 2) 77 + 60 / 85 + 86, 16000, a choice each, (4, 2) 112 + 108 / 120 + 103.
+int routed_row_tile(int dtype, int slots, int D, int F, int E, bool no_wide) {
+  const int bm = gemm_row_tile(dtype, slots, F, 0);
+  if (bm < 128) return bm;
+  const bool direct = !no_wide && D % 128 == 0 && F % 64 == 0;
+  if (direct && D >= 192 && F % 256 == 0) {
+    const long rows = slots / 256 + 3 * E / 4;
+    auto full = [](long t) { return 5 * t >= 4 * 256 * ((t + 255) / 256); };
+    if (full(rows * (F / 256)) && full(rows * (D / 128))) return 256;
+  }
+  // the second product is a long contraction of activations from F = kQuarterK on: of the kernels with 128-row tiles only the
+  // direct-to-LDS ones take it (they keep the running sum of its four runs)
+  return F >= kQuarterK && !direct ? 64 : 128;
 }
 
 template <int AM, int EP, typename S>

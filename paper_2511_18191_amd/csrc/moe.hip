@@ -106,7 +106,9 @@ __device__ __forceinline__ unsigned long long lanes_of_my_expert(int id, bool va
 // set bits of that expert's mask below its own lane.  So the only scans left are the two small
 // ones over wavefronts and over experts.  The first pass counts and keeps the expert ids in LDS
 // (one byte each); the second pass places.  The tile map of the grouped GEMMs (one entry per
-// BM-row tile of an expert's run of slots) is written by one lane per tile.  EMAX (8 or 16) is the
+// BM-row tile of an expert's run of slots) is written by one lane per tile, with their number behind it: the products deal
+// their tiles to the XCDs by it (by the largest possible number an XCD had 33 of 240 tiles to do on 32 compute units: 256-row tiles
+// of 9216 slots 83 us, 53 now).  EMAX (8 or 16) is the
 // compile-time bound of the expert count.
 template <int EMAX>
 __global__ __launch_bounds__(1024) void permute_kernel(const int* ids, int n_assign, int topk, int E, int BM, int n_mtiles,
@@ -193,15 +195,17 @@ __global__ __launch_bounds__(1024) void permute_kernel(const int* ids, int n_ass
       slot_of[a] = slot;
     }
   }
-  // tile map: tile j belongs to the expert e with tile_beg[e] <= j < tile_beg[e + 1]
-  for (int j = t; j < n_mtiles; j += 1024) {
-    int4 entry = make_int4(-1, 0, 0, 0);
+  // tile map: tile j belongs to the expert e with tile_beg[e] <= j < tile_beg[e + 1]; behind the largest possible number of tiles, theirs
+  const int tiles = tile_beg[EMAX];
+  for (int j = t; j < tiles; j += 1024) {
+    int4 entry = make_int4(0, 0, 0, 0);
 #pragma unroll
     for (int e = 0; e < EMAX; ++e)
       if (e < E && j >= tile_beg[e] && j < tile_beg[e + 1])
         entry = make_int4(e, beg[e] + (j - tile_beg[e]) * BM, beg[e + 1], 0);
     tile_map[j] = entry;
   }
+  if (t == 0) tile_map[n_mtiles] = make_int4(tiles, 0, 0, 0);
 }
 
 // TOPK > 0: the number of choices per token at compile time, so that the slots and gates of all

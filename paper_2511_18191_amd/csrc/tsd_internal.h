@@ -83,10 +83,10 @@ struct GemmP {
   int D, Hh, hd, PT;
   int pt_shift;  // log2(PT)
   // grouped (routed-FFN) mode: the row tiles come from a device-side map, one expert per tile
-  const void* tile_map;  // int4 per row tile: (expert or -1, first slot, end slot of the expert, 0); NULL = dense
+  const void* tile_map;  // int4 per row tile: (expert, first slot, end slot of the expert, 0); NULL = dense
   const int* src_row;    // A row of slot s is src_row[s] (NULL: the slot itself)
   long w_stride;         // elements between consecutive experts' matrices in W
-  int n_mtiles;          // entries of tile_map
+  int n_mtiles;          // row tiles of tile_map at most; the entry behind them starts with their number
   int force_bm;          // row-tile size the map was built for (0 = pick by problem size)
   int allow_skinny;      // the handle runs its <= 32-row passes through the skinny kernel
   int no_wide;           // never pick the direct-to-LDS kernels (gemm_direct64.hip, gemm_wide.hip)
@@ -141,6 +141,7 @@ int gemm_row_tile(int dtype, int M, int N, int force_bm);
 // direct-to-LDS kernels (gemm_direct64.hip, gemm_wide.hip): the tile for this product, or kTileNone for the register-staged kernels
 enum DirectTile { kTileNone = 0, kTile64 = 64, kTile128x64 = 127, kTile128 = 128, kTile128x256 = 129, kTile256x128 = 256, kTile256 = 257, kTileRuns = 464 };
 DirectTile gemm_direct_tile(int dtype, int amode, int epi, const GemmP& p);
+int routed_row_tile(int dtype, int slots, int D, int F, int E, bool no_wide);
 hipError_t launch_gemm_f32(int amode, int epi, const GemmP& p, hipStream_t st);  // (gemm_f32.hip: every fp32 product)
 hipError_t launch_gemm_direct64(int amode, int epi, const GemmP& p, hipStream_t st);
 hipError_t prepare_gemm_direct64();

@@ -7,7 +7,7 @@ import paper_2511_18191_amd as tsd
 from synth import ModelCfg
 
 pytestmark = pytest.mark.gpu
-QKV = 1  # TSD_K_QKV
+QKV, GELU = 1, 4  # TSD_K_QKV, TSD_K_GELU
 
 
 @pytest.mark.parametrize("M,N,K,variant", [
@@ -69,3 +69,31 @@ def test_rotary_epilogue_same_bits_as_register_staged(D, heads, B, N, tile):
     assert tile in used[0] and not any(t > 2000 for t in used[1]), used
     for k in res[0]:
         assert torch.isfinite(res[0][k]).all() and torch.equal(res[0][k], res[1][k]), k
+
+
+@pytest.mark.parametrize("D,F,E,k,B", [(256, 1024, 8, 2, 640), (512, 1024, 3, 1, 690)])
+def test_grouped_products_on_256_row_maps_same_bits_as_register_staged(D, F, E, k, B):
+    """A context pass of 12800 / 13800 rows: both products of the experts on maps of 256 rows, last tiles of any length."""
+    P, N, T, K = 16, 21, 2, 2
+    target, draft = ModelCfg(1, D, D // 64, F, E, k), ModelCfg(1, 64, 1, 256)
+    g = torch.Generator().manual_seed(D + E)
+    n = lambda m: P * m.d_model + 2 * m.d_model + 4 * m.d_model ** 2 + m.d_model + m.d_model * P + (
+        m.d_model * m.n_experts + m.n_experts * 2 * m.d_model * m.d_ff if m.n_experts else 2 * m.d_model * m.d_ff)
+    w = [(torch.randn(n(m), generator=g) * 0.05).bfloat16().float() for m in (target, draft)]
+    series = torch.randn(B, N * P, generator=g)
+    res, used = [], []
+    for flags in (0, tsd.TSD_FLAG_NO_WIDE_GEMM):
+        sess = tsd.Session(tsd.make_config(target, draft, P, K, B, N + T + K, "bf16", 1.0, seed=3, flags=flags))
+        sess.load_weights(tsd.TSD_TARGET, w[0].cuda())
+        sess.load_weights(tsd.TSD_DRAFT, w[1].cuda())
+        sess.profile_begin(GELU)
+        sess.prefill(series.cuda(), N, T * P)
+        sess.profile_end()
+        used.append({r["tile"] for r in sess.profile_launches()})
+        sess.round()
+        io = sess.get_round_io()
+        res.append({x: io[x].cpu() for x in ("X", "mu_p")})
+        sess.close()
+    assert 2257 in used[0] and not any(t > 2000 for t in used[1]), used
+    for x in res[0]:
+        assert torch.isfinite(res[0][x]).all() and torch.equal(res[0][x], res[1][x]), x
