@@ -16,7 +16,7 @@ import numpy as np
 
 import synth
 
-from .binding import session_for
+from .binding import _check as check, lib, session_for
 
 
 def run_stream(sess, contexts, n_ctx, horizon, track=False, min_refill=1):
@@ -41,36 +41,55 @@ def run_stream(sess, contexts, n_ctx, horizon, track=False, min_refill=1):
     nxt, pending = B, B
     live = B                            # slots that were decoding after the last look
     free = []                           # harvested slots waiting for a newcomer
-    while pending:
-        sess.round()
-        n = sess.num_active()
-        if n == live:                   # nobody finished in this round: nothing to harvest
-            continue
-        committed = sess.get_state()["committed"].cpu().numpy()
-        done = [b for b in range(B) if owner[b] >= 0 and committed[b] >= T]
-        if done:
-            fc = sess.get_forecast()
-            with torch.cuda.stream(sess.stream):
-                out[[owner[b] for b in done]] = fc[done]
-            sess.sync()
-            pending -= len(done)
-            for b in done:
-                owner[b] = -1
-            free += done
-        take = min(len(free), S - nxt)
-        if take and (len(free) >= min_refill or n == 0 or S - nxt <= len(free)):
-            slots, free = free[:take], free[take:]
-            if track:
-                rounds = sess.get_series_stats()[:, 0].cpu().numpy()
-                for j, b in enumerate(slots):
-                    placement[nxt + j] = (b, int(rounds[b]))
-            sess.refill(slots, ctx_dev[nxt:nxt + take])
-            for j, b in enumerate(slots):
-                owner[b] = nxt + j
-            nxt += take
-            pending += take
+    # A harvest is a chain of short operations behind a finished round, so what counts is how often the host waits: once, for the
+    # committed lengths; the forecasts are made meanwhile and their rows moved on the session's stream, by indices from pinned memory
+    # (160 series through 64 slots: a tenth of 7.6 ms).  Buffers that only that stream uses are allocated on it.
+    h, raw = sess.h, sess.stream.cuda_stream
+    with torch.cuda.stream(sess.stream):
+        fc = torch.empty(B, horizon, dtype=torch.float32, device=sess.device)
+        committed = torch.empty(B, dtype=torch.int32, device=sess.device)
+    committed_host = torch.empty(B, dtype=torch.int32, pin_memory=True)
+    rows_host = torch.empty(2 * B, dtype=torch.int64, pin_memory=True)
+    try:
+        while pending:
+            sess.round()
             n = sess.num_active()
-        live = n
+            if n == live:               # nobody finished in this round: nothing to harvest
+                continue
+            check(lib().tsd_get_state(h, None, committed.data_ptr(), None, raw), h)
+            with torch.cuda.stream(sess.stream):
+                committed_host.copy_(committed, non_blocking=True)
+            landed = sess.stream.record_event()
+            check(lib().tsd_get_forecast(h, fc.data_ptr(), raw), h)
+            landed.synchronize()        # (rows_host is free again, too: its last copy is older)
+            got = committed_host.tolist()
+            done = [b for b in range(B) if owner[b] >= 0 and got[b] >= T]
+            if done:
+                k = len(done)
+                rows_host[:2 * k] = torch.tensor(done + [owner[b] for b in done])
+                with torch.cuda.stream(sess.stream):
+                    rows = rows_host[:2 * k].to(sess.device, non_blocking=True)
+                    out.index_copy_(0, rows[k:], fc.index_select(0, rows[:k]))
+                pending -= k
+                for b in done:
+                    owner[b] = -1
+                free += done
+            take = min(len(free), S - nxt)
+            if take and (len(free) >= min_refill or n == 0 or S - nxt <= len(free)):
+                slots, free = free[:take], free[take:]
+                if track:
+                    rounds = sess.get_series_stats()[:, 0].cpu().numpy()
+                    for j, b in enumerate(slots):
+                        placement[nxt + j] = (b, int(rounds[b]))
+                sess.refill(slots, ctx_dev[nxt:nxt + take])
+                for j, b in enumerate(slots):
+                    owner[b] = nxt + j
+                nxt += take
+                pending += take
+                n = sess.num_active()
+            live = n
+    finally:
+        sess.sync()                     # `out` belongs to the caller's stream
     return out, placement
 
 
