@@ -176,7 +176,7 @@ MARK = None
 
 
 TILE_LABEL = {128: "128x128", 64: "64x64", 464: "64x64k4", 16: "skinny", 2256: "w256x128", 2128: "w128x128", 2064: "w64x64", 2127: "w128x64", 2129: "w128x256",
-              2257: "w256x256", 2464: "w64x64k4"}
+              2257: "w256x256", 2464: "w64x64k4", 2016: "w64x64s"}
 
 
 def kernel_rooflines(sess, dtype, steps, traffic, cfg=None):

@@ -376,9 +376,9 @@ int tsd_profile_end(tsd_ctx* ctx, int64_t* launches_host, double* ms_host, doubl
 /* The launches of the measurement that the last tsd_profile_end closed, one record each, in launch order:
  * family, model (TSD_TARGET / TSD_DRAFT, -1 for the acceptance kernel), and for the GEMM families the kernel the
  * launcher picked (`tile`: 128 or 64 = tile size of the tiled kernel, 464 = 64 x 64 tiles with K split over four
- * wavefront groups, 16 = the skinny weight-streaming kernel, 2064 / 2127 / 2128 / 2129 / 2256 / 2257 = the direct-to-LDS
- * kernels with 64 x 64, 128 x 64, 128 x 128, 128 x 256, 256 x 128 and 256 x 256 tiles, 2464 = 64 x 64 tiles with K split
- * over four workgroups) and the product's shape as launched (rows M as
+ * wavefront groups, 16 = the skinny weight-streaming kernel, 2016 = 64 x 64 direct-to-LDS tiles with its sums, 2064 / 2127 /
+ * 2128 / 2129 / 2256 / 2257 = the direct-to-LDS kernels with 64 x 64, 128 x 64, 128 x 128, 128 x 256, 256 x 128 and
+ * 256 x 256 tiles, 2464 = 64 x 64 tiles with K split over four workgroups) and the product's shape as launched (rows M as
  * sized on the host: a replayed or device-capped launch may run fewer); attention: M = query rows, N = model
  * width; duration between the two events in milliseconds; algorithmic work as summed by tsd_profile_end.
  * out_host: max_records entries; *n_host receives the number of launches recorded (which may exceed

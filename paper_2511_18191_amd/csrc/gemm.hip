@@ -452,7 +452,7 @@ static hipError_t launch_t(int amode, int epi, const GemmP& p, hipStream_t st) {
 }
 
 int gemm_variant(int dtype, int amode, int epi, const GemmP& p) {
-  if (p.allow_skinny && skinny_applicable(dtype, amode, epi, p)) return 16;
+  if (p.allow_skinny && skinny_applicable(dtype, amode, epi, p)) return skinny_as_tiles(amode, epi, p) ? 2016 : 16;
   if (dtype != TSD_BF16) return 64;
   if (const int tile = gemm_direct_tile(dtype, amode, epi, p)) return 2000 + tile;
   if (!(amode == A_ACT && p.K >= kQuarterK) && gemm_row_tile(TSD_BF16, p.M, p.N, p.force_bm) == 128) return 128;
@@ -461,7 +461,8 @@ int gemm_variant(int dtype, int amode, int epi, const GemmP& p) {
 
 hipError_t launch_gemm(int dtype, int amode, int epi, const GemmP& p, hipStream_t st) {
   if (p.M <= 0 || p.N <= 0 || p.K <= 0) return hipErrorInvalidValue;
-  if (p.allow_skinny && skinny_applicable(dtype, amode, epi, p)) return launch_gemm_skinny(amode, epi, p, st);
+  if (p.allow_skinny && skinny_applicable(dtype, amode, epi, p))
+    return skinny_as_tiles(amode, epi, p) ? launch_gemm_shares(amode, epi, p, st) : launch_gemm_skinny(amode, epi, p, st);
   if (const DirectTile tile = gemm_direct_tile(dtype, amode, epi, p))
     return tile == kTile64     ? launch_gemm_direct64(amode, epi, p, st)
            : tile == kTileRuns ? launch_gemm_runs(p, st)

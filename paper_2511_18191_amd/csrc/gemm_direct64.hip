@@ -38,14 +38,32 @@ constexpr int BIAS = REGION / 2;                  // M0 points here inside the r
 constexpr int LDC = BN + 4;
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kSc1 = 16;  // cache policy of what workgroups hand each other: agent scope
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr size_t SMEM = (size_t)NS * STAGE + BM * 12;  // stages, then row_scale / row_pos / row_page
 static_assert(64 * LDC * 4 <= NS * STAGE, "the epilogue's buffer reuses the stages");
 
+// (v[l] + v[l ^ 16]) + (v[l ^ 32] + v[l ^ 48]), lanes exchanged in registers
+__device__ __forceinline__ float add_quarters(float v) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  const unsigned half = __float_as_uint(__uint_as_float(p[0]) + __uint_as_float(p[1]));
+  const auto q = __builtin_amdgcn_permlane32_swap(half, half, false, false);
+  return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+}
+
+// How a tile sums over k.
+enum Sums {
+  kWhole,   // in one run, long contractions of activations in four (see gemm.hip)
+  kOneRun,  // (EP_STORE) p.K is one run of a longer contraction, its sums are for another workgroup of the launch
+  // As gemm_skinny.hip: a share per wavefront of its workgroups, 32 k at a time, the shares added in order (same bits).  What it costs over
+  // kWhole is the vector arithmetic at a share's end, every 32 k at K = 512, and the chains of row sums (145x1536x512 7.6 us against
+  // 5.8, without the norm 145x512x512 5.5 against 5.1); the MFMAs of a first step without an addend gained nothing (7.5).
+  kShares,
+};
+
 // Rows m0 .. min(m0 + 64, M) - 1, columns n0 .. n0 + 63, by a workgroup of NT lanes.  ldk: elements between rows of A and of W.
-// kRun (EP_STORE): p.K is one run of a longer contraction, its sums are for another workgroup of the launch.
-template <int AM, int EP, bool kRun>
+template <int AM, int EP, Sums SUMS>
 __device__ __forceinline__ void tile64(const GemmP& p, int ldk, int M, int m0, int n0, unsigned char* smem) {
-  constexpr bool kNorm = (AM == A_NORM);
+  constexpr bool kNorm = (AM == A_NORM), kSkinny = SUMS == kShares;
   float* Cs = reinterpret_cast<float*>(smem);                            // [64][LDC], after the main loop
   float* row_scale = reinterpret_cast<float*>(smem + NS * STAGE);        // [BM]
   int* row_pos = reinterpret_cast<int*>(smem + NS * STAGE + BM * 4);     // [BM] EP_QKV
@@ -95,17 +113,39 @@ __device__ __forceinline__ void tile64(const GemmP& p, int ldk, int M, int m0, i
     issue_loads<0, NL, BIAS>(gp, (long)kt * BK, TSD_LDS_PTR(smem + slot * STAGE + wid * REGION + BIAS));
   };
 
-  // ---- fragments: lane l reads row l % 32 of a 32-row block, chunk 2 s + l / 32 of k16 sub-step s
+  // ---- fragments: lane l reads row l % 32 of a 32-row block, chunk 2 s + l / 32 of k16 sub-step s (kShares: row l % 16 of 16-row block s % 2,
+  // chunk 4 (s / 2) + l / 16 of k32 step s / 2)
   f32x16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
   // Long contractions of activations are summed in four runs of ceil(nk / 4) k-tiles, each from zero, the runs added in
   // order (the order of the split workgroups of gemm.hip, which every kernel that can take such a product keeps to)
-  constexpr bool kQuarters = AM == A_ACT && !kRun;
+  constexpr bool kQuarters = AM == A_ACT && SUMS == kWhole;
   f32x16 tot;
   float ss[4] = {0.f, 0.f, 0.f, 0.f};  // row-sum chains of this lane: chunk positions hi, 2 + hi, 4 + hi, 6 + hi of a 64-wide k-run
-  const int r31 = lane & 31, hi = lane >> 5;
-  const int RA = wm * 32 + r31, RB = BM + wn * 32 + r31;
+  const int r31 = lane & 31, hi = lane >> 5, l15 = lane & 15, lg = lane >> 4;
+  const int RA = wm * 32 + (kSkinny ? l15 : r31), RB = BM + wn * 32 + (kSkinny ? l15 : r31);
+  // kShares: the share's sums, the shares' sums so far; k32 steps of a share, and those still to come of the one under way
+  f32x4 part[2][2], sum[2][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) part[i >> 1][i & 1] = sum[i >> 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float share_ss = 0.f, sum_ss = 0.f;  // row sums of this wavefront's 16-row block number wn
+  const int share = (K / 32 + skinny_shares(K) - 1) / skinny_shares(K);
+  int left = share;
+  auto end_share = [&] {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        sum[i][j] += part[i][j];
+        part[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    if constexpr (kNorm) {
+      sum_ss += add_quarters(share_ss);
+      share_ss = 0.f;
+    }
+    left = share;
+  };
   const int offA = RA * ROWB, offB = RB * ROWB, swA = swizzle(RA), swB = swizzle(RB);
 
   // The k loop: a k-tile is four k16 sub-steps, one MFMA each, a chain of dependent sums that leaves LDS latency nothing to hide behind.
@@ -122,8 +162,10 @@ __device__ __forceinline__ void tile64(const GemmP& p, int ldk, int M, int m0, i
     const unsigned char* st = smem + (kt % NS) * STAGE;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      fa[F][s] = *reinterpret_cast<const bf16x8*>(st + offA + (((2 * s + hi) ^ swA) << 4));
-      fb[F][s] = *reinterpret_cast<const bf16x8*>(st + offB + (((2 * s + hi) ^ swB) << 4));
+      // (rows 16 apart have the same swizzle)
+      const int chunk = kSkinny ? 4 * (s >> 1) + lg : 2 * s + hi, block = kSkinny ? (s & 1) * 16 * ROWB : 0;
+      fa[F][s] = *reinterpret_cast<const bf16x8*>(st + offA + block + ((chunk ^ swA) << 4));
+      fb[F][s] = *reinterpret_cast<const bf16x8*>(st + offB + block + ((chunk ^ swB) << 4));
     }
   };
   // One k-tile.  SET: its fragments; PEND: the loads this wavefront may leave in flight at the barrier (those of the k-tiles after
@@ -137,6 +179,23 @@ __device__ __forceinline__ void tile64(const GemmP& p, int ldk, int M, int m0, i
     if constexpr (PEND >= 0) read_frags(IC<1 - F>{}, kt + 1);
     if constexpr (REFILL) issue_stage(kt % NS, kt + NS);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kSkinny) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) part[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[F][2 * t + i], fb[F][2 * t + j], part[i][j], 0, 0, 0);
+        if constexpr (kNorm) {
+          const bf16x8 a = wn ? fa[F][2 * t + 1] : fa[F][2 * t];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) share_ss = fmaf((float)a[e], (float)a[e], share_ss);
+        }
+        if (--left == 0) end_share();
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      return;
+    }
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       if constexpr (kNorm) {
@@ -204,6 +263,10 @@ __device__ __forceinline__ void tile64(const GemmP& p, int ldk, int M, int m0, i
     }
   }
 
+  if constexpr (kSkinny) {
+    if (left != share) end_share();
+  }
+
   if constexpr (EP == EP_QKV) {
     if (tid < BM) {
       row_pos[tid] = my_meta.x;
@@ -211,7 +274,9 @@ __device__ __forceinline__ void tile64(const GemmP& p, int ldk, int M, int m0, i
     }
   }
   // ---- RMSNorm row scale: this lane's chains are the chunk positions hi, 2 + hi, 4 + hi, 6 + hi ---------------------------
-  if constexpr (kNorm) {
+  if constexpr (kNorm && kSkinny) {
+    if (lg == 0) row_scale[wm * 32 + wn * 16 + l15] = rsqrtf(sum_ss / (float)K + kRmsEps);
+  } else if constexpr (kNorm) {
     const float b = (ss[0] + ss[2]) + (ss[1] + ss[3]);  // (P[hi] + P[4 + hi]) + (P[2 + hi] + P[6 + hi])
     const float all = b + __shfl_xor(b, 32);
     if (wn == 0 && hi == 0) row_scale[RA] = rsqrtf(all / (float)K + kRmsEps);
@@ -221,9 +286,12 @@ __device__ __forceinline__ void tile64(const GemmP& p, int ldk, int M, int m0, i
   auto read_c4 = [&](int row, int col) { return *reinterpret_cast<const float4*>(Cs + row * LDC + col); };
   __syncthreads();  // the stages are no longer read
 #pragma unroll
-  for (int r = 0; r < 16; ++r) Cs[(wm * 32 + (r >> 2) * 8 + hi * 4 + (r & 3)) * LDC + wn * 32 + r31] = acc[r];
+  for (int r = 0; r < 16; ++r) {
+    if constexpr (kSkinny) Cs[(wm * 32 + (r >> 3) * 16 + lg * 4 + (r & 3)) * LDC + wn * 32 + (r >> 2 & 1) * 16 + l15] = sum[r >> 3][r >> 2 & 1][r & 3];
+    else Cs[(wm * 32 + (r >> 2) * 8 + hi * 4 + (r & 3)) * LDC + wn * 32 + r31] = acc[r];
+  }
   __syncthreads();
-  if constexpr (kRun) {  // written through to memory
+  if constexpr (SUMS == kOneRun) {  // written through to memory
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(p.Cf, 0, 0x7fffffff, 0x00020000);
 #pragma unroll
     for (int it = 0; it < 64 * (BN / 4) / NT; ++it) {
@@ -251,7 +319,7 @@ __device__ __forceinline__ void resid_run64(const bf16* A, const bf16* W, int K,
   g.W = W + run * r * 64;
   g.Cf = parts + run * part_elems;
   g.Cb = nullptr;
-  tile64<A_ACT, EP_STORE, true>(g, K, M, m0, n0, smem);
+  tile64<A_ACT, EP_STORE, kOneRun>(g, K, M, m0, n0, smem);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // every wavefront's sums are there
   __syncthreads();
   if (tid == 0) *word = (int)__hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -291,7 +359,7 @@ __device__ __forceinline__ void resid_run64(const bf16* A, const bf16* W, int K,
 
 }  // namespace d64
 
-template <int AM, int EP>
+template <int AM, int EP, d64::Sums SUMS>
 __global__ __launch_bounds__(d64::NT, 2) void gemm_direct64_kernel(const GemmP p) {
   using namespace d64;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -310,7 +378,7 @@ __global__ __launch_bounds__(d64::NT, 2) void gemm_direct64_kernel(const GemmP p
   const int gw = min(GW, tiles_n - gc * GW);
   const int tm = rem / gw, tn = gc * GW + rem - tm * gw;
   const int m0 = tm * BM, n0 = tn * BN;
-  tile64<AM, EP, false>(p, p.K, M, m0, n0, smem);
+  tile64<AM, EP, SUMS>(p, p.K, M, m0, n0, smem);
 }
 
 // The long contractions of few rows, x += A W^T, a run of the four per workgroup (resid_run64).  With one workgroup per tile, whatever its
@@ -332,10 +400,10 @@ __global__ __launch_bounds__(d64::NT, 2) void gemm_runs_kernel(const GemmP p) {
 }
 
 // ---- host side -------------------------------------------------------------------------------------------------
-template <int AM, int EP>
+template <int AM, int EP, d64::Sums SUMS = d64::kWhole>
 static hipError_t launch_t(const GemmP& p, hipStream_t st) {
   const long tiles = (long)((p.M + d64::BM - 1) / d64::BM) * (p.N / d64::BN);
-  hipLaunchKernelGGL((gemm_direct64_kernel<AM, EP>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(d64::NT), d64::SMEM, st, p);
+  hipLaunchKernelGGL((gemm_direct64_kernel<AM, EP, SUMS>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(d64::NT), d64::SMEM, st, p);
   return hipGetLastError();
 }
 
@@ -348,15 +416,22 @@ hipError_t launch_gemm_direct64(int amode, int epi, const GemmP& p, hipStream_t 
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_gemm_shares(int amode, int epi, const GemmP& p, hipStream_t st) {
+  if (amode == A_ACT && epi == EP_RESID) return launch_t<A_ACT, EP_RESID, d64::kShares>(p, st);
+  if (amode == A_NORM && epi == EP_GELU) return launch_t<A_NORM, EP_GELU, d64::kShares>(p, st);
+  if (amode == A_NORM && epi == EP_QKV) return launch_t<A_NORM, EP_QKV, d64::kShares>(p, st);
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_gemm_runs(const GemmP& p, hipStream_t st) {
   const long tiles = (long)((p.M + d64::BM - 1) / d64::BM) * (p.N / d64::BN);
   hipLaunchKernelGGL(gemm_runs_kernel, dim3((unsigned)((tiles + 7) / 8 * 32)), dim3(d64::NT), d64::SMEM + 64, st, p);
   return hipGetLastError();
 }
 
-template <int AM, int EP>
+template <int AM, int EP, d64::Sums SUMS = d64::kWhole>
 static hipError_t raise() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_direct64_kernel<AM, EP>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)d64::SMEM);
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_direct64_kernel<AM, EP, SUMS>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)d64::SMEM);
 }
 
 // More than 64 KB of dynamic LDS needs a one-time opt-in per kernel, outside any stream capture.
@@ -367,7 +442,10 @@ hipError_t prepare_gemm_direct64() {
   if ((e = raise<A_ACT, EP_RESID>()) != hipSuccess) return e;
   if ((e = raise<A_NORM, EP_STORE>()) != hipSuccess) return e;
   if ((e = raise<A_NORM, EP_GELU>()) != hipSuccess) return e;
-  return raise<A_NORM, EP_QKV>();
+  if ((e = raise<A_NORM, EP_QKV>()) != hipSuccess) return e;
+  if ((e = raise<A_ACT, EP_RESID, d64::kShares>()) != hipSuccess) return e;
+  if ((e = raise<A_NORM, EP_GELU, d64::kShares>()) != hipSuccess) return e;
+  return raise<A_NORM, EP_QKV, d64::kShares>();
 }
 
 }  // namespace tsd

@@ -1,5 +1,6 @@
 // Skinny GEMM for passes of at most 32 rows (batch 1..few series: the latency regime):
 //   C[M,N] = A[M,K] * Wt[N,K]^T,  M <= 32, bf16 operands, fp32 accumulation.
+// (Short contexts of such handles run in tiles of 32 rows; which of their products do: skinny_as_tiles.)
 //
 // With so few rows the product is a stream over the weights (every byte of Wt is needed once,
 // there is nothing to reuse), so the kernel is built around HBM: a workgroup owns 16 output
@@ -47,7 +48,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const GemmP p) {
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int li = lane & 15, lg = lane >> 4;
-  const int M = p.M, N = p.N, K = p.K;
+  const int m0 = blockIdx.y * kRowsMax, M = min(p.M - m0, kRowsMax);  // this workgroup's rows (one tile of them but for context passes)
+  const int N = p.N, K = p.K;
 
   // ---- the 16 columns of this workgroup ----
   int col_of[2];  // first global column of LDS columns 0..7 and 8..15
@@ -68,7 +70,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const GemmP p) {
   const char* arow[2];
 #pragma unroll
   for (int r = 0; r < 2; ++r) {
-    const int gm = min(r * 16 + li, M - 1);
+    const int gm = m0 + min(r * 16 + li, M - 1);
     if constexpr (AM == A_TOK) {
       int b = gm / p.nq;
       const int t = gm % p.nq;
@@ -87,13 +89,13 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const GemmP p) {
   // epilogue inputs that do not depend on the product
   if constexpr (EP == EP_QKV) {
     if (tid < kRowsMax) {
-      const int2 meta = p.row_meta[min(tid, M - 1)];
+      const int2 meta = p.row_meta[m0 + min(tid, M - 1)];
       row_pos[tid] = meta.x;
       row_page[tid] = meta.y;
     }
   }
   if constexpr (AM == A_TOK) {
-    if (p.row_meta && blockIdx.x == 0 && tid < M) p.row_meta[tid] = row_meta_of(p, tid);
+    if (p.row_meta && blockIdx.x == 0 && tid < M) p.row_meta[m0 + tid] = row_meta_of(p, m0 + tid);
   }
 
   // ---- this wavefront's share of K, in steps of 32 ----
@@ -187,8 +189,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const GemmP p) {
   if (tid >= kRowsMax * 4) return;
   const int row = tid >> 2, c4 = (tid & 3) * 4;
   // a launch replayed from a graph stores only the rows of series that are still active
-  if (row >= (p.n_dev ? min(M, *p.n_dev * p.nq) : M)) return;
-  const int gm = row;
+  if (row >= (p.n_dev ? min(M, *p.n_dev * p.nq - m0) : M)) return;
+  const int gm = m0 + row;
   const int gn = col_of[c4 >> 3] + (c4 & 7);
   if (gn >= N) return;
   float4 v = make_float4(0.f, 0.f, 0.f, 0.f), pv = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -267,8 +269,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const GemmP p) {
 
 template <int AM, int EP>
 hipError_t launch_nw(const GemmP& p, hipStream_t st) {
-  const dim3 grid((unsigned)(p.N / 16));
-  if (p.K >= 512)
+  const dim3 grid((unsigned)(p.N / 16), (unsigned)((p.M + kRowsMax - 1) / kRowsMax));
+  if (skinny_shares(p.K) == 16)
     hipLaunchKernelGGL((gemm_skinny_kernel<AM, EP, 16>), grid, dim3(16 * 64), 0, st, p);
   else
     hipLaunchKernelGGL((gemm_skinny_kernel<AM, EP, 4>), grid, dim3(4 * 64), 0, st, p);
@@ -277,12 +279,25 @@ hipError_t launch_nw(const GemmP& p, hipStream_t st) {
 
 }  // namespace
 
-// True when the skinny kernel can take this product (bf16, at most 32 rows, whole 16-column groups, dense, and
-// for the QKV product head_dim 64 so that rotary partners pair up as 8 + 8 columns).
+// True when the skinny kernel can take this product (bf16, at most 32 rows or, where allow_skinny is 2, any number in tiles of 32, whole 16-column groups,
+// dense, and for the QKV product head_dim 64 so that rotary partners pair up as 8 + 8 columns).
 bool skinny_applicable(int dtype, int amode, int epi, const GemmP& p) {
-  if (dtype != TSD_BF16 || p.M > kRowsMax || p.M < 1 || (p.N % 16) || (p.K % 8) || p.K < 8 || p.tile_map) return false;
+  if (dtype != TSD_BF16 || (p.M > kRowsMax && p.allow_skinny < 2) || p.M < 1 || (p.N % 16) || (p.K % 8) || p.K < 8 || p.tile_map) return false;
   if (epi == EP_QKV && p.hd != 64) return false;
   return true;
+}
+
+// More than 32 rows: whether the 64 x 64 tiles that form the same sums (kShares in gemm_direct64.hip) take the product.  They read every
+// weight once per 64 rows where this kernel reads it once per 32, and take no LDS round trip per share (this kernel / the tiles, us:
+// 145x1536x512 15.7 / 7.6, 145x2048x512 19.9 / 7.0, 58x1536x512 9.2 / 7.3, 145x512x512 7.9 / 5.5, 512x512x2048 15.1 / 10.0,
+// 145x768x3072 13.8 / 12.6, 145x1024x4096 23.2 / 18.6).  The one exception: the long contractions, a chain of k-tiles on a few compute
+// units there, stay here while the workgroups do not outnumber the compute units and a wavefront's share is whole batches of loads
+// (145x512x2048 8.1 / 9.8, 232x512x2048 8.4 / 9.7, 58x1024x4096 13.3 / 15.3).
+bool skinny_as_tiles(int amode, int epi, const GemmP& p) {
+  const bool combo = (amode == A_ACT && epi == EP_RESID) || (amode == A_NORM && (epi == EP_GELU || epi == EP_QKV));
+  if (!combo || p.M <= kRowsMax || p.no_wide || p.K % 64 || p.K < 256 || p.N % 64) return false;
+  const long workgroups = (long)(p.N / 16) * ((p.M + kRowsMax - 1) / kRowsMax);
+  return !(p.K % (skinny_shares(p.K) * kU * 32) == 0 && workgroups <= 256);
 }
 
 hipError_t launch_gemm_skinny(int amode, int epi, const GemmP& p, hipStream_t st) {

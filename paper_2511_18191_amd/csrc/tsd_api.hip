@@ -449,12 +449,17 @@ Shape shape_of(const tsd_ctx* ctx, int which, int amode, int epi, const GemmP& g
   return Shape{which, gemm_variant(ctx->cfg.dtype, amode, epi, g), g.M, g.N, g.K};
 }
 
-// Context passes of a handle whose decode passes are skinny: contexts of at most 32 rows in all take the skinny products too.  Longer
-// ones fill the 64 x 64 tiles, which read every weight once where the skinny kernel reads it once per 32 rows (context passes, us,
-// skinny / tiled, 24 layers of 1024 and 8 of 512: 5 series of 29 rows 2490 / 1181 and 518 / 311, 2 of 29 1450 / 1285 and 371 / 308;
-// one of 29 1182 / 1160 and 358 / 300, one of 19 1044 / 1160 and 330 / 300, one of 5 811 / 1160 and 264 / 300).  The two sum k in
-// different orders, so a context's last bits can depend on how many series are prefilled or refilled with it.
-int context_skinny(const tsd_ctx* ctx, int n, int nq) { return ctx->skinny && (long)n * nq <= 32 ? 1 : 0; }
+// Context passes of a handle whose decode passes are skinny: short contexts (at most 32 rows in the chunk of series that one
+// round's rows hold, `n` of them or fewer) have the skinny products' sums too, the order they have had since a context pass was one
+// chunk; on 64 x 64 tiles where they have more than 32 rows (skinny_as_tiles).  Which sums a series' context has, and so its last
+// bits, can therefore depend on how many series are prefilled or refilled with it (12 rows and 42 tokens: up to two series skinny, three
+// tiled).  Context passes, us, skinny kernel / with those tiles / other sums on 64 x 64 tiles: 5 series of 29 rows through 8 layers of
+// 512 531 / 342 / 297, through 24 of 1024 2517 / 1285 / 999; 16 of 32 rows through 8 of 512 1127 / 364 / 325.
+int context_skinny(const tsd_ctx* ctx, int n, int nq) {
+  const tsd_config& c = ctx->cfg;
+  const long chunk = std::max(1L, std::max((long)c.max_batch * (ctx->K_max + 1), (long)c.max_tokens) / nq);
+  return ctx->skinny && std::min(chunk, (long)n) * nq <= 32 ? 2 : 0;
+}
 
 // Launches `fn` on `st`; if kernel family `cls` is being profiled (or all are), brackets it with two events.
 template <typename F>

@@ -88,7 +88,7 @@ struct GemmP {
   long w_stride;         // elements between consecutive experts' matrices in W
   int n_mtiles;          // row tiles of tile_map at most; the entry behind them starts with their number
   int force_bm;          // row-tile size the map was built for (0 = pick by problem size)
-  int allow_skinny;      // the handle runs its <= 32-row passes through the skinny kernel
+  int allow_skinny;      // 1: the handle runs its <= 32-row passes through the skinny kernel; 2: this pass has the skinny kernel's sums, whatever its rows
   int no_wide;           // never pick the direct-to-LDS kernels (gemm_direct64.hip, gemm_wide.hip)
   // sums of the runs of a long contraction, kRunTiles tiles of 64 x 64 each, and a counter per tile, zero between launches (NULL: none)
   float* parts;
@@ -136,6 +136,8 @@ constexpr bool split_runs(int K) { return K >= kQuarterK && K % 64 == 0 && K / 6
 constexpr int kRunTiles = 112;  // 64 x 64 tiles of such a product at most
 // skinny path (at most 32 rows): see gemm_skinny.hip
 bool skinny_applicable(int dtype, int amode, int epi, const GemmP& p);
+bool skinny_as_tiles(int amode, int epi, const GemmP& p);
+constexpr int skinny_shares(int K) { return K >= 512 ? 16 : 4; }  // wavefronts that share a contraction
 hipError_t launch_gemm_skinny(int amode, int epi, const GemmP& p, hipStream_t st);
 int gemm_row_tile(int dtype, int M, int N, int force_bm);
 // direct-to-LDS kernels (gemm_direct64.hip, gemm_wide.hip): the tile for this product, or kTileNone for the register-staged kernels
@@ -145,10 +147,11 @@ int routed_row_tile(int dtype, int slots, int D, int F, int E, bool no_wide);
 hipError_t launch_gemm_f32(int amode, int epi, const GemmP& p, hipStream_t st);  // (gemm_f32.hip: every fp32 product)
 hipError_t launch_gemm_direct64(int amode, int epi, const GemmP& p, hipStream_t st);
 hipError_t prepare_gemm_direct64();
+hipError_t launch_gemm_shares(int amode, int epi, const GemmP& p, hipStream_t st);
 hipError_t launch_gemm_runs(const GemmP& p, hipStream_t st);
 hipError_t launch_gemm_wide(int amode, int epi, DirectTile tile, const GemmP& p, hipStream_t st);
 hipError_t prepare_gemm_wide();
-// which kernel launch_gemm picks for this product: 16 = skinny, 64 / 128 = tile size, 464 = 64 x 64 tiles with K split over four wavefront groups,
+// which kernel launch_gemm picks for this product: 16 = skinny, 2016 = direct-to-LDS tiles with its sums, 64 / 128 = tile size, 464 = 64 x 64 tiles with K split over four wavefront groups,
 // 2000 + DirectTile = the direct-to-LDS kernels
 int gemm_variant(int dtype, int amode, int epi, const GemmP& p);
 // s_max: upper bound on (position of the pass's last token) + 1 over all series; sizes the score buffer.
