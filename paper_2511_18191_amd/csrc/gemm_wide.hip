@@ -466,78 +466,10 @@ using Wide128Deep = WideShape<128, 128, 64, 2, 2, 3>; // ... one workgroup
 using Wide128x64 = WideShape<128, 64, 64, 4, 1, 2>;   // four of 32 x 64, three workgroups
 using Wide128x64Deep = WideShape<128, 64, 64, 4, 1, 3>;  // ... two workgroups
 
-// Which direct-to-LDS tile, if any, this product should take (kTileNone: the register-staged kernels of gemm.hip).  Every kernel
-// gives the same bits, so the product's shape alone decides.  Measured over M of 256 to 16343 and models of 512, 768 and 1024
-// columns, weights of 24 layers in turn; us.
 DirectTile gemm_direct_tile(int dtype, int amode, int epi, const GemmP& p) {
   if (dtype != TSD_BF16 || p.no_wide) return kTileNone;
-  const bool combo = (amode == A_ACT && (epi == EP_STORE || epi == EP_RESID)) ||
-                     (amode == A_NORM && (epi == EP_STORE || epi == EP_GELU || epi == EP_QKV));
-  if (!combo || (p.K % 64) || p.K < 192) return kTileNone;
-  // grouped products of the routed FFN: their tile map was built for force_bm-row tiles (routed_row_tile)
-  if (p.tile_map) {
-    if (p.force_bm == 256) return amode == A_NORM ? kTile256 : kTile256x128;
-    return p.force_bm == 128 && p.N % 128 == 0 ? kTile128 : kTileNone;
-  }
-  if (p.src_row || p.force_bm) return kTileNone;
-  auto tiles = [&](int bm, int bn) { return (long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
-  const long t64 = tiles(64, 64), t128 = tiles(128, 128);
-  // Long contractions with at most one 64 x 64 tile per compute unit are latency-bound chains of k-steps, where four groups of
-  // wavefronts that stream a quarter of K each (gemm.hip) are faster: 1280x512x2048 10.2 split, 11.5 here; 512x1024x4096 17.2 / 18.9.
-  const bool split = amode == A_ACT && p.K >= kQuarterK && t64 <= 256;
-  // From K = 2048 on a workgroup per run (gemm_runs_kernel) is faster still while all of them are resident together, two per compute unit,
-  // with room to spare (split workgroups / a workgroup per run: 256x512x2048 9.9 / 7.0, 768x512x2048, 96 tiles, 10.2 / 10.0; 256x768x3072
-  // 13.4 / 8.8, 558x768x3072, 108, 13.7 / 12.2, 768x768x3072, 144, 13.7 / 15.6; 320x1024x4096, 80, 16.7 / 11.5, 558, 144, 17.0 / 17.1);
-  // shorter ones gain nothing (256x1024x1024 6.95 / 7.04).
-  if (split && t64 <= kRunTiles && p.parts && epi == EP_RESID && p.Cb && p.K >= 2048 && split_runs(p.K) && p.N % 64 == 0) return kTileRuns;
-  const DirectTile narrow = !split && p.K >= 256 && p.N % 64 == 0 ? kTile64 : kTileNone;
-  if (amode == A_NORM && epi != EP_STORE) {
-    const bool heads64 = epi != EP_QKV || p.hd == 64;  // (one rotary pair of blocks per 64 columns of a wavefront)
-    // 256 x 256: 14 + 20 K / 1024 us per round of one tile per compute unit, the fewest operand bytes of all; taken where its rounds
-    // are four fifths full (16343x4096x1024, 4 rounds: 144 against 162 at 128 x 256 and 166 at 128 x 128; 7168x4096x1024, 1.75: 67 / 75
-    // / 75; 4608x3072x1024, 0.84: 37 / 40 / 43; but 12000x3072x768, 2.2 of 3 rounds: 83 / 79 / 76)
-    if (heads64 && p.N % 256 == 0) {
-      const long t256 = tiles(256, 256), rounds = (t256 + 255) / 256;
-      if (5 * t256 >= 4 * 256 * rounds) return kTile256;
-      // QKV only: 7168x3072x1024 60 against 66 at 128 x 128, 16343x1536x512 41 / 44, 12000x3072x1024 98 / 100
-      if (epi == EP_QKV && tiles(128, 256) >= 512) return kTile128x256;
-    }
-    // one 64 x 64 tile per compute unit or less: the fewest k-steps in a row (558x1536x512 6.1 against 7.0 at 128 x 64)
-    if (narrow && t64 <= 256) return narrow;
-    // ... two or more: 128 x 64 tiles, two or three workgroups per compute unit (64 x 64 / 128 x 64 / 128 x 128: 1280x1536x512 8.0 / 7.3 /
-    // 10.9, 1000x3072x768 14.4 / 11.1 / 13.2, 1280x4096x1024 23 / 19 / 21), up to three of them
-    if (p.N % 64 == 0 && (p.N % 128 || tiles(128, 64) <= 768)) return kTile128x64;
-    return p.N % 128 == 0 ? kTile128 : narrow;
-  }
-  if (p.N % 128) return narrow;
-  // Two 64 x 64 tiles per compute unit or less (2000x1024x4096 29 against 37 at 128 x 128, 3000x1024x1024 ...)
-  if (narrow && t64 <= 512) return narrow;
-  // the long contractions: 256 x 128 with three stages (16343x1024x4096 131 against 142 at 128 x 128, 4608x1024x4096, 144 tiles, 57 / 63)
-  if (p.K >= 2048 && tiles(256, 128) >= 140) return kTile256x128;
-  // up to one 128 x 128 tile per compute unit three stages (4608x768x3072, 216 tiles, 32 against 36 with two and 41 at 64 x 64;
-  // 4608x768x768 12.8 / 14.1 / 14.8), beyond two workgroups with two; short contractions need some more of them
-  // (12000x384x384, 282, 12.0 at 128 x 128 and 11.6 at 64 x 64)
-  if (!split && (t128 >= 384 || p.K >= 512)) return kTile128;
-  return narrow;
-}
-
-// Rows of a tile of the grouped products of a routed FFN (`slots` assignments, FFN D x F, E experts): both walk one tile map.
-// 256 (256 x 256 up, 256 x 128 down, one workgroup per compute unit) where the rounds of both are four fifths full, as long as the
-// experts' last tiles do not spill into another one: half a tile each on average, three quarters allowed for.  Up + down, us, 128 rows /
-// 256 rows: 768 x 3072, 8 experts, 9200 slots (2 rounds, 1) 72 + 58 / 64 + 53, 25600 167 + 165 / 152 + 159; 1024 x 4096, 4 experts,
-// 15360 168 + 159 / 151 + 138; but 768 x 3072, 10240 slots (3, 2) 77 + 60 / 85 + 86, 16000, a choice each, (4, 2) 112 + 108 / 120 + 103.
-int routed_row_tile(int dtype, int slots, int D, int F, int E, bool no_wide) {
-  const int bm = gemm_row_tile(dtype, slots, F, 0);
-  if (bm < 128) return bm;
-  const bool direct = !no_wide && D % 128 == 0 && F % 64 == 0;
-  if (direct && D >= 192 && F % 256 == 0) {
-    const long rows = slots / 256 + 3 * E / 4;
-    auto full = [](long t) { return 5 * t >= 4 * 256 * ((t + 255) / 256); };
-    if (full(rows * (F / 256)) && full(rows * (D / 128))) return 256;
-  }
-  // the second product is a long contraction of activations from F = kQuarterK on: of the kernels with 128-row tiles only the
-  // direct-to-LDS ones take it (they keep the running sum of its four runs)
-  return F >= kQuarterK && !direct ? 64 : 128;
+  if (!p.tile_map && (p.src_row || p.force_bm)) return kTileNone;
+  return direct_tile(amode, epi, p.M, p.N, p.K, p.hd, p.tile_map ? p.force_bm : 0, p.parts && p.Cb);
 }
 
 template <int AM, int EP, typename S>
@@ -549,21 +481,27 @@ static hipError_t launch_shape(const GemmP& p, hipStream_t st) {
 
 template <int AM, int EP>
 static hipError_t launch_tile(DirectTile tile, const GemmP& p, hipStream_t st) {
-  if constexpr (AM == A_ACT) {
+  if constexpr (has_direct_kernel(AM, EP, kTile256x128)) {
     if (tile == kTile256x128) return launch_shape<AM, EP, Wide256x128>(p, st);
-    const long t128 = (long)((p.M + 127) / 128) * (p.N / 128);
-    if (tile == kTile128 && !p.tile_map && t128 <= 256 && p.K >= 256) return launch_shape<AM, EP, Wide128Deep>(p, st);
-  } else if constexpr (EP != EP_STORE) {
+  }
+  if constexpr (has_direct_kernel(AM, EP, kTile256)) {
     if (tile == kTile256) return launch_shape<AM, EP, Wide256>(p, st);
+  }
+  if constexpr (has_direct_kernel(AM, EP, kTile128x256)) {
+    if (tile == kTile128x256) return launch_shape<AM, EP, Wide128x256>(p, st);
+  }
+  if constexpr (has_direct_kernel(AM, EP, kTile128x64)) {
     if (tile == kTile128x64) {
       const long t = (long)((p.M + 127) / 128) * (p.N / 64);
       return t <= 512 && p.K >= 256 ? launch_shape<AM, EP, Wide128x64Deep>(p, st) : launch_shape<AM, EP, Wide128x64>(p, st);
     }
-    if constexpr (EP == EP_QKV) {
-      if (tile == kTile128x256) return launch_shape<AM, EP, Wide128x256>(p, st);
-    }
   }
-  return tile == kTile128 ? launch_shape<AM, EP, Wide128>(p, st) : hipErrorInvalidValue;
+  if (tile != kTile128) return hipErrorInvalidValue;
+  if constexpr (AM == A_ACT) {
+    const long t128 = (long)((p.M + 127) / 128) * (p.N / 128);
+    if (!p.tile_map && t128 <= 256 && p.K >= 256) return launch_shape<AM, EP, Wide128Deep>(p, st);
+  }
+  return launch_shape<AM, EP, Wide128>(p, st);
 }
 
 hipError_t launch_gemm_wide(int amode, int epi, DirectTile tile, const GemmP& p, hipStream_t st) {

@@ -7,6 +7,7 @@
 #include <thread>
 #include <vector>
 
+#include "gemm_tiles.h"
 #include "small_round_plan.h"
 #include "tsd.h"
 
@@ -34,21 +35,6 @@ __device__ __forceinline__ float gelu_tanh(float z) {
   return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(q));
 }
 #endif
-
-// ---- A-operand sources and epilogues of the fused GEMM family ------------------------------
-enum AMode {
-  A_TOK = 0,   // fp32 patches gathered from two per-series segments (patch embedding)
-  A_NORM = 1,  // fp32 residual stream; RMSNorm applied as a per-row scale of the product
-  A_ACT = 2,   // activations already in the compute dtype
-  A_NORM32 = 3 // like A_NORM but reads the fp32 residual itself (output head; split hi+lo in bf16 mode)
-};
-enum Epi {
-  EP_STORE = 0,  // x = C                       (fp32)
-  EP_RESID = 1,  // x += C                      (fp32 residual stream)
-  EP_GELU = 2,   // h = GELU_tanh(C)            (compute dtype)
-  EP_QKV = 3,    // RoPE on q,k; q -> buffer, k,v -> paged KV cache
-  EP_HEAD = 4    // mu = C, fp32, scattered to [series][token - t_skip]
-};
 
 struct GemmP {
   int M, N, K;
@@ -129,21 +115,13 @@ struct AttnP {
 // ---- launchers (each returns the hipError_t of the launch) ---------------------------------
 hipError_t launch_gemm(int dtype, int amode, int epi, const GemmP& p, hipStream_t st);
 hipError_t prepare_gemm(int dtype);
-// bf16 products of activations with K >= kQuarterK are summed in four runs of k-steps (see gemm.hip)
-constexpr int kQuarterK = 1024;
-// ... and, where every run is at least as long as a tile's ring, the runs can be workgroups of their own (gemm_direct64.hip)
-constexpr bool split_runs(int K) { return K >= kQuarterK && K % 64 == 0 && K / 64 - 3 * ((K / 64 + 3) / 4) >= 4; }
-constexpr int kRunTiles = 112;  // 64 x 64 tiles of such a product at most
 // skinny path (at most 32 rows): see gemm_skinny.hip
 bool skinny_applicable(int dtype, int amode, int epi, const GemmP& p);
 bool skinny_as_tiles(int amode, int epi, const GemmP& p);
 constexpr int skinny_shares(int K) { return K >= 512 ? 16 : 4; }  // wavefronts that share a contraction
 hipError_t launch_gemm_skinny(int amode, int epi, const GemmP& p, hipStream_t st);
-int gemm_row_tile(int dtype, int M, int N, int force_bm);
 // direct-to-LDS kernels (gemm_direct64.hip, gemm_wide.hip): the tile for this product, or kTileNone for the register-staged kernels
-enum DirectTile { kTileNone = 0, kTile64 = 64, kTile128x64 = 127, kTile128 = 128, kTile128x256 = 129, kTile256x128 = 256, kTile256 = 257, kTileRuns = 464 };
 DirectTile gemm_direct_tile(int dtype, int amode, int epi, const GemmP& p);
-int routed_row_tile(int dtype, int slots, int D, int F, int E, bool no_wide);
 hipError_t launch_gemm_f32(int amode, int epi, const GemmP& p, hipStream_t st);  // (gemm_f32.hip: every fp32 product)
 hipError_t launch_gemm_direct64(int amode, int epi, const GemmP& p, hipStream_t st);
 hipError_t prepare_gemm_direct64();

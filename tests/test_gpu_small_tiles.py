@@ -9,11 +9,16 @@ from synth import ModelCfg
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,N,K,variant", [
-    (1, 64, 256, 1), (63, 192, 256, 3), (64, 128, 320, 2), (65, 64, 512, 0),     # shortest contraction (no steady k-tile), ragged rows
-    (558, 2304, 768, 1), (1281, 2048, 512, 3), (4097, 320, 384, 2),              # a last tile of one row, columns of no 128-multiple
-    (1025, 1024, 1024, 2), (1030, 1024, 4096, 0), (4160, 448, 1088, 2),          # four runs of k-tiles (one tile more than the split takes)
-])
+# rows, columns, k, variant of tsd_bench_gemm, the tile they take (tests/test_gemm_tiles.py holds the rule to it)
+PRODUCTS = [
+    (1, 64, 256, 1, 64), (63, 192, 256, 3, 64), (64, 128, 320, 2, 64), (65, 64, 512, 0, 64),   # shortest contraction (no steady k-tile), ragged rows
+    (558, 2304, 768, 1, 64), (65, 2048, 512, 3, 64), (4097, 320, 384, 2, 64),                  # a last tile of one row, columns of no 128-multiple
+    (1281, 2048, 512, 3, 127),                                                                 # (one 64 x 64 tile too many: 128 x 64)
+    (1025, 1024, 1024, 2, 64), (1030, 1024, 4096, 0, 64), (4160, 448, 1088, 2, 64),            # four runs of k-tiles (one tile more than the split takes)
+]
+
+
+@pytest.mark.parametrize("M,N,K,variant", [p[:4] for p in PRODUCTS])
 def test_small_direct_tiles_same_bits_as_register_staged_and_fp64(M, N, K, variant):
     g = torch.Generator().manual_seed(M + N + K + variant)
     A = torch.randn(M, K, generator=g).to(torch.bfloat16).cuda()

@@ -8,16 +8,19 @@ from synth import ModelCfg
 
 pytestmark = pytest.mark.gpu
 QKV, GELU = 1, 4  # TSD_K_QKV, TSD_K_GELU
+# rows, columns, k, variant of tsd_bench_gemm, the tile they take (tests/test_gemm_tiles.py holds the rule to it)
+PRODUCTS = [
+    (6529, 2048, 192, 3, 257), (13057, 1024, 256, 3, 257), (6401, 2048, 192, 3, 257),   # 256 x 256: three k-tiles, a last tile of one row
+    (321, 4096, 192, 3, 127), (321, 4096, 256, 3, 127), (1281, 4160, 320, 3, 127),      # 128 x 64: two stages, three, columns of no 128-multiple
+    (6401, 1152, 192, 3, 128), (4097, 3200, 512, 3, 128), (4480, 1024, 2048, 1, 128),   # 128 x 128 behind the norm, long too
+    (4500, 768, 512, 2, 128), (2817, 1280, 1088, 0, 128),                               # 128 x 128 with three stages, four runs of k-tiles
+    (4500, 768, 256, 2, 64),                                                            # ... too short for them
+    (6529, 1024, 512, 2, 128), (16300, 384, 192, 0, 128),                               # ... with two
+    (4400, 1024, 2112, 2, 256), (8999, 512, 2048, 0, 256),                              # 256 x 128: 33 k-tiles, runs of unequal length
+]
 
 
-@pytest.mark.parametrize("M,N,K,variant", [
-    (6529, 2048, 192, 3), (13057, 1024, 256, 3),                              # 256 x 256: three k-tiles, a last tile of one row
-    (321, 4096, 192, 3), (321, 4096, 256, 3), (1281, 4160, 320, 3),           # 128 x 64: two stages, three, columns of no 128-multiple
-    (6401, 2048, 192, 3), (4097, 3200, 512, 3),                               # 128 x 128 behind the norm
-    (4500, 768, 256, 2), (2817, 1280, 1088, 0),                               # 128 x 128 with three stages, four runs of k-tiles
-    (6529, 1024, 512, 2), (16300, 384, 192, 0),                               # ... with two
-    (4400, 1024, 2112, 2), (8999, 512, 2048, 0),                              # 256 x 128: 33 k-tiles, runs of unequal length
-])
+@pytest.mark.parametrize("M,N,K,variant", [p[:4] for p in PRODUCTS])
 def test_wide_tiles_same_bits_as_register_staged_and_fp64(M, N, K, variant):
     g = torch.Generator().manual_seed(M + N + K + variant)
     A = torch.randn(M, K, generator=g).to(torch.bfloat16).cuda()
@@ -32,8 +35,10 @@ def test_wide_tiles_same_bits_as_register_staged_and_fp64(M, N, K, variant):
     rows = torch.cat([torch.arange(0, 300), torch.arange(M - 300, M)])
     a, w = A.cpu().double()[rows], W.cpu().double()
     ref = a @ w.T
+    if variant in (1, 3):
+        ref = ref * torch.rsqrt((a * a).mean(-1, keepdim=True) + 1e-6)
     if variant == 3:
-        ref = torch.nn.functional.gelu(ref * torch.rsqrt((a * a).mean(-1, keepdim=True) + 1e-6), approximate="tanh")
+        ref = torch.nn.functional.gelu(ref, approximate="tanh")
     if variant == 2:
         ref = ref + 0.5
     err = (outs[0][rows].double() - ref).abs().max() / ref.abs().max()
