@@ -112,9 +112,9 @@ typedef struct {
  * One size for one arena: the KV pools and the scratch share an allocation the caller makes
  * once, instead of a KV size and a scratch size for two; the library carves it (256-byte
  * aligned parts) and never allocates device memory itself.  The activation workspace counts in for as many rows as a context
- * pass of the whole batch has, up to 16384 (256 series of 42 tokens through 8 layers of 512: 99 of 393 MB; 512 of 200 through 16 routed layers of
+ * pass of the whole batch has, up to 16384 (256 series of 42 tokens through 8 layers of 512: 99 of 400 MB; 512 of 200 through 16 routed layers of
  * 768: 529 of 7300), and so does what the resident decode kernel of small handles needs (one series through 24 layers of 1024: 15 of
- * 634 MB); tsd_create takes smaller arenas too.
+ * 642 MB) and 7 MB for partial sums where a product takes them; tsd_create takes smaller arenas too.
  * Host-only; never touches the GPU. */
 int tsd_workspace_bytes(const tsd_config* cfg, size_t* bytes_host);
 
@@ -129,8 +129,8 @@ int tsd_weights_count(const tsd_config* cfg, int which, size_t* n_floats_host);
  * tsd_workspace_bytes for full speed).  The arena must outlive the handle.  Fills the rotary tables
  * (synchronous host-to-device copies).  A smaller arena is taken, with the same results, as long as it holds the weights, caches
  * and state and the rows of one round or of one context, whichever are more
- * (305 MB of the 393 above): contexts then run in more passes, and
- * without the resident kernel where that does not fit either.  Smaller still: TSD_E_INVALID_ARG. */
+ * (305 MB of the 400 above): contexts then run in more passes, and
+ * without the partial sums and the resident kernel where those do not fit either.  Smaller still: TSD_E_INVALID_ARG. */
 int tsd_create(const tsd_config* cfg, void* arena_dev, size_t arena_bytes, tsd_ctx** out);
 
 /* Release the handle (host memory only).  Synchronises the device first. */

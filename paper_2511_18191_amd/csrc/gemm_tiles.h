@@ -25,6 +25,11 @@ constexpr int kQuarterK = 1024;
 // ... and, where every run is at least as long as a tile's ring, the runs can be workgroups of their own (gemm_direct64.hip)
 constexpr bool split_runs(int K) { return K >= kQuarterK && K % 64 == 0 && K / 64 - 3 * ((K / 64 + 3) / 4) >= 4; }
 constexpr int kRunTiles = 112;  // 64 x 64 tiles of such a product at most
+// From K = 2048 on a workgroup per run is faster than any other way while all of them are resident together, two per compute unit,
+// with room to spare (split workgroups of gemm.hip / a workgroup per run, us: 256x512x2048 9.9 / 7.0, 768x512x2048, 96 tiles, 10.2 / 10.0;
+// 256x768x3072 13.4 / 8.8, 558x768x3072, 108, 13.7 / 12.2, 768x768x3072, 144, 13.7 / 15.6; 320x1024x4096, 80, 16.7 / 11.5, 558, 144,
+// 17.0 / 17.1); shorter ones gain nothing (256x1024x1024 6.95 / 7.04).
+constexpr bool takes_runs(int N, int K, int M) { return K >= 2048 && split_runs(K) && N % 64 == 0 && (long)((M + 63) / 64) * (N / 64) <= kRunTiles; }
 // The tiles of the direct-to-LDS kernels (gemm_direct64.hip, gemm_wide.hip); kTileNone: the register-staged kernels (gemm.hip).
 enum DirectTile { kTileNone = 0, kTile64 = 64, kTile128x64 = 127, kTile128 = 128, kTile128x256 = 129, kTile256x128 = 256, kTile256 = 257, kTileRuns = 464 };
 
@@ -68,11 +73,7 @@ inline DirectTile direct_tile(int amode, int epi, int M, int N, int K, int hd, i
   // Long contractions with at most one 64 x 64 tile per compute unit are latency-bound chains of k-steps, where four groups of
   // wavefronts that stream a quarter of K each (gemm.hip) are faster: 1280x512x2048 10.2 split, 11.5 here; 512x1024x4096 17.2 / 18.9.
   const bool split = amode == A_ACT && K >= kQuarterK && t64 <= 256;
-  // From K = 2048 on a workgroup per run (gemm_runs_kernel) is faster still while all of them are resident together, two per compute unit,
-  // with room to spare (split workgroups / a workgroup per run: 256x512x2048 9.9 / 7.0, 768x512x2048, 96 tiles, 10.2 / 10.0; 256x768x3072
-  // 13.4 / 8.8, 558x768x3072, 108, 13.7 / 12.2, 768x768x3072, 144, 13.7 / 15.6; 320x1024x4096, 80, 16.7 / 11.5, 558, 144, 17.0 / 17.1);
-  // shorter ones gain nothing (256x1024x1024 6.95 / 7.04).
-  if (split && t64 <= kRunTiles && runs && epi == EP_RESID && K >= 2048 && split_runs(K) && N % 64 == 0) return kTileRuns;
+  if (split && runs && epi == EP_RESID && takes_runs(N, K, M)) return kTileRuns;
   const DirectTile narrow = !split && K >= 256 && N % 64 == 0 ? kTile64 : kTileNone;
   if (amode == A_NORM && epi != EP_STORE) {
     const bool heads64 = epi != EP_QKV || hd == 64;  // (one rotary pair of blocks per 64 columns of a wavefront)

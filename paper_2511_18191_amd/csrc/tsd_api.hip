@@ -232,7 +232,12 @@ Layout full_layout(const tsd_config& c) {
   long want = std::min((long)c.max_batch * c.max_tokens, kContextRows);
   for (const tsd_model_cfg* m : {&c.target, &c.draft})
     if (m->n_experts > 0) want = std::min(want, (long)kMaxSortSlots / m->top_k);
-  return Layout{std::max(least_rows(c), (size_t)std::max(want, 0L)), true, small_round_ok(c), c.dtype == TSD_BF16 && !(c.flags & TSD_FLAG_NO_WIDE_GEMM)};
+  // (a model's output projection, or a dense one's FFN down, long enough for a workgroup per run)
+  bool runs = false;
+  for (const tsd_model_cfg* m : {&c.target, &c.draft})
+    for (const int k : {m->d_model, m->n_experts > 0 ? 0 : m->d_ff}) runs = runs || takes_runs(m->d_model, k, 1);
+  runs = runs && c.dtype == TSD_BF16 && !(c.flags & TSD_FLAG_NO_WIDE_GEMM);
+  return Layout{std::max(least_rows(c), (size_t)std::max(want, 0L)), true, small_round_ok(c), runs};
 }
 
 struct Carver {
@@ -413,14 +418,14 @@ size_t carve(const tsd_config& c, const Layout& lay, tsd_ctx* ctx) {
   return (cv.off + 255) & ~(size_t)255;
 }
 
-// The layout for an arena of `bytes`: the full one where it fits (tsd_workspace_bytes asks for it), else without what costs speed
-// only, as many rows as fit.  False: not even the least does.
+// The layout for an arena of `bytes`: the full one where it fits (tsd_workspace_bytes asks for it), else with fewer rows, then also without
+// what costs speed only, the largest part first; as many rows as fit.  False: not even the least does.
 bool layout_for(const tsd_config& c, size_t bytes, Layout* lay) {
   *lay = full_layout(c);
   if (carve(c, *lay, nullptr) <= bytes) return true;
   const size_t most = lay->rows, least = least_rows(c);
-  const bool resident = lay->resident;
-  for (const Layout& l : {Layout{least, true, resident, false}, Layout{least, true, false, false}, Layout{least, false, false, false}}) {
+  const bool resident = lay->resident, runs = lay->runs;
+  for (const Layout& l : {Layout{least, true, resident, runs}, Layout{least, true, resident, false}, Layout{least, true, false, false}, Layout{least, false, false, false}}) {
     *lay = l;
     if (carve(c, *lay, nullptr) > bytes) continue;
     for (size_t step = most - least; lay->rows < most && step > 0; step /= 2)  // (more rows never take less)

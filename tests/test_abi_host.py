@@ -155,3 +155,22 @@ def test_arenas_of_the_former_size_are_accepted(name, before):
     assert L.tsd_create(C.byref(cfg), 0x1000, n.value, C.byref(h)) not in (0, refused)
     assert L.tsd_create(C.byref(cfg), 0x1000, before, C.byref(h)) not in (0, refused)
     assert L.tsd_create(C.byref(cfg), 0x1000, before - 256, C.byref(h)) == refused and b"arena" in L.tsd_last_error(None)
+
+
+@pytest.mark.parametrize("target,takes", [
+    ((8, 512, 8, 2048), True), ((4, 256, 4, 2112), True),          # FFN down of K = 2048 and more
+    ((8, 512, 8, 1984), False), ((2, 2048, 32, 1024), True),       # too short; an output projection of K = 2048
+    ((8, 512, 8, 2304, 4, 2), False), ((8, 480, 15, 2048), False),  # routed; columns that are no whole tiles
+])
+def test_room_for_partial_sums_only_where_a_product_takes_them(target, takes):
+    L, n = tsd.lib(), C.c_size_t()
+
+    def size(dtype, flags):
+        cfg = tsd.make_config(synth.ModelCfg(*target), synth.ModelCfg(2, 256, 4, 1024), 96, 4, 64, 40, dtype, 1.0, flags=flags)
+        assert L.tsd_workspace_bytes(C.byref(cfg), C.byref(n)) == 0, L.tsd_last_error(None)
+        return n.value
+
+    # four runs of 112 tiles of 64 x 64 fp32 sums, and a counter per tile
+    room = 4 * 112 * 64 * 64 * 4 + 512
+    assert size("bf16", 0) - size("bf16", tsd.TSD_FLAG_NO_WIDE_GEMM) == (room if takes else 0)
+    assert size("fp32", 0) == size("fp32", tsd.TSD_FLAG_NO_WIDE_GEMM)

@@ -1,5 +1,7 @@
 """The 64 x 64 direct-to-LDS tiles (products that leave less than a 128-row tile per compute unit) against the
 register-staged tiles, bit for bit, and against float64."""
+import ctypes as C
+
 import pytest
 import torch
 
@@ -76,3 +78,35 @@ def test_runs_of_a_contraction_in_workgroups_of_their_own(D, F, B):
     assert torch.isfinite(res[0]).all()
     for other in res[1:]:
         assert torch.equal(res[0], other)
+
+
+def test_arenas_too_small_for_all_rows_keep_the_runs():
+    """The partial sums go after the context's rows: an arena a little short of the full size still takes them, the least one does without."""
+    P, N, T, K, B, D, F = 16, 20, 4, 2, 100, 256, 2048
+    m, d = ModelCfg(2, D, D // 64, F), ModelCfg(1, 64, 1, 96)
+    g = torch.Generator().manual_seed(5)
+    w = (torch.randn(P * D + 2 * (2 * D + 4 * D * D + 2 * D * F) + D + D * P, generator=g) * 0.05).bfloat16().float().cuda()
+    series = torch.randn(B, N * P, generator=g).cuda()
+    sess = tsd.Session(tsd.make_config(m, d, P, K, B, N + T + K, "bf16", 1.0, seed=3))
+    full, base = sess.arena_bytes, (sess.arena.data_ptr() + 255) & ~255
+    room = 4 * 112 * 64 * 64 * 4 + 512
+    rows = (B * (N + T + K) - B * (K + 1)) * (4 * D + 3 * 2 * D + 2 * F + 8)   # what the contexts' rows take beyond a round's
+    res = []
+    for size, tile in ((full, 2464), (full - 256, 2464), ((full - rows // 2) // 256 * 256, 2464), ((full - rows - room // 2) // 256 * 256, 464)):
+        sess.close()
+        h = C.c_void_p()
+        assert tsd.lib().tsd_create(C.byref(sess.cfg), base, size, C.byref(h)) == 0
+        sess.h = h
+        sess.load_weights(tsd.TSD_TARGET, w)
+        sess.load_weights(tsd.TSD_DRAFT, torch.zeros(P * 64 + 2 * 64 + 4 * 64 * 64 + 2 * 64 * 96 + 64 + 64 * P))
+        sess.prefill(series, N, T * P)
+        sess.profile_begin(3)  # TSD_K_RESID
+        sess.target_step()
+        sess.profile_end()
+        assert {r["tile"] for r in sess.profile_launches() if r["K"] == F} == {tile}, size
+        for _ in range(T - 1):
+            sess.target_step()
+        res.append(sess.get_forecast().cpu())
+    sess.close()
+    for other in res:
+        assert torch.isfinite(other).all() and torch.equal(res[0], other)
