@@ -48,6 +48,7 @@ def test_small_direct_tiles_same_bits_as_register_staged_and_fp64(M, N, K, varia
 @pytest.mark.parametrize("D,F,B", [
     (512, 2048, 33), (512, 2112, 65), (256, 2560, 250), (512, 2048, 896),   # runs of unequal length, a last row tile of one row, most tiles
     (768, 3072, 100), (512, 2048, 897), (512, 2176, 64),                    # ... one tile too many, a last run of 4 k-tiles
+    (2048, 256, 97), (2048, 256, 193),                                      # an output projection of K = 2048: two row tiles, too many
 ])
 def test_runs_of_a_contraction_in_workgroups_of_their_own(D, F, B):
     """FFN down of few rows: four workgroups per tile, whichever finishes last adds their sums.  Bit for bit the handle without them, over
@@ -67,12 +68,47 @@ def test_runs_of_a_contraction_in_workgroups_of_their_own(D, F, B):
         sess.profile_begin(3)  # TSD_K_RESID
         sess.target_step()
         sess.profile_end()
-        tiles = {r["tile"] for r in sess.profile_launches() if r["K"] == F}
+        tiles = {r["tile"] for r in sess.profile_launches() if r["K"] == max(D, F)}
         assert tiles == {464 if flags or (B + 63) // 64 * (D // 64) > 112 else 2464}, tiles
         for _ in range(3):
             sess.prefill(series, N, T * P)
             for _ in range(T):
                 sess.target_step()
+            res.append(sess.get_forecast().cpu())
+        sess.close()
+    assert torch.isfinite(res[0]).all()
+    for other in res[1:]:
+        assert torch.equal(res[0], other)
+
+
+@pytest.mark.parametrize("D,F,B", [(256, 2048, 150), (512, 2048, 90)])
+def test_runs_capped_on_the_device_while_series_finish(D, F, B):
+    """Rounds without a look at the counts between them: launches sized for the whole batch, rows capped by the count on the device as
+    series finish at different times.  Bit for bit the handle that neither compacts nor takes the runs."""
+    P, N, T, K = 16, 5, 9, 2
+    m = ModelCfg(2, D, D // 64, F)
+    g = torch.Generator().manual_seed(D + B)
+    w = (torch.randn(P * D + 2 * (2 * D + 4 * D * D + 2 * D * F) + D + D * P, generator=g) * 0.05).bfloat16().float().cuda()
+    series = torch.randn(B, N * P, generator=g).cuda()
+    res = []
+    for flags in (0, tsd.TSD_FLAG_NO_GRAPH, tsd.TSD_FLAG_NO_COMPACT | tsd.TSD_FLAG_NO_WIDE_GEMM):
+        sess = tsd.Session(tsd.make_config(m, ModelCfg(1, 64, 1, 96), P, K, B, N + T + K, "bf16", 1.0, seed=3, flags=flags))
+        sess.load_weights(tsd.TSD_TARGET, w)
+        sess.load_weights(tsd.TSD_DRAFT, torch.zeros(P * 64 + 2 * 64 + 4 * 64 * 64 + 2 * 64 * 96 + 64 + 64 * P))
+        sess.set_accept_override(0.5)
+        for polled in (True, False):
+            sess.prefill(series, N, T * P)
+            sess.profile_begin(3)  # TSD_K_RESID
+            sess.round()
+            sess.profile_end()
+            tiles = {r["tile"] for r in sess.profile_launches() if r["K"] == F}
+            assert tiles == {464 if flags & tsd.TSD_FLAG_NO_WIDE_GEMM else 2464}, tiles
+            left = {sess.num_active()}
+            for _ in range(T):
+                sess.round()
+                if polled:
+                    left.add(sess.num_active())
+            assert sess.num_active() == 0 and (not polled or len(left) > 3), left
             res.append(sess.get_forecast().cpu())
         sess.close()
     assert torch.isfinite(res[0]).all()

@@ -7,7 +7,7 @@ import paper_2511_18191_amd as tsd
 from synth import ModelCfg
 
 pytestmark = pytest.mark.gpu
-QKV, GELU = 1, 4  # TSD_K_QKV, TSD_K_GELU
+QKV, RESID, GELU = 1, 3, 4  # TSD_K_QKV, TSD_K_RESID, TSD_K_GELU
 # rows, columns, k, variant of tsd_bench_gemm, the tile they take (tests/test_gemm_tiles.py holds the rule to it)
 PRODUCTS = [
     (6529, 2048, 192, 3, 257), (13057, 1024, 256, 3, 257), (6401, 2048, 192, 3, 257),   # 256 x 256: three k-tiles, a last tile of one row
@@ -91,14 +91,16 @@ def test_grouped_products_on_256_row_maps_same_bits_as_register_staged(D, F, E, 
         sess = tsd.Session(tsd.make_config(target, draft, P, K, B, N + T + K, "bf16", 1.0, seed=3, flags=flags))
         sess.load_weights(tsd.TSD_TARGET, w[0].cuda())
         sess.load_weights(tsd.TSD_DRAFT, w[1].cuda())
-        sess.profile_begin(GELU)
+        sess.profile_begin(9)  # TSD_K_COUNT
         sess.prefill(series.cuda(), N, T * P)
         sess.profile_end()
-        used.append({r["tile"] for r in sess.profile_launches()})
+        # the experts' products: their rows are the assignments
+        used.append({(r["kernel_class"], r["tile"]) for r in sess.profile_launches() if r["model"] == tsd.TSD_TARGET
+                     and r["M"] == B * (N - 1) * k and (r["kernel_class"] == GELU or r["K"] == F)})
         sess.round()
         io = sess.get_round_io()
         res.append({x: io[x].cpu() for x in ("X", "mu_p")})
         sess.close()
-    assert 2257 in used[0] and not any(t > 2000 for t in used[1]), used
+    assert used[0] == {(GELU, 2257), (RESID, 2256)} and len(used[1]) == 2 and not any(t > 2000 for _, t in used[1]), used
     for x in res[0]:
         assert torch.isfinite(res[0][x]).all() and torch.equal(res[0][x], res[1][x]), x
