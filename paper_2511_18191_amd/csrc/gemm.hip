@@ -72,8 +72,7 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
   }
 
   // ---- A loader set-up ----------------------------------------------------------------------
-  constexpr bool kASrcF32 = (AM == A_TOK) || (AM == A_NORM32);  // source rows are fp32 (the others: the bf16 shadow of the residual)
-  constexpr int CHA = kASrcF32 ? 4 : 8;              // elements per 16-byte chunk
+  constexpr int CHA = kSplit ? 4 : 8;                // elements per 16-byte chunk
   constexpr int CPRA = BK / CHA;                     // chunks per tile row
   constexpr int NA = BM * CPRA / 256;
   static_assert(NA >= 1, "tile too small for 256 threads");
@@ -97,7 +96,7 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
         const float* src = (t < p.n0) ? p.src0 + (long)b * p.stride0 + (long)t * K
                                       : p.src1 + (long)b * p.stride1 + (long)(t - p.n0) * K;
         arow[i] = reinterpret_cast<const char*>(src);
-      } else if constexpr (kASrcF32) {
+      } else if constexpr (kSplit) {
         arow[i] = reinterpret_cast<const char*>(reinterpret_cast<const float*>(p.A) + (long)gm * K);
       } else {
         arow[i] = reinterpret_cast<const char*>(reinterpret_cast<const T*>(p.A) + (long)gm * K);
@@ -131,7 +130,7 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
       const int k = min(kt * BK + a_kc[i] * CHA, K - CHA);
-      xa[i] = *reinterpret_cast<const uint4*>(arow[i] + (long)k * (kASrcF32 ? 4 : 2));
+      xa[i] = *reinterpret_cast<const uint4*>(arow[i] + (long)k * (kSplit ? 4 : 2));
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
@@ -144,16 +143,12 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
     for (int i = 0; i < NA; ++i) {
       T* dst = As + ((buf * NAS) * BM + a_r[i]) * LDT + a_kc[i] * CHA;
       if (kt * BK + a_kc[i] * CHA >= K) ra[i] = make_uint4(0, 0, 0, 0);
-      if constexpr (kASrcF32) {
+      if constexpr (kSplit) {
         float4 f = *reinterpret_cast<float4*>(&ra[i]);
         if constexpr (kNorm) ss[i] += f.x * f.x + f.y * f.y + f.z * f.z + f.w * f.w;
-        if constexpr (kSplit) {
-          const float4 hi = make_float4((float)(bf16)f.x, (float)(bf16)f.y, (float)(bf16)f.z, (float)(bf16)f.w);
-          store4<bf16>(reinterpret_cast<bf16*>(dst), hi);
-          store4<bf16>(reinterpret_cast<bf16*>(dst + BM * LDT), make_float4(f.x - hi.x, f.y - hi.y, f.z - hi.z, f.w - hi.w));
-        } else {
-          store4<bf16>(reinterpret_cast<bf16*>(dst), f);
-        }
+        const float4 hi = make_float4((float)(bf16)f.x, (float)(bf16)f.y, (float)(bf16)f.z, (float)(bf16)f.w);
+        store4<bf16>(reinterpret_cast<bf16*>(dst), hi);
+        store4<bf16>(reinterpret_cast<bf16*>(dst + BM * LDT), make_float4(f.x - hi.x, f.y - hi.y, f.z - hi.z, f.w - hi.w));
       } else {
         if constexpr (kNorm) {
           // a chain of packed bf16 dot products per 16-byte chunk position: the direct-to-LDS kernels (gemm_direct64.hip)
@@ -324,13 +319,7 @@ __global__ __launch_bounds__(256 * G) void gemm_kernel(const GemmP p) {
   }
 
   // ---- epilogue, 64 rows at a time through LDS ----------------------------------------------
-  auto read_c1 = [&](int row, int col) {  // one element / four consecutive elements of the product
-    float v = Cs[row * LDC + col];
-#pragma unroll
-    for (int g = 1; g < G; ++g) v += Cs[(g * 64 + row) * LDC + col];
-    return v;
-  };
-  auto read_c4 = [&](int row, int col) {
+  auto read_c4 = [&](int row, int col) {  // four consecutive elements of the product
     float4 v = *reinterpret_cast<const float4*>(Cs + row * LDC + col);
 #pragma unroll
     for (int g = 1; g < G; ++g) {
