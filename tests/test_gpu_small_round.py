@@ -203,7 +203,11 @@ def test_a_capture_of_the_callers_goes_on():
     torch.cuda.synchronize()
     x = torch.zeros(8, device="cuda")
     graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph, capture_error_mode="global"):
+    # (torch deals its streams out of a ring of 32: the one it captures on by default may be a session's)
+    own = torch.cuda.Stream()
+    while own.cuda_stream in [s.stream.cuda_stream for s in sess]:
+        own = torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=own, capture_error_mode="global"):
         x += 1
         for _ in range(c.T):
             for s in sess:
