@@ -22,6 +22,7 @@
 //     same instruction, so all kernels give the same bits and the launcher may pick any by the product's shape.
 #include "direct_lds.h"
 #include "gemm_epilogue.h"
+#include "tile_order.h"
 
 namespace tsd {
 
@@ -365,18 +366,8 @@ __global__ __launch_bounds__(d64::NT, 2) void gemm_direct64_kernel(const GemmP p
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   // rows of the product: fixed at launch, or capped by a device-side series count (workgroups past the cap leave)
   const int M = p.n_dev ? min(p.M, *p.n_dev * p.nq) : p.M;
-  // tile order: every XCD walks one contiguous run of the tile list, the list ordered in groups of 8 tile columns
-  // walked row by row (see gemm.hip)
-  const int tiles_m = (M + BM - 1) / BM, tiles_n = p.N / BN;
-  const int n_tiles = tiles_m * tiles_n;
-  const int per_xcd = (n_tiles + 7) >> 3;
-  if ((int)(blockIdx.x >> 3) >= per_xcd) return;
-  const int lin = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (lin >= n_tiles) return;
-  constexpr int GW = 8;
-  const int gc = lin / (GW * tiles_m), rem = lin - gc * (GW * tiles_m);
-  const int gw = min(GW, tiles_n - gc * GW);
-  const int tm = rem / gw, tn = gc * GW + rem - tm * gw;
+  int tm, tn;
+  if (!own_tile((M + BM - 1) / BM, p.N / BN, tm, tn)) return;
   const int m0 = tm * BM, n0 = tn * BN;
   tile64<AM, EP, SUMS>(p, p.K, M, m0, n0, smem);
 }

@@ -11,6 +11,7 @@
 //   * LDS rows are BK + 4 words: 16-byte writes, and the fragment reads (16 rows, four consecutive k) fall on all 64 banks.
 #include "tsd_internal.h"
 #include "gemm_epilogue.h"
+#include "tile_order.h"
 
 namespace tsd {
 
@@ -43,18 +44,8 @@ __global__ __launch_bounds__(f32::NT) void gemm_f32_kernel(const GemmP p) {
   // is replayed from a graph while series finish (workgroups past the cap leave at once)
   const int M = p.n_dev ? min(p.M, *p.n_dev * p.nq) : p.M;
   const int N = p.N, K = p.K;
-  // tile order: every XCD walks one contiguous run of the tile list, the list ordered in groups of 8 tile columns
-  // walked row by row (see gemm.hip)
-  const int tiles_m = p.tile_map ? reinterpret_cast<const int4*>(p.tile_map)[p.n_mtiles].x : (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  const int n_tiles = tiles_m * tiles_n;
-  const int per_xcd = (n_tiles + 7) >> 3;
-  if ((int)(blockIdx.x >> 3) >= per_xcd) return;
-  const int lin = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (lin >= n_tiles) return;
-  constexpr int GW = 8;
-  const int gc = lin / (GW * tiles_m), rem = lin - gc * (GW * tiles_m);
-  const int gw = min(GW, tiles_n - gc * GW);
-  const int tm = rem / gw, tn = gc * GW + rem - tm * gw;
+  int tm, tn;
+  if (!own_tile(row_tiles<BM>(p, M), (N + BN - 1) / BN, tm, tn)) return;
   int m0 = tm * BM, m_lim = M;
   const int n0 = tn * BN;
   const float* W = reinterpret_cast<const float*>(p.W);
