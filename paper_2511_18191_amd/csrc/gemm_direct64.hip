@@ -9,7 +9,7 @@
 // 2 % slower in a whole pass of 93 series, where the weights come from HBM; six (one workgroup) is 10 % slower.
 //
 //   * A stage is its rows back to back (A rows, then B rows), 128 bytes per row; the eight 16-byte chunks of a row
-//     sit at chunk ^ ((row >> 1) & 7), which makes the fragment reads (32 consecutive rows, one chunk) conflict-free
+//     sit at chunk ^ ((row >> 1) & 7), which makes the fragment reads (32 consecutive rows, one chunk; or 16 and two) conflict-free
 //     without padding.  A load instruction fills 1 KB = 8 rows; lane l fetches the chunk that belongs at l.
 //   * A wavefront owns one contiguous run of every stage and addresses its loads through the instruction's immediate
 //     offset around one base, so M0 (the LDS base of such a load) is written once per k-tile.
@@ -20,6 +20,7 @@
 //     16-byte chunk position of a 64-wide k-run, each a chain of packed bf16 dot products, combined as
 //     ((P0 + P4) + (P2 + P6)) + ((P1 + P5) + (P3 + P7)).  The products accumulate k in the same order with the
 //     same instruction, so all kernels give the same bits and the launcher may pick any by the product's shape.
+//     (Contexts of small handles have the sums of gemm_skinny.hip instead: kShares.)
 #include "direct_lds.h"
 #include "gemm_epilogue.h"
 #include "tile_order.h"
@@ -39,7 +40,6 @@ constexpr int BIAS = REGION / 2;                  // M0 points here inside the r
 constexpr int LDC = BN + 4;
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kSc1 = 16;  // cache policy of what workgroups hand each other: agent scope
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr size_t SMEM = (size_t)NS * STAGE + BM * 12;  // stages, then row_scale / row_pos / row_page
 static_assert(64 * LDC * 4 <= NS * STAGE, "the epilogue's buffer reuses the stages");
 
@@ -373,8 +373,8 @@ __global__ __launch_bounds__(d64::NT, 2) void gemm_direct64_kernel(const GemmP p
 }
 
 // The long contractions of few rows, x += A W^T, a run of the four per workgroup (resid_run64).  With one workgroup per tile, whatever its
-// wavefronts do, the few busy compute units pull 0.5 to 0.8 MB of operands each at 75 GB/s (gemm.hip's split workgroups: 256x512x2048
-// 11.1 us); here four times as many share them.
+// wavefronts do, the few busy compute units pull 0.5 to 0.8 MB of operands each at 75 GB/s; here four times as many share them (figures
+// of both at takes_runs; inside target-only steps of 256 series 256x512x2048 takes 10.3 us split, 7.8 here).
 __global__ __launch_bounds__(d64::NT, 2) void gemm_runs_kernel(const GemmP p) {
   using namespace d64;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];

@@ -425,7 +425,8 @@ bool layout_for(const tsd_config& c, size_t bytes, Layout* lay) {
   if (carve(c, *lay, nullptr) <= bytes) return true;
   const size_t most = lay->rows, least = least_rows(c);
   const bool resident = lay->resident, runs = lay->runs;
-  for (const Layout& l : {Layout{least, true, resident, runs}, Layout{least, true, resident, false}, Layout{least, true, false, false}, Layout{least, false, false, false}}) {
+  for (const Layout& l : {Layout{least, true, resident, runs}, Layout{least, true, resident, false}, Layout{least, true, false, false},
+                          Layout{least, false, false, false}}) {
     *lay = l;
     if (carve(c, *lay, nullptr) > bytes) continue;
     for (size_t step = most - least; lay->rows < most && step > 0; step /= 2)  // (more rows never take less)

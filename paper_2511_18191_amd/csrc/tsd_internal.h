@@ -129,7 +129,8 @@ hipError_t launch_gemm_shares(int amode, int epi, const GemmP& p, hipStream_t st
 hipError_t launch_gemm_runs(const GemmP& p, hipStream_t st);
 hipError_t launch_gemm_wide(int amode, int epi, DirectTile tile, const GemmP& p, hipStream_t st);
 hipError_t prepare_gemm_wide();
-// which kernel launch_gemm picks for this product: 16 = skinny, 2016 = direct-to-LDS tiles with its sums, 64 / 128 = tile size, 464 = 64 x 64 tiles with K split over four wavefront groups,
+// which kernel launch_gemm picks for this product: 16 = skinny, 2016 = direct-to-LDS tiles with its sums, 64 / 128 = tile size,
+// 464 = 64 x 64 tiles with K split over four wavefront groups,
 // 2000 + DirectTile = the direct-to-LDS kernels
 int gemm_variant(int dtype, int amode, int epi, const GemmP& p);
 // s_max: upper bound on (position of the pass's last token) + 1 over all series; sizes the score buffer.
