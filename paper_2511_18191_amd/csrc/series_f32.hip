@@ -1,0 +1,679 @@
+// Passes of small fp32 models, a series per workgroup: all draft steps of a round, the verification pass, the acceptance step and
+// the compaction behind it as one launch, and the context pass of both models as another.
+//
+// Kernel by kernel such a round is some 35 dependent launches of 4 to 6 us that each touch a few KB.  Series never exchange
+// anything inside a round, so a workgroup of 16 wavefronts takes its series through every stage with barriers of its own in
+// place of launches; residual, activations and the layer's keys and values sit in LDS.  What bounds it: every workgroup streams
+// all weights through its compute unit's load path (a layer of 64 x 256 is 0.2 MB), the chain of K / 4 matrix instructions of
+// a product, and the barriers in between.
+//
+//   * A wavefront takes every 16th block of 16 columns of a product and its whole k range: v_mfma_f32_16x16x4_f32, k in ascending
+//     order as in gemm_f32.hip, same bits.  The weights are a second copy in the order the lanes want them (16 bytes of a row's
+//     16-wide k-run per lane and load, a KB per load); activations in LDS have the four k of a run that belong to a lane next to
+//     each other (run_pos).
+//   * The first loads of a wavefront's next product are issued as soon as its registers are free, before the epilogue and the
+//     barrier in between (a bare barrier: weight loads stay in flight across it).
+//   * QKV columns are packed in rotary-pair order: a block is eight columns of the first half of a head and their partners.
+//   * Attention: a wavefront per (query, head), the sums of attn_kernel (attn.hip) in the same order.
+#include <type_traits>
+
+#include "accept_step.h"
+#include "tsd_internal.h"
+
+namespace tsd {
+
+namespace {
+
+constexpr int kWaves = 8, kThreads = kWaves * 64;
+constexpr int kChunk = 8;   // 16-wide k-runs whose weights are in registers at a time
+
+// Position of column c of an activation row in LDS: within a run of 16, lane group c % 4's four columns next to each other.
+__host__ __device__ constexpr int run_pos(int c) { return (c & ~15) | ((c & 3) << 2) | ((c >> 2) & 3); }
+__host__ __device__ constexpr int up16(int n) { return (n + 15) & ~15; }
+
+// LDS of a workgroup, in words (rows: a multiple of 16; S: cached tokens at most).
+struct Carve {
+  int x, cos, sin, pos, table, probs, shared, total;
+};
+// Words of the part that one stage after the other uses: queries, attention output, keys and values; hidden rows; patches.
+__host__ __device__ constexpr int shared_words(int D, int F, int P, int rows, int S) {
+  const int attn = (2 * rows + 2 * S) * (D + 4), hid = rows * (up16(F) + 4), patch = rows * (up16(P) + 4);
+  return attn > hid ? (attn > patch ? attn : patch) : (hid > patch ? hid : patch);
+}
+__host__ __device__ constexpr Carve carve_of(int D, int half, int rows, int S, int shared) {
+  Carve c{};
+  c.x = 0;
+  c.cos = rows * (D + 4);
+  c.sin = c.cos + rows * half;
+  c.pos = c.sin + rows * half;
+  c.table = c.pos + rows;
+  c.probs = c.table + 64;
+  c.shared = (c.probs + kWaves * ((S + 3) & ~3) + 3) & ~3;
+  c.total = c.shared + shared;
+  return c;
+}
+
+// (a bare barrier that orders LDS traffic: weight loads stay in flight across it)
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The weights of a product: blocks of 16 columns, each its 16-wide k-runs of 1 KB one after the other.  A wavefront takes every 8th
+// block; Frags holds up to kChunk runs of one.
+struct Frags {
+  float4 w[kChunk];
+};
+template <int N>
+__device__ __forceinline__ void load_runs(const float* W, int first, int lane, Frags& f) {  // `first`: run number in the product
+  const float4* src = reinterpret_cast<const float4*>(W) + first * 64 + lane;
+#pragma unroll
+  for (int t = 0; t < N; ++t) f.w[t] = src[t * 64];
+}
+__device__ __forceinline__ void load_some_runs(const float* W, int first, int n, int lane, Frags& f) {
+  const float4* src = reinterpret_cast<const float4*>(W) + first * 64 + lane;
+#pragma unroll
+  for (int t = 0; t < kChunk; ++t)
+    if (t < n) f.w[t] = src[t * 64];
+}
+
+// acc += N runs of the rows of A (whose reads go out together) times f.
+template <int RT, int N>
+__device__ __forceinline__ void add_runs(const float* a0, int ld, const float4* w, f32x4* acc) {
+  float4 a[N][RT];
+#pragma unroll
+  for (int t = 0; t < N; ++t)
+#pragma unroll
+    for (int i = 0; i < RT; ++i) a[t][i] = *reinterpret_cast<const float4*>(a0 + i * 16 * ld + t * 16);
+#pragma unroll
+  for (int t = 0; t < N; ++t) {
+#pragma unroll
+    for (int i = 0; i < RT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t][i].x, w[t].x, acc[i], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < RT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t][i].y, w[t].y, acc[i], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < RT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t][i].z, w[t].z, acc[i], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < RT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t][i].w, w[t].w, acc[i], 0, 0, 0);
+  }
+}
+
+template <int RT>
+__device__ __forceinline__ void clear(f32x4* acc) {
+#pragma unroll
+  for (int i = 0; i < RT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+
+// Rows of A (LDS, LD words apart) times the wavefront's blocks: f[0] holds the first loads; later ones go to f[1] and f[0] in turn, and
+// next() brings those of the next product to f[0].
+// fin(block, acc): lane l holds rows 16 i + 4 (l / 16) + r, column l % 16 of the block in acc[i][r].
+template <int RT, int BLOCKS, int RUNS, int LD, typename Next, typename Fin>
+__device__ __forceinline__ void product(const float* W, const float* A, int wave, int lane, Frags* f, Next next, Fin fin) {
+  constexpr int NB = (BLOCKS + kWaves - 1) / kWaves, N = RUNS < kChunk ? RUNS : kChunk, NC = RUNS / N;
+  static_assert(RUNS % N == 0, "whole chunks");
+  if (wave >= BLOCKS) {
+    next();
+    return;
+  }
+  const float* a0 = A + (lane & 15) * LD + (lane >> 4) * 4;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int blk = wave + b * kWaves;
+    if (BLOCKS % kWaves && b + 1 == NB && b > 0 && blk >= BLOCKS) break;
+    f32x4 acc[RT];
+    clear<RT>(acc);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int i = b * NC + c;  // chunk number
+      if (c + 1 < NC) load_runs<N>(W, blk * RUNS + (c + 1) * N, lane, f[(i + 1) & 1]);
+      else if (b + 1 < NB && blk + kWaves < BLOCKS) load_runs<N>(W, (blk + kWaves) * RUNS, lane, f[(i + 1) & 1]);
+      add_runs<RT, N>(a0 + c * N * 16, LD, f[i & 1].w, acc);
+    }
+    if (b + 1 == NB || blk + kWaves >= BLOCKS) next();
+    fin(blk, acc);
+  }
+}
+
+// Sums over l ^ 32, l ^ 16, .. in that order, lanes exchanged in registers: within 16 lanes a rotation reaches the lane wanted or one
+// that holds the same sum already.  (By shuffles through LDS a step took 100 cycles; there are 12 in a row per query.)
+template <typename N>
+__device__ __forceinline__ float rotate16(float v, N) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N::value, 0xf, 0xf, false));
+}
+template <typename Op>
+__device__ __forceinline__ float over_halves(float v, Op op) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return op(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+template <typename Op>
+__device__ __forceinline__ float over_rows(float v, Op op) {  // l ^ 16
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return op(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+template <typename Op>
+__device__ __forceinline__ float over_wave(float v, Op op) {
+  v = over_rows(over_halves(v, op), op);
+  v = op(v, rotate16(v, std::integral_constant<int, 8>{}));
+  v = op(v, rotate16(v, std::integral_constant<int, 4>{}));
+  v = op(v, rotate16(v, std::integral_constant<int, 2>{}));
+  return op(v, rotate16(v, std::integral_constant<int, 1>{}));
+}
+struct Add {
+  __device__ __forceinline__ float operator()(float a, float b) const { return a + b; }
+};
+struct Max {
+  __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); }
+};
+
+// RMSNorm scales of the rows of x: lane l gets that of row 16 i + l % 16 in rs[i].  Per row four partial sums, one per 16-byte
+// piece of a run, combined as (P0 + P2) + (P1 + P3): the order of gemm_f32.hip.
+template <int RT, int D>
+__device__ __forceinline__ void row_scales(const float* x, int lane, float* rs) {
+#pragma unroll
+  for (int i = 0; i < RT; ++i) {
+    const float* row = x + (16 * i + (lane & 15)) * (D + 4) + (lane >> 4);
+    float ss = 0.f;
+#pragma unroll
+    for (int t = 0; t < D; t += 16) {
+      const float f0 = row[t], f1 = row[t + 4], f2 = row[t + 8], f3 = row[t + 12];
+      ss += f0 * f0 + f1 * f1 + f2 * f2 + f3 * f3;
+    }
+    const float s = over_rows(over_halves(ss, Add{}), Add{});
+    rs[i] = rsqrtf(s / (float)D + kRmsEps);
+  }
+}
+// ... applied to a block's sums
+template <int RT>
+__device__ __forceinline__ void scale_rows(const float* rs, int lane, f32x4* acc) {
+#pragma unroll
+  for (int i = 0; i < RT; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[i][r] *= __shfl(rs[i], 4 * (lane >> 4) + r);
+}
+
+// One query of one head over keys 0 .. nkeys - 1 by a wavefront: q and out are the head's columns, K and V those of token 0.
+template <int HD>
+__device__ __forceinline__ void attend(const float* q, const float* Ks, const float* Vs, int ld, int nkeys, float* ps, float* out_row, int c0, int lane) {
+  constexpr int G = 64 / HD;
+  const int nk4 = (nkeys + 3) & ~3;
+  float m = -INFINITY;
+  for (int s = lane; s < nk4; s += 64) {
+    float sc = 0.f;
+    const float* kr = Ks + min(s, nkeys - 1) * ld;
+#pragma unroll
+    for (int e = 0; e < HD; e += 4) {
+      const float4 k = *reinterpret_cast<const float4*>(kr + e), qq = *reinterpret_cast<const float4*>(q + e);
+      sc = fmaf(k.x, qq.x, sc);
+      sc = fmaf(k.y, qq.y, sc);
+      sc = fmaf(k.z, qq.z, sc);
+      sc = fmaf(k.w, qq.w, sc);
+    }
+    sc = s < nkeys ? sc : -INFINITY;
+    ps[s] = sc;
+    m = fmaxf(m, sc);
+  }
+  m = over_wave(m, Max{});
+  float sum = 0.f;
+  for (int s = lane; s < nk4; s += 64) {  // (a lane's own scores)
+    const float e = __expf(ps[s] - m);
+    ps[s] = e;
+    sum += e;
+  }
+  const float inv = 1.f / over_wave(sum, Add{});
+  wave_lds_order();
+  const int d = lane % HD, sg = lane / HD;
+  float acc = 0.f;
+  for (int s4 = sg * 4; s4 < nk4; s4 += 4 * G) {
+    const float4 pp = *reinterpret_cast<const float4*>(ps + s4);
+    float vv[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) vv[u] = s4 + u < nkeys ? Vs[(s4 + u) * ld + d] : 0.f;
+    acc = fmaf(pp.x, vv[0], acc);
+    acc = fmaf(pp.y, vv[1], acc);
+    acc = fmaf(pp.z, vv[2], acc);
+    acc = fmaf(pp.w, vv[3], acc);
+  }
+  if constexpr (HD == 16) acc = over_rows(acc, Add{});
+  if constexpr (HD <= 32) acc = over_halves(acc, Add{});
+  if (sg == 0) out_row[run_pos(c0 + d)] = acc * inv;
+  wave_lds_order();
+}
+
+// One pass of one series: nq tokens (at most 16 RT) at positions base, base + 1, ..
+struct SeriesPass {
+  int nq, base;
+  const float *src0, *src1;  // token t's patch: src0 + t P (t < n0), else src1 + (t - n0) P
+  int n0;
+  float* out;  // head outputs of tokens t_skip, .. (NULL: no head)
+  int t_skip;
+};
+
+// The model sizes there are kernels for: widths of 32, 64 and 128 with a four times as wide FFN.  (Sizes known only at run time made
+// a product's stage some 1000 instructions long, 4000 clocks for 500 of matrix instructions.)
+template <int D_, int HD_>
+struct Shape {
+  static constexpr int D = D_, F = 4 * D_, HD = HD_, H = D_ / HD_, HALF = HD_ / 2, DB = D_ / 16, FB = F / 16, LDX = D_ + 4, LDH = F + 4;
+};
+
+__device__ __forceinline__ void prefetch_embed(const SeriesModel& m, int P, int wave, int lane, Frags* f) {
+  const int runs = up16(P) >> 4;
+  if (wave < m.D >> 4) load_some_runs(m.We, wave * runs, runs, lane, f[0]);
+}
+
+// f[0] holds the first loads of the model's embedding; after() brings those of the next pass's.
+template <typename M, int RT, typename After>
+__device__ __forceinline__ void run_series_pass(const SeriesP& p, const SeriesModel& m, const SeriesPass& ps, float* lds, Frags* f, After after) {
+  constexpr int D = M::D, LDX = M::LDX, LDH = M::LDH, HD = M::HD, H = M::H, HALF = M::HALF, DB = M::DB, FB = M::FB, R = 16 * RT;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // (an opaque copy: keeps the address arithmetic of all shapes from being hoisted out of the passes)
+  int lane = tid & 63, l15 = lane & 15, lq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int P = p.P, nq = ps.nq, base = ps.base, S = base + nq, ldp = up16(P) + 4, pr = up16(P) >> 4;
+  const Carve c = carve_of(p.D_max, p.half_max, R, p.S_max, 0);
+  float *x = lds + c.x, *cs = lds + c.cos, *sn = lds + c.sin, *shared = lds + c.shared;
+  int *row_at = reinterpret_cast<int*>(lds + c.pos), *table = reinterpret_cast<int*>(lds + c.table);
+  float *q = shared, *att = q + R * LDX, *Ks = att + R * LDX, *Vs = Ks + S * LDX, *hid = shared, *patch = shared;
+  float* probs = lds + c.probs + wave * ((p.S_max + 3) & ~3);
+  const int plane = p.PT * HD;  // a head's keys of a page; its values are H planes on
+  auto token_at = [&](int tok) { return (table[tok >> p.pt_shift] * 2 * H * p.PT + (tok & (p.PT - 1))) * HD; };
+
+  // ---- patches, rotary factors, where the rows' keys go ----
+  for (int t = wave; t < nq; t += kWaves)
+    for (int k4 = lane; k4 < pr * 4; k4 += 64) {
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (k4 < P >> 2) v = *reinterpret_cast<const float4*>((t < ps.n0 ? ps.src0 + t * P : ps.src1 + (t - ps.n0) * P) + k4 * 4);
+      float* to = patch + t * ldp + (k4 & ~3) * 4 + (k4 & 3);
+      to[0] = v.x;
+      to[4] = v.y;
+      to[8] = v.z;
+      to[12] = v.w;
+    }
+  for (int i = tid; i < nq * HALF; i += kThreads) {  // (positions are consecutive)
+    cs[i] = m.rope_cos[base * HALF + i];
+    sn[i] = m.rope_sin[base * HALF + i];
+  }
+  if (tid < nq) row_at[tid] = token_at(base + tid);
+  // keys and values of earlier passes, 16 bytes at a time: half a wavefront the keys, half the values of FIT tokens, the wavefronts
+  // tokens in turn
+  constexpr int C4 = D / 4, FIT = 32 / C4, U = 4, STEP = kWaves * FIT;
+  const int cc = (lane & 31) % C4, tok_first = wave * FIT + (lane & 31) / C4;
+  const int old_from = ((lane >> 5) * H + cc / (HD / 4)) * plane + cc % (HD / 4) * 4;
+  float* old_to = (lane < 32 ? Ks : Vs) + cc * 4;
+  auto fetch = [&](const float* pool, int tok0, float4* old) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      old[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (tok0 + u * STEP < base) old[u] = *reinterpret_cast<const float4*>(pool + (old_from + token_at(tok0 + u * STEP)));
+    }
+  };
+  auto put = [&](int tok0, const float4* old) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (tok0 + u * STEP < base) *reinterpret_cast<float4*>(old_to + (tok0 + u * STEP) * LDX) = old[u];
+  };
+  auto x_at = [&](int blk) { return x + 4 * lq * LDX + 16 * blk + run_pos(l15); };
+  auto add_to_x = [&](int blk, f32x4* acc) {
+    float* to = x_at(blk);
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][r] = to[(16 * i + r) * LDX] + acc[i][r];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) to[(16 * i + r) * LDX] = acc[i][r];
+  };
+  const float* W = m.layers;
+  auto first_of = [&](const float* Wn, int blocks, auto runs) {
+    constexpr int RUNS = decltype(runs)::value;
+    if (wave < blocks) load_runs < RUNS < kChunk ? RUNS : kChunk > (Wn, wave * RUNS, lane, f[0]);
+  };
+  using Db = std::integral_constant<int, DB>;
+  using Fb = std::integral_constant<int, FB>;
+
+  lds_barrier();
+  if (wave < DB) {
+    const float* a0 = patch + l15 * ldp + lq * 4;
+    f32x4 acc[RT];
+    clear<RT>(acc);
+    for (int t0 = 0; t0 < pr; t0 += kChunk) {
+      if (t0) load_some_runs(m.We, wave * pr + t0, pr - t0, lane, f[0]);
+#pragma unroll
+      for (int t = 0; t < kChunk; ++t)
+        if (t0 + t < pr) add_runs<RT, 1>(a0 + (t0 + t) * 16, ldp, &f[0].w[t], acc);
+    }
+    first_of(W, 3 * DB, Db{});
+    float* to = x_at(wave);
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) to[(16 * i + r) * LDX] = acc[i][r];
+  } else {
+    first_of(W, 3 * DB, Db{});
+  }
+  lds_barrier();
+
+#pragma unroll 1
+  for (int l = 0; l < m.L; ++l, W += m.layer_words) {
+    asm volatile("" : "+v"(lane));  // (nor out of the layers)
+    l15 = lane & 15;
+    lq = lane >> 4;
+    float* pool = m.kv_pool + (size_t)l * m.layer_pool_elems;
+    float4 old[U];
+    fetch(pool, tok_first, old);  // (put down behind the product)
+    {
+      float rs[RT];
+      row_scales<RT, D>(x, lane, rs);
+      product<RT, 3 * DB, DB, LDX>(W, x, wave, lane, f, [&] { first_of(W + m.o_out, DB, Db{}); }, [&](int blk, f32x4* acc) {
+        scale_rows<RT>(rs, lane, acc);
+        constexpr int BPH = HD / 16;
+        const int hs = blk / BPH, i8 = blk % BPH * 8 + (l15 & 7), which = hs / H, h = hs % H;
+        const int col = h * HD + i8 + (l15 < 8 ? 0 : HALF);
+        if (which < 2) {
+          const float sg = l15 < 8 ? -1.f : 1.f;
+#pragma unroll
+          for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float pv = rotate16(acc[i][r], std::integral_constant<int, 8>{});
+              const int at = (16 * i + 4 * lq + r) * HALF + i8;  // (rows past nq: whatever is there, dropped)
+              acc[i][r] = acc[i][r] * cs[at] + sg * pv * sn[at];
+            }
+        }
+        if (which == 0) {
+#pragma unroll
+          for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) q[(16 * i + 4 * lq + r) * LDX + col] = acc[i][r] * m.scale;
+        } else {
+          float* to = (which == 1 ? Ks : Vs) + base * LDX + col;
+          float* cache = pool + ((which - 1) * H + h) * plane + (col - h * HD);
+#pragma unroll
+          for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int row = 16 * i + 4 * lq + r;
+              if (row < nq) {
+                to[row * LDX] = acc[i][r];
+                cache[row_at[row]] = acc[i][r];
+              }
+            }
+        }
+      });
+    }
+    put(tok_first, old);
+    for (int tok = tok_first + U * STEP; tok < base; tok += U * STEP) {
+      fetch(pool, tok, old);
+      put(tok, old);
+    }
+    lds_barrier();
+    // ---- attention ----
+    for (int t = wave; t < nq * H; t += kWaves) {
+      const int row = t / H, c0 = t % H * HD;
+      attend<HD>(q + row * LDX + c0, Ks + c0, Vs + c0, LDX, base + row + 1, probs, att + row * LDX, c0, lane);
+    }
+    lds_barrier();
+    product<RT, DB, DB, LDX>(W + m.o_out, att, wave, lane, f, [&] { first_of(W + m.o_up, FB, Db{}); }, add_to_x);
+    lds_barrier();
+    {
+      float rs[RT];
+      row_scales<RT, D>(x, lane, rs);
+      product<RT, FB, DB, LDX>(W + m.o_up, x, wave, lane, f, [&] { first_of(W + m.o_down, DB, Fb{}); }, [&](int blk, f32x4* acc) {
+        scale_rows<RT>(rs, lane, acc);
+        float* to = hid + 4 * lq * LDH + 16 * blk + run_pos(l15);
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) to[(16 * i + r) * LDH] = gelu_tanh(acc[i][r]);
+      });
+    }
+    lds_barrier();
+    product<RT, DB, FB, LDH>(W + m.o_down, hid, wave, lane, f, [&] {
+      if (l + 1 < m.L) first_of(W + m.layer_words, 3 * DB, Db{});
+      else if (ps.out) first_of(m.Wh, pr, Db{});
+      else after();
+    }, add_to_x);
+    lds_barrier();
+  }
+  if (ps.out) {
+    float rs[RT];
+    row_scales<RT, D>(x, lane, rs);
+    const float* a0 = x + l15 * LDX + lq * 4;
+    if (wave >= pr) after();
+    for (int blk = wave; blk < pr; blk += kWaves) {
+      if (blk != wave) load_runs<DB>(m.Wh, blk * DB, lane, f[0]);
+      f32x4 acc[RT];
+      clear<RT>(acc);
+      add_runs<RT, DB>(a0, LDX, f[0].w, acc);
+      if (blk + kWaves >= pr) after();
+      scale_rows<RT>(rs, lane, acc);
+      const int col = 16 * blk + l15;
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = 16 * i + 4 * lq + r;
+          if (col < P && row < nq && row >= ps.t_skip) ps.out[(row - ps.t_skip) * P + col] = acc[i][r];
+        }
+    }
+  }
+  __syncthreads();  // the pass's cache rows and outputs are there for this workgroup
+}
+
+// The number of a model's Shape (-1: there is none).
+constexpr int shape_of(int D, int H, int F) {
+  if (F != 4 * D || H < 1 || D % H) return -1;
+  const int hd = D / H, h = hd == 16 ? 0 : hd == 32 ? 1 : hd == 64 ? 2 : 3;
+  return h > 2 || hd > D ? -1 : D == 32 ? h : D == 64 ? 2 + h : D == 128 ? 5 + h : -1;
+}
+template <int RT, typename After>
+__device__ __forceinline__ void run_any_pass(const SeriesP& p, const SeriesModel& m, const SeriesPass& ps, float* lds, Frags* f, After after) {
+  switch (m.shape) {
+    case 0: return run_series_pass<Shape<32, 16>, RT>(p, m, ps, lds, f, after);
+    case 1: return run_series_pass<Shape<32, 32>, RT>(p, m, ps, lds, f, after);
+    case 2: return run_series_pass<Shape<64, 16>, RT>(p, m, ps, lds, f, after);
+    case 3: return run_series_pass<Shape<64, 32>, RT>(p, m, ps, lds, f, after);
+    case 4: return run_series_pass<Shape<64, 64>, RT>(p, m, ps, lds, f, after);
+    case 5: return run_series_pass<Shape<128, 16>, RT>(p, m, ps, lds, f, after);
+    case 6: return run_series_pass<Shape<128, 32>, RT>(p, m, ps, lds, f, after);
+    case 7: return run_series_pass<Shape<128, 64>, RT>(p, m, ps, lds, f, after);
+  }
+}
+
+__device__ __forceinline__ void load_table(const SeriesP& p, int b, int rows, float* lds) {
+  int* table = reinterpret_cast<int*>(lds + carve_of(p.D_max, p.half_max, rows, p.S_max, 0).table);
+  if ((int)threadIdx.x < p.pt_stride) table[threadIdx.x] = p.page_table[(long)b * p.pt_stride + threadIdx.x];
+  __syncthreads();
+}
+
+// What compact_active_kernel (misc.hip) does, by the workgroup of a round that commits last.  What the others committed has gone
+// through to memory (publish) before they were counted; it is read past the caches.
+__device__ __forceinline__ void compact(const CompactP& c) {
+  __shared__ int wave_cnt[4], most[4];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  auto fresh = [](const int* a) { return __hip_atomic_load(const_cast<int*>(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  int base = 0, rem = 0;
+  for (int b0 = 0; b0 < c.B; b0 += 256) {
+    const int b = b0 + tid;
+    const bool on = b < c.B && fresh(c.active + b) != 0;
+    if (on) rem = max(rem, c.T - fresh(c.committed + b));
+    const unsigned long long m = __ballot(on);
+    if (lane == 0) wave_cnt[w] = __popcll(m);
+    __syncthreads();
+    int off = base;
+    for (int i = 0; i < 4; ++i) {
+      if (i < w) off += wave_cnt[i];
+      base += wave_cnt[i];
+    }
+    if (on) c.list[off + __popcll(m & ((1ull << lane) - 1ull))] = b;
+    __syncthreads();
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) rem = max(rem, __shfl_xor(rem, o));
+  if (lane == 0) most[w] = rem;
+  __syncthreads();
+  if (tid == 0) {
+    rem = max(max(most[0], most[1]), max(most[2], most[3]));
+    c.count[0] = base;
+    c.count[1] = rem;
+    const int seq = c.count[4] + 1;
+    c.count[4] = seq;
+    c.host[0] = base;
+    c.host[1] = rem;
+    __hip_atomic_store(&c.host[2], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
+}  // namespace
+
+// Slot blockIdx.x of the list: the draft steps (p.phases & 1), the target pass (& 2), the acceptance step (& 4), and behind the
+// last of them the compaction (c.host not NULL).
+template <int RT>
+__global__ __launch_bounds__(kThreads) void series_round_kernel(const SeriesP p, const AcceptP a, const CompactP c) {
+  extern __shared__ __attribute__((aligned(16))) float series_lds[];
+  const int n = p.counts ? min(p.counts[0], p.n) : p.n;
+  if ((int)blockIdx.x >= n) {
+    if (n == 0 && blockIdx.x == 0 && c.host && threadIdx.x < 256) compact(c);  // (nobody is left; the caller waits for the count)
+    return;
+  }
+  const int b = p.act ? p.act[blockIdx.x] : (int)blockIdx.x;
+  const int Kr = p.follow_need ? max(1, min(p.K, p.counts[1])) : p.K;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  Frags f[2];
+  prefetch_embed(p.m[p.phases & 1 ? 1 : 0], p.P, wave, tid & 63, f);
+  const int len = p.len[b], P = p.P;
+  load_table(p, b, 16 * RT, series_lds);
+  float* X = p.X + (long)b * p.x_stride;
+  const float* pending = p.pending + (long)b * P;
+  const int steps = p.phases & 1 ? Kr : 0, passes = steps + (p.phases & 2 ? 1 : 0);
+#pragma unroll 1
+  for (int i = 0; i < passes; ++i) {
+    SeriesPass ps;
+    const bool draft = i < steps;
+    if (draft) {
+      // step 1 takes the token before the pending one along (see tsd_draft_propose)
+      ps = i == 0 ? SeriesPass{2, len - 1, p.prev + (long)b * P, pending, 1, X, 1} : SeriesPass{1, len + i, X + (long)(i - 1) * P, nullptr, 1, X + (long)i * P, 0};
+    } else {
+      ps = SeriesPass{p.step_only ? 1 : Kr + 1, len, pending, X, 1, p.mu_p + (long)b * p.mu_stride, 0};
+    }
+    run_any_pass<RT>(p, p.m[draft ? 1 : 0], ps, series_lds, f, [&] {
+      if (i + 1 < passes) prefetch_embed(p.m[i + 1 < steps ? 1 : 0], P, wave, tid & 63, f);
+    });
+  }
+  if (!(p.phases & 4)) return;
+  if (tid >= 256) return;  // (a barrier waits for the wavefronts that are left)
+  accept_step(a);
+  if (!c.host) return;
+  __shared__ int last;
+  if (tid == 0) {
+    // (this lane wrote both)
+    __hip_atomic_store(c.active + b, a.active[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(c.committed + b, a.committed[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    last = __hip_atomic_fetch_add(c.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+    if (last) __hip_atomic_store(c.ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (last) compact(c);
+}
+
+// The context of series blockIdx.x of the list through model blockIdx.y, 16 RT tokens at a time.
+template <int RT>
+__global__ __launch_bounds__(kThreads) void series_context_kernel(const SeriesP p, const float* znorm, int N) {
+  extern __shared__ __attribute__((aligned(16))) float series_lds[];
+  const int b = p.act ? p.act[blockIdx.x] : (int)blockIdx.x;
+  const SeriesModel& m = p.m[blockIdx.y];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  Frags f[2];
+  prefetch_embed(m, p.P, wave, threadIdx.x & 63, f);
+  load_table(p, b, 16 * RT, series_lds);
+  const float* z = znorm + (long)b * N * p.P;
+#pragma unroll 1
+  for (int t0 = 0; t0 < N - 1; t0 += 16 * RT) {
+    const int nq = min(16 * RT, N - 1 - t0);
+    run_any_pass<RT>(p, m, SeriesPass{nq, t0, z + (long)t0 * p.P, nullptr, nq, nullptr, 0}, series_lds, f,
+                     [&] { prefetch_embed(m, p.P, wave, threadIdx.x & 63, f); });
+  }
+}
+
+namespace {
+
+// The weights [N][K] in the order the products read them; qkv_hd > 0: columns in rotary-pair order within heads of qkv_hd.
+__global__ __launch_bounds__(256) void series_pack_kernel(const float* src, float* dst, int N, int K, int runs, int qkv_hd) {
+  const long total = (long)up16(N) * runs * 16;
+  for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long)gridDim.x * 256) {
+    const int j = (int)(i & 3), lane = (int)((i >> 2) & 63);
+    const long br = i >> 8;
+    const int t = (int)(br % runs), blk = (int)(br / runs), l15 = lane & 15, k = t * 16 + j * 4 + (lane >> 4);
+    int col = blk * 16 + l15;
+    if (qkv_hd) {
+      const int bph = qkv_hd >> 4, hs = blk / bph;
+      col = hs * qkv_hd + (blk - hs * bph) * 8 + (l15 & 7) + (l15 < 8 ? 0 : qkv_hd >> 1);
+    }
+    dst[i] = k < K && col < N ? src[(long)col * K + k] : 0.f;
+  }
+}
+
+int rows_of(int tokens) { return tokens <= 16 ? 16 : 32; }
+
+size_t lds_bytes(const tsd_config& c, int rows) {
+  int shared = 0, D = 0, half = 0;
+  for (const tsd_model_cfg* m : {&c.target, &c.draft}) {
+    const int w = shared_words(m->d_model, m->d_ff, c.patch, rows, c.max_tokens);
+    shared = w > shared ? w : shared;
+    D = m->d_model > D ? m->d_model : D;
+    half = m->d_model / m->n_heads / 2 > half ? m->d_model / m->n_heads / 2 : half;
+  }
+  return (size_t)carve_of(D, half, rows, c.max_tokens, shared).total * 4;
+}
+
+}  // namespace
+
+size_t series_packed_words(int N, int K) { return (size_t)up16(N) * up16(K); }
+
+hipError_t launch_series_pack(const float* src, float* dst, int N, int K, int qkv_hd, hipStream_t st) {
+  const size_t total = series_packed_words(N, K);
+  hipLaunchKernelGGL(series_pack_kernel, dim3((unsigned)std::min<size_t>((total + 255) / 256, 4096)), dim3(256), 0, st, src, dst, N, K, up16(K) >> 4, qkv_hd);
+  return hipGetLastError();
+}
+
+bool series_rounds_ok(const tsd_config& c) {
+  if (c.dtype != TSD_F32 || c.target.n_experts || c.draft.n_experts || (c.flags & (TSD_FLAG_SAMPLE_PROPOSALS | TSD_FLAG_NAIVE_VERIFY))) return false;
+  if (c.max_batch > 256) return false;
+  for (const tsd_model_cfg* m : {&c.target, &c.draft})
+    if (shape_of(m->d_model, m->n_heads, m->d_ff) < 0) return false;
+  return lds_bytes(c, 32) + 4096 <= 160 * 1024;
+}
+
+int series_shape(const tsd_model_cfg& m) { return shape_of(m.d_model, m.n_heads, m.d_ff); }
+bool series_context_short(int tokens) { return tokens <= 128; }
+
+hipError_t prepare_series() {
+  const void* fns[4] = {reinterpret_cast<const void*>(&series_round_kernel<1>), reinterpret_cast<const void*>(&series_round_kernel<2>),
+                        reinterpret_cast<const void*>(&series_context_kernel<1>), reinterpret_cast<const void*>(&series_context_kernel<2>)};
+  for (const void* f : fns) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_series_round(const tsd_config& c, const SeriesP& p, const AcceptP& a, const CompactP& k, hipStream_t st) {
+  const int rows = rows_of(std::max(2, p.step_only ? 1 : p.K + 1));
+  const size_t smem = lds_bytes(c, rows);
+  if (rows == 16) hipLaunchKernelGGL(series_round_kernel<1>, dim3(p.n), dim3(kThreads), smem, st, p, a, k);
+  else hipLaunchKernelGGL(series_round_kernel<2>, dim3(p.n), dim3(kThreads), smem, st, p, a, k);
+  return hipGetLastError();
+}
+
+hipError_t launch_series_context(const tsd_config& c, const SeriesP& p, const float* znorm, int N, hipStream_t st) {
+  const int rows = rows_of(N - 1);
+  const size_t smem = lds_bytes(c, rows);
+  if (rows == 16) hipLaunchKernelGGL(series_context_kernel<1>, dim3(p.n, 2), dim3(kThreads), smem, st, p, znorm, N);
+  else hipLaunchKernelGGL(series_context_kernel<2>, dim3(p.n, 2), dim3(kThreads), smem, st, p, znorm, N);
+  return hipGetLastError();
+}
+
+}  // namespace tsd

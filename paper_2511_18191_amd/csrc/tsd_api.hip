@@ -31,6 +31,7 @@ struct ModelDev {
   char* fW_e = nullptr;
   char* fW_h = nullptr;
   std::vector<Layer> flayers;
+  SeriesModel series{};  // third copy, of both models, for passes of a series per workgroup (small fp32 handles)
   float *rope_cos, *rope_sin;
   char* kv_pool;
   size_t layer_pool_bytes;
@@ -70,6 +71,8 @@ struct tsd_ctx {
   bool trace_on = false;
   int skinny;  // all decode passes have at most 32 rows: they take the skinny GEMM (fixed per handle so that a
                // series' bits never depend on how many other series are still active)
+  bool series = false;              // small fp32 models: a series per workgroup (see series_f32.hip)
+  int64_t series_passes = 0;        // launches of those kernels
   bool small_round = false;         // ... as one resident kernel (see small_round.hip)
   unsigned* small_flags = nullptr;  // its workgroups' flags
   unsigned small_epoch = 0;         // what they hold at most
@@ -203,6 +206,7 @@ int check_config(const tsd_config* c, std::string& why) {
   return TSD_OK;
 }
 
+constexpr int kTicket = 16;     // word of count_out: series of the round in flight that have committed
 constexpr int kGaveUp = 12;     // word of count_out (and 3 of the pinned words): a launch of the resident kernel gave up waiting
 
 constexpr int kTraceMax = 512;  // stage stamps tsd_trace_draft can return
@@ -222,6 +226,7 @@ struct Layout {
   bool meta;      // the rows' positions and cache pages, looked up once per pass instead of before every layer
   bool resident;  // flags and exchange buffer of the resident decode kernel
   bool runs;      // sums of the runs of long contractions
+  bool series;    // weights in the order of the fp32 passes of a series per workgroup
 };
 
 // A round's tokens of the whole batch, or the longest context of one series.
@@ -237,7 +242,7 @@ Layout full_layout(const tsd_config& c) {
   for (const tsd_model_cfg* m : {&c.target, &c.draft})
     for (const int k : {m->d_model, m->n_experts > 0 ? 0 : m->d_ff}) runs = runs || takes_runs(m->d_model, k, 1);
   runs = runs && c.dtype == TSD_BF16 && !(c.flags & TSD_FLAG_NO_WIDE_GEMM);
-  return Layout{std::max(least_rows(c), (size_t)std::max(want, 0L)), true, small_round_ok(c), runs};
+  return Layout{std::max(least_rows(c), (size_t)std::max(want, 0L)), true, small_round_ok(c), runs, series_rounds_ok(c)};
 }
 
 struct Carver {
@@ -316,6 +321,26 @@ size_t carve(const tsd_config& c, const Layout& lay, tsd_ctx* ctx) {
         if (md) md->flayers[l] = Layer{at(fq), at(fo), at(f1), at(f2), nullptr};
       }
     }
+    if (lay.series) {
+      const size_t n_qkv = series_packed_words((int)(3 * D), (int)D), n_out = series_packed_words((int)D, (int)D),
+                   n_up = series_packed_words((int)F, (int)D), n_down = series_packed_words((int)D, (int)F);
+      const size_t se = cv.take(series_packed_words((int)D, P) * 4), sh = cv.take(series_packed_words(P, (int)D) * 4),
+                   sl = cv.take((n_qkv + n_out + n_up + n_down) * m.n_layers * 4);
+      if (md) {
+        SeriesModel& s = md->series;
+        s.We = (const float*)at(se);
+        s.Wh = (const float*)at(sh);
+        s.layers = (const float*)at(sl);
+        s.o_out = n_qkv;
+        s.o_up = n_qkv + n_out;
+        s.o_down = n_qkv + n_out + n_up;
+        s.layer_words = n_qkv + n_out + n_up + n_down;
+        s.L = m.n_layers;
+        s.D = (int)D;
+        s.shape = series_shape(m);
+        s.scale = 1.0f / std::sqrt((float)hd);
+      }
+    }
     size_t oc = cv.take((size_t)c.max_tokens * (hd / 2) * 4), os = cv.take((size_t)c.max_tokens * (hd / 2) * 4);
     if (md) {
       md->rope_cos = (float*)at(oc);
@@ -326,6 +351,10 @@ size_t carve(const tsd_config& c, const Layout& lay, tsd_ctx* ctx) {
     if (md) {
       md->kv_pool = at(o);
       md->layer_pool_bytes = layer_pool;
+      md->series.kv_pool = (float*)at(o);
+      md->series.layer_pool_elems = layer_pool / es;
+      md->series.rope_cos = md->rope_cos;
+      md->series.rope_sin = md->rope_sin;
     }
   }
   size_t o_pt = cv.take(n_pages * 4);
@@ -424,9 +453,9 @@ bool layout_for(const tsd_config& c, size_t bytes, Layout* lay) {
   *lay = full_layout(c);
   if (carve(c, *lay, nullptr) <= bytes) return true;
   const size_t most = lay->rows, least = least_rows(c);
-  const bool resident = lay->resident, runs = lay->runs;
-  for (const Layout& l : {Layout{least, true, resident, runs}, Layout{least, true, resident, false}, Layout{least, true, false, false},
-                          Layout{least, false, false, false}}) {
+  const bool resident = lay->resident, runs = lay->runs, series = lay->series;
+  for (const Layout& l : {Layout{least, true, resident, runs, series}, Layout{least, true, resident, false, series},
+                          Layout{least, true, false, false, series}, Layout{least, true, false, false, false}, Layout{least, false, false, false, false}}) {
     *lay = l;
     if (carve(c, *lay, nullptr) > bytes) continue;
     for (size_t step = most - least; lay->rows < most && step > 0; step /= 2)  // (more rows never take less)
@@ -848,6 +877,84 @@ bool use_small_round(tsd_ctx* ctx, hipStream_t st) {
   return true;
 }
 
+// Whether the next pass may run a series per workgroup (not under a measurement, which times the kernels one by one).
+bool use_series(const tsd_ctx* ctx) { return ctx->series && ctx->prof_class < 0; }
+
+SeriesP series_args(const tsd_ctx* ctx) {
+  const tsd_config& c = ctx->cfg;
+  SeriesP p;
+  std::memset(&p, 0, sizeof(p));
+  for (int i = 0; i < 2; ++i) {
+    p.m[i] = ctx->model[i].series;
+    p.D_max = std::max(p.D_max, ctx->model[i].c.d_model);
+    p.half_max = std::max(p.half_max, ctx->model[i].hd / 2);
+  }
+  p.S_max = c.max_tokens;
+  p.page_table = ctx->page_table;
+  p.pt_stride = ctx->pages_per_series;
+  p.PT = c.page_tokens;
+  p.pt_shift = __builtin_ctz(c.page_tokens);
+  p.len = ctx->len;
+  p.P = c.patch;
+  p.prev = ctx->prev;
+  p.pending = ctx->pending;
+  p.X = ctx->X;
+  p.x_stride = (long)c.K * c.patch;
+  p.mu_p = ctx->mu_p;
+  return p;
+}
+
+void accept_args(tsd_ctx* ctx, const int32_t* forced, int K, AcceptP& a);
+
+// phases: 1 the draft steps, 2 the target pass, 4 the acceptance step; step_only: the target pass over the pending token alone;
+// deliver: with the compaction behind it.
+int run_series_round(tsd_ctx* ctx, int phases, bool step_only, bool deliver, hipStream_t st) {
+  const tsd_config& c = ctx->cfg;
+  SeriesP p = series_args(ctx);
+  p.K = round_positions(ctx);
+  p.mu_stride = step_only ? c.patch : (long)(c.K + 1) * c.patch;
+  const Cover cv = cover(ctx);
+  if (cv.n == 0) {
+    if (deliver)
+      HIP_TRY(ctx, launch_compact_active(ctx->active, ctx->committed, ctx->T, ctx->B, compact_target(ctx), ctx->count_out, ctx->host_counts, st));
+    return TSD_OK;
+  }
+  p.act = cv.act;
+  p.counts = cv.n_dev;
+  p.n = cv.n;
+  if (phases == 7 && device_counts(ctx)) {  // a whole round reads the list and its length on the device ...
+    p.act = ctx->act_list;
+    p.counts = ctx->count_out;
+    // ... and the positions to propose, once a round of this decode has counted them
+    p.follow_need = ctx->seq_launched > ctx->seq_floor ? 1 : 0;
+  }
+  p.phases = phases;
+  p.step_only = step_only ? 1 : 0;
+  AcceptP a;
+  accept_args(ctx, nullptr, step_only ? 0 : c.K, a);
+  a.act = p.act;
+  a.n_dev = p.counts;
+  a.B = p.n;
+  CompactP k;
+  std::memset(&k, 0, sizeof(k));
+  k.active = ctx->active;
+  k.committed = ctx->committed;
+  k.T = ctx->T;
+  k.B = ctx->B;
+  k.list = compact_target(ctx);
+  k.count = ctx->count_out;
+  k.host = deliver ? ctx->host_counts : nullptr;
+  k.ticket = ctx->count_out + kTicket;
+  HIP_TRY(ctx, launch_series_round(c, p, a, k, st));
+  ctx->series_passes++;
+  if (phases & 4) {
+    ctx->injected = false;
+    ctx->compact_pending = false;  // (as in accept_commit_impl)
+    ctx->need_lb = 0;
+  }
+  return TSD_OK;
+}
+
 constexpr int kResidentBusy = 1;  // (error codes are negative)
 
 // phases: 1 the draft steps, 2 the target pass; step_only: the target pass over the pending token alone.  kResidentBusy:
@@ -925,10 +1032,9 @@ int run_small_phase(tsd_ctx* ctx, int phase, hipStream_t st) {
   return rc;
 }
 
-// `after`: the resident launch whose results it takes (NULL or n == 0: none).
-int accept_commit_impl(tsd_ctx* ctx, const int32_t* forced, int K, hipStream_t st, const SmallRoundP* after = nullptr) {
+// Everything but who takes part.
+void accept_args(tsd_ctx* ctx, const int32_t* forced, int K, AcceptP& a) {
   const tsd_config& c = ctx->cfg;
-  AcceptP a;
   std::memset(&a, 0, sizeof(a));
   a.X = ctx->X;
   const bool sampled = (c.flags & TSD_FLAG_SAMPLE_PROPOSALS) != 0;
@@ -946,14 +1052,6 @@ int accept_commit_impl(tsd_ctx* ctx, const int32_t* forced, int K, hipStream_t s
   a.ell = ctx->ell;
   a.logu = ctx->logu;
   a.stat = ctx->stat;
-  const Cover cv = cover(ctx);
-  if (cv.n == 0) {
-    if (after && after->n > 0) HIP_TRY(ctx, launch_small_round_alone(*after, st));
-    return TSD_OK;
-  }
-  a.B = cv.n;
-  a.act = cv.act;
-  a.n_dev = cv.n_dev;
   a.K = K;
   a.P = c.patch;
   a.T = ctx->T;
@@ -971,6 +1069,21 @@ int accept_commit_impl(tsd_ctx* ctx, const int32_t* forced, int K, hipStream_t s
   a.key0 = (unsigned)(c.seed & 0xFFFFFFFFull);
   a.key1 = (unsigned)(c.seed >> 32);
   a.threshold = (c.flags & TSD_FLAG_THRESHOLD_RULE) ? 1 : 0;
+}
+
+// `after`: the resident launch whose results it takes (NULL or n == 0: none).
+int accept_commit_impl(tsd_ctx* ctx, const int32_t* forced, int K, hipStream_t st, const SmallRoundP* after = nullptr) {
+  const tsd_config& c = ctx->cfg;
+  AcceptP a;
+  accept_args(ctx, forced, K, a);
+  const Cover cv = cover(ctx);
+  if (cv.n == 0) {
+    if (after && after->n > 0) HIP_TRY(ctx, launch_small_round_alone(*after, st));
+    return TSD_OK;
+  }
+  a.B = cv.n;
+  a.act = cv.act;
+  a.n_dev = cv.n_dev;
   auto launch = [&] { return after && after->n > 0 ? launch_small_round_accept(*after, a, st) : launch_accept(a, st); };
   if ((c.flags & TSD_FLAG_BATCH_SYNC) && K > 0) {
     // the series' own counts first (their minimum lands in the sync word), then the commit
@@ -1089,6 +1202,12 @@ int tsd_create(const tsd_config* cfg, void* arena_dev, size_t arena_bytes, tsd_c
     }
     (void)hipGetLastError();
   }
+  if (lay.series) {
+    hipError_t e = hipMemset(ctx->count_out + kTicket, 0, 4);
+    if (e == hipSuccess) e = prepare_series();
+    ctx->series = e == hipSuccess;
+    (void)hipGetLastError();
+  }
   if (cfg->target.n_experts > 0 || cfg->draft.n_experts > 0) {
     hipError_t e = prepare_moe();
     if (e != hipSuccess) {
@@ -1205,6 +1324,21 @@ int tsd_load_weights(tsd_ctx* ctx, int which, const float* blob_dev, size_t n_fl
       HIP_TRY(ctx, frag(md.layers[l].W2, md.flayers[l].W2, D, F, 0));
     }
   }
+  if (ctx->series) {
+    const SeriesModel& s = md.series;
+    auto order = [&](const char* src, const float* dst, size_t N, size_t K, int qkv_hd) {
+      return launch_series_pack(reinterpret_cast<const float*>(src), const_cast<float*>(dst), (int)N, (int)K, qkv_hd, st);
+    };
+    HIP_TRY(ctx, order(md.W_e, s.We, D, P, 0));
+    HIP_TRY(ctx, order(md.W_h, s.Wh, P, D, 0));
+    for (int l = 0; l < md.c.n_layers; ++l) {
+      const float* to = s.layers + (size_t)l * s.layer_words;
+      HIP_TRY(ctx, order(md.layers[l].Wqkv, to, 3 * D, D, md.hd));
+      HIP_TRY(ctx, order(md.layers[l].Wo, to + s.o_out, D, D, 0));
+      HIP_TRY(ctx, order(md.layers[l].W1, to + s.o_up, F, D, 0));
+      HIP_TRY(ctx, order(md.layers[l].W2, to + s.o_down, D, F, 0));
+    }
+  }
   md.loaded = true;
   return TSD_OK;
 }
@@ -1289,13 +1423,20 @@ int tsd_prefill(tsd_ctx* ctx, const float* series_dev, int32_t B, int32_t n_ctx_
   // first runs launch by launch, a program that forecasts once pays for no capture).  Larger batches keep the GPU busy
   // for longer than their launches take to enqueue.
   const bool again = ctx->context_B == B && ctx->context_N == N;
+  const bool series = use_series(ctx) && series_context_short(nq);
   if (!again && ctx->graph_context) {
     (void)hipGraphExecDestroy(ctx->graph_context);
     ctx->graph_context = nullptr;
   }
   ctx->context_B = B;
   ctx->context_N = N;
-  const int rc = (again && B <= chunk) ? run_graphed(ctx, &ctx->graph_context, st, context, /*counts=*/false) : context();
+  if (series) {
+    SeriesP p = series_args(ctx);
+    p.n = B;
+    HIP_TRY(ctx, launch_series_context(c, p, ctx->znorm, N, st));
+    ctx->series_passes++;
+  }
+  const int rc = series ? (int)TSD_OK : (again && B <= chunk) ? run_graphed(ctx, &ctx->graph_context, st, context, /*counts=*/false) : context();
   if (rc) return rc;
   ctx->prefilled = true;
   if (!ctx->small_round) HIP_TRY(ctx, note_pass(&ctx->use, st));  // (a small handle's context is short, its first round tells)
@@ -1327,7 +1468,15 @@ int tsd_refill(tsd_ctx* ctx, const int32_t* slots_host, int32_t n, const float* 
   HIP_TRY(ctx, launch_identity_list(ctx->act_list, ctx->count_out, ctx->B, ctx->T, st));
   const int nq = N - 1;
   const int chunk = std::max(1, ctx->rows_max / nq);
-  for (int which = 0; which < 2; ++which)
+  const bool series = use_series(ctx) && series_context_short(nq);
+  if (series) {
+    SeriesP p = series_args(ctx);
+    p.act = ctx->refill_list;
+    p.n = n;
+    HIP_TRY(ctx, launch_series_context(c, p, ctx->znorm, N, st));
+    ctx->series_passes++;
+  }
+  for (int which = 0; which < 2 && !series; ++which)
     for (int s0 = 0; s0 < n; s0 += chunk) {
       Pass ps;
       std::memset(&ps, 0, sizeof(ps));
@@ -1380,6 +1529,11 @@ int tsd_draft_propose(tsd_ctx* ctx, void* stream) {
   // one.  After a fully accepted round the draft cache lacks the former (it proposed x_K but
   // never consumed it); for the other series the rewrite stores identical values.
   if (!ctx->fused_draft && use_small_round(ctx, st) && (rc = run_small_phase(ctx, 1, st)) != kResidentBusy) return rc;
+  if (use_series(ctx)) {
+    if ((rc = run_series_round(ctx, 1, false, false, st))) return rc;
+    HIP_TRY(ctx, note_pass(&ctx->use, st));
+    return TSD_OK;
+  }
   const Cover cv = cover(ctx);
   if (cv.n == 0) return TSD_OK;
   if (ctx->fused_draft) {
@@ -1512,6 +1666,11 @@ int tsd_target_verify(tsd_ctx* ctx, void* stream) {
   const tsd_config& c = ctx->cfg;
   const int P = c.patch, K = c.K;
   if (use_small_round(ctx, (hipStream_t)stream) && (rc = run_small_phase(ctx, 2, (hipStream_t)stream)) != kResidentBusy) return rc;
+  if (use_series(ctx)) {
+    if ((rc = run_series_round(ctx, 2, false, false, (hipStream_t)stream))) return rc;
+    HIP_TRY(ctx, note_pass(&ctx->use, (hipStream_t)stream));
+    return TSD_OK;
+  }
   const int Kr = round_positions(ctx);  // boundaries beyond Kr + 1 belong to patches no active series can commit
   const Cover cv = cover(ctx);
   if (cv.n == 0) return TSD_OK;
@@ -1572,6 +1731,17 @@ int tsd_round(tsd_ctx* ctx, void* stream) {
     if ((rc = run_small_round(ctx, 3, false, (hipStream_t)stream, resident)) == kResidentBusy) small = false;
     else if (rc) return rc;
   }
+  if (use_series(ctx) && !(ctx->cfg.flags & TSD_FLAG_BATCH_SYNC)) {
+    ctx->injected = false;
+    if ((rc = run_series_round(ctx, 7, false, deliver, (hipStream_t)stream))) return rc;
+    HIP_TRY(ctx, note_pass(&ctx->use, (hipStream_t)stream));
+    ctx->need_lb = std::max(0, need_before - (ctx->cfg.K + 1));
+    if (deliver) {
+      ctx->seq_launched++;
+      ctx->compact_pending = true;
+    }
+    return TSD_OK;
+  }
   const int cls = device_counts(ctx) ? size_class(ctx) : 0;
   ctx->capture_rows = class_rows(ctx, cls);
   auto body = [&]() {
@@ -1608,6 +1778,11 @@ int tsd_target_step(tsd_ctx* ctx, void* stream) {
   if (use_small_round(ctx, (hipStream_t)stream) && (rc = run_small_round(ctx, 2, true, (hipStream_t)stream, resident)) != kResidentBusy) {
     if (rc) return rc;
     return accept_commit_impl(ctx, nullptr, 0, (hipStream_t)stream, &resident);
+  }
+  if (use_series(ctx)) {
+    if ((rc = run_series_round(ctx, 6, true, false, (hipStream_t)stream))) return rc;
+    HIP_TRY(ctx, note_pass(&ctx->use, (hipStream_t)stream));
+    return TSD_OK;
   }
   rc = run_graphed(ctx, &ctx->graph_step, (hipStream_t)stream, [&]() {
     Pass ps;
@@ -1840,7 +2015,7 @@ int tsd_profile_launches(tsd_ctx* ctx, tsd_launch_rec* out_host, int32_t max_rec
 int tsd_resident_passes(tsd_ctx* ctx, int64_t* n_host) {
   if (!ctx) return fail(nullptr, TSD_E_INVALID_ARG, "ctx is NULL");
   if (!n_host) return fail(ctx, TSD_E_INVALID_ARG, "n_host is NULL");
-  *n_host = ctx->small_passes;
+  *n_host = ctx->small_passes + ctx->series_passes;
   return TSD_OK;
 }
 

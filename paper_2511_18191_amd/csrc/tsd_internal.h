@@ -255,6 +255,53 @@ struct AcceptP;
 hipError_t launch_small_round_alone(const SmallRoundP& p, hipStream_t st);
 hipError_t launch_small_round_accept(const SmallRoundP& r, const AcceptP& p, hipStream_t st);
 
+// ---- passes of small fp32 models, a series per workgroup: see series_f32.hip ----
+struct SeriesModel {
+  // weights in the order its products read them (launch_series_pack): embedding, head; the layers, layer_words apart, each QKV, output
+  // projection (at o_out words), FFN up and down
+  const float *We, *Wh, *layers;
+  size_t layer_words, o_out, o_up, o_down;
+  float* kv_pool;               // layer after layer
+  size_t layer_pool_elems;
+  const float *rope_cos, *rope_sin;
+  int L, D, shape;              // shape: number of its kernel's sizes (series_shape)
+  float scale;                  // 1 / sqrt(head_dim)
+};
+struct SeriesP {
+  SeriesModel m[2];             // TSD_TARGET, TSD_DRAFT
+  int D_max, half_max, S_max;   // widest model, most rotary pairs, cached tokens at most: the layout of its LDS
+  const int* page_table;
+  int pt_stride, PT, pt_shift;
+  const int* len;
+  const int* act;               // slot j is series act[j] (NULL: series j)
+  const int* counts;            // device-side {listed series, most patches still needed} (NULL: n series)
+  int n;                        // listed series at most
+  int K, P;                     // positions at most ...
+  int follow_need;              // ... and no more than counts[1]
+  int phases;                   // 1: draft steps, 2: target pass, 4: acceptance step
+  int step_only;                // target pass over the pending token alone
+  const float *prev, *pending;  // [B][P]
+  float* X;
+  long x_stride;
+  float* mu_p;
+  long mu_stride;
+};
+struct CompactP {               // compaction behind a round (see launch_compact_active; host NULL: none)
+  int *active, *committed;
+  int T, B;
+  int *list, *count, *host;
+  int* ticket;                  // workgroups of the launch that have committed, zero between launches
+};
+struct AcceptP;
+bool series_rounds_ok(const tsd_config& c);
+int series_shape(const tsd_model_cfg& m);
+bool series_context_short(int tokens);  // a context pass of so many tokens is one of them
+size_t series_packed_words(int N, int K);
+hipError_t launch_series_pack(const float* src, float* dst, int N, int K, int qkv_hd, hipStream_t st);
+hipError_t prepare_series();
+hipError_t launch_series_round(const tsd_config& c, const SeriesP& p, const AcceptP& a, const CompactP& k, hipStream_t st);
+hipError_t launch_series_context(const tsd_config& c, const SeriesP& p, const float* znorm, int N, hipStream_t st);
+
 struct PackP {
   const float* W;     // [K][N] row-major source (y = x W)
   const float* gain;  // [K] or NULL: folded as W'[n][k] = gain[k] * W[k][n]
