@@ -257,7 +257,11 @@ int tsd_accept_commit_static(const float* X_dev, const float* mu_q_dev, const fl
  * (launch by launch the two overlap); tsd_resident_passes tells how often it ran.  Should its
  * workgroups not become resident together (another process's launch may hold compute units) within the time of
  * tsd_set_resident_wait, one workgroup finishes the pass alone: the results are the same, the pass takes some 3 us per workgroup and
- * stage, and the handle runs kernel by kernel from then on. */
+ * stage, and the handle runs kernel by kernel from then on.
+ * An fp32 handle of small dense models (d_model of 32, 64 or 128, d_ff four times that; a layer's keys and values of one series in
+ * LDS) runs a round of at most 512 series, the acceptance and the count of active series included, a target-only step and a short
+ * context pass as ONE launch each, a workgroup per series, bit for bit the kernel-by-kernel result; not between
+ * tsd_profile_begin and tsd_profile_end, nor with TSD_FLAG_SAMPLE_PROPOSALS or TSD_FLAG_NAIVE_VERIFY. */
 int tsd_round(tsd_ctx* ctx, void* stream);
 
 /* Rounds until no series needs patches any more (or max_rounds rounds have run): the loop
@@ -390,8 +394,9 @@ typedef struct {
 } tsd_launch_rec;
 int tsd_profile_launches(tsd_ctx* ctx, tsd_launch_rec* out_host, int32_t max_records, int32_t* n_host);
 
-/* Launches of the resident decode kernel (see tsd_round) this handle has made since tsd_create: one per tsd_round,
- * tsd_target_step, tsd_draft_propose or tsd_target_verify that took it.  Host-only. */
+/* Passes this handle has run as one launch since tsd_create (see tsd_round), on the resident decode kernel or, of small fp32 models, a
+ * workgroup per series: one per tsd_round, tsd_target_step, tsd_draft_propose or tsd_target_verify that took it, and of the latter
+ * kind tsd_prefill and tsd_refill.  Host-only. */
 int tsd_resident_passes(tsd_ctx* ctx, int64_t* n_host);
 
 /* How long the workgroups of later launches of the resident kernel wait for one another, 1000 ms unless set; 0: not at

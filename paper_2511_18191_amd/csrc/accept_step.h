@@ -14,9 +14,10 @@ namespace tsd {
 // The kernel is a chain of memory round trips, so there are three of them: the state words together with all patches (those
 // of positions that turn out not to count included), then the rows to copy, then the stores.  One wavefront per series,
 // positions in fours and the state words one after the other, took 10.6 us at 1024 series of 6 x 96, 7.9 at one of 4 x 96.
-__device__ __forceinline__ void accept_step(const AcceptP& p) {
+// Returned, by lane 0 alone: whether the series goes on, and how many patches it has committed.
+__device__ __forceinline__ int2 accept_step(const AcceptP& p) {
   __shared__ float energy[2][16];
-  if (p.n_dev && (int)blockIdx.x >= *p.n_dev) return;
+  if (p.n_dev && (int)blockIdx.x >= *p.n_dev) return make_int2(0, 0);
   const int b = p.act ? p.act[blockIdx.x] : (int)blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int K = p.K, P = p.P;
   const int KE = K > 0 ? K : 1;
@@ -71,7 +72,7 @@ __device__ __forceinline__ void accept_step(const AcceptP& p) {
       p.ell[(long)b * KE + tid] = NAN;
       p.logu[(long)b * KE + tid] = NAN;
     }
-    return;
+    return make_int2(0, c0);
   }
   // a series with fewer than K patches left proposes and tests only as many positions as it
   // still needs: later ones could never be committed
@@ -111,7 +112,7 @@ __device__ __forceinline__ void accept_step(const AcceptP& p) {
   }
   if (p.mode == 1) {  // synchronised round, first launch: only the minimum over the series
     if (tid == 0) atomicMin(p.sync, n);
-    return;
+    return make_int2(1, c0);
   }
   if (p.mode == 2) n = min(n, *p.sync);
   if (tid < K && p.ell) p.ell[(long)b * KE + tid] = is_tested ? ell : NAN;
@@ -150,6 +151,7 @@ __device__ __forceinline__ void accept_step(const AcceptP& p) {
       st[4] += __popcll(near);
     }
   }
+  return make_int2(c0 + Lc < p.T ? 1 : 0, c0 + Lc);
 }
 
 }  // namespace tsd

@@ -2,19 +2,22 @@
 // the compaction behind it as one launch, and the context pass of both models as another.
 //
 // Kernel by kernel such a round is some 35 dependent launches of 4 to 6 us that each touch a few KB.  Series never exchange
-// anything inside a round, so a workgroup of 16 wavefronts takes its series through every stage with barriers of its own in
-// place of launches; residual, activations and the layer's keys and values sit in LDS.  What bounds it: every workgroup streams
-// all weights through its compute unit's load path (a layer of 64 x 256 is 0.2 MB), the chain of K / 4 matrix instructions of
-// a product, and the barriers in between.
+// anything inside a round, so a workgroup of 8 wavefronts takes its series through every stage with barriers of its own in
+// place of launches; residual, activations, patches and the layer's keys and values sit in LDS.  8 series through 2 layers of 64 (draft 1 of
+// 32, 32 patches of context, K = 4): 544 us a forecast kernel by kernel, 188 here; a round 64 us, the context 33.  What bounds it: the
+// chain of latencies of a stage (a barrier, LDS, 8 to 64 matrix instructions of 32 clocks, an epilogue: 1 to 2 us), not bytes.
 //
-//   * A wavefront takes every 16th block of 16 columns of a product and its whole k range: v_mfma_f32_16x16x4_f32, k in ascending
+//   * Sizes are template parameters (Shape): known only at run time they made a product's stage some 1000 instructions long, 4000
+//     clocks for 500 of matrix instructions, and a round of 127 us.
+//   * A wavefront takes every 8th block of 16 columns of a product and its whole k range: v_mfma_f32_16x16x4_f32, k in ascending
 //     order as in gemm_f32.hip, same bits.  The weights are a second copy in the order the lanes want them (16 bytes of a row's
 //     16-wide k-run per lane and load, a KB per load); activations in LDS have the four k of a run that belong to a lane next to
 //     each other (run_pos).
 //   * The first loads of a wavefront's next product are issued as soon as its registers are free, before the epilogue and the
 //     barrier in between (a bare barrier: weight loads stay in flight across it).
 //   * QKV columns are packed in rotary-pair order: a block is eight columns of the first half of a head and their partners.
-//   * Attention: a wavefront per (query, head), the sums of attn_kernel (attn.hip) in the same order.
+//   * Attention: up to eight queries a wavefront per (query, head), the sums of attn_kernel (attn.hip) in the same order; more of them
+//     16 at a time on the matrix cores (attend16), with the same bits.
 #include <type_traits>
 
 #include "accept_step.h"
@@ -31,25 +34,30 @@ constexpr int kChunk = 8;   // 16-wide k-runs whose weights are in registers at 
 __host__ __device__ constexpr int run_pos(int c) { return (c & ~15) | ((c & 3) << 2) | ((c >> 2) & 3); }
 __host__ __device__ constexpr int up16(int n) { return (n + 15) & ~15; }
 
-// LDS of a workgroup, in words (rows: a multiple of 16; S: cached tokens at most).
+// LDS of a workgroup, in words.  `rows`: of a pass, a multiple of 16; `tokens`: a launch has patches and rotary factors for at a
+// time, for as many models; S: cached tokens at most.
 struct Carve {
-  int x, cos, sin, pos, table, probs, shared, total;
+  int x, cos, sin, patch, odd, table, probs, shared, total;
 };
-// Words of the part that one stage after the other uses: queries, attention output, keys and values; hidden rows; patches.
-__host__ __device__ constexpr int shared_words(int D, int F, int P, int rows, int S) {
-  const int attn = (2 * rows + 2 * S) * (D + 4), hid = rows * (up16(F) + 4), patch = rows * (up16(P) + 4);
-  return attn > hid ? (attn > patch ? attn : patch) : (hid > patch ? hid : patch);
+// A wavefront's attention weights: of one query, or of 16 and 32 keys.
+constexpr int kTileKeys = 64, kLdProbs = 36;
+__host__ __device__ constexpr int probs_words(int S) { return up16(S) > 16 * kLdProbs ? up16(S) : 16 * kLdProbs; }
+// Words of the part that one stage after the other uses: queries, attention output, keys and values; hidden rows.
+__host__ __device__ constexpr int shared_words(int D, int F, int rows, int S) {
+  const int attn = (2 * rows + 2 * S) * (D + 4), hid = rows * (F + 4);
+  return attn > hid ? attn : hid;
 }
-__host__ __device__ constexpr Carve carve_of(int D, int half, int rows, int S, int shared) {
+__host__ __device__ constexpr Carve carve_of(int D, int half, int P, int rows, int tokens, int models, int S, int shared) {
   Carve c{};
   c.x = 0;
   c.cos = rows * (D + 4);
-  c.sin = c.cos + rows * half;
-  c.pos = c.sin + rows * half;
-  c.table = c.pos + rows;
+  c.sin = c.cos + models * tokens * half;
+  c.patch = c.sin + models * tokens * half;
+  c.odd = c.patch + tokens * (up16(P) + 4);
+  c.table = c.odd + 4;
   c.probs = c.table + 64;
-  c.shared = (c.probs + kWaves * ((S + 3) & ~3) + 3) & ~3;
-  c.total = c.shared + shared;
+  c.shared = c.probs + kWaves * probs_words(S);
+  c.total = c.shared + shared;  // (a pass of fewer than its rows reads on behind its rotary factors: they are in front)
   return c;
 }
 
@@ -153,12 +161,15 @@ __device__ __forceinline__ float over_rows(float v, Op op) {  // l ^ 16
   return op(__uint_as_float(p[0]), __uint_as_float(p[1]));
 }
 template <typename Op>
-__device__ __forceinline__ float over_wave(float v, Op op) {
-  v = over_rows(over_halves(v, op), op);
+__device__ __forceinline__ float over16(float v, Op op) {
   v = op(v, rotate16(v, std::integral_constant<int, 8>{}));
   v = op(v, rotate16(v, std::integral_constant<int, 4>{}));
   v = op(v, rotate16(v, std::integral_constant<int, 2>{}));
   return op(v, rotate16(v, std::integral_constant<int, 1>{}));
+}
+template <typename Op>
+__device__ __forceinline__ float over_wave(float v, Op op) {
+  return over16(over_rows(over_halves(v, op), op), op);
 }
 struct Add {
   __device__ __forceinline__ float operator()(float a, float b) const { return a + b; }
@@ -241,17 +252,95 @@ __device__ __forceinline__ void attend(const float* q, const float* Ks, const fl
   wave_lds_order();
 }
 
-// One pass of one series: nq tokens (at most 16 RT) at positions base, base + 1, ..
+// The same for the 16 queries q, q + ld, .. of a head (`rows` of them there are) on the matrix cores, key `base` the first query's own,
+// S keys in all, at most kTileKeys: the same bits.  Scores: a matrix instruction adds its four products in ascending order, as the
+// chain above does.  Sums of the exponentials: a lane holds key l % 16 of a block of 16, and the four blocks of 64 keys are what
+// the lanes 16 apart held.  Output: four keys per instruction, the 64 / HD groups of keys in sums of their own, added in their order.
+// A weight of a key the query does not see is zero, and its value has to be finite (see run_series_pass).
+// ps: 16 x kLdProbs words of this wavefront's.
+template <int HD, int LDX>
+__device__ __forceinline__ void attend16(const float* q, const float* Ks, const float* Vs, int base, int S, float* ps, float* out, int c0, int lane) {
+  constexpr int NKB = kTileKeys / 16, G = 64 / HD, CB = HD / 16;
+  const int l15 = lane & 15, lq = lane >> 4, n_kb = (S + 15) >> 4;
+  f32x4 sc[NKB];
+  {
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb) sc[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float qf[HD / 4];
+#pragma unroll
+    for (int e = 0; e < HD / 4; ++e) qf[e] = q[l15 * LDX + 4 * e + lq];
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb) {
+      if (kb >= n_kb) break;
+      const float* kr = Ks + min(16 * kb + l15, S - 1) * LDX + lq;
+#pragma unroll
+      for (int e = 0; e < HD / 4; ++e) sc[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(qf[e], kr[4 * e], sc[kb], 0, 0, 0);
+    }
+  }
+  // this lane: queries 4 lq + r, keys 16 kb + l15
+  float inv[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int seen = min(base + 4 * lq + r, S - 1);
+    float m = -INFINITY;
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb) {
+      if (kb >= n_kb) break;
+      if (16 * kb + l15 > seen) sc[kb][r] = -INFINITY;
+      m = fmaxf(m, sc[kb][r]);
+    }
+    m = over16(m, Max{});
+    float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb) {
+      if (kb >= n_kb) break;
+      sc[kb][r] = __expf(sc[kb][r] - m);
+      part[kb & 3] += sc[kb][r];
+    }
+    inv[r] = 1.f / over16((part[0] + part[2]) + (part[1] + part[3]), Add{});
+  }
+  f32x4 o[4];  // group g, block of 16 output columns cb: o[g * CB + cb]
+  clear<4>(o);
+#pragma unroll
+  for (int k2 = 0; k2 < NKB / 2; ++k2) {  // 32 keys at a time through LDS
+    if (2 * k2 >= n_kb) break;
+    wave_lds_order();
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) ps[(4 * lq + r) * kLdProbs + 16 * j + l15] = 2 * k2 + j < n_kb ? sc[2 * k2 + j][r] : 0.f;
+    wave_lds_order();
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int key = 32 * k2 + 4 * j + lq;
+      const float w = ps[l15 * kLdProbs + 4 * j + lq];
+      const float* vr = Vs + min(key, S - 1) * LDX + l15;
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) {
+        const float v = key < S ? vr[16 * cb] : 0.f;
+        o[j % G * CB + cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, v, o[j % G * CB + cb], 0, 0, 0);
+      }
+    }
+  }
+  wave_lds_order();
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) {
+    if constexpr (G == 4) o[cb] = (o[0] + o[1]) + (o[2] + o[3]);
+    if constexpr (G == 2) o[cb] = o[cb] + o[CB + cb];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[(4 * lq + r) * LDX + run_pos(c0 + 16 * cb + l15)] = o[cb][r] * inv[r];
+  }
+}
+
+// One pass of one series: nq tokens (at most 16 RT) at positions base, base + 1, .., which are tokens first, first + 1, .. of the launch
 struct SeriesPass {
-  int nq, base;
-  const float *src0, *src1;  // token t's patch: src0 + t P (t < n0), else src1 + (t - n0) P
-  int n0;
+  int nq, base, first;
   float* out;  // head outputs of tokens t_skip, .. (NULL: no head)
   int t_skip;
+  int keep;    // they are the patches of tokens keep, .. of the launch (0: they are not)
 };
 
-// The model sizes there are kernels for: widths of 32, 64 and 128 with a four times as wide FFN.  (Sizes known only at run time made
-// a product's stage some 1000 instructions long, 4000 clocks for 500 of matrix instructions.)
+// The model sizes there are kernels for: widths of 32, 64 and 128 with a four times as wide FFN.
 template <int D_, int HD_>
 struct Shape {
   static constexpr int D = D_, F = 4 * D_, HD = HD_, H = D_ / HD_, HALF = HD_ / 2, DB = D_ / 16, FB = F / 16, LDX = D_ + 4, LDH = F + 4;
@@ -271,30 +360,15 @@ __device__ __forceinline__ void run_series_pass(const SeriesP& p, const SeriesMo
   int lane = tid & 63, l15 = lane & 15, lq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int P = p.P, nq = ps.nq, base = ps.base, S = base + nq, ldp = up16(P) + 4, pr = up16(P) >> 4;
-  const Carve c = carve_of(p.D_max, p.half_max, R, p.S_max, 0);
-  float *x = lds + c.x, *cs = lds + c.cos, *sn = lds + c.sin, *shared = lds + c.shared;
-  int *row_at = reinterpret_cast<int*>(lds + c.pos), *table = reinterpret_cast<int*>(lds + c.table);
-  float *q = shared, *att = q + R * LDX, *Ks = att + R * LDX, *Vs = Ks + S * LDX, *hid = shared, *patch = shared;
-  float* probs = lds + c.probs + wave * ((p.S_max + 3) & ~3);
+  const Carve c = carve_of(p.D_max, p.half_max, P, R, p.tokens, p.models, p.S_max, 0);
+  const int rope = (p.models == 2 ? m.draft * p.tokens * p.half_max : 0) + ps.first * HALF;
+  float *x = lds + c.x, *cs = lds + c.cos + rope, *sn = lds + c.sin + rope, *shared = lds + c.shared, *patch = lds + c.patch;
+  const int* table = reinterpret_cast<const int*>(lds + c.table);
+  float *q = shared, *att = q + R * LDX, *Ks = att + R * LDX, *Vs = Ks + S * LDX, *hid = shared;
+  float* probs = lds + c.probs + wave * probs_words(p.S_max);
+  volatile int* odd = reinterpret_cast<int*>(lds + c.odd);  // a value of the pass's tokens is not finite
   const int plane = p.PT * HD;  // a head's keys of a page; its values are H planes on
   auto token_at = [&](int tok) { return (table[tok >> p.pt_shift] * 2 * H * p.PT + (tok & (p.PT - 1))) * HD; };
-
-  // ---- patches, rotary factors, where the rows' keys go ----
-  for (int t = wave; t < nq; t += kWaves)
-    for (int k4 = lane; k4 < pr * 4; k4 += 64) {
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (k4 < P >> 2) v = *reinterpret_cast<const float4*>((t < ps.n0 ? ps.src0 + t * P : ps.src1 + (t - ps.n0) * P) + k4 * 4);
-      float* to = patch + t * ldp + (k4 & ~3) * 4 + (k4 & 3);
-      to[0] = v.x;
-      to[4] = v.y;
-      to[8] = v.z;
-      to[12] = v.w;
-    }
-  for (int i = tid; i < nq * HALF; i += kThreads) {  // (positions are consecutive)
-    cs[i] = m.rope_cos[base * HALF + i];
-    sn[i] = m.rope_sin[base * HALF + i];
-  }
-  if (tid < nq) row_at[tid] = token_at(base + tid);
   // keys and values of earlier passes, 16 bytes at a time: half a wavefront the keys, half the values of FIT tokens, the wavefronts
   // tokens in turn
   constexpr int C4 = D / 4, FIT = 32 / C4, U = 4, STEP = kWaves * FIT;
@@ -333,16 +407,22 @@ __device__ __forceinline__ void run_series_pass(const SeriesP& p, const SeriesMo
   using Db = std::integral_constant<int, DB>;
   using Fb = std::integral_constant<int, FB>;
 
-  lds_barrier();
+  float4 old[U];
+  fetch(m.kv_pool, tok_first, old);
   if (wave < DB) {
-    const float* a0 = patch + l15 * ldp + lq * 4;
+    const float* a0[RT];  // (rows past nq: the last one's patch)
+#pragma unroll
+    for (int i = 0; i < RT; ++i) a0[i] = patch + (ps.first + min(16 * i + l15, nq - 1)) * ldp + lq * 4;
     f32x4 acc[RT];
     clear<RT>(acc);
     for (int t0 = 0; t0 < pr; t0 += kChunk) {
       if (t0) load_some_runs(m.We, wave * pr + t0, pr - t0, lane, f[0]);
 #pragma unroll
       for (int t = 0; t < kChunk; ++t)
-        if (t0 + t < pr) add_runs<RT, 1>(a0 + (t0 + t) * 16, ldp, &f[0].w[t], acc);
+        if (t0 + t < pr) {
+#pragma unroll
+          for (int i = 0; i < RT; ++i) add_runs<1, 1>(a0[i] + (t0 + t) * 16, 0, &f[0].w[t], acc + i);
+        }
     }
     first_of(W, 3 * DB, Db{});
     float* to = x_at(wave);
@@ -361,8 +441,6 @@ __device__ __forceinline__ void run_series_pass(const SeriesP& p, const SeriesMo
     l15 = lane & 15;
     lq = lane >> 4;
     float* pool = m.kv_pool + (size_t)l * m.layer_pool_elems;
-    float4 old[U];
-    fetch(pool, tok_first, old);  // (put down behind the product)
     {
       float rs[RT];
       row_scales<RT, D>(x, lane, rs);
@@ -396,8 +474,10 @@ __device__ __forceinline__ void run_series_pass(const SeriesP& p, const SeriesMo
             for (int r = 0; r < 4; ++r) {
               const int row = 16 * i + 4 * lq + r;
               if (row < nq) {
+                // (a value that is none: only queries that see its key may, and attention takes them one by one)
+                if (which == 2 && !(fabsf(acc[i][r]) < INFINITY)) *odd = 1;
                 to[row * LDX] = acc[i][r];
-                cache[row_at[row]] = acc[i][r];
+                cache[token_at(base + row)] = acc[i][r];
               }
             }
         }
@@ -410,9 +490,17 @@ __device__ __forceinline__ void run_series_pass(const SeriesP& p, const SeriesMo
     }
     lds_barrier();
     // ---- attention ----
-    for (int t = wave; t < nq * H; t += kWaves) {
-      const int row = t / H, c0 = t % H * HD;
-      attend<HD>(q + row * LDX + c0, Ks + c0, Vs + c0, LDX, base + row + 1, probs, att + row * LDX, c0, lane);
+    // (up to eight queries a wavefront each is faster: a round of 5 tokens 61 us against 70, a context of 31 48 against 33)
+    if (nq > 8 && S <= kTileKeys && !*odd) {
+      for (int t = wave; t < ((nq + 15) >> 4) * H; t += kWaves) {
+        const int row = t / H * 16, c0 = t % H * HD;
+        attend16<HD, LDX>(q + row * LDX + c0, Ks + c0, Vs + c0, base + row, S, probs, att + row * LDX, c0, lane);
+      }
+    } else {
+      for (int t = wave; t < nq * H; t += kWaves) {
+        const int row = t / H, c0 = t % H * HD;
+        attend<HD>(q + row * LDX + c0, Ks + c0, Vs + c0, LDX, base + row + 1, probs, att + row * LDX, c0, lane);
+      }
     }
     lds_barrier();
     product<RT, DB, DB, LDX>(W + m.o_out, att, wave, lane, f, [&] { first_of(W + m.o_up, FB, Db{}); }, add_to_x);
@@ -429,6 +517,7 @@ __device__ __forceinline__ void run_series_pass(const SeriesP& p, const SeriesMo
           for (int r = 0; r < 4; ++r) to[(16 * i + r) * LDH] = gelu_tanh(acc[i][r]);
       });
     }
+    if (l + 1 < m.L) fetch(pool + m.layer_pool_elems, tok_first, old);  // (put down behind the next QKV product)
     lds_barrier();
     product<RT, DB, FB, LDH>(W + m.o_down, hid, wave, lane, f, [&] {
       if (l + 1 < m.L) first_of(W + m.layer_words, 3 * DB, Db{});
@@ -455,7 +544,10 @@ __device__ __forceinline__ void run_series_pass(const SeriesP& p, const SeriesMo
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int row = 16 * i + 4 * lq + r;
-          if (col < P && row < nq && row >= ps.t_skip) ps.out[(row - ps.t_skip) * P + col] = acc[i][r];
+          if (col < P && row < nq && row >= ps.t_skip) {
+            ps.out[(row - ps.t_skip) * P + col] = acc[i][r];
+            if (ps.keep) patch[(ps.keep + row - ps.t_skip) * ldp + 16 * blk + run_pos(l15)] = acc[i][r];
+          }
         }
     }
   }
@@ -482,9 +574,39 @@ __device__ __forceinline__ void run_any_pass(const SeriesP& p, const SeriesModel
   }
 }
 
-__device__ __forceinline__ void load_table(const SeriesP& p, int b, int rows, float* lds) {
-  int* table = reinterpret_cast<int*>(lds + carve_of(p.D_max, p.half_max, rows, p.S_max, 0).table);
-  if ((int)threadIdx.x < p.pt_stride) table[threadIdx.x] = p.page_table[(long)b * p.pt_stride + threadIdx.x];
+// What the passes of a launch share: patches of its tokens, as far as they are there before it, their rotary factors, the page table.
+// Token t sits at position pos + t; model: the first of p.models; patch_of(t): its patch (NULL: a pass of the launch makes it).
+template <int RT, typename Patch>
+__device__ __forceinline__ void set_up(const SeriesP& p, int model, int b, int pos, int n, float* lds, Patch patch_of) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const Carve c = carve_of(p.D_max, p.half_max, p.P, 16 * RT, p.tokens, p.models, p.S_max, 0);
+  int* table = reinterpret_cast<int*>(lds + c.table);
+  if (tid < p.pt_stride) table[tid] = p.page_table[(long)b * p.pt_stride + tid];
+  if (tid == 64) reinterpret_cast<int*>(lds + c.odd)[0] = 0;
+  const int n4 = up16(p.P) >> 2;
+  for (int t = wave; t < n; t += kWaves) {
+    const float* src = patch_of(t);
+    for (int k4 = lane; k4 < n4; k4 += 64) {
+      const bool in = k4 < p.P >> 2;
+      if (!src && in) continue;
+      const float4 v = in ? *reinterpret_cast<const float4*>(src + k4 * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+      float* to = lds + c.patch + t * (n4 * 4 + 4) + (k4 & ~3) * 4 + (k4 & 3);
+      to[0] = v.x;
+      to[4] = v.y;
+      to[8] = v.z;
+      to[12] = v.w;
+    }
+  }
+#pragma unroll
+  for (int w = 0; w < 2; ++w) {
+    if (w == p.models) break;
+    const SeriesModel& m = p.m[model + w];
+    const int at = w * p.tokens * p.half_max;
+    for (int i = tid; i < n * m.half; i += kThreads) {  // (positions are consecutive)
+      lds[c.cos + at + i] = m.rope_cos[pos * m.half + i];
+      lds[c.sin + at + i] = m.rope_sin[pos * m.half + i];
+    }
+  }
   __syncthreads();
 }
 
@@ -494,11 +616,12 @@ __device__ __forceinline__ void compact(const CompactP& c) {
   __shared__ int wave_cnt[4], most[4];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   auto fresh = [](const int* a) { return __hip_atomic_load(const_cast<int*>(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  const int seq = c.count[4] + 1;
   int base = 0, rem = 0;
   for (int b0 = 0; b0 < c.B; b0 += 256) {
-    const int b = b0 + tid;
-    const bool on = b < c.B && fresh(c.active + b) != 0;
-    if (on) rem = max(rem, c.T - fresh(c.committed + b));
+    const int b = min(b0 + tid, c.B - 1), on_b = fresh(c.active + b), done = fresh(c.committed + b);
+    const bool on = b0 + tid < c.B && on_b != 0;
+    if (on) rem = max(rem, c.T - done);
     const unsigned long long m = __ballot(on);
     if (lane == 0) wave_cnt[w] = __popcll(m);
     __syncthreads();
@@ -518,11 +641,12 @@ __device__ __forceinline__ void compact(const CompactP& c) {
     rem = max(max(most[0], most[1]), max(most[2], most[3]));
     c.count[0] = base;
     c.count[1] = rem;
-    const int seq = c.count[4] + 1;
     c.count[4] = seq;
-    c.host[0] = base;
-    c.host[1] = rem;
-    __hip_atomic_store(&c.host[2], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    // (the launch's number goes last: the caller watches it)
+    __hip_atomic_store(&c.host[0], base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&c.host[1], rem, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __hip_atomic_store(&c.host[2], seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -544,9 +668,12 @@ __global__ __launch_bounds__(kThreads) void series_round_kernel(const SeriesP p,
   Frags f[2];
   prefetch_embed(p.m[p.phases & 1 ? 1 : 0], p.P, wave, tid & 63, f);
   const int len = p.len[b], P = p.P;
-  load_table(p, b, 16 * RT, series_lds);
   float* X = p.X + (long)b * p.x_stride;
-  const float* pending = p.pending + (long)b * P;
+  // tokens of the launch: the one before the pending one, the pending one, the proposals
+  set_up<RT>(p, 0, b, len - 1, p.step_only ? 2 : Kr + 2, series_lds, [&](int t) -> const float* {
+    if (t < 2) return (t ? p.pending : p.prev) + (long)b * P;
+    return p.phases & 1 ? nullptr : X + (t - 2) * P;
+  });
   const int steps = p.phases & 1 ? Kr : 0, passes = steps + (p.phases & 2 ? 1 : 0);
 #pragma unroll 1
   for (int i = 0; i < passes; ++i) {
@@ -554,9 +681,9 @@ __global__ __launch_bounds__(kThreads) void series_round_kernel(const SeriesP p,
     const bool draft = i < steps;
     if (draft) {
       // step 1 takes the token before the pending one along (see tsd_draft_propose)
-      ps = i == 0 ? SeriesPass{2, len - 1, p.prev + (long)b * P, pending, 1, X, 1} : SeriesPass{1, len + i, X + (long)(i - 1) * P, nullptr, 1, X + (long)i * P, 0};
+      ps = i == 0 ? SeriesPass{2, len - 1, 0, X, 1, 2} : SeriesPass{1, len + i, i + 1, X + (long)i * P, 0, i + 2};
     } else {
-      ps = SeriesPass{p.step_only ? 1 : Kr + 1, len, pending, X, 1, p.mu_p + (long)b * p.mu_stride, 0};
+      ps = SeriesPass{p.step_only ? 1 : Kr + 1, len, 1, p.mu_p + (long)b * p.mu_stride, 0, 0};
     }
     run_any_pass<RT>(p, p.m[draft ? 1 : 0], ps, series_lds, f, [&] {
       if (i + 1 < passes) prefetch_embed(p.m[i + 1 < steps ? 1 : 0], P, wave, tid & 63, f);
@@ -564,13 +691,12 @@ __global__ __launch_bounds__(kThreads) void series_round_kernel(const SeriesP p,
   }
   if (!(p.phases & 4)) return;
   if (tid >= 256) return;  // (a barrier waits for the wavefronts that are left)
-  accept_step(a);
+  const int2 now = accept_step(a);
   if (!c.host) return;
   __shared__ int last;
   if (tid == 0) {
-    // (this lane wrote both)
-    __hip_atomic_store(c.active + b, a.active[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(c.committed + b, a.committed[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(c.active + b, now.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(c.committed + b, now.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     last = __hip_atomic_fetch_add(c.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
     if (last) __hip_atomic_store(c.ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -588,12 +714,12 @@ __global__ __launch_bounds__(kThreads) void series_context_kernel(const SeriesP 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   Frags f[2];
   prefetch_embed(m, p.P, wave, threadIdx.x & 63, f);
-  load_table(p, b, 16 * RT, series_lds);
   const float* z = znorm + (long)b * N * p.P;
 #pragma unroll 1
   for (int t0 = 0; t0 < N - 1; t0 += 16 * RT) {
     const int nq = min(16 * RT, N - 1 - t0);
-    run_any_pass<RT>(p, m, SeriesPass{nq, t0, z + (long)t0 * p.P, nullptr, nq, nullptr, 0}, series_lds, f,
+    set_up<RT>(p, blockIdx.y, b, t0, nq, series_lds, [&](int t) { return z + (long)(t0 + t) * p.P; });
+    run_any_pass<RT>(p, m, SeriesPass{nq, t0, 0, nullptr, 0, 0}, series_lds, f,
                      [&] { prefetch_embed(m, p.P, wave, threadIdx.x & 63, f); });
   }
 }
@@ -618,15 +744,25 @@ __global__ __launch_bounds__(256) void series_pack_kernel(const float* src, floa
 
 int rows_of(int tokens) { return tokens <= 16 ? 16 : 32; }
 
-size_t lds_bytes(const tsd_config& c, int rows) {
+constexpr size_t kMostLds = 156 * 1024;  // (the rest is the acceptance step's)
+
+// LDS of a launch with passes of `rows` rows over `tokens` tokens
+size_t lds_bytes(const tsd_config& c, int rows, int tokens, int models) {
   int shared = 0, D = 0, half = 0;
   for (const tsd_model_cfg* m : {&c.target, &c.draft}) {
-    const int w = shared_words(m->d_model, m->d_ff, c.patch, rows, c.max_tokens);
-    shared = w > shared ? w : shared;
-    D = m->d_model > D ? m->d_model : D;
-    half = m->d_model / m->n_heads / 2 > half ? m->d_model / m->n_heads / 2 : half;
+    shared = std::max(shared, shared_words(m->d_model, m->d_ff, rows, c.max_tokens));
+    D = std::max(D, m->d_model);
+    half = std::max(half, m->d_model / m->n_heads / 2);
   }
-  return (size_t)carve_of(D, half, rows, c.max_tokens, shared).total * 4;
+  return (size_t)carve_of(D, half, c.patch, rows, tokens, models, c.max_tokens, shared).total * 4;
+}
+
+// Rows at a time of a context pass of so many tokens (0: it is none of this kernel's).
+int context_rows(const tsd_config& c, int tokens) {
+  if (tokens > 128) return 0;
+  for (int rows = rows_of(tokens); rows >= 16; rows -= 16)
+    if (lds_bytes(c, rows, rows, 1) <= kMostLds) return rows;
+  return 0;
 }
 
 }  // namespace
@@ -639,38 +775,55 @@ hipError_t launch_series_pack(const float* src, float* dst, int N, int K, int qk
   return hipGetLastError();
 }
 
+// Series of a decode that one round takes a workgroup each for, two for every compute unit: behind that the launches of the tiled path
+// fill the chip (decodes and target-only steps, us, kernel by kernel / this: 2 layers of 64, 512 series 673 and 471 / 309 and 292, 1024
+// series 768 and 568 / 551 and 566; 3 layers of 128, 512 series 1143 and 981 / 677 and 895, 1024 series 1347 and 1243 / 1211 and 1764).
+constexpr int kMostSeries = 512;
+bool series_round_ok(int n) { return n <= kMostSeries; }
+
 bool series_rounds_ok(const tsd_config& c) {
   if (c.dtype != TSD_F32 || c.target.n_experts || c.draft.n_experts || (c.flags & (TSD_FLAG_SAMPLE_PROPOSALS | TSD_FLAG_NAIVE_VERIFY))) return false;
-  if (c.max_batch > 256) return false;
   for (const tsd_model_cfg* m : {&c.target, &c.draft})
     if (shape_of(m->d_model, m->n_heads, m->d_ff) < 0) return false;
-  return lds_bytes(c, 32) + 4096 <= 160 * 1024;
+  return lds_bytes(c, rows_of(c.K + 1), c.K + 2, 2) <= kMostLds;
 }
 
 int series_shape(const tsd_model_cfg& m) { return shape_of(m.d_model, m.n_heads, m.d_ff); }
-bool series_context_short(int tokens) { return tokens <= 128; }
+// A workgroup takes a context block by block of 32 tokens, so a few series with a long one leave the chip idle, where the launches of the
+// tiled path do not get longer (us, kernel by kernel / this: 2 layers of 64, 32 patches 95 / 36 and 64 patches 96 / 68 for 1 series, 96
+// patches 99 / 135; 3 layers of 128, 32 patches 158 / 118, 64 patches 163 / 238 for 1 series, 224 / 241 for 32, 415 / 246 for 128).
+bool series_context_ok(const tsd_config& c, int n, int tokens) {
+  const int wide = std::max(c.target.d_model, c.draft.d_model);
+  return (tokens <= (wide <= 64 ? 64 : 32) || n >= 64) && context_rows(c, tokens) > 0;
+}
 
 hipError_t prepare_series() {
   const void* fns[4] = {reinterpret_cast<const void*>(&series_round_kernel<1>), reinterpret_cast<const void*>(&series_round_kernel<2>),
                         reinterpret_cast<const void*>(&series_context_kernel<1>), reinterpret_cast<const void*>(&series_context_kernel<2>)};
   for (const void* f : fns) {
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMostLds);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
-hipError_t launch_series_round(const tsd_config& c, const SeriesP& p, const AcceptP& a, const CompactP& k, hipStream_t st) {
+hipError_t launch_series_round(const tsd_config& c, SeriesP p, const AcceptP& a, const CompactP& k, hipStream_t st) {
   const int rows = rows_of(std::max(2, p.step_only ? 1 : p.K + 1));
-  const size_t smem = lds_bytes(c, rows);
+  p.tokens = p.K + 2;
+  p.models = 2;
+  const size_t smem = lds_bytes(c, rows, p.tokens, 2);
+  if (smem > kMostLds) return hipErrorInvalidValue;
   if (rows == 16) hipLaunchKernelGGL(series_round_kernel<1>, dim3(p.n), dim3(kThreads), smem, st, p, a, k);
   else hipLaunchKernelGGL(series_round_kernel<2>, dim3(p.n), dim3(kThreads), smem, st, p, a, k);
   return hipGetLastError();
 }
 
-hipError_t launch_series_context(const tsd_config& c, const SeriesP& p, const float* znorm, int N, hipStream_t st) {
-  const int rows = rows_of(N - 1);
-  const size_t smem = lds_bytes(c, rows);
+hipError_t launch_series_context(const tsd_config& c, SeriesP p, const float* znorm, int N, hipStream_t st) {
+  const int rows = context_rows(c, N - 1);
+  if (!rows) return hipErrorInvalidValue;
+  p.tokens = rows;
+  p.models = 1;
+  const size_t smem = lds_bytes(c, rows, rows, 1);
   if (rows == 16) hipLaunchKernelGGL(series_context_kernel<1>, dim3(p.n, 2), dim3(kThreads), smem, st, p, znorm, N);
   else hipLaunchKernelGGL(series_context_kernel<2>, dim3(p.n, 2), dim3(kThreads), smem, st, p, znorm, N);
   return hipGetLastError();

@@ -31,7 +31,7 @@ struct ModelDev {
   char* fW_e = nullptr;
   char* fW_h = nullptr;
   std::vector<Layer> flayers;
-  SeriesModel series{};  // third copy, of both models, for passes of a series per workgroup (small fp32 handles)
+  SeriesModel series{};  // second copy, of both models, for passes of a series per workgroup (small fp32 handles)
   float *rope_cos, *rope_sin;
   char* kv_pool;
   size_t layer_pool_bytes;
@@ -337,6 +337,8 @@ size_t carve(const tsd_config& c, const Layout& lay, tsd_ctx* ctx) {
         s.layer_words = n_qkv + n_out + n_up + n_down;
         s.L = m.n_layers;
         s.D = (int)D;
+        s.half = hd / 2;
+        s.draft = w;
         s.shape = series_shape(m);
         s.scale = 1.0f / std::sqrt((float)hd);
       }
@@ -1423,7 +1425,7 @@ int tsd_prefill(tsd_ctx* ctx, const float* series_dev, int32_t B, int32_t n_ctx_
   // first runs launch by launch, a program that forecasts once pays for no capture).  Larger batches keep the GPU busy
   // for longer than their launches take to enqueue.
   const bool again = ctx->context_B == B && ctx->context_N == N;
-  const bool series = use_series(ctx) && series_context_short(nq);
+  const bool series = use_series(ctx) && series_context_ok(c, B, nq);
   if (!again && ctx->graph_context) {
     (void)hipGraphExecDestroy(ctx->graph_context);
     ctx->graph_context = nullptr;
@@ -1468,7 +1470,7 @@ int tsd_refill(tsd_ctx* ctx, const int32_t* slots_host, int32_t n, const float* 
   HIP_TRY(ctx, launch_identity_list(ctx->act_list, ctx->count_out, ctx->B, ctx->T, st));
   const int nq = N - 1;
   const int chunk = std::max(1, ctx->rows_max / nq);
-  const bool series = use_series(ctx) && series_context_short(nq);
+  const bool series = use_series(ctx) && series_context_ok(c, n, nq);
   if (series) {
     SeriesP p = series_args(ctx);
     p.act = ctx->refill_list;
@@ -1529,7 +1531,7 @@ int tsd_draft_propose(tsd_ctx* ctx, void* stream) {
   // one.  After a fully accepted round the draft cache lacks the former (it proposed x_K but
   // never consumed it); for the other series the rewrite stores identical values.
   if (!ctx->fused_draft && use_small_round(ctx, st) && (rc = run_small_phase(ctx, 1, st)) != kResidentBusy) return rc;
-  if (use_series(ctx)) {
+  if (use_series(ctx) && series_round_ok(ctx->B)) {
     if ((rc = run_series_round(ctx, 1, false, false, st))) return rc;
     HIP_TRY(ctx, note_pass(&ctx->use, st));
     return TSD_OK;
@@ -1666,7 +1668,7 @@ int tsd_target_verify(tsd_ctx* ctx, void* stream) {
   const tsd_config& c = ctx->cfg;
   const int P = c.patch, K = c.K;
   if (use_small_round(ctx, (hipStream_t)stream) && (rc = run_small_phase(ctx, 2, (hipStream_t)stream)) != kResidentBusy) return rc;
-  if (use_series(ctx)) {
+  if (use_series(ctx) && series_round_ok(ctx->B)) {
     if ((rc = run_series_round(ctx, 2, false, false, (hipStream_t)stream))) return rc;
     HIP_TRY(ctx, note_pass(&ctx->use, (hipStream_t)stream));
     return TSD_OK;
@@ -1731,7 +1733,7 @@ int tsd_round(tsd_ctx* ctx, void* stream) {
     if ((rc = run_small_round(ctx, 3, false, (hipStream_t)stream, resident)) == kResidentBusy) small = false;
     else if (rc) return rc;
   }
-  if (use_series(ctx) && !(ctx->cfg.flags & TSD_FLAG_BATCH_SYNC)) {
+  if (use_series(ctx) && series_round_ok(ctx->B) && !(ctx->cfg.flags & TSD_FLAG_BATCH_SYNC)) {
     ctx->injected = false;
     if ((rc = run_series_round(ctx, 7, false, deliver, (hipStream_t)stream))) return rc;
     HIP_TRY(ctx, note_pass(&ctx->use, (hipStream_t)stream));
@@ -1779,7 +1781,7 @@ int tsd_target_step(tsd_ctx* ctx, void* stream) {
     if (rc) return rc;
     return accept_commit_impl(ctx, nullptr, 0, (hipStream_t)stream, &resident);
   }
-  if (use_series(ctx)) {
+  if (use_series(ctx) && series_round_ok(ctx->B)) {
     if ((rc = run_series_round(ctx, 6, true, false, (hipStream_t)stream))) return rc;
     HIP_TRY(ctx, note_pass(&ctx->use, (hipStream_t)stream));
     return TSD_OK;

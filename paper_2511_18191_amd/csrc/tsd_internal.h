@@ -264,12 +264,12 @@ struct SeriesModel {
   float* kv_pool;               // layer after layer
   size_t layer_pool_elems;
   const float *rope_cos, *rope_sin;
-  int L, D, shape;              // shape: number of its kernel's sizes (series_shape)
+  int L, D, half, draft, shape; // half: rotary pairs of a head; shape: number of its kernel's sizes (series_shape)
   float scale;                  // 1 / sqrt(head_dim)
 };
 struct SeriesP {
   SeriesModel m[2];             // TSD_TARGET, TSD_DRAFT
-  int D_max, half_max, S_max;   // widest model, most rotary pairs, cached tokens at most: the layout of its LDS
+  int D_max, half_max, S_max, tokens, models;  // widest model, most rotary pairs, cached tokens at most; of the launch: the layout of its LDS
   const int* page_table;
   int pt_stride, PT, pt_shift;
   const int* len;
@@ -293,14 +293,15 @@ struct CompactP {               // compaction behind a round (see launch_compact
   int* ticket;                  // workgroups of the launch that have committed, zero between launches
 };
 struct AcceptP;
-bool series_rounds_ok(const tsd_config& c);
+bool series_rounds_ok(const tsd_config& c);  // the handle can have them
+bool series_round_ok(int n);                 // a decode of n series takes them
 int series_shape(const tsd_model_cfg& m);
-bool series_context_short(int tokens);  // a context pass of so many tokens is one of them
+bool series_context_ok(const tsd_config& c, int n, int tokens);  // a context pass of n series of so many tokens is one of them
 size_t series_packed_words(int N, int K);
 hipError_t launch_series_pack(const float* src, float* dst, int N, int K, int qkv_hd, hipStream_t st);
 hipError_t prepare_series();
-hipError_t launch_series_round(const tsd_config& c, const SeriesP& p, const AcceptP& a, const CompactP& k, hipStream_t st);
-hipError_t launch_series_context(const tsd_config& c, const SeriesP& p, const float* znorm, int N, hipStream_t st);
+hipError_t launch_series_round(const tsd_config& c, SeriesP p, const AcceptP& a, const CompactP& k, hipStream_t st);
+hipError_t launch_series_context(const tsd_config& c, SeriesP p, const float* znorm, int N, hipStream_t st);
 
 struct PackP {
   const float* W;     // [K][N] row-major source (y = x W)

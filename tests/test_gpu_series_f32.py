@@ -37,7 +37,7 @@ def m(L, D, H):
     (8, 4, T64, D32, 16, 32, 6), (1, 1, T64, D32, 16, 4, 3), (3, 15, T64, D32, 8, 17, 18), (2, 16, m(1, 64, 2), m(2, 32, 1), 24, 18, 19),  # 2, 16, 17 rows
     (5, 3, m(3, 128, 2), m(1, 64, 2), 32, 40, 5), (4, 2, m(1, 128, 4), m(2, 64, 1), 40, 34, 5),    # 24 blocks, a patch of two and a half k-runs
     (2, 2, m(1, 128, 8), m(1, 128, 2), 200, 50, 4), (2, 16, m(2, 64, 2), m(1, 64, 4), 16, 125, 18), (3, 6, m(2, 128, 2), D32, 16, 50, 12),  # twelve and a half; 124 tokens
-    (40, 2, T64, D32, 16, 12, 7), (200, 3, m(1, 64, 1), D32, 16, 5, 5),
+    (40, 2, T64, D32, 16, 12, 7), (200, 3, m(1, 64, 1), D32, 16, 5, 5), (512, 1, T64, D32, 16, 3, 3),
 ])
 def test_same_bits_as_kernel_by_kernel(B, K, target, draft, P, N, T):
     case = Case("cfg1", B=B, K=K, target=target, draft=draft, patch=P, context=N * P, horizon=T * P - P // 2, random_gains=True)
