@@ -85,7 +85,7 @@ SYMBOLS = {
     "tsd_set_sigma": ([C.c_void_p, C.c_float, C.c_float], C.c_int),
 }
 
-_lib = None
+_lib = _calls = None
 
 
 def library_path():
@@ -93,21 +93,24 @@ def library_path():
 
 
 def lib():
-    """Load libtsd.so (building it first only if it does not exist).  Raises if unavailable:
-    there is no fallback implementation."""
-    global _lib
+    """Load libtsd.so and the extension beside it (building them first only if they do not exist).  Raises if
+    unavailable: there is no fallback implementation."""
+    global _lib, _calls
     if _lib is None:
         # torch ships its own HIP runtime; load it first so that libtsd binds to the same one
         # (two runtimes in one process do not share device pointers or streams)
         import torch  # noqa: F401
         path = library_path()
-        if not os.path.exists(path):
-            from . import build as _build
+        from . import build as _build
+        if not os.path.exists(path) or not os.path.exists(_build.CALLS):
             _build.build(verbose=False)
         handle = C.CDLL(path)
         for name, (argtypes, restype) in SYMBOLS.items():
             fn = getattr(handle, name)
             fn.argtypes, fn.restype = argtypes, restype
+        from . import _torch_calls
+        _torch_calls.bind(C.cast(handle.tsd_accept_commit_static, C.c_void_p).value)
+        _calls = _torch_calls
         _lib = handle
     return _lib
 
@@ -125,15 +128,6 @@ def _check(rc, ctx=None):
     if rc != 0:
         msg = lib().tsd_last_error(ctx)
         raise TsdError(rc, msg.decode() if msg else "")
-
-
-def _raw_stream(device):
-    """torch's current stream on `device` as a pointer (without building a Stream object, which takes longer than a launch)."""
-    import torch
-    index = device.index  # (None: a tensor that is not on a GPU, whose pointer must not reach a kernel; asking for the type takes 0.2 us)
-    if index is None:
-        raise ValueError(f"Expected a cuda device, but got: {device}")
-    return torch._C._cuda_getCurrentRawStream(index)
 
 
 def bench_gemm(A, Wt, out=None, variant=0):
@@ -155,20 +149,10 @@ def accept_commit_static(X, mu_q, mu_p, sigma_p, sigma_q=None, rounds=None, fall
     """tsd_accept_commit_static on torch's current stream.  X, mu_q: [B,K,P], mu_p: [B,K+1,P] float32 GPU tensors;
     rounds: int32 [B] or None.  Returns dict(n_acc, commit, ell, logu); the output tensors are allocated HERE, by
     the caller's side, before the call: the library call itself allocates nothing."""
-    import torch
-    B, K, P = X.shape
-    dev = X.device
-    stream = _raw_stream(dev)
-    # (the kernel writes every entry: nothing to fill beforehand)
-    n_acc = torch.empty(B, dtype=torch.int32, device=dev)
-    commit = torch.empty(B, K + 1, P, dtype=torch.float32, device=dev)
-    ell = logu = e_ptr = l_ptr = None
-    if want_taps:
-        ell, logu = torch.empty(2, B, K, dtype=torch.float32, device=dev).unbind(0)
-        e_ptr, l_ptr = ell.data_ptr(), logu.data_ptr()
-    rc = lib().tsd_accept_commit_static(X.data_ptr(), mu_q.data_ptr(), mu_p.data_ptr(), None if rounds is None else rounds.data_ptr(),
-                                        B, K, P, sigma_p, sigma_p if sigma_q is None else sigma_q, fallback_r, seed, flags | TSD_FLAG_CLEAR_REST,
-                                        n_acc.data_ptr(), commit.data_ptr(), e_ptr, l_ptr, stream)
+    if _calls is None:
+        lib()
+    rc, n_acc, commit, ell, logu = _calls.accept_commit_static(X, mu_q, mu_p, rounds, sigma_p, sigma_p if sigma_q is None else sigma_q,
+                                                               fallback_r, seed, flags | TSD_FLAG_CLEAR_REST, want_taps)
     if rc:
         _check(rc)
     return dict(n_acc=n_acc, commit=commit, ell=ell, logu=logu)
@@ -308,7 +292,8 @@ class Session:
         return n.value
 
     def get_forecast(self):
-        out = self._new(self.B, self.H)
+        # (what writes the buffer is enqueued behind everything that may still read a former owner of its memory: one wait, at the end)
+        out = self.torch.empty(self.B, self.H, dtype=self.torch.float32, device=self.device)
         _check(lib().tsd_get_forecast(self.h, out.data_ptr(), self._stream()), self.h)
         self.sync()
         return out
