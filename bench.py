@@ -393,7 +393,7 @@ def run_config(torch, tsd, synth, a, name, steps, warmup, fam_steps, flags, case
     t_spec = timed(torch, lambda: decode_spec(sess), steps)
     n_res = sess.resident_passes()
     decode_spec(sess)
-    n_res = sess.resident_passes() - n_res      # launches of the resident decode kernel per decode (small batches)
+    n_res = sess.resident_passes() - n_res      # launches that are a round's passes in one, per decode (small batches, small fp32 models)
     log(f"{c.name}: {t_spec * 1e3:.2f} ms per speculative decode; target-only decodes")
     for _ in range(max(1, warmup // 2)):
         decode_target_only(sess, c.T)
@@ -465,7 +465,7 @@ def run_config(torch, tsd, synth, a, name, steps, warmup, fam_steps, flags, case
         "resident_launches_per_decode": n_res,
     }
     if n_res:
-        rec["roofline"]["path"] = f"kernel by kernel, as under the timing pass; the timed decode runs {n_res} launches of the resident kernel instead"
+        rec["roofline"]["path"] = f"kernel by kernel, as under the timing pass; the timed decode runs {n_res} launches of one-launch rounds instead"
     return rec
 
 
