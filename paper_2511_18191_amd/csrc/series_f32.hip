@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "accept_step.h"
+#include "series_plan.h"
 #include "tsd_internal.h"
 
 namespace tsd {
@@ -368,7 +369,7 @@ __device__ __forceinline__ void run_series_pass(const SeriesP& p, const SeriesMo
   float* probs = lds + c.probs + wave * probs_words(p.S_max);
   volatile int* odd = reinterpret_cast<int*>(lds + c.odd);  // a value of the pass's tokens is not finite
   const int plane = p.PT * HD;  // a head's keys of a page; its values are H planes on
-  auto token_at = [&](int tok) { return (table[tok >> p.pt_shift] * 2 * H * p.PT + (tok & (p.PT - 1))) * HD; };
+  auto token_at = [&](int tok) { return kv_token(table[tok >> p.pt_shift], tok & (p.PT - 1), H, p.PT, HD); };
   // keys and values of earlier passes, 16 bytes at a time: half a wavefront the keys, half the values of FIT tokens, the wavefronts
   // tokens in turn
   constexpr int C4 = D / 4, FIT = 32 / C4, U = 4, STEP = kWaves * FIT;
