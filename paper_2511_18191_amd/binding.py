@@ -148,7 +148,7 @@ def bench_gemm(A, Wt, out=None, variant=0):
 def accept_commit_static(X, mu_q, mu_p, sigma_p, sigma_q=None, rounds=None, fallback_r=0.0, seed=0, flags=0, want_taps=True):
     """tsd_accept_commit_static on torch's current stream.  X, mu_q: [B,K,P], mu_p: [B,K+1,P] float32 GPU tensors;
     rounds: int32 [B] or None.  Returns dict(n_acc, commit, ell, logu); the output tensors are allocated HERE, by
-    the caller's side, before the call: the library call itself allocates nothing."""
+    the caller's side, before the call (ell and logu over one allocation): the library call itself allocates nothing."""
     if _calls is None:
         lib()
     rc, n_acc, commit, ell, logu = _calls.accept_commit_static(X, mu_q, mu_p, rounds, sigma_p, sigma_p if sigma_q is None else sigma_q,

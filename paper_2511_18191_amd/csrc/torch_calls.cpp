@@ -1,7 +1,7 @@
 // Calls whose way through Python takes longer than the kernel behind them, as a Python extension on torch's own tensors.
 //
 // tsd_accept_commit_static is one launch of some 4 us.  Through ctypes, with its outputs allocated by torch.empty, a call took 10.5 us: three
-// allocations and a view 5.4, the arguments' conversion and the launch 3.5.
+// allocations and a view 5.4, the arguments' conversion and the launch 3.5.  From here 8 series of 4 x 16 take 6.2 us.
 #include <Python.h>
 
 #include <ATen/core/Tensor.h>
@@ -18,11 +18,11 @@ using AcceptFn = int (*)(const float*, const float*, const float*, const int32_t
                          uint32_t, int32_t*, float*, float*, float*, void*);
 AcceptFn accept_fn = nullptr;
 
-// A contiguous tensor of its own over `whole`'s memory from byte `offset` on.
-at::Tensor over(const at::Tensor& whole, caffe2::TypeMeta dtype, at::IntArrayRef sizes, int64_t offset) {
-  at::Tensor t = at::detail::make_tensor<c10::TensorImpl>(c10::Storage(whole.storage()), whole.key_set(), dtype);
+// A contiguous tensor of its own over `whole`'s memory from element `offset` on.
+at::Tensor over(const at::Tensor& whole, at::IntArrayRef sizes, int64_t offset) {
+  at::Tensor t = at::detail::make_tensor<c10::TensorImpl>(c10::Storage(whole.storage()), whole.key_set(), whole.dtype());
   t.unsafeGetTensorImpl()->set_sizes_contiguous(sizes);
-  t.unsafeGetTensorImpl()->set_storage_offset(offset / (int64_t)dtype.itemsize());
+  t.unsafeGetTensorImpl()->set_storage_offset(offset);
   return t;
 }
 
@@ -67,12 +67,13 @@ PyObject* accept_commit_static(PyObject*, PyObject* const* args, Py_ssize_t n) {
     const int64_t B = X->size(0), K = X->size(1), P = X->size(2);
     const auto f32 = at::TensorOptions().dtype(at::kFloat).device(X->device());
     // (the kernel writes every entry: nothing to fill beforehand)
-    // (the small outputs in one allocation: four of their own take 1.5 us longer.  Not the patches, which a kept count would keep.)
-    const at::Tensor commit = at::empty({B, K + 1, P}, f32), small = at::empty({taps ? B * (1 + 2 * K) : B}, f32);
-    at::Tensor n_acc = over(small, caffe2::TypeMeta::Make<int32_t>(), {B}, taps ? 8 * B * K : 0), ell, logu;
+    // (the two taps in one allocation.  Not the counts with them: torch.save refuses tensors of two types over one memory, and a kept count
+    // would keep the taps.)
+    at::Tensor n_acc = at::empty({B}, f32.dtype(at::kInt)), commit = at::empty({B, K + 1, P}, f32), ell, logu;
     if (taps) {
-      ell = over(small, caffe2::TypeMeta::Make<float>(), {B, K}, 0);
-      logu = over(small, caffe2::TypeMeta::Make<float>(), {B, K}, 4 * B * K);
+      const at::Tensor both = at::empty({2, B, K}, f32);
+      ell = over(both, {B, K}, 0);
+      logu = over(both, {B, K}, B * K);
     }
     auto at_of = [](const at::Tensor& t) { return static_cast<float*>(t.data_ptr()); };
     const float *x = at_of(*X), *q = at_of(*mu_q), *p = at_of(*mu_p);

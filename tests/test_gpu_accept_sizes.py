@@ -1,5 +1,7 @@
 """The acceptance kernel at the edges of its split (four wavefronts over positions, 64 lanes over a patch): statistics against
-float64, decisions, committed rows, and what lies behind them, untouched or zeroed."""
+float64, decisions, committed rows, and what lies behind them, untouched or zeroed; and what the Python call returns."""
+import io
+
 import numpy as np
 import pytest
 import torch
@@ -47,3 +49,37 @@ def test_static_acceptance(K, P, clear):
         np.testing.assert_array_equal(commit[b, :n], X[b, :n])
         np.testing.assert_array_equal(commit[b, n], mu_p[b, n])
         np.testing.assert_array_equal(commit[b, n + 1:], 0.0 if clear else 5.0)
+
+
+@pytest.mark.parametrize("B,K,P", [(1, 1, 8), (37, 1, 24), (5, 16, 16), (1023, 6, 96)])
+@pytest.mark.parametrize("taps", [True, False])
+def test_returned_tensors(B, K, P, taps):
+    """What the call returns is what the C entry writes into buffers of one's own; the counts and the patches have memory of
+    their own, and all of it can be saved and loaded."""
+    g = torch.Generator(device="cuda").manual_seed(B + K)
+    mu_q = torch.randn(B, K, P, generator=g, device="cuda")
+    X, mu_p = mu_q + 0.2 * torch.randn(B, K, P, generator=g, device="cuda"), torch.randn(B, K + 1, P, generator=g, device="cuda")
+    mu_p[:, :K] = mu_q + 0.5 * mu_p[:, :K]
+    rounds = torch.arange(B, dtype=torch.int32, device="cuda")
+    want = dict(n_acc=torch.full((B,), -7, dtype=torch.int32, device="cuda"), commit=torch.full((B, K + 1, P), 5.0, device="cuda"),
+                ell=torch.full((B, K), 5.0, device="cuda"), logu=torch.full((B, K), 5.0, device="cuda"))
+    rc = tsd.lib().tsd_accept_commit_static(X.data_ptr(), mu_q.data_ptr(), mu_p.data_ptr(), rounds.data_ptr(), B, K, P, 0.9, 0.7, 0.0, 3,
+                                            tsd.binding.TSD_FLAG_CLEAR_REST, *(t.data_ptr() for t in want.values()), torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    got = tsd.accept_commit_static(X, mu_q, mu_p, 0.9, 0.7, rounds=rounds, seed=3, want_taps=taps)
+    if not taps:
+        want["ell"] = want["logu"] = None
+    buf = io.BytesIO()
+    torch.save(got, buf)
+    buf.seek(0)
+    loaded = torch.load(buf, weights_only=True)
+    assert list(got) == list(loaded) == list(want)
+    for name, w in want.items():
+        if w is None:
+            assert got[name] is None and loaded[name] is None
+            continue
+        assert got[name].dtype == w.dtype and got[name].is_contiguous() and got[name].device == X.device
+        np.testing.assert_array_equal(got[name].cpu().numpy(), w.cpu().numpy())
+        np.testing.assert_array_equal(loaded[name].cpu().numpy(), w.cpu().numpy())
+    for name in ("n_acc", "commit"):
+        assert got[name].untyped_storage().nbytes() == got[name].numel() * 4
