@@ -7,6 +7,7 @@
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
@@ -95,8 +96,8 @@ PyObject* accept_commit_static(PyObject*, PyObject* const* args, Py_ssize_t n) {
       PyTuple_SET_ITEM(out, 3 + i, o);
     }
     return out;
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
+  } catch (const std::exception&) {
+    torch::translate_exception_to_python(std::current_exception());  // (torch.OutOfMemoryError among them)
     return nullptr;
   }
 }

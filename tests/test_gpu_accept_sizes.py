@@ -83,3 +83,10 @@ def test_returned_tensors(B, K, P, taps):
         np.testing.assert_array_equal(loaded[name].cpu().numpy(), w.cpu().numpy())
     for name in ("n_acc", "commit"):
         assert got[name].untyped_storage().nbytes() == got[name].numel() * 4
+
+
+def test_no_memory_for_the_outputs():
+    """What torch raises where it has no memory (16 TB here), from before any launch."""
+    X = torch.zeros(1, 1, 1, device="cuda").expand(1 << 22, 16, 1 << 16)
+    with pytest.raises(torch.OutOfMemoryError):
+        tsd.accept_commit_static(X, X, X, 1.0)
