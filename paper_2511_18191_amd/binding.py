@@ -2,6 +2,7 @@
 with plain pointers; `Session` bundles the calls with torch-owned device memory (torch is used
 for allocation and streams only; every step of the method runs inside the library's kernels)."""
 import ctypes as C
+import importlib
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -93,26 +94,36 @@ def library_path():
 
 
 def lib():
-    """Load libtsd.so and the extension beside it (building them first only if they do not exist).  Raises if
-    unavailable: there is no fallback implementation."""
-    global _lib, _calls
+    """Load libtsd.so (building it first only if it does not exist).  Raises if unavailable:
+    there is no fallback implementation."""
+    global _lib
     if _lib is None:
         # torch ships its own HIP runtime; load it first so that libtsd binds to the same one
         # (two runtimes in one process do not share device pointers or streams)
         import torch  # noqa: F401
         path = library_path()
-        from . import build as _build
-        if not os.path.exists(path) or not os.path.exists(_build.CALLS):
-            _build.build(verbose=False)
+        if not os.path.exists(path):
+            from . import build as _build
+            _build.build_library(verbose=False)
         handle = C.CDLL(path)
         for name, (argtypes, restype) in SYMBOLS.items():
             fn = getattr(handle, name)
             fn.argtypes, fn.restype = argtypes, restype
-        from . import _torch_calls
-        _torch_calls.bind(C.cast(handle.tsd_accept_commit_static, C.c_void_p).value)
-        _calls = _torch_calls
         _lib = handle
     return _lib
+
+
+def _bind_calls():
+    """Load the extension beside the library (building it first only if it does not exist) and hand it the library's entry."""
+    global _calls
+    handle = lib()
+    from . import build as _build
+    if not os.path.exists(_build.CALLS):
+        _build.build_calls()
+        importlib.invalidate_caches()
+    from . import _torch_calls
+    _torch_calls.bind(C.cast(handle.tsd_accept_commit_static, C.c_void_p).value)
+    _calls = _torch_calls
 
 
 def make_config(target, draft, patch, K, max_batch, max_tokens, dtype, sigma_p, sigma_q=None, seed=0,
@@ -150,7 +161,7 @@ def accept_commit_static(X, mu_q, mu_p, sigma_p, sigma_q=None, rounds=None, fall
     rounds: int32 [B] or None.  Returns dict(n_acc, commit, ell, logu); the output tensors are allocated HERE, by
     the caller's side, before the call (ell and logu over one allocation): the library call itself allocates nothing."""
     if _calls is None:
-        lib()
+        _bind_calls()
     rc, n_acc, commit, ell, logu = _calls.accept_commit_static(X, mu_q, mu_p, rounds, sigma_p, sigma_p if sigma_q is None else sigma_q,
                                                                fallback_r, seed, flags | TSD_FLAG_CLEAR_REST, want_taps)
     if rc:

@@ -46,7 +46,8 @@ def build_calls():
           "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-o", CALLS])
 
 
-def build(verbose=True):
+def build_library(verbose=True):
+    """libtsd.so: what every call but the acceptance call on torch's tensors needs."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     bdir = os.path.join(HERE, "_build")
     os.makedirs(bdir, exist_ok=True)
@@ -57,12 +58,18 @@ def build(verbose=True):
         return _run([hipcc, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj])
 
     with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
-        calls = ex.submit(build_calls)
         for src, warn in zip(SOURCES, ex.map(one, zip(SOURCES, objs))):
             if verbose and warn.strip():
                 print(f"[{src}]\n{warn}", file=sys.stderr)
-        calls.result()
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", OUT])
+    return OUT
+
+
+def build(verbose=True):
+    with ThreadPoolExecutor(max_workers=1) as ex:
+        calls = ex.submit(build_calls)
+        build_library(verbose)
+        calls.result()  # (behind the library, which does without)
     if verbose:
         print("built", OUT, CALLS)
     return OUT

@@ -3,6 +3,8 @@ validates arguments before touching a GPU."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -128,17 +130,62 @@ def test_static_accept_validates_before_touching_the_gpu():
     assert L.tsd_accept_commit_static(dummy, dummy, dummy, None, 8, 4, 16, 1.0, 1.0, 2.0, 0, 0, dummy, dummy, None, None, None) == -1
 
 
-def test_static_accept_refuses_tensors_of_the_host(monkeypatch):
-    # their pointers would reach a kernel; as on a machine with a GPU, where the current device and its stream can be asked for
+@pytest.fixture
+def entry_calls():
+    """The acceptance call's way into the library ends in a list here."""
+    got, binding = [], tsd.binding
+    binding._bind_calls()
+    entry = C.CFUNCTYPE(binding.SYMBOLS["tsd_accept_commit_static"][1], *binding.SYMBOLS["tsd_accept_commit_static"][0])(lambda *a: got.append(a) or 0)
+    binding._calls.bind(C.cast(entry, C.c_void_p).value)
+    yield got
+    binding._bind_calls()
+
+
+def test_static_accept_refuses_tensors_of_the_host(entry_calls):
     import torch
-    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
-    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda index: 0, raising=False)
-    called = []
-    monkeypatch.setattr(tsd.binding, "lib", lambda: type("L", (), {"tsd_accept_commit_static": lambda self, *a: called.append(a) or 0})())
     X, p = torch.zeros(2, 3, 8), torch.zeros(2, 4, 8)
-    with pytest.raises(ValueError, match="cuda"):
+    with pytest.raises(ValueError, match="cuda"):  # (their pointers would reach a kernel)
         tsd.accept_commit_static(X, X, p, 1.0)
-    assert not called
+    assert not entry_calls
+
+
+def test_static_accept_refuses_what_is_no_tensor(entry_calls):
+    import torch
+    X, p = torch.zeros(2, 3, 8), torch.zeros(2, 4, 8)
+    for args in ((X.numpy(), X, p), (X, None, p), (X, X, p.tolist())):
+        with pytest.raises(TypeError, match="tensor"):
+            tsd.accept_commit_static(*args, 1.0)
+    with pytest.raises(TypeError, match="rounds"):
+        tsd.accept_commit_static(X, X, p, 1.0, rounds=[0, 1])
+    with pytest.raises(ValueError, match="B, K, P"):
+        tsd.accept_commit_static(X[0], X, p, 1.0)
+    with pytest.raises(TypeError):
+        tsd.accept_commit_static(X, X, p, "1.0")
+    assert not entry_calls
+
+
+def test_library_without_the_extension(tmp_path):
+    """A program that never makes the acceptance call needs no C++ compiler; the call itself says what is missing."""
+    tsd.lib()
+    pkg = os.path.dirname(tsd.__file__)
+    copy = tmp_path / os.path.basename(pkg)
+    copy.mkdir()
+    for name in os.listdir(pkg):
+        if name.endswith((".py", "libtsd.so")):
+            os.symlink(os.path.join(pkg, name), copy / name)
+    prog = """
+import torch, paper_2511_18191_amd as tsd
+assert tsd.lib().tsd_abi_version() == 1 and tsd.__file__.startswith(%r)
+X = torch.zeros(2, 3, 8)
+try:
+    tsd.accept_commit_static(X, X, X, 1.0)
+except Exception as e:
+    print(type(e).__name__, e)
+""" % str(tmp_path)
+    env = dict(os.environ, PYTHONPATH=str(tmp_path), CXX="/bin/false", HIPCC="/bin/false")
+    r = subprocess.run([sys.executable, "-c", prog], cwd=tmp_path, env=env, capture_output=True, text=True)
+    assert r.returncode == 0 and "/bin/false" in r.stdout, r.stderr
+    assert not (copy / "_torch_calls.so").exists()
 
 
 # What tsd_workspace_bytes gave while the workspace held one round's rows or one context, not the contexts of a whole batch.
