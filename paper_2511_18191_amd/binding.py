@@ -223,9 +223,15 @@ class Session:
         return t
 
     def _new(self, *shape, dtype=None):
-        """Output buffer for the library to fill; allocated after the library's stream is idle."""
-        self.sync()
-        return self.torch.empty(*shape, dtype=dtype or self.torch.float32, device=self.device)
+        """Output buffer for the library to fill.  Its memory is that of torch's current stream, on which a freed tensor's last reader
+        may still run: the library's stream, which fills it, is ordered behind that."""
+        torch = self.torch
+        out = torch.empty(*shape, dtype=dtype or torch.float32, device=self.device)
+        current = torch.cuda.current_stream(self.device)
+        # (mostly idle: asking takes 1 us, an event 4.  What a caller is only capturing does not run, and must not be asked about)
+        if not torch.cuda.is_current_stream_capturing() and not current.query():
+            self.stream.wait_stream(current)
+        return out
 
     def close(self):
         if self.h:
@@ -303,8 +309,7 @@ class Session:
         return n.value
 
     def get_forecast(self):
-        # (what writes the buffer is enqueued behind everything that may still read a former owner of its memory: one wait, at the end)
-        out = self.torch.empty(self.B, self.H, dtype=self.torch.float32, device=self.device)
+        out = self._new(self.B, self.H)
         _check(lib().tsd_get_forecast(self.h, out.data_ptr(), self._stream()), self.h)
         self.sync()
         return out
