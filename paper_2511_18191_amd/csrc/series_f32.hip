@@ -18,6 +18,7 @@
 //   * QKV columns are packed in rotary-pair order: a block is eight columns of the first half of a head and their partners.
 //   * Attention: up to eight queries a wavefront per (query, head), the sums of attn_kernel (attn.hip) in the same order; more of them
 //     16 at a time on the matrix cores (attend16), with the same bits.
+#include <algorithm>
 #include <type_traits>
 
 #include "accept_step.h"
@@ -760,7 +761,6 @@ size_t lds_bytes(const tsd_config& c, int rows, int tokens, int models) {
 
 // Rows at a time of a context pass of so many tokens (0: it is none of this kernel's).
 int context_rows(const tsd_config& c, int tokens) {
-  if (tokens > 128) return 0;
   for (int rows = rows_of(tokens); rows >= 16; rows -= 16)
     if (lds_bytes(c, rows, rows, 1) <= kMostLds) return rows;
   return 0;
@@ -790,12 +790,8 @@ bool series_rounds_ok(const tsd_config& c) {
 }
 
 int series_shape(const tsd_model_cfg& m) { return shape_of(m.d_model, m.n_heads, m.d_ff); }
-// A workgroup takes a context block by block of 32 tokens, so a few series with a long one leave the chip idle, where the launches of the
-// tiled path do not get longer (us, kernel by kernel / this: 2 layers of 64, 32 patches 95 / 36 and 64 patches 96 / 68 for 1 series, 96
-// patches 99 / 135; 3 layers of 128, 32 patches 158 / 118, 64 patches 163 / 238 for 1 series, 224 / 241 for 32, 415 / 246 for 128).
 bool series_context_ok(const tsd_config& c, int n, int tokens) {
-  const int wide = std::max(c.target.d_model, c.draft.d_model);
-  return (tokens <= (wide <= 64 ? 64 : 32) || n >= 64) && context_rows(c, tokens) > 0;
+  return series_context_pays(std::max(c.target.d_model, c.draft.d_model), n, tokens) && context_rows(c, tokens) > 0;
 }
 
 hipError_t prepare_series() {

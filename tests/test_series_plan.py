@@ -2,6 +2,8 @@
 import os
 import subprocess
 
+import pytest
+
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2511_18191_amd", "csrc")
 
 # Pages up to the last one of the largest handle there can be (2^20 series, 64 pages each), every width, head size and page size: the
@@ -31,9 +33,42 @@ int main() {
 """
 
 
-def test_cache_offsets_of_large_batches(tmp_path):
-    src, exe = tmp_path / "walk.cpp", tmp_path / "walk"
-    src.write_text(WALK)
+def _build(folder, source):
+    src, exe = folder / "walk.cpp", folder / "walk"
+    src.write_text(source)
     subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-O1", "-I", CSRC, str(src), "-o", str(exe)], check=True)
-    seen, large, wrong, outside = map(int, subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split())
+    return lambda *args: [int(x) for x in subprocess.run([str(exe), *map(str, args)], check=True, capture_output=True, text=True).stdout.split()]
+
+
+def test_cache_offsets_of_large_batches(tmp_path):
+    seen, large, wrong, outside = _build(tmp_path, WALK)()
     assert seen > 3000 and large > 100 and (wrong, outside) == (0, 0)
+
+
+PAYS = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "series_plan.h"
+int main(int, char** a) { printf("%d", tsd::series_context_pays(atoi(a[1]), atoi(a[2]), atoi(a[3]))); }
+"""
+
+
+@pytest.fixture(scope="module")
+def pays(tmp_path_factory):
+    run = _build(tmp_path_factory.mktemp("pays"), PAYS)
+    return lambda *args: bool(run(*args)[0])
+
+
+# Times of the launch-by-launch path over those of a workgroup per series, measured: (wider model, series, tokens).
+@pytest.mark.parametrize("case", [(64, 1536, 1), (64, 2048, 3), (64, 16384, 9), (64, 64, 128), (64, 96, 112), (128, 768, 1), (128, 4096, 3),
+                                  (128, 16384, 7), (128, 64, 74), (128, 96, 96), (128, 129, 101), (32, 2048, 1), (32, 32768, 12), (32, 65536, 17),
+                                  (64, 1, 95), (128, 1, 63)])
+def test_contexts_that_are_slower_by_a_series_per_workgroup(pays, case):
+    assert not pays(*case)  # (0.16 to 0.98)
+
+
+@pytest.mark.parametrize("case", [(64, 1, 1), (64, 512, 1), (64, 768, 3), (64, 1, 64), (64, 64, 65), (64, 129, 128), (64, 16384, 17), (64, 4096, 12),
+                                  (128, 512, 1), (128, 1280, 7), (128, 1, 32), (128, 64, 33), (128, 129, 89), (128, 16384, 16), (32, 512, 1),
+                                  (32, 16384, 16)])
+def test_contexts_that_are_faster_by_a_series_per_workgroup(pays, case):
+    assert pays(*case)  # (1.04 to 6.1)
