@@ -207,9 +207,6 @@ __device__ __forceinline__ void wave_gemm(const Wsrc& w, const Wsrc& next, const
   prime<NW, CH>(next, wave, lane, B);
 }
 
-// Workgroup barrier that orders LDS traffic only: weight loads primed ahead stay in flight across it.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // RMSNorm scales 1 / sqrt(mean_k a[r][k]^2 + eps) of the 16 rows, computed by every wavefront for itself
 // (four lanes per row, K a multiple of 32) so that no barrier separates them from the product that applies
 // them: out[i] is the scale of row 4 (lane / 16) + i, the rows of this lane's accumulator.

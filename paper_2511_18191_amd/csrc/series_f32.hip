@@ -63,8 +63,6 @@ __host__ __device__ constexpr Carve carve_of(int D, int half, int P, int rows, i
   return c;
 }
 
-// (a bare barrier that orders LDS traffic: weight loads stay in flight across it)
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();

@@ -64,8 +64,6 @@ __device__ __forceinline__ void publish_bf16x2(bf16* p, float a, float b) {
   const bf16x2 v = {(bf16)a, (bf16)b};
   publish4(p, __builtin_bit_cast(unsigned, v));
 }
-// (a bare barrier that orders LDS traffic: weight loads stay in flight across it)
-__device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // Everything between two hops is executed by a handful of wavefronts one after the other, so its duration is the number of
 // instructions on the way (a first version with divisions, clamps and selects on the way took 3.4 us per product for 0.9 us
@@ -395,7 +393,7 @@ __device__ __forceinline__ bool attend(const SmallRoundP& p, const bf16* pool, c
     const int sb = s0 + wave * 32;
     const int steps = min(kWorkers, (total - s0 + 31) >> 5);  // of this trip
     float sv[8];
-    if (s0) wg_barrier();  // the previous trip's reads are done
+    if (s0) lds_barrier();  // the previous trip's reads are done
     if (sb < total) {
       if (s0 || !early) fetch(sb);
       f32x4 sc[2];
@@ -427,7 +425,7 @@ __device__ __forceinline__ bool attend(const SmallRoundP& p, const bf16* pool, c
       for (int i = 0; i < 4; ++i)
         *reinterpret_cast<bf16x8*>(sh.u.a.vt[wave] + ((lane >> 3) + 8 * i) * 64 + (((lane & 7) * 8 + 16 * i) & 63)) = vf[i];
     }
-    wg_barrier();
+    lds_barrier();
     if (sb < total) {
       float m_old = m_run;
 #pragma unroll
@@ -449,7 +447,7 @@ __device__ __forceinline__ bool attend(const SmallRoundP& p, const bf16* pool, c
         sh.u.a.m[wave][qi] = m_new;
       }
     }
-    wg_barrier();
+    lds_barrier();
     typedef short short4v __attribute__((ext_vector_type(4)));
     typedef short short8v __attribute__((ext_vector_type(8)));
 #pragma unroll
@@ -489,9 +487,9 @@ __device__ __forceinline__ bool attend(const SmallRoundP& p, const bf16* pool, c
 // Barriers of attend() after the hop, for the control wavefront to take part in.
 __device__ __forceinline__ void attend_barriers(int total) {
   for (int s0 = 0; s0 < total; s0 += 32 * kWorkers) {
-    if (s0) wg_barrier();
-    wg_barrier();
-    wg_barrier();
+    if (s0) lds_barrier();
+    lds_barrier();
+    lds_barrier();
   }
 }
 
@@ -619,7 +617,7 @@ __device__ __forceinline__ void give_up(const SmallRoundP& p) {
 }
 
 __device__ __forceinline__ bool hop_worker(Shared& sh) {
-  wg_barrier();
+  lds_barrier();
   return *reinterpret_cast<volatile int*>(&sh.quit) == 0;
 }
 
@@ -635,9 +633,9 @@ __device__ __forceinline__ void worker_loop(const SmallRoundP& p, int n, int Kr,
     const SmallModel& m = *v.m;
     const int D = v.D, M = v.M, nq = v.nq, tasks = n * m.Hh;
     const Rsrc patches = patches_of(p);
-    wg_barrier();  // (the previous pass's rows are no longer read)
+    lds_barrier();  // (the previous pass's rows are no longer read)
     set_rows(p, v, sh);
-    wg_barrier();
+    lds_barrier();
     // this workgroup's (series slot, head)
     int head = 0, r0 = 0, base = 0, my_page = 0;
     if (wg < tasks) {
@@ -651,7 +649,7 @@ __device__ __forceinline__ void worker_loop(const SmallRoundP& p, int n, int Kr,
     if (wg < m.embed.units) {
       if (!hop_worker(sh)) return;
       product_f32<false>(m.embed, M, wave, lane, w, sh, [&](int r, int k, float* f) { load_patch(p, v, sh, patches, r, k, f); });
-      wg_barrier();
+      lds_barrier();
     }
     // (after the barrier: the control wavefront does not wait for the loads to be issued)
     prefetch<true>(m.qkv, m.qkv.W, wg, wave, lane, w);
@@ -667,7 +665,7 @@ __device__ __forceinline__ void worker_loop(const SmallRoundP& p, int n, int Kr,
                       D, head, m.Hh, my_page, base, nq, wave, lane, sh, [&] { return hop_worker(sh); }))
             return;
           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-          wg_barrier();
+          lds_barrier();
           continue;
         }
         const SmallProd& d = kind == kQkv ? m.qkv : kind == kOut ? m.out : kind == kUp ? m.up : m.down;
@@ -675,7 +673,7 @@ __device__ __forceinline__ void worker_loop(const SmallRoundP& p, int n, int Kr,
           if (!hop_worker(sh)) return;
           product(d, v.rows(l, kind == kQkv ? kIn : kind == kOut ? kMixed : kind == kUp ? kMid : kHidden), M, kind == kQkv || kind == kUp,
                   wave, lane, w, sh);
-          wg_barrier();
+          lds_barrier();
           // (768 clocks later: issued at once, 8 MB of weights stand in front of the few KB the control wavefront publishes
           //  next)
           __builtin_amdgcn_s_sleep(12);
@@ -698,7 +696,7 @@ __device__ __forceinline__ void worker_loop(const SmallRoundP& p, int n, int Kr,
         *reinterpret_cast<float4*>(f) = *reinterpret_cast<const float4*>(xf + (r * D + k));
         *reinterpret_cast<float4*>(f + 4) = *reinterpret_cast<const float4*>(xf + (r * D + k + 4));
       });
-      wg_barrier();
+      lds_barrier();
     }
     if (more) {
       const SmallModel& nm = p.m[ps + 1 < Kd ? 1 : 0];
@@ -739,7 +737,7 @@ __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr
         }
       }
     }
-    wg_barrier();
+    lds_barrier();
     return go;
   };
   auto raise = [&]() { raise_flag(p, wg, lane, walk.ep + 1); };
@@ -748,8 +746,8 @@ __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr
     const PassView v(p, ps, Kd, Kr, n);
     const SmallModel& m = *v.m;
     const int D = v.D, Hh = m.Hh, M = v.M, nq = v.nq;
-    wg_barrier();
-    wg_barrier();
+    lds_barrier();
+    lds_barrier();
     // its elements of the QKV product (the same in every layer): row, column inside the head, rotary factors
     const SmallProd& q = m.qkv;
     const int qhalf = 1 << (q.cs - 1), qsft = q.cs - 1, qn = M << qsft;
@@ -774,7 +772,7 @@ __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr
     const SmallProd& e = m.embed;
     if (wg < e.units) {
       if (!hop()) return;
-      wg_barrier();
+      lds_barrier();
       bf16* x0 = v.rows(0, kIn) + (wg << e.cs);
       each_pair(e, M, lane, [&](int row, int c) {
         const float2 s = sums_of<false, false>(sh, row, c, 0, e.used).a;
@@ -791,7 +789,7 @@ __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr
       if (wg < q.units) {
         if (!hop()) return;
         bf16* dst = which == 0 ? v.rows(l, kQuery) : m.kv_pool + (size_t)l * m.layer_pool_elems;
-        wg_barrier();
+        lds_barrier();
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const int i = lane + 64 * j;
@@ -821,7 +819,7 @@ __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr
         const int total = sh.pos[(wg / Hh) * nq] + nq;
         if (!hop()) return;
         attend_barriers(total);
-        wg_barrier();  // (the workers have published)
+        lds_barrier();  // (the workers have published)
         raise();
       }
       walk.done(n * Hh);
@@ -830,7 +828,7 @@ __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr
       auto residual = [&](const SmallProd& d, bf16* out, bool last) -> bool {
         if (wg < d.units) {
           if (!hop()) return false;
-          wg_barrier();
+          lds_barrier();
           const int at0 = wg << d.cs;
           float* res = v.residual();
           each_pair(d, M, lane, [&](int row, int c) {
@@ -858,7 +856,7 @@ __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr
       const SmallProd& f1 = m.up;
       if (wg < f1.units) {
         if (!hop()) return;
-        wg_barrier();
+        lds_barrier();
         finish_up(m, v, v.rows(l, kHidden), wg, lane, sh);
         raise();
       }
@@ -870,7 +868,7 @@ __device__ __forceinline__ void control_loop(const SmallRoundP& p, int n, int Kr
     const SmallProd& hd = m.head;
     if (wg < hd.units) {
       if (!hop()) return;
-      wg_barrier();
+      lds_barrier();
       finish_head(p, m, v, wg, lane, sh);
       raise();
     }
@@ -902,7 +900,7 @@ __global__ __launch_bounds__(kThreads) void small_round_kernel(const SmallRoundP
     return;
   }
   if (threadIdx.x == 0) sh.quit = 0;
-  wg_barrier();
+  lds_barrier();
   if (wave == kWorkers)
     control_loop(p, x.n, x.Kr, x.Kd, x.n_pass, lane, sh);
   else

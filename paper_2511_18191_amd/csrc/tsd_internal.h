@@ -34,6 +34,8 @@ __device__ __forceinline__ float gelu_tanh(float z) {
   const float q = z * fmaf(z * z, b, a);
   return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(q));
 }
+// Workgroup barrier that orders LDS traffic only: weight loads asked for ahead stay in flight across it.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 #endif
 
 struct GemmP {
