@@ -4,6 +4,7 @@
 #include <type_traits>
 
 #include "accept_step.h"
+#include "compact_step.h"
 #include "philox.h"
 #include "tsd_internal.h"
 
@@ -185,44 +186,17 @@ hipError_t launch_forecast_out(const float* forecast, const float* mean, const f
 // needs (T - committed).
 __global__ __launch_bounds__(1024) void compact_active_kernel(const int* active, const int* committed, int T, int B,
                                                               int* list, int* count, int* host) {
-  __shared__ int wave_cnt[16];
-  __shared__ int base_s, max_rem;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int2 now = compact_step<16>(active, committed, T, B, list, [](const int* a) { return *a; });
   if (threadIdx.x == 0) {
-    base_s = 0;
-    max_rem = 0;
-  }
-  __syncthreads();
-  for (int b0 = 0; b0 < B; b0 += 1024) {
-    const int b = b0 + threadIdx.x;
-    const bool on = b < B && active[b] != 0;
-    const unsigned long long m = __ballot(on);
-    if (lane == 0) wave_cnt[w] = __popcll(m);
-    __syncthreads();
-    int off = base_s;
-    for (int i = 0; i < w; ++i) off += wave_cnt[i];
-    if (on) {
-      list[off + __popcll(m & ((1ull << lane) - 1ull))] = b;
-      atomicMax(&max_rem, T - committed[b]);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int t = 0;
-      for (int i = 0; i < 16; ++i) t += wave_cnt[i];
-      base_s += t;
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    count[0] = base_s;
-    count[1] = max_rem;
+    count[0] = now.x;
+    count[1] = now.y;
     if (host) {
       // straight into pinned host memory, so the caller needs neither a copy nor a stream wait: it watches
       // host[2] for this launch's number, which is stored last
       const int seq = count[4] + 1;
       count[4] = seq;
-      host[0] = base_s;
-      host[1] = max_rem;
+      host[0] = now.x;
+      host[1] = now.y;
       __hip_atomic_store(&host[2], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }

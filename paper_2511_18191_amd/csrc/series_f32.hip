@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "accept_step.h"
+#include "compact_step.h"
 #include "series_plan.h"
 #include "tsd_internal.h"
 
@@ -610,41 +611,19 @@ __device__ __forceinline__ void set_up(const SeriesP& p, int model, int b, int p
   __syncthreads();
 }
 
-// What compact_active_kernel (misc.hip) does, by the workgroup of a round that commits last.  What the others committed has gone
-// through to memory (publish) before they were counted; it is read past the caches.
+// By the workgroup of a round that commits last.  What the others committed has gone through to memory before they were counted; it is
+// read past the caches.
 __device__ __forceinline__ void compact(const CompactP& c) {
-  __shared__ int wave_cnt[4], most[4];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  auto fresh = [](const int* a) { return __hip_atomic_load(const_cast<int*>(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
   const int seq = c.count[4] + 1;
-  int base = 0, rem = 0;
-  for (int b0 = 0; b0 < c.B; b0 += 256) {
-    const int b = min(b0 + tid, c.B - 1), on_b = fresh(c.active + b), done = fresh(c.committed + b);
-    const bool on = b0 + tid < c.B && on_b != 0;
-    if (on) rem = max(rem, c.T - done);
-    const unsigned long long m = __ballot(on);
-    if (lane == 0) wave_cnt[w] = __popcll(m);
-    __syncthreads();
-    int off = base;
-    for (int i = 0; i < 4; ++i) {
-      if (i < w) off += wave_cnt[i];
-      base += wave_cnt[i];
-    }
-    if (on) c.list[off + __popcll(m & ((1ull << lane) - 1ull))] = b;
-    __syncthreads();
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) rem = max(rem, __shfl_xor(rem, o));
-  if (lane == 0) most[w] = rem;
-  __syncthreads();
-  if (tid == 0) {
-    rem = max(max(most[0], most[1]), max(most[2], most[3]));
-    c.count[0] = base;
-    c.count[1] = rem;
+  const int2 now = compact_step<4>(c.active, c.committed, c.T, c.B, c.list,
+                                   [](const int* a) { return __hip_atomic_load(const_cast<int*>(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); });
+  if (threadIdx.x == 0) {
+    c.count[0] = now.x;
+    c.count[1] = now.y;
     c.count[4] = seq;
     // (the launch's number goes last: the caller watches it)
-    __hip_atomic_store(&c.host[0], base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    __hip_atomic_store(&c.host[1], rem, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&c.host[0], now.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&c.host[1], now.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __hip_atomic_store(&c.host[2], seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }

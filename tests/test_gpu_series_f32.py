@@ -143,6 +143,29 @@ def test_contexts(B, target, draft, N, T):
     sess.close()
 
 
+@pytest.mark.parametrize("B", [257, 512, 1500])
+def test_list_of_active_series(B):
+    """Several trips of the compaction, inside a round and as a kernel of its own: whoever still decodes is on the list once, so that
+    every decode ends where one without a list does."""
+    case = Case("cfg1", B=B, K=2, target=m(1, 32, 1), draft=m(1, 32, 2), patch=16, context=6 * 16, horizon=7 * 16, sigma=0.15)
+    c = case.cfg
+    sess, ref = case.session(), case.session(flags=tsd.TSD_FLAG_NO_COMPACT)
+    for s in (sess, ref):
+        s.prefill(case.context, c.n_ctx, c.horizon)
+    counts = []
+    while not counts or counts[-1]:
+        for s in (sess, ref):
+            s.round()
+        counts.append(sess.num_active())
+        committed = sess.get_state()["committed"]
+        np.testing.assert_array_equal(committed.cpu().numpy(), ref.get_state()["committed"].cpu().numpy())
+        assert counts[-1] == int((committed < c.T).sum())
+    assert any(0 < n < B for n in counts)
+    np.testing.assert_array_equal(sess.get_forecast().cpu().numpy(), ref.get_forecast().cpu().numpy())
+    for s in (sess, ref):
+        s.close()
+
+
 @pytest.mark.parametrize("bad", [np.inf, np.nan])
 @pytest.mark.parametrize("K,target", [(9, T64), (16, T64), (16, m(1, 32, 1)), (12, m(2, 128, 2))])
 def test_values_that_are_none(bad, K, target):
