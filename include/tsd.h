@@ -259,8 +259,9 @@ int tsd_accept_commit_static(const float* X_dev, const float* mu_q_dev, const fl
  * tsd_set_resident_wait, one workgroup finishes the pass alone: the results are the same, the pass takes some 3 us per workgroup and
  * stage, and the handle runs kernel by kernel from then on.
  * An fp32 handle of small dense models (d_model of 32, 64 or 128, d_ff four times that; a layer's keys and values of one series in
- * LDS) runs a round of at most 512 series, the acceptance and the count of active series included, a target-only step and a short
- * context pass as ONE launch each, a workgroup per series, bit for bit the kernel-by-kernel result; not between
+ * LDS) runs a round or a target-only step of at most 512 series, the acceptance and the count of active series included, and a context
+ * pass of at most 128 tokens, where that is the faster way, as ONE launch each, a workgroup per series, bit for bit the kernel-by-kernel
+ * result (a proposal that is not finite spoils the outputs of the tokens that see it; kernel by kernel also those before it); not between
  * tsd_profile_begin and tsd_profile_end, nor with TSD_FLAG_SAMPLE_PROPOSALS or TSD_FLAG_NAIVE_VERIFY. */
 int tsd_round(tsd_ctx* ctx, void* stream);
 

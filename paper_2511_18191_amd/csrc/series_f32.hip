@@ -4,8 +4,11 @@
 // Kernel by kernel such a round is some 35 dependent launches of 4 to 6 us that each touch a few KB.  Series never exchange
 // anything inside a round, so a workgroup of 8 wavefronts takes its series through every stage with barriers of its own in
 // place of launches; residual, activations, patches and the layer's keys and values sit in LDS.  8 series through 2 layers of 64 (draft 1 of
-// 32, 32 patches of context, K = 4): 544 us a forecast kernel by kernel, 188 here; a round 64 us, the context 33.  What bounds it: the
-// chain of latencies of a stage (a barrier, LDS, 8 to 64 matrix instructions of 32 clocks, an epilogue: 1 to 2 us), not bytes.
+// 32, 32 patches of context, K = 4): 544 us a forecast kernel by kernel, 165 to 177 here; a round of four proposals 64 us, of one 39, the
+// context 34.  What bounds it: the chain of latencies of a stage (a barrier, LDS, 8 to 64 matrix instructions of 32 clocks, an epilogue:
+// 1 to 2 us), not bytes.  Of a round's wavefront cycles 58 % wait (barriers, LDS, loads), 16 % for an instruction to issue; the matrix cores
+// in use are busy for 14 % of the time, LDS bank conflicts are half a per cent, and the weights come from behind the L2s, each of which has
+// them to fetch anew in a launch.
 //
 //   * Sizes are template parameters (Shape): known only at run time they made a product's stage some 1000 instructions long, 4000
 //     clocks for 500 of matrix instructions, and a round of 127 us.
@@ -491,7 +494,8 @@ __device__ __forceinline__ void run_series_pass(const SeriesP& p, const SeriesMo
     }
     lds_barrier();
     // ---- attention ----
-    // (up to eight queries a wavefront each is faster: a round of 5 tokens 61 us against 70, a context of 31 48 against 33)
+    // (Up to eight queries a wavefront each is the faster way, more of them the matrix cores.  Against the other way, timed when the rule was
+    // made: a round of 5 tokens 61 us / 70, a context of 31 33 us / 48.)
     if (nq > 8 && S <= kTileKeys && !*odd) {
       for (int t = wave; t < ((nq + 15) >> 4) * H; t += kWaves) {
         const int row = t / H * 16, c0 = t % H * HD;
@@ -753,9 +757,12 @@ hipError_t launch_series_pack(const float* src, float* dst, int N, int K, int qk
   return hipGetLastError();
 }
 
-// Series of a decode that one round takes a workgroup each for, two for every compute unit: behind that the launches of the tiled path
-// fill the chip (decodes and target-only steps, us, kernel by kernel / this: 2 layers of 64, 512 series 673 and 471 / 309 and 292, 1024
-// series 768 and 568 / 551 and 566; 3 layers of 128, 512 series 1143 and 981 / 677 and 895, 1024 series 1347 and 1243 / 1211 and 1764).
+// Series of a decode that one round takes a workgroup each for, two for every compute unit.  Behind that the launches of the tiled path
+// fill the chip: target-only steps gain no more, whole decodes still a little; rounds and steps have one limit, so that a batch's decode is
+// one kind of pass.  (Decodes and target-only steps, us, kernel by kernel / this: 2 layers of 64, 512 series 673 and 471 / 309 and 292, 1024
+// series 768 and 568 / 551 and 566; 3 layers of 128, 512 series 1143 and 981 / 677 and 895, 1024 series 1347 and 1243 / 1211 and 1764.  Up to
+// 512 series, widths 32 to 128, 1 to 12 layers, 8 to 400 patches of context: decodes 1.3 to 3.6 times as fast, steps 1.06 to 4.9.)  The
+// batch counts, not who is still active: the late rounds of a larger batch stay launch by launch.
 constexpr int kMostSeries = 512;
 bool series_round_ok(int n) { return n <= kMostSeries; }
 
