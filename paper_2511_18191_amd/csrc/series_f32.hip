@@ -7,8 +7,8 @@
 // 32, 32 patches of context, K = 4): 544 us a forecast kernel by kernel, 165 to 177 here; a round of four proposals 64 us, of one 39, the
 // context 34.  What bounds it: the chain of latencies of a stage (a barrier, LDS, 8 to 64 matrix instructions of 32 clocks, an epilogue:
 // 1 to 2 us), not bytes.  Of a round's wavefront cycles 58 % wait (barriers, LDS, loads), 16 % for an instruction to issue; the matrix cores
-// in use are busy for 14 % of the time, LDS bank conflicts are half a per cent, and the weights come from behind the L2s, each of which has
-// them to fetch anew in a launch.
+// in use are busy for 14 % of the time, bank conflicts take 4 % of a compute unit's clocks, and the weights come from behind the L2s, each
+// of which has them to fetch anew in a launch (22 % L2 hits, 390 clocks a read).
 //
 //   * Sizes are template parameters (Shape): known only at run time they made a product's stage some 1000 instructions long, 4000
 //     clocks for 500 of matrix instructions, and a round of 127 us.
